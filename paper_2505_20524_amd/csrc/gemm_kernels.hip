@@ -30,21 +30,15 @@
 // The MFMA is issued with the B fragment as first operand so that a lane ends up with four
 // consecutive output columns per register quad and can store 8 bytes of bf16 at a time.
 //
-// Contraction split.  A launch with fewer tiles than compute units leaves the rest of the chip idle
-// (the weight gradient of a 2048 x 2048 projection over 16384 tokens is 64 tiles of K = 16384).  With a
-// caller workspace such a product is cut along K into `splits` chunks: the unit of work becomes
-// (tile, chunk), every unit leaves its binary32 accumulators in the workspace, and a second kernel adds
-// the chunks of a tile in a fixed order, applies the scales and rounds once to bf16.  Deterministic (no
-// atomics); the sums differ from the unsplit kernel's only in the order of binary32 additions.
-#include "common.h"
-#include "launch.h"
+// Launches whose 256 x 256 tiles would leave much of the chip idle (few tiles, or a nearly empty last round) take the
+// kernels of gemm_tile_kernels.hip: see plan_product below.
+#include "gemm_common.h"
 #include "../../include/fog_probe.h"
 
 namespace {
 
-constexpr int BM = 256, BN = 256, BK = 64;
+constexpr int BM = 256, BN = 256;
 constexpr int kThreads = 256;
-constexpr int PAIR_K = 2 * BK;               // contraction bytes per load unit
 constexpr int OPERAND_BYTES = 256 * PAIR_K;  // 32 KB per operand and pair stage, both storage forms
 // LDS map: the two pair stages of the A operand first (64 KB), then those of B (64 KB), so that
 // "stage * 32 KB + K-step half + tile row offset" of any fragment read fits the 16-bit immediate
@@ -55,50 +49,6 @@ constexpr int EPI_STRIDE = 64 + 16;           // epilogue staging: 32 rows x 32 
 constexpr int EPI_BUF = 32 * EPI_STRIDE;      // one staged block
 constexpr int EPI_BYTES = 2 * EPI_BUF;        // per wave: two blocks
 constexpr int LDS_BYTES = RING_BYTES + 4 * EPI_BYTES;  // 151552
-constexpr uint32_t OOB = 0x80000000u;        // a buffer offset past any operand (spans are < 2^31 bytes)
-
-struct GemmArgs {
-  const uint8_t* A;
-  const uint8_t* B;
-  uint16_t* C;
-  const float* sinv_a;
-  const float* sinv_b;
-  int64_t lda, ldb, ldc;
-  int M, N, K;
-  int tiles_m, tiles_n;
-  int vec_store;  // C rows allow 16-byte stores
-  int wide_store; // interior tiles are stored as whole 128-byte lines (launches of several tiles per workgroup)
-  uint32_t a_bytes, b_bytes;  // addressable span of each operand
-  // contraction split (splits == 1: none): work item = chunk * tiles + tile, chunk c covers
-  // contraction indices [c * k_chunk, min(K, (c + 1) * k_chunk)); partial holds splits * tiles blocks
-  // of 256 x 256 floats in the register order of the accumulators
-  int splits, k_chunk;
-  float* partial;
-};
-
-typedef __attribute__((address_space(3))) v2i* lds_v2i_ptr;
-
-// 16 bytes per lane from buffer `rsrc` at byte offset `voff` (zero when out of range) to
-// LDS[m0 + 16 * lane].  Issued as inline assembly so that the compiler's own wait-count
-// insertion does not serialise the LDS reads of other stages behind these loads; completion is
-// awaited explicitly with s_waitcnt vmcnt + barrier in the main loop.
-FOG_DEVICE void load_to_lds(v4i rsrc, uint32_t voff, uint32_t lds_addr_uniform) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-               :
-               : "v"(voff), "s"(rsrc), "s"(lds_addr_uniform)
-               : "memory", "m0");
-}
-
-// Raw buffer descriptor (stride 0): 48-bit base, byte count for the bounds check, dword-format flags.
-FOG_DEVICE v4i make_rsrc(const void* base, uint32_t bytes) {
-  const uint64_t b = reinterpret_cast<uint64_t>(base);
-  v4i r;
-  r[0] = (int)(uint32_t)b;
-  r[1] = (int)((uint32_t)(b >> 32) & 0xFFFFu);
-  r[2] = (int)bytes;
-  r[3] = 0x00020000;
-  return r;
-}
 
 // Per-thread state of one operand's direct loads.  A wave fetches 8 pieces of 1 KB per pair of
 // K-steps; piece j of wave w lands at byte 8192 w + 1024 j of the operand's pair stage.  The
@@ -115,8 +65,7 @@ struct LoadPlan {
 };
 
 // K-contiguous operand: piece j covers tile rows 64 w + 8 j .. + 7; lane -> (row, LDS chunk position).
-// The plans cover contraction indices kb .. kb + K - 1 of the operand (a chunk of a split product, or all of it).
-FOG_DEVICE LoadPlan plan_kc(int64_t ld, int row0, int rows, int kb, int K) {
+FOG_DEVICE LoadPlan plan_kc(int64_t ld, int row0, int rows, int K) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int r8 = l >> 3, pos = l & 7;
   LoadPlan p;
@@ -130,12 +79,12 @@ FOG_DEVICE LoadPlan plan_kc(int64_t ld, int row0, int rows, int kb, int K) {
     // row = 64 w + 8 j + r8: the swizzle key (row >> 1) & 7 is (r8 >> 1) ^ 4 (j & 1)
     const int c = pos ^ (r8 >> 1) ^ (4 * par);  // global chunk that lives at LDS position pos of this row
     p.klim[par] = K - 16 * c;
-    p.off[par] = (uint32_t)((int64_t)(first + 8 * par) * ld + 16 * c + kb);
+    p.off[par] = (uint32_t)((int64_t)(first + 8 * par) * ld + 16 * c);
   }
   return p;
 }
 // K-major operand: piece j covers contraction rows 32 w + 4 j .. + 3 of the pair; lane -> (k, LDS chunk position).
-FOG_DEVICE LoadPlan plan_km(int64_t ld, int col0, int cols, int kb, int K) {
+FOG_DEVICE LoadPlan plan_km(int64_t ld, int col0, int cols, int K) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   LoadPlan p;
   p.step = (uint32_t)(PAIR_K * ld);
@@ -147,7 +96,7 @@ FOG_DEVICE LoadPlan plan_km(int64_t ld, int col0, int cols, int kb, int K) {
     // k + 4 j: the swizzle key (k + 4 j) & 7 is ((l >> 4) & 7) ^ 4 (j & 1)
     const int c = (l & 15) ^ (l >> 4) ^ (4 * par);
     p.klim[par] = K - k;
-    p.off[par] = (col0 + 16 * c < cols) ? (uint32_t)((int64_t)(kb + k + 4 * par) * ld + col0 + 16 * c) : OOB;  // cols % 16 == 0
+    p.off[par] = (col0 + 16 * c < cols) ? (uint32_t)((int64_t)(k + 4 * par) * ld + col0 + 16 * c) : OOB;  // cols % 16 == 0
   }
   return p;
 }
@@ -250,26 +199,16 @@ FOG_DEVICE void tile_origin(int logical, int tiles_m, int tiles_n, int& m0, int&
   n0 = (rem / gsz) * BN;
 }
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-// Two floats -> packed bf16 with the hardware convert (round to nearest even).
-FOG_DEVICE uint32_t cvt_pk_bf16(float lo, float hi) {
-  f32x2 v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-// SPLIT: the work items are (tile, contraction chunk) pairs and the epilogue leaves the binary32
-// accumulators in the workspace instead of writing C (see the header comment).
 // PRODUCTS_ONLY (measurement helper fog_probe_gemm_products_only, never the product path): interior tiles skip
 // their epilogue, so that the launch shows what the conversion, staging and stores of the finished tiles cost.
-template <int LAYOUT, int FA, int FB, bool SPLIT, bool PRODUCTS_ONLY = false>
+template <int LAYOUT, int FA, int FB, bool PRODUCTS_ONLY = false>
 __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   constexpr bool A_KM = LAYOUT == FOG_TN;
   constexpr bool B_KM = LAYOUT != FOG_NT;
 
   const int ntiles = g.tiles_m * g.tiles_n;
-  const TileWalk walk = tile_walk(SPLIT ? ntiles * g.splits : ntiles);
+  const TileWalk walk = tile_walk(ntiles);
   if (walk.first >= walk.end) return;
 
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
@@ -289,19 +228,8 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) zero16[r] = 0.0f;
 
-  const int nk = ((SPLIT ? g.k_chunk : g.K) + BK - 1) / BK;   // every chunk of a split takes the steps of a full chunk
+  const int nk = (g.K + BK - 1) / BK;
   const int nk4 = (nk + 3) & ~3;  // steps are handled four at a time (two pair stages); steps past K multiply zeros
-  // work item -> tile, first contraction index, number of contraction indices
-  auto item_range = [&](int item, int& logical, int& kb, int& klen) {
-    if (SPLIT) {
-      const int c = item / ntiles;
-      logical = item - c * ntiles;
-      kb = c * g.k_chunk;
-      klen = min(g.K - kb, g.k_chunk);
-    } else {
-      logical = item; kb = 0; klen = g.K;
-    }
-  };
 
 #define FOG_LOAD_A(j, k0, ST) issue_piece<A_KM>(pa, j, rsrc_a, k0, lds_w + RING_A + (ST) * OPERAND_BYTES + 1024u * (j))
 #define FOG_LOAD_B(j, k0, ST) issue_piece<B_KM>(pb, j, rsrc_b, k0, lds_w + RING_B + (ST) * OPERAND_BYTES + 1024u * (j))
@@ -395,11 +323,10 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
   // tile the first two pairs of the workgroup's next tile are already being fetched, so a new tile
   // starts with its data in LDS and its first fragments in registers, and the epilogue's stores
   // drain while the next tile computes.
-  int m0, n0, logical, kb, klen;
-  item_range(walk.first, logical, kb, klen);
-  tile_origin(logical, g.tiles_m, g.tiles_n, m0, n0);
-  LoadPlan pa = A_KM ? plan_km(g.lda, m0, g.M, kb, klen) : plan_kc(g.lda, m0, g.M, kb, klen);
-  LoadPlan pb = B_KM ? plan_km(g.ldb, n0, g.N, kb, klen) : plan_kc(g.ldb, n0, g.N, kb, klen);
+  int m0, n0;
+  tile_origin(walk.first, g.tiles_m, g.tiles_n, m0, n0);
+  LoadPlan pa = A_KM ? plan_km(g.lda, m0, g.M, g.K) : plan_kc(g.lda, m0, g.M, g.K);
+  LoadPlan pb = B_KM ? plan_km(g.ldb, n0, g.N, g.K) : plan_kc(g.ldb, n0, g.N, g.K);
   v8i fa[4], fa3, xb[4], yb[4];   // A fragments (row 3 twice), B fragments twice
   FOG_ISSUE_PAIR(0, 0);
   FOG_ISSUE_PAIR(PAIR_K, 1);
@@ -423,10 +350,9 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
       /* last four steps of this tile: the loads issued now belong to the next tile (all zero-fill  \
          if there is none, which keeps the outstanding-load count the waits assume) */              \
       if (next < walk.end) {                                                                         \
-        item_range(next, logical, kb, klen);                                                         \
-        tile_origin(logical, g.tiles_m, g.tiles_n, m0, n0);                                          \
-        pa = A_KM ? plan_km(g.lda, m0, g.M, kb, klen) : plan_kc(g.lda, m0, g.M, kb, klen);           \
-        pb = B_KM ? plan_km(g.ldb, n0, g.N, kb, klen) : plan_kc(g.ldb, n0, g.N, kb, klen);           \
+        tile_origin(next, g.tiles_m, g.tiles_n, m0, n0);                                             \
+        pa = A_KM ? plan_km(g.lda, m0, g.M, g.K) : plan_kc(g.lda, m0, g.M, g.K);                     \
+        pb = B_KM ? plan_km(g.ldb, n0, g.N, g.K) : plan_kc(g.ldb, n0, g.N, g.K);                     \
       } else {                                                                                       \
         pa.off[0] = pa.off[1] = pb.off[0] = pb.off[1] = OOB;                                         \
       }                                                                                              \
@@ -452,21 +378,6 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
     // stored as 16-byte pieces, four lanes per 64-byte row segment: 32 coalesced stores per lane.  The stores are
     // non-temporal: a result of 100 to 235 MB cannot stay in the caches anyway, and as ordinary stores its dirty lines
     // were written back during whatever kernel came next (the abs-max pass of the next layer ran a third slower).
-    if (SPLIT) {
-      // The accumulators as they are: float4 number ((w * 16 + 4 i + j) * 4 + qd) * 64 + l of this item's block,
-      // i.e. 1 KB per wave and store instruction.  Waited for at once (the next item's prefetch is waited for
-      // with them, as on the edge-tile path below).
-      float4* dst = reinterpret_cast<float4*>(g.partial) + (int64_t)tile * (BM * BN / 4) + (w * 16) * 256 + l;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int qd = 0; qd < 4; ++qd)
-            dst[((4 * i + j) * 4 + qd) * 64] = make_float4(acc[i][j][4 * qd + 0], acc[i][j][4 * qd + 1], acc[i][j][4 * qd + 2], acc[i][j][4 * qd + 3]);
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-      continue;
-    }
     const bool fast = g.vec_store != 0 && m_cur + BM <= g.M && n_cur + BN <= g.N;
     if (PRODUCTS_ONLY && fast) {
 #pragma unroll
@@ -528,7 +439,7 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
         }
       }
     } else {
-      // edge tiles and unaligned C: the same staging, element-wise guarded stores
+      // edge tiles and unaligned C: the same staging, row pieces stored whole where they lie inside an aligned C
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
 #pragma unroll
@@ -545,13 +456,7 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
             const uint4 v = *reinterpret_cast<const uint4*>(buf + (16 * t + prow) * EPI_STRIDE + 16 * piece);
             const int m = m_cur + wm + 32 * i + 16 * t + prow;
             const int n = n_cur + wn + 32 * j + 8 * piece;
-            if (m < g.M) {
-              uint16_t* dst = g.C + (int64_t)m * g.ldc + n;
-              const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-              for (int e = 0; e < 8; ++e)
-                if (n + e < g.N) dst[e] = (uint16_t)(wv[e >> 1] >> (16 * (e & 1)));
-            }
+            if (m < g.M && n < g.N) store_row_piece(g, m, n, v);
           }
         }
       }
@@ -611,16 +516,13 @@ int persistent_grid(int64_t total, int* rounds_out = nullptr) {
   return grid;
 }
 
-// Split of the contraction (1 = none) for a product of `tiles` output tiles over K, from a cost model in
-// shader cycles: a K-step costs about 1100 cycles, the bf16 epilogue of a tile about 9000 (all CUs write at
-// once), the binary32 one twice that, and the reduce pass moves its bytes at about 2000 per cycle plus a
-// launch.  A split is only taken when the model promises a clear gain (measured: the 64-tile weight gradient of
-// a 2048 x 2048 projection over 16384 tokens 131 -> 72 us, the 128-tile data gradient 4096 x 2048 over 8192 81 ->
-// 74 us; a 192-tile product, which the model rejects, loses when forced: 179 -> 227 us).
-struct SplitPlan { int splits, k_chunk; };
-SplitPlan choose_split(int64_t M, int64_t N, int64_t K, int64_t tiles) {
-  SplitPlan best{1, (int)K};
-  if (tiles >= compute_units() || K < 1024) return best;
+// Room for binary32 partial tiles that the workspace query asks for: `splits` chunks of the contraction over the 256 x 256
+// tiles of C, from a cost model in shader cycles of such a split (a K-step about 1100, the bf16 epilogue 9000, the binary32 one
+// twice that, the reduce pass 2000 bytes per cycle plus a launch); 0 where it promises less than 7 %.  plan_product decides
+// what the room is used for.
+size_t split_room(int64_t M, int64_t N, int64_t K) {
+  const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+  if (tiles >= compute_units() || K < 1024) return 0;
   auto cost = [&](int splits, int64_t k_chunk) {
     int rounds = 0;
     persistent_grid(tiles * splits, &rounds);
@@ -629,78 +531,77 @@ SplitPlan choose_split(int64_t M, int64_t N, int64_t K, int64_t tiles) {
     if (splits > 1) c += ((double)tiles * splits * BM * BN * 4 + 2.0 * M * N) / 2000.0 + 6000.0;
     return c;
   };
-#ifndef FOG_SPLIT_MIN_GAIN
-#define FOG_SPLIT_MIN_GAIN 0.93   /* a split must promise this fraction of the unsplit time, or less */
-#endif
-  const double unsplit = cost(1, K);
-  double best_cost = unsplit * FOG_SPLIT_MIN_GAIN;
+  double best_cost = cost(1, K) * 0.93;
+  int best = 0;
   for (int want = 2; want <= 16; ++want) {
     const int64_t k_chunk = ((K + want - 1) / want + 255) / 256 * 256;
     if (k_chunk < 512) break;
     const int splits = (int)((K + k_chunk - 1) / k_chunk);
     if (splits < 2) continue;
     const double c = cost(splits, k_chunk);
-    if (c < best_cost) { best_cost = c; best = SplitPlan{splits, (int)k_chunk}; }
+    if (c < best_cost) { best_cost = c; best = splits; }
+  }
+  return (size_t)best * tiles * BM * BN * sizeof(float);
+}
+
+// Which kernel computes a product.  The 256 x 256 kernel moves the fewest operand bytes per matrix instruction and is the
+// fastest wherever its tiles fill the chip; every smaller tile costs more per flop (operand bytes from L2) and fills it with
+// less work: 46 -> 21 us on 1777 x 3088 x 2064 (91 tiles), 14.6 -> 4.7 us on 512 x 1024 x 1024 (8 tiles), but 98 -> 109 us on
+// 8192 x 4096 x 4096.  The estimate in microseconds, fitted to the kernel times of 110 shapes in the three layouts (M 64 to
+// 16384, N and K 256 to 14336; rms error 12 to 20 %, the chosen kernel is on average within 1 % of the fastest one):
+//   2 + sum over rounds of (stages * s(n) + epilogue),  stage = 128 contraction bytes, n = workgroups resident in the round,
+//   s(n) = s_few + (s_full - s_few) n / 256 up to one workgroup per compute unit, rising to s_two with two;
+//   a contraction split adds 6 us (second launch) and its partial tiles, written and read, at 16 TB/s (they stay in the caches).
+struct TileCost { int bm, bn, resident; double epilogue, s_few, s_full, s_two; };
+constexpr TileCost kTileCost[] = {
+    {256, 128, 256, 4.27, 0.52, 0.81, 0.81},   // TILE_256x128
+    {128, 128, 256, 2.77, 0.39, 0.53, 0.53},   // TILE_128x128
+    {128, 128, 512, 1.88, 0.53, 0.92, 1.09},   // TILE_128x128_2WG
+    {64, 64, 512, 1.48, 0.12, 0.37, 0.41},     // TILE_64x64
+};
+struct ProductPlan { int tile, splits, k_chunk; };   // tile: GemmTile, or -1 for the 256 x 256 kernel
+ProductPlan plan_product(fog_layout layout, int64_t M, int64_t N, int64_t K, size_t room) {
+  ProductPlan best{-1, 1, (int)K};
+  const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+  int rounds = 0;
+  const int grid = persistent_grid(tiles, &rounds);
+  const double stages = 2.0 * ((K + 4 * BK - 1) / (4 * BK));     // four K-steps per trip
+  // a smaller tile has to promise 10 %: where the chip is full the estimates lie closer together than their error
+  double best_cost = 0.9 * (2.0 + rounds * (stages * (1.03 + 0.47 * (grid < 256 ? grid / 256.0 : 1.0)) + 6.62));
+  for (int t = 0; t < 4; ++t) {
+    const TileCost& c = kTileCost[t];
+    const int64_t n_tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    if (n_tiles > (1 << 24)) continue;
+    // pieces of a 64-byte wide tile of a K-major operand are half lines
+    const double half_lines = c.bn != 64 || layout == FOG_NT ? 1.0 : layout == FOG_NN ? 1.3 : 1.5;
+    for (int want = 1; want <= 16; ++want) {
+      const int64_t k_chunk = ((K + want - 1) / want + PAIR_K - 1) / PAIR_K * PAIR_K;
+      const int splits = (int)((K + k_chunk - 1) / k_chunk);
+      if (want > 1 && (splits != want || k_chunk < 512)) continue;
+      const int64_t items = n_tiles * splits;
+      if (splits > 1 && (items * c.bm * c.bn * sizeof(float) > room || items > 2 * c.resident)) break;
+      const double n_st = (double)(k_chunk / PAIR_K);
+      auto round_cost = [&](int64_t n) {
+        const double s = n <= 256 ? c.s_few + (c.s_full - c.s_few) * (n / 256.0) : c.s_full + (c.s_two - c.s_full) * ((n - 256) / 256.0);
+        return n > 0 ? n_st * s * half_lines + c.epilogue : 0.0;
+      };
+      double cost = 2.0 + (double)(items / c.resident) * round_cost(c.resident) + round_cost(items % c.resident);
+      if (splits > 1) cost += 6.0 + (double)items * c.bm * c.bn * 8.0 / 16e6;
+      if (cost < best_cost) { best_cost = cost; best = ProductPlan{t, splits, splits > 1 ? (int)k_chunk : (int)K}; }
+    }
   }
   return best;
 }
 
-// Second pass of a split product: a workgroup owns one 32 x 32 block of C (the 256 float4 that one wave
-// wrote with four consecutive store instructions), adds the chunks in ascending order, scales, rounds to
-// bf16 and writes the block through LDS as 16-byte row pieces.
-__global__ __launch_bounds__(256) void gemm_split_reduce_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) uint8_t blk[32 * EPI_STRIDE];
-  const int ntiles = g.tiles_m * g.tiles_n;
-  const int logical = blockIdx.x >> 6, sub = blockIdx.x & 63;     // 64 blocks of 32 x 32 per tile: sub = w * 16 + 4 i + j
-  const int t = threadIdx.x, l = t & 63, qd = t >> 6;
-  const float4* src = reinterpret_cast<const float4*>(g.partial) + (int64_t)logical * (BM * BN / 4) + sub * 256 + t;
-  float4 acc = src[0];
-  for (int c = 1; c < g.splits; ++c) {
-    const float4 v = src[(int64_t)c * ntiles * (BM * BN / 4)];
-    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-  }
-  const float alpha = (*g.sinv_a) * (*g.sinv_b);
-  *reinterpret_cast<uint2*>(blk + (l & 31) * EPI_STRIDE + 16 * qd + 8 * (l >> 5)) =
-      make_uint2(cvt_pk_bf16(acc.x * alpha, acc.y * alpha), cvt_pk_bf16(acc.z * alpha, acc.w * alpha));
-  __syncthreads();
-  int m0, n0;
-  tile_origin(logical, g.tiles_m, g.tiles_n, m0, n0);
-  const int w = sub >> 4, i = (sub >> 2) & 3, j = sub & 3;
-  const int mb = m0 + (w >> 1) * 128 + 32 * i, nb = n0 + (w & 1) * 128 + 32 * j;   // origin of the block in C
-  if (t < 128) {
-    const int row = t >> 2, piece = t & 3;
-    const int m = mb + row, n = nb + 8 * piece;
-    if (m < g.M && n < g.N) {
-      const uint4 v = *reinterpret_cast<const uint4*>(blk + row * EPI_STRIDE + 16 * piece);
-      uint16_t* dst = g.C + (int64_t)m * g.ldc + n;
-      if (g.vec_store && n + 8 <= g.N) {
-        st_nt16(dst, v);
-      } else {
-        const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (n + e < g.N) dst[e] = (uint16_t)(wv[e >> 1] >> (16 * (e & 1)));
-      }
-    }
-  }
-}
-
 template <int LAYOUT, int FA, int FB>
 fog_status launch(const GemmArgs& g, hipStream_t s) {
-  static bool configured = false;  // per instantiation pair; the attribute is sticky for the process
+  static bool configured = false;  // per instantiation; the attribute is sticky for the process
   if (!configured) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(fp8_gemm_kernel<LAYOUT, FA, FB, false>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(fp8_gemm_kernel<LAYOUT, FA, FB, true>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess)
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(fp8_gemm_kernel<LAYOUT, FA, FB>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess)
       return FOG_ERR_HIP;
     configured = true;
   }
-  const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
-  if (g.splits > 1) {
-    fp8_gemm_kernel<LAYOUT, FA, FB, true><<<persistent_grid(tiles * g.splits), kThreads, LDS_BYTES, s>>>(g);
-    gemm_split_reduce_kernel<<<(int)(tiles * 64), 256, 0, s>>>(g);
-  } else {
-    fp8_gemm_kernel<LAYOUT, FA, FB, false><<<persistent_grid(tiles), kThreads, LDS_BYTES, s>>>(g);
-  }
+  fp8_gemm_kernel<LAYOUT, FA, FB><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n), kThreads, LDS_BYTES, s>>>(g);
   return fog_launch_status();
 }
 
@@ -716,9 +617,7 @@ inline bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintp
 
 extern "C" size_t fog_fp8_gemm_workspace(fog_layout, int64_t M, int64_t N, int64_t K) {
   if (M <= 0 || N <= 0 || K <= 0 || M > 0x7FFFFF00 || N > 0x7FFFFF00 || K > 0x7FFFFF00) return 0;
-  const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  const SplitPlan sp = choose_split(M, N, K, tiles);
-  return sp.splits > 1 ? (size_t)sp.splits * tiles * BM * BN * sizeof(float) : 0;
+  return split_room(M, N, K);
 }
 
 extern "C" fog_status fog_fp8_gemm(fog_layout layout, int64_t M, int64_t N, int64_t K,
@@ -756,19 +655,24 @@ extern "C" fog_status fog_fp8_gemm(fog_layout layout, int64_t M, int64_t N, int6
   if (a_span >= 0x7FFFFFFF || b_span >= 0x7FFFFFFF) return FOG_ERR_UNSUPPORTED;  // 32-bit buffer offsets
   g.a_bytes = (uint32_t)a_span; g.b_bytes = (uint32_t)b_span;
   g.splits = 1; g.k_chunk = (int)K; g.partial = nullptr;
-  if (K > 0 && workspace && aligned(workspace, 16)) {
-    // the split the workspace query promised, when the caller brought that much
-    const SplitPlan sp = choose_split(M, N, K, (int64_t)g.tiles_m * g.tiles_n);
-    if (sp.splits > 1 && workspace_bytes >= (size_t)sp.splits * g.tiles_m * g.tiles_n * BM * BN * sizeof(float)) {
-      g.splits = sp.splits; g.k_chunk = sp.k_chunk; g.partial = reinterpret_cast<float*>(workspace);
-    }
-  }
   hipStream_t s = (hipStream_t)stream;
   if (K == 0) {
     int64_t blocks = (M * N + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     gemm_zero_kernel<<<(int)blocks, 256, 0, s>>>(g.C, ldc, g.M, g.N);
     return fog_launch_status();
+  }
+  // the contraction is only split when the caller brought the room that the workspace query names
+  size_t room = 0;
+  if (workspace && aligned(workspace, 16)) {
+    room = split_room(M, N, K);
+    if (workspace_bytes < room) room = 0;
+  }
+  const ProductPlan plan = plan_product(layout, M, N, K, room);
+  if (plan.tile >= 0) {
+    g.splits = plan.splits; g.k_chunk = plan.k_chunk;
+    if (plan.splits > 1) g.partial = reinterpret_cast<float*>(workspace);
+    return gemm_tile_launch((GemmTile)plan.tile, layout, fmtA, fmtB, g, s);
   }
   switch (layout) {
     case FOG_NT: return launch_fmt<FOG_NT>(g, fmtA, fmtB, s);
@@ -799,10 +703,10 @@ extern "C" fog_status fog_probe_gemm_products_only(int64_t M, int64_t N, int64_t
   g.splits = 1; g.k_chunk = (int)K; g.partial = nullptr;
   static bool configured = false;
   if (!configured) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(fp8_gemm_kernel<FOG_NT, 0, 0, false, true>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess)
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(fp8_gemm_kernel<FOG_NT, 0, 0, true>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess)
       return FOG_ERR_HIP;
     configured = true;
   }
-  fp8_gemm_kernel<FOG_NT, 0, 0, false, true><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n), kThreads, LDS_BYTES, (hipStream_t)stream>>>(g);
+  fp8_gemm_kernel<FOG_NT, 0, 0, true><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n), kThreads, LDS_BYTES, (hipStream_t)stream>>>(g);
   return fog_launch_status();
 }

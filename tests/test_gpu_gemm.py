@@ -249,3 +249,55 @@ def test_gemm_split_exact_integers_and_query():
     assert np.array_equal(synth.bf16_bits_to_f32(got).astype(np.float64), (Ai @ Bi.T) / 4.0)
     for (layout, m, n, k) in [(gemm.NT, 8192, 12288, 4096), (gemm.TN, 14336, 4096, 8192), (gemm.NT, 512, 1024, 1024)]:
         assert fog.fp8_gemm_workspace(layout, m, n, k) == 0
+
+
+TILE_SHAPES = [   # (layout, M, N, K, padding of C's rows): products of few 256 x 256 tiles, one of each smaller tile per layout
+    (gemm.NT, 65, 63, 16, 1), (gemm.NT, 500, 776, 1040, 8), (gemm.NN, 129, 80, 272, 3), (gemm.TN, 64, 144, 5, 0),      # 64 x 64
+    (gemm.NT, 1900, 1500, 3088, 8), (gemm.NN, 1777, 2064, 3088, 0), (gemm.TN, 1296, 1040, 2001, 5),                      # 128 x 128
+    (gemm.NT, 7900, 1184, 384, 0), (gemm.NN, 2050, 3216, 144, 8), (gemm.TN, 6336, 1104, 155, 0),                        # 128 x 128, two per CU
+    (gemm.NT, 1777, 3088, 2064, 0), (gemm.NN, 4000, 1808, 2064, 3), (gemm.TN, 3088, 2064, 1777, 8),                     # 256 x 128
+]
+
+
+@pytest.mark.parametrize("layout,M,N,K,pad", TILE_SHAPES)
+def test_gemm_small_tiles(layout, M, N, K, pad):
+    """Products whose 256 x 256 tiles would leave most of the chip idle run on smaller tiles: edges of the tiles, contractions
+    that end inside a stage, padded and unaligned C, against the oracle; nothing outside C's rows is written."""
+    fa, fb = (fp8.E5M2, fp8.E4M3) if layout != gemm.NT else (fp8.E4M3, fp8.E4M3)
+    A8, sa, B8, sb = quantized_layer(M + 5 * N + K, M, N, K, fa, fb)
+    a, b = lay(layout, A8, B8)
+    ref = gemm.fp8_gemm(layout, a, fa, sa, b, fb, sb)
+    store = torch.full((M + 1, N + pad), 0x7FC0, dtype=torch.int16, device="cuda")
+    C = store[:M, :N]
+    fog.fp8_gemm(layout, M, N, K, dev(a), fa, fscalar(sa), dev(b), fb, fscalar(sb), C)
+    torch.cuda.synchronize()
+    got = host_u16(store)
+    assert (got[M] == 0x7FC0).all() and (got[:, N:] == 0x7FC0).all()
+    what = "tiles %d %dx%dx%d" % (layout, M, N, K)
+    check_bf16(got[:M, :N], ref, what=what)
+    check_gemm_elementwise(got[:M, :N], ref, absdot(layout, a, fa, sa, b, fb, sb), what=what)
+
+
+@pytest.mark.parametrize("layout,M,N,K", [(gemm.NT, 66, 1936, 9520), (gemm.NN, 80, 368, 11520), (gemm.TN, 304, 272, 8200), (gemm.NT, 328, 1584, 6000),
+                                          (gemm.NN, 2339, 400, 9616)])
+def test_gemm_small_tile_split(layout, M, N, K):
+    """The contraction split on smaller tiles: partial tiles that reach past C, a last chunk shorter than the others, the
+    workspace full of NaN patterns beforehand and its end untouched; the same bits on a second call."""
+    fa, fb = (fp8.E5M2, fp8.E4M3) if layout != gemm.NT else (fp8.E4M3, fp8.E4M3)
+    A8, sa, B8, sb = quantized_layer(M + 7 * N + K, M, N, K, fa, fb)
+    a, b = lay(layout, A8, B8)
+    ref = gemm.fp8_gemm(layout, a, fa, sa, b, fb, sb)
+    need = fog.fp8_gemm_workspace(layout, M, N, K)
+    assert need > 0
+    got = []
+    for _ in range(2):
+        store = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+        C = torch.full((M, N), 0x7FC0, dtype=torch.int16, device="cuda")
+        fog.fp8_gemm(layout, M, N, K, dev(a), fa, fscalar(sa), dev(b), fb, fscalar(sb), C, workspace=store[:need])
+        torch.cuda.synchronize()
+        assert (store[need:] == 0xFF).all()
+        got.append(host_u16(C))
+    assert np.array_equal(got[0], got[1])
+    what = "split tiles %d %dx%dx%d" % (layout, M, N, K)
+    check_bf16(got[0], ref, what=what)
+    check_gemm_elementwise(got[0], ref, absdot(layout, a, fa, sa, b, fb, sb), what=what)
