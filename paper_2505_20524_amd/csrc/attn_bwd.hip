@@ -7,15 +7,14 @@
 //     dP  = sinv_do sinv_v (dO~ V~^T)               dS = P o (dP - D_i),  dS~ = E5M2(rho_ds dS)
 //     dQ  = s sinv_k / rho_ds (dS~ K~)              dK = s sinv_q / rho_ds (dS~^T Q~)
 //
-// Three kernels.  (0) D_i, one pass over the bf16 tensors.  (1) dK/dV: a workgroup owns 128 keys
-// (32 per wave) and walks the query blocks at or below its diagonal; the score tile is produced
-// with lane = key, which is the B-operand shape of both dV^T += dO^T P and dK^T += Q^T dS.
-// (2) dQ: a workgroup owns 128 queries and walks the key blocks, scores transposed (lane = query),
-// the B-operand shape of dQ^T += K^T dS^T.  Recomputing S and dP in both kernels costs two extra
+// Three kernels.  (0) D_i and two per-row constants, one pass over the bf16 tensors.  (1) dK/dV: a workgroup owns
+// 64 keys and walks the query blocks at or below its diagonal.  (2) dQ: a workgroup owns 128 queries and walks
+// the key blocks.  Both produce the score tile with lane = query; its packed dS is then the B operand of
+// dQ^T += K^T dS^T as it lies in the registers, and reaches lane = key, the B operand of dV^T += dO^T P and
+// dK^T += Q^T dS, through a small exchange tile in LDS.  Recomputing S and dP in both kernels costs two extra
 // products but keeps every accumulator in registers, needs no atomics and is deterministic.
 // Operands whose contraction index is their row index (dO^T, Q^T, K^T) are gathered from the
-// row-major LDS tiles with the byte-transposing read, in the key/query order the packed
-// probabilities have (see the forward kernel).
+// row-major LDS tiles with the byte-transposing read, in the order the packed scores have.
 #include <mutex>
 
 #include "common.h"
@@ -25,10 +24,10 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int HD = 128;
-constexpr int BLK = 128;           // rows owned by a workgroup (keys in kernel 1, queries in kernel 2)
+constexpr int BLK = 128;           // queries owned by a workgroup of kernel 2
 constexpr int STEP = 64;           // rows of the streamed operands per step
 constexpr int TILE = STEP * HD;    // 8 KB, 16-byte chunks swizzled by swz(row)
-constexpr int NSTAGE = 4;
+constexpr int NSTAGE = 4;          // ring of kernel 2
 constexpr uint32_t OOB = 0x80000000u;
 // The ring stage of a block as a compile-time constant: the loops are unrolled over the ring so that every LDS address is a
 // per-lane constant plus an immediate offset (a stage taken from the block number at run time costs an integer add per
@@ -195,64 +194,75 @@ FOG_DEVICE void clamp_block(v16f* x) {
 }
 
 // ------------------------------------------------------------------ kernel 1: dK, dV
+// A workgroup of four waves owns 64 keys, a pair of waves 32 of them.  Of every block of 64 queries each wave of a pair takes 32
+// through scores, dP, softmax and the casts (lane = query, so the row constants are one register per lane), and sums dV and dK
+// over all 64 for its half of the head dimension.  The packed probabilities and dS travel between the two, and from lane = query
+// to lane = key, through a 4 KB exchange tile in LDS that is written by rows and read with the byte-transposing read.
+//
+// Why pairs: dV and dK of 32 keys are 128 accumulator registers; with the score tiles and the keys' own fragments a wave that
+// holds them all needs more than 256 registers and runs alone on its SIMD.  As two launches, one per output, S was computed
+// twice; a pair holds 64 accumulators per wave, computes S and P once, and at 168 registers three workgroups share a CU.  What
+// bounds the kernel is the vector ALU (exponential, dS, two casts per score), the matrix core close behind it (54 % and 47 % of the
+// cycles); two barriers per block of queries are the price, which three independent workgroups hide.  Tried and slower: eight
+// waves and 128 keys per workgroup (335 us), the products of one block dealt out between the vector work of the next inside the
+// wave (311 us), a three-stage ring with one barrier and two workgroups per CU (318 us).
+// Times of dK and dV, 2 x 32 heads x 4096 causal: 177 + 243 us as two launches -> 292 us; whole backward there 629 -> 530 us, 4 x
+// 16 x 2048 201 -> 171 us, 2 x 32/8 (grouped) x 4096 660 -> 520 us, 1 x 16/4 x 576 80 -> 45 us.
+//
 // Ring stage: Q tile, dO tile, then 64 lse and 64 D values.  Five direct loads per thread and stage.
 constexpr int KV_STAGE = 2 * TILE + 512;
-// MODE 0 produces dK and dV together (one wave per SIMD: 128 accumulator registers for the outputs plus
-// double-buffered score tiles); MODE 1 produces dV only and MODE 2 dK only, each with 64 accumulator
-// registers and no score prefetch, so that two workgroups share a CU and one's exponentials and casts
-// run under the other's matrix instructions.  The pair 1 + 2 recomputes S once more than MODE 0 and is
-// still the faster route (same results: the arithmetic per output is identical).
-template <bool CAUSAL, int MODE>
-__global__ __launch_bounds__(kThreads, MODE == 0 ? 1 : 2) void attn_bwd_dkdv_kernel(BwdArgs a) {
-  constexpr bool WANT_DV = MODE != 2, WANT_DK = MODE != 1, PREFETCH = MODE == 0;
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[NSTAGE * KV_STAGE];
+constexpr int PAIR_THREADS = 256;
+constexpr int PAIR_KEYS = 64;
+constexpr int XCHG = 2 * 64 * 32;               // exchange tiles of a pair: P and dS, [64 queries][32 keys] each
+constexpr int PAIR_STAGES = 2;
+// Position of a key among the 32 bytes of an exchange row (and so the lane that ends up with it): a lane of the scores holds
+// keys 8 qd + 4 g + b, and stores them as its 16 bytes 4 qd + b of half g.
+FOG_DEVICE int key_of_position(int pos) { return 8 * ((pos >> 2) & 3) + 4 * (pos >> 4) + (pos & 3); }
+template <bool CAUSAL>
+__global__ __launch_bounds__(PAIR_THREADS, 3) void attn_bwd_dkdv_kernel(BwdArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[PAIR_STAGES * KV_STAGE + 2 * XCHG];
   const int bhk = blockIdx.x % a.BHkv;                 // key/value head; its query heads are bhk * G .. + G - 1
   const int kblk = blockIdx.x / a.BHkv;                // early key blocks see the most queries: launched first
-  const int t = threadIdx.x, w = t >> 6, l = t & 63, g = l >> 5;
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, g = l >> 5, pair = w >> 1, half = w & 1;
   const int S = a.S, G = a.G;
   const int64_t hoff = (int64_t)bhk * S;               // rows of this K/V head
   const int64_t qoff = hoff * G;                       // first row of the group's first query head
-  const int key0 = kblk * BLK + 32 * w;
-  const int key = key0 + (l & 31);
-  const bool wave_on = key0 < S;
+  const int key0 = kblk * PAIR_KEYS + 32 * pair;
 
-  v8i kf[2], vf[2];                                    // this wave's 32 keys, both halves of d
+  v8i kf[2], vf[2];                                    // the pair's 32 keys, both halves of d
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    kf[h] = frag_global(a.K + hoff * HD, wave_on ? key : 0, h);
-    if (WANT_DK) vf[h] = frag_global(a.V + hoff * HD, wave_on ? key : 0, h);
+    kf[h] = frag_global(a.K + hoff * HD, key0 + (l & 31), h);
+    vf[h] = frag_global(a.V + hoff * HD, key0 + (l & 31), h);
   }
   const float rho_p = *a.scale_p, rho_ds = *a.scale_ds;
   const float c = a.softmax_scale * 1.44269504088896340736f * (*a.sinv_q) * (*a.sinv_k);
   const float cdpk = (*a.sinv_do) * (*a.sinv_v) * (rho_ds / rho_p);   // dP scale times rho_ds / rho_p
-  const bool clamp_p = !(rho_p <= 448.0f);   // rho_p P <= rho_p: the cast of P can only overflow for a scale above the format's maximum
+  saturating_converts();
 
-  v16f dv[4], dk[4];
+  v16f dv[2], dk[2];
 #pragma unroll
-  for (int d = 0; d < 4; ++d)
+  for (int d = 0; d < 2; ++d)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      if (WANT_DV) dv[d][r] = 0.0f;
-      if (WANT_DK) dk[d][r] = 0.0f;
-    }
+    for (int r = 0; r < 16; ++r) { dv[d][r] = 0.0f; dk[d][r] = 0.0f; }
 
-  const int qb_first = CAUSAL ? (kblk * BLK) / STEP : 0;
+  const int qb_first = CAUSAL ? kblk : 0;              // PAIR_KEYS == STEP: the diagonal block comes first
   const int nqb = S / STEP - qb_first;                 // query blocks of one head this workgroup walks
   const int total = nqb * G;                           // ... and of the whole group: head after head, one stream
-  // first block (relative, within a head) this wave needs: blocks whose last query is below the wave's first key are skipped
-  const int skip = !wave_on ? nqb : (CAUSAL ? max(0, key0 / STEP - qb_first) : 0);
 
   const uint32_t group_bytes = (uint32_t)G * S * HD;
   const v4i rsrc_q = make_rsrc(a.Q + qoff * HD, group_bytes), rsrc_do = make_rsrc(a.dO8 + qoff * HD, group_bytes);
   const int64_t nrows = (int64_t)a.BH * S;
   const v4i rsrc_lse = make_rsrc(a.Dws + 2 * nrows + qoff, (uint32_t)G * S * 4), rsrc_d = make_rsrc(a.Dws + nrows + qoff, (uint32_t)G * S * 4);
+  // direct loads: two pieces (8 rows each) of Q and two of dO per wave and block, and the 64 row constants (even waves lse, odd
+  // waves D: two copies each, identical bytes)
   uint32_t off[2];
   tile_load_offsets(off);
   const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)smem);
-  const uint32_t lds_w = lds0 + 2048u * (uint32_t)__builtin_amdgcn_readfirstlane(w);
-  const bool rows_d = __builtin_amdgcn_readfirstlane(w) & 1;   // odd waves fetch D, even waves lse (two copies each: identical bytes)
+  const uint32_t lds_w = lds0 + 2048u * (uint32_t)w;
+  const bool rows_d = w & 1;
   int iss_i = 0, iss_g = 0;   // query block and head of the next block to issue (issue() is called once per block, in order)
-  auto issue = [&](auto stg) {  // the next block of the stream -> stage stg (= its number % 4); blocks past the end fetch zeros
+  auto issue = [&](auto stg) {  // the next block of the stream -> stage stg; blocks past the end fetch zeros
     const uint32_t row0 = (uint32_t)(iss_g * S + (qb_first + iss_i) * STEP);
     const uint32_t adv = iss_g < G ? row0 * HD : OOB;
     const uint32_t radv = iss_g < G ? row0 * 4 : OOB;
@@ -265,145 +275,135 @@ __global__ __launch_bounds__(kThreads, MODE == 0 ? 1 : 2) void attn_bwd_dkdv_ker
     load4_to_lds(rows_d ? rsrc_d : rsrc_lse, (uint32_t)(4 * l) + radv, lds0 + base + 2 * TILE + (rows_d ? 256u : 0u));
     if (++iss_i == nqb) { iss_i = 0; ++iss_g; }
   };
-  const RowFrag rf = rowfrag_addr();
-  const ColFrag cf = colfrag_addr();
+  // fragment addresses: rows of this wave's 32 queries; columns of its half of the head dimension, read r of the transposing
+  // read covering queries 16 r + 8 g .. + 7 (the swizzle does not change from read to read); the exchange tiles in that order
+  RowFrag rf = rowfrag_addr();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) { rf.a[h][0] += 4096u * half; rf.a[h][1] += 4096u * half; }
+  const int crow = 8 * g + ((l & 15) >> 1);
+  uint32_t ca[2];
+#pragma unroll
+  for (int d = 0; d < 2; ++d) ca[d] = (uint32_t)(crow * HD + (((4 * half + 2 * d + ((l & 16) >> 4)) ^ swz(crow)) << 4) + 8 * (l & 1));
+  const uint8_t* xbase = smem + PAIR_STAGES * KV_STAGE + pair * XCHG;   // + 2048 for dS
+  // (the 16-byte halves of an exchange row trade places with bit 3 of the row: one read touches rows 0..7 and 8..15 together)
+  const uint8_t* xread = xbase + crow * 32 + ((l & 16) ^ (16 * g)) + 8 * (l & 1);
+  uint8_t* xwrite = const_cast<uint8_t*>(xbase) + (32 * half + (l & 31)) * 32 + ((16 * g) ^ (2 * (l & 8)));
+  const uint32_t row_const = 2 * TILE + 4 * (32 * half + (l & 31));           // lse - log2 rho_p; + 256: D rho_ds / rho_p
+  const int q_rel = 32 * half + (l & 31) - 32 * pair - 4 * g;                 // this lane's query of the diagonal block against key register 0
 
-  // S and dP tiles with lane = key: element r of tile qt is query qbase + 32 qt + 8 (r/4) + 4 g + (r%4)
-  auto scores = [&](auto stg, v16f* st, v16f* dp) {
-    const uint8_t* sq = smem + decltype(stg)::value * KV_STAGE;
-    const uint8_t* sdo = sq + TILE;
-#pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        st[qt][r] = 0.0f;
-        if (WANT_DK) dp[qt][r] = 0.0f;
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        st[qt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(read_rowfrag(sq, rf, qt, h), kf[h], st[qt], 0, 0, 0, 0, 0, 0);
-        if (WANT_DK) dp[qt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(read_rowfrag(sdo, rf, qt, h), vf[h], dp[qt], 1, 0, 0, 0, 0, 0);
-      }
-    }
-  };
-
-  FOG_SETTLE(kf[0]); FOG_SETTLE(kf[1]);
-  if (WANT_DK) { FOG_SETTLE(vf[0]); FOG_SETTLE(vf[1]); }
+  FOG_SETTLE(kf[0]); FOG_SETTLE(kf[1]); FOG_SETTLE(vf[0]); FOG_SETTLE(vf[1]);
   issue(Stg<0>{});
   issue(Stg<1>{});
-  issue(Stg<2>{});
-  __builtin_amdgcn_s_waitcnt(0x0F7A);  // vmcnt = 10: block 0 has landed (5 direct loads per thread and block)
-  __syncthreads();
-  v16f sa[2], da[2], sb[2], db[2];   // without the prefetch only sa / da are used
-  if (PREFETCH && skip == 0 && total > 0) scores(Stg<0>{}, sa, da);
 
+  auto colfrag = [&](const uint8_t* tile, int d) {
+    v8i f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const v2i v = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(tile + ca[d] + 2048 * r));
+      f[2 * r] = v[0];
+      f[2 * r + 1] = v[1];
+    }
+    return f;
+  };
+  auto packed = [&](int which) {   // 0: P~, 1: dS~ of a block of 64 queries, lane = key position
+    v8i f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const v2i v = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(xread + 2048 * which + 512 * r));
+      f[2 * r] = v[0];
+      f[2 * r + 1] = v[1];
+    }
+    return f;
+  };
+  auto clear = [&](v16f& x) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = 0.0f;
+  };
+
+  __builtin_amdgcn_s_waitcnt(0x0F75);   // vmcnt = 5: block 0 has landed (5 direct loads per thread and block)
+  __syncthreads();
   int cur_i = 0;
-  auto block = [&](const bool CLAMP_P, auto stg, int it, v16f* st, v16f* dp, v16f* stn, v16f* dpn) __attribute__((always_inline)) {
-    constexpr int STG = decltype(stg)::value;   // = it % NSTAGE
-    // vmcnt = 5: block it + 1 has landed (its scores are produced during this block); without the
-    // prefetch only block it is needed and two younger blocks may stay in flight (vmcnt = 10).
-    // lgkmcnt = 0: own LDS reads done
-    if (PREFETCH) __builtin_amdgcn_s_waitcnt(0x0075);
-    else if (it > 0) __builtin_amdgcn_s_waitcnt(0x007A);
-    if (PREFETCH || it > 0) __syncthreads();
-    issue(Stg<(STG + 3) % NSTAGE>{});   // block it + 3
-    const int i = cur_i, i_next = i + 1 == nqb ? 0 : i + 1;   // query block within its head, of this block and of the next
-    cur_i = i_next;
-    const bool cur = i >= skip, nxt = i_next >= skip && it + 1 < total;
-    if (PREFETCH) {
-      if (nxt) scores(Stg<(STG + 1) % NSTAGE>{}, stn, dpn);
-    } else if (cur) {
-      scores(stg, st, dp);
+  auto block = [&](const bool CLAMP, auto stg, int it) __attribute__((always_inline)) {
+    constexpr int STG = decltype(stg)::value;
+    const uint8_t* sq = smem + STG * KV_STAGE;
+    const uint8_t* sdo = sq + TILE;
+    const float lse = *reinterpret_cast<const float*>(sq + row_const);
+    const float Dq = *reinterpret_cast<const float*>(sq + row_const + 256);
+    v16f st, dp;
+    clear(st); clear(dp);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      st = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kf[h], read_rowfrag(sq, rf, 0, h), st, 0, 0, 0, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf[h], read_rowfrag(sdo, rf, 0, h), dp, 0, 1, 0, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (cur) {
-      const uint8_t* sq = smem + STG * KV_STAGE;
-      const uint8_t* sdo = sq + TILE;
-      const float* srow = reinterpret_cast<const float*>(sq + 2 * TILE);   // [0..63] lse - log2 rho_p, [64..127] D rho_ds / rho_p
-      const int qbase = (qb_first + i) * STEP;
-      if (CAUSAL && qbase < key0 + 31) {   // diagonal blocks: queries before the key see nothing of it
+    uint32_t pk[4], dsk[4];
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt)
+    for (int qd = 0; qd < 4; ++qd) {
+      float p[4], s[4];
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (qbase + 32 * qt + 8 * (r >> 2) + 4 * g + (r & 3) < key) st[qt][r] = -INFINITY;
+      for (int e = 0; e < 4; ++e) {
+        p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[4 * qd + e], c, -lse));          // rho_p P
+        s[e] = p[e] * __builtin_fmaf(dp[4 * qd + e], cdpk, -Dq);                         // rho_ds dS
+        if (CLAMP) s[e] = __builtin_amdgcn_fmed3f(s[e], -57344.0f, 57344.0f);
       }
-      v8i pf, dsf;
+      const uint32_t plo = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], any_u32(), false), slo = __builtin_amdgcn_cvt_pk_bf8_f32(s[0], s[1], any_u32(), false);
+      pk[qd] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], plo, true);
+      dsk[qd] = __builtin_amdgcn_cvt_pk_bf8_f32(s[2], s[3], slo, true);
+    }
+    if (CAUSAL && cur_i == 0) {
+      // The first query block of every head is the diagonal one (PAIR_KEYS == STEP): a query sees nothing of the keys after it.
+      // The codes of those are cleared here, whatever the exponential of a score that has no place in its row became.
+      int q = q_rel;
+      asm volatile("" : "+v"(q));           // the masks are made here, not kept in registers over the loop
 #pragma unroll
-      for (int qt = 0; qt < 2; ++qt) {
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-          const int qi = 32 * qt + 8 * qd + 4 * g;
-          const float4 ls = *reinterpret_cast<const float4*>(srow + qi);
-          float4 dd = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-          if (WANT_DK) dd = *reinterpret_cast<const float4*>(srow + 64 + qi);
-          const float lsv[4] = {ls.x, ls.y, ls.z, ls.w}, ddv[4] = {dd.x, dd.y, dd.z, dd.w};
-          float pq[4];
-#pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const int r = 4 * qd + b;
-            pq[b] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[qt][r], c, -lsv[b]));            // rho_p P
-            if (WANT_DK) dp[qt][r] = pq[b] * __builtin_fmaf(dp[qt][r], cdpk, -ddv[b]);        // rho_ds dS, left in the registers of dP
-          }
-          if (WANT_DV) {
-            if (CLAMP_P) {
-              pf[4 * qt + qd] = (int)cvt4_fp8<FOG_E4M3>(pq[0], pq[1], pq[2], pq[3]);
-            } else {
-              uint32_t pk = __builtin_amdgcn_cvt_pk_fp8_f32(pq[0], pq[1], any_u32(), false);
-              pf[4 * qt + qd] = (int)__builtin_amdgcn_cvt_pk_fp8_f32(pq[2], pq[3], pk, true);
-            }
-          }
-        }
+      for (int qd = 0; qd < 4; ++qd) {
+        const int n = q - 8 * qd + 1;       // keys 8 qd .. 8 qd + n - 1 count
+        const uint32_t m = n <= 0 ? 0u : n >= 4 ? 0xFFFFFFFFu : (1u << (8 * n)) - 1u;
+        pk[qd] &= m;
+        dsk[qd] &= m;
       }
-      if (WANT_DK) {
-        // the clamp before the cast of dS runs only when the block holds a magnitude above the largest finite E5M2 value
-        // (see the dQ kernel); finding that out costs half an instruction per value, the clamp one
-        if (__builtin_expect(__any(block_absmax(dp) > 57344.0f), 0)) clamp_block(dp);
-#pragma unroll
-        for (int qt = 0; qt < 2; ++qt)
-#pragma unroll
-          for (int qd = 0; qd < 4; ++qd) {
-            const uint32_t pk = __builtin_amdgcn_cvt_pk_bf8_f32(dp[qt][4 * qd + 0], dp[qt][4 * qd + 1], any_u32(), false);
-            dsf[4 * qt + qd] = (int)__builtin_amdgcn_cvt_pk_bf8_f32(dp[qt][4 * qd + 2], dp[qt][4 * qd + 3], pk, true);
-          }
-      }
-      // dV^T += dO^T P~ ;  dK^T += Q^T dS~   (contraction over the 64 queries of this step)
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        if (WANT_DV) dv[d] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(read_colfrag(sdo, cf, d), pf, dv[d], 1, 0, 0, 0, 0, 0);
-        if (WANT_DK) dk[d] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(read_colfrag(sq, cf, d), dsf, dk[d], 0, 1, 0, 0, 0, 0);
-      }
+    }
+    cur_i = cur_i + 1 == nqb ? 0 : cur_i + 1;
+    *reinterpret_cast<uint4*>(xwrite) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+    *reinterpret_cast<uint4*>(xwrite + 2048) = make_uint4(dsk[0], dsk[1], dsk[2], dsk[3]);
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt = 0
+    __syncthreads();                      // both halves of the block are in the exchange tiles
+    const v8i pf = packed(0), dsf = packed(1);
+    const v8i o0 = colfrag(sdo, 0), q0 = colfrag(sq, 0), o1 = colfrag(sdo, 1), q1 = colfrag(sq, 1);
+    __builtin_amdgcn_s_waitcnt(0x0070);   // every fragment of this block is in registers, block it + 1 has landed
+    __syncthreads();
+    issue(stg);                           // block it + 2, into the stage of this block
+    dv[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(o0, pf, dv[0], 1, 0, 0, 0, 0, 0);
+    dk[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(q0, dsf, dk[0], 0, 1, 0, 0, 0, 0);
+    dv[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(o1, pf, dv[1], 1, 0, 0, 0, 0, 0);
+    dk[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(q1, dsf, dk[1], 0, 1, 0, 0, 0, 0);
+  };
+  // two blocks per trip: the ring stage is a constant in each copy
+  auto trips = [&](const bool CLAMP) __attribute__((always_inline)) {
+    for (int it = 0; it < total; it += PAIR_STAGES) {
+      block(CLAMP, Stg<0>{}, it);
+      if (it + 1 < total) block(CLAMP, Stg<1>{}, it + 1);
     }
   };
-  // The saturating form of the P cast is only needed for a scale above the format's maximum; the
-  // choice is made once, outside the loop, so that the loop body stays one straight-line block.
-  // four blocks per trip: the ring stage is a constant in each copy, and the score registers just swap roles
-  auto trips = [&](const bool CLAMP_P) __attribute__((always_inline)) {
-    for (int it = 0; it < total; it += NSTAGE) {
-      block(CLAMP_P, Stg<0>{}, it, sa, da, sb, db);
-      if (it + 1 < total) block(CLAMP_P, Stg<1>{}, it + 1, sb, db, sa, da);
-      if (it + 2 < total) block(CLAMP_P, Stg<2>{}, it + 2, sa, da, sb, db);
-      if (it + 3 < total) block(CLAMP_P, Stg<3>{}, it + 3, sb, db, sa, da);
-    }
-  };
-  if (clamp_p) trips(true);
-  else         trips(false);
+  // the converts saturate finite values; only a scale beyond any gradient's range could make rho_ds dS infinite
+  if (rho_ds > 1.0e18f) trips(true);
+  else                  trips(false);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): no direct load may still be writing LDS when the workgroup retires
-  if (!wave_on) return;
   const float sdv = (*a.sinv_do) / rho_p;
   const float sdk = a.softmax_scale * (*a.sinv_q) / rho_ds;
-  uint16_t* dvrow = a.dV + (hoff + key) * HD;
-  uint16_t* dkrow = a.dK + (hoff + key) * HD;
+  const int64_t orow = hoff + key0 + key_of_position(l & 31);
+  uint16_t* dvrow = a.dV + orow * HD + 64 * half;
+  uint16_t* dkrow = a.dK + orow * HD + 64 * half;
 #pragma unroll
-  for (int d = 0; d < 4; ++d)
+  for (int d = 0; d < 2; ++d)
 #pragma unroll
     for (int qd = 0; qd < 4; ++qd) {
       const int col = 32 * d + 8 * qd + 4 * g;
-      if (WANT_DV)
-        *reinterpret_cast<uint2*>(dvrow + col) = make_uint2(pack_bf16x2(dv[d][4 * qd] * sdv, dv[d][4 * qd + 1] * sdv),
-                                                            pack_bf16x2(dv[d][4 * qd + 2] * sdv, dv[d][4 * qd + 3] * sdv));
-      if (WANT_DK)
-        *reinterpret_cast<uint2*>(dkrow + col) = make_uint2(pack_bf16x2(dk[d][4 * qd] * sdk, dk[d][4 * qd + 1] * sdk),
-                                                            pack_bf16x2(dk[d][4 * qd + 2] * sdk, dk[d][4 * qd + 3] * sdk));
+      *reinterpret_cast<uint2*>(dvrow + col) = make_uint2(pack_bf16x2(dv[d][4 * qd] * sdv, dv[d][4 * qd + 1] * sdv),
+                                                          pack_bf16x2(dv[d][4 * qd + 2] * sdv, dv[d][4 * qd + 3] * sdv));
+      *reinterpret_cast<uint2*>(dkrow + col) = make_uint2(pack_bf16x2(dk[d][4 * qd] * sdk, dk[d][4 * qd + 1] * sdk),
+                                                          pack_bf16x2(dk[d][4 * qd + 2] * sdk, dk[d][4 * qd + 3] * sdk));
     }
 }
 
@@ -611,25 +611,9 @@ static fog_status bwd_launch(int B, int H, int H_kv, int S, float softmax_scale,
   const int64_t rows = (int64_t)a.BH * S;
   attn_bwd_rowdot_kernel<<<(int)((rows + 15) / 16), kThreads, 0, s>>>(a.O, a.dO, a.lse, a.scale_p, a.scale_ds, a.Dws, rows,
                                                                       amax_ds ? a.amax_ds : nullptr);
-  const int grid = a.BH * a.nblk, grid_kv = a.BHkv * a.nblk;
-  // dV and dK as two launches (two workgroups per CU each) when there are enough key blocks to fill the
-  // chip four times over; with few key/value heads the single combined launch balances better.
-  const bool split = grid_kv >= 1024;
-  if (causal) {
-    if (split) {
-      attn_bwd_dkdv_kernel<true, 1><<<grid_kv, kThreads, 0, s>>>(a);
-      attn_bwd_dkdv_kernel<true, 2><<<grid_kv, kThreads, 0, s>>>(a);
-    } else {
-      attn_bwd_dkdv_kernel<true, 0><<<grid_kv, kThreads, 0, s>>>(a);
-    }
-  } else {
-    if (split) {
-      attn_bwd_dkdv_kernel<false, 1><<<grid_kv, kThreads, 0, s>>>(a);
-      attn_bwd_dkdv_kernel<false, 2><<<grid_kv, kThreads, 0, s>>>(a);
-    } else {
-      attn_bwd_dkdv_kernel<false, 0><<<grid_kv, kThreads, 0, s>>>(a);
-    }
-  }
+  const int grid = a.BH * a.nblk, grid_kv = a.BHkv * (S / PAIR_KEYS);
+  if (causal) attn_bwd_dkdv_kernel<true><<<grid_kv, PAIR_THREADS, 0, s>>>(a);
+  else        attn_bwd_dkdv_kernel<false><<<grid_kv, PAIR_THREADS, 0, s>>>(a);
   if (causal) { if (amax_ds) attn_bwd_dq_kernel<true, true><<<grid, kThreads, 0, s>>>(a); else attn_bwd_dq_kernel<true, false><<<grid, kThreads, 0, s>>>(a); }
   else        { if (amax_ds) attn_bwd_dq_kernel<false, true><<<grid, kThreads, 0, s>>>(a); else attn_bwd_dq_kernel<false, false><<<grid, kThreads, 0, s>>>(a); }
   return fog_launch_status();

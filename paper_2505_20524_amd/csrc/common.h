@@ -55,6 +55,10 @@ FOG_DEVICE uint32_t cvt4_fp8(float a, float b, float c, float d) {
   return r;
 }
 
+// Switches the wave's FP8 converts to saturation (MODE.FP16_OVFL): a finite value beyond the format becomes the largest finite
+// code, which makes the clamp above unnecessary; a NaN keeps its NaN code, an infinity is not clamped.
+FOG_DEVICE void saturating_converts() { __builtin_amdgcn_s_setreg(1 | (23 << 6) | (0 << 11), 1); }
+
 // The same cast for tensors that may hold NaN (the bulk casts): the clamp above returns the smallest of
 // its operands for a NaN input, i.e. the largest finite code with a minus sign, so NaN inputs are patched
 // afterwards to the NaN code 0x7F with the input's sign.  Infinities saturate through the clamp.  The test

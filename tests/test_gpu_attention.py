@@ -182,6 +182,16 @@ def test_backward_with_a_stale_ds_scale_saturates_like_the_oracle(factor):
     run_bwd(c, B, H, S, 1 / math.sqrt(128), True, [(b, h) for b in range(B) for h in range(H)], do, ds_scale_factor=factor)
 
 
+@pytest.mark.parametrize("causal", [True, False])
+def test_backward_with_a_scale_beyond_any_gradient(causal):
+    """A scale of dS so large (above 1e18) that rho_ds dS may leave binary32: the dK/dV kernel clamps before its casts, which
+    saturate finite values only.  Every dS that is not tiny saturates, in the oracle too."""
+    B, H, S = 1, 2, 192
+    q, k, v, do = synth.small_attention(2700, B, H, S)
+    c = cast_all(q, k, v, do)
+    run_bwd(c, B, H, S, 1 / math.sqrt(128), causal, [(b, h) for b in range(B) for h in range(H)], do, ds_scale_factor=2.0 ** 50)
+
+
 def gqa_case(seed, B, H, Hkv, S):
     """Grouped-query inputs: Q and dO with H heads, K and V with H_kv heads (same recipe, own seed)."""
     q, _, _, do = synth.small_attention(seed, B, H, S)
