@@ -218,16 +218,21 @@ constexpr int PAIR_STAGES = 2;
 // Position of a key among the 32 bytes of an exchange row (and so the lane that ends up with it): a lane of the scores holds
 // keys 8 qd + 4 g + b, and stores them as its 16 bytes 4 qd + b of half g.
 FOG_DEVICE int key_of_position(int pos) { return 8 * ((pos >> 2) & 3) + 4 * (pos >> 4) + (pos & 3); }
-template <bool CAUSAL>
-__global__ __launch_bounds__(PAIR_THREADS, 3) void attn_bwd_dkdv_kernel(BwdArgs a) {
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[PAIR_STAGES * KV_STAGE + 2 * XCHG];
+// QSPLIT: both pairs own the same 32 keys and take the query blocks in turns, each through a ring of its own; the second pair's
+// sums are added to the first's at the end.  Twice the workgroups and half the blocks in each, for launches that cannot fill the
+// chip otherwise; a stage then serves 32 keys instead of 64.
+template <bool CAUSAL, bool QSPLIT>
+__global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_kernel(BwdArgs a) {
+  constexpr int KEYS = QSPLIT ? 32 : PAIR_KEYS, TURNS = QSPLIT ? 2 : 1;   // keys of a workgroup, pairs that share them
+  constexpr int RING = PAIR_STAGES * KV_STAGE;                            // bytes of one ring
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[TURNS * RING + 2 * XCHG];
   const int bhk = blockIdx.x % a.BHkv;                 // key/value head; its query heads are bhk * G .. + G - 1
   const int kblk = blockIdx.x / a.BHkv;                // early key blocks see the most queries: launched first
   const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, g = l >> 5, pair = w >> 1, half = w & 1;
   const int S = a.S, G = a.G;
   const int64_t hoff = (int64_t)bhk * S;               // rows of this K/V head
   const int64_t qoff = hoff * G;                       // first row of the group's first query head
-  const int key0 = kblk * PAIR_KEYS + 32 * pair;
+  const int key0 = kblk * KEYS + (QSPLIT ? 0 : 32 * pair);
 
   v8i kf[2], vf[2];                                    // the pair's 32 keys, both halves of d
 #pragma unroll
@@ -246,7 +251,7 @@ __global__ __launch_bounds__(PAIR_THREADS, 3) void attn_bwd_dkdv_kernel(BwdArgs 
 #pragma unroll
     for (int r = 0; r < 16; ++r) { dv[d][r] = 0.0f; dk[d][r] = 0.0f; }
 
-  const int qb_first = CAUSAL ? kblk : 0;              // PAIR_KEYS == STEP: the diagonal block comes first
+  const int qb_first = CAUSAL ? key0 / STEP : 0;       // the diagonal block comes first
   const int nqb = S / STEP - qb_first;                 // query blocks of one head this workgroup walks
   const int total = nqb * G;                           // ... and of the whole group: head after head, one stream
 
@@ -254,26 +259,39 @@ __global__ __launch_bounds__(PAIR_THREADS, 3) void attn_bwd_dkdv_kernel(BwdArgs 
   const v4i rsrc_q = make_rsrc(a.Q + qoff * HD, group_bytes), rsrc_do = make_rsrc(a.dO8 + qoff * HD, group_bytes);
   const int64_t nrows = (int64_t)a.BH * S;
   const v4i rsrc_lse = make_rsrc(a.Dws + 2 * nrows + qoff, (uint32_t)G * S * 4), rsrc_d = make_rsrc(a.Dws + nrows + qoff, (uint32_t)G * S * 4);
-  // direct loads: two pieces (8 rows each) of Q and two of dO per wave and block, and the 64 row constants (even waves lse, odd
-  // waves D: two copies each, identical bytes)
-  uint32_t off[2];
-  tile_load_offsets(off);
-  const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)smem);
-  const uint32_t lds_w = lds0 + 2048u * (uint32_t)w;
+  // direct loads: the waves that share a ring fetch NP pieces (8 rows each) of Q and of dO each per block, and the 64 row constants
+  // (even waves lse, odd waves D; four waves leave two copies each, identical bytes)
+  constexpr int NP = 2 * TURNS, LOADS = 2 * NP + 1;
+  const int lw = QSPLIT ? half : w;                    // number of this wave among those of its ring
+  uint32_t off[NP];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    const int row = 8 * (NP * lw + j) + (l >> 3);
+    off[j] = (uint32_t)(row * HD + (((l & 7) ^ swz(row)) << 4));
+  }
+  uint8_t* ring = smem + (QSPLIT ? pair * RING : 0);
+  const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)ring);
+  const uint32_t lds_w = lds0 + 1024u * NP * (uint32_t)lw;
   const bool rows_d = w & 1;
-  int iss_i = 0, iss_g = 0;   // query block and head of the next block to issue (issue() is called once per block, in order)
+  // query block and head of the next block to issue (issue() is called once per block, in order); a pair that takes turns starts
+  // at its own and skips the other's
+  int iss_i = 0, iss_g = 0;
+  auto next_block = [&](int& i, int& head) { if (++i == nqb) { i = 0; ++head; } };
+  if (QSPLIT && pair) next_block(iss_i, iss_g);
+  int cur_i = iss_i;          // query block (within its head) of the block in hand
   auto issue = [&](auto stg) {  // the next block of the stream -> stage stg; blocks past the end fetch zeros
     const uint32_t row0 = (uint32_t)(iss_g * S + (qb_first + iss_i) * STEP);
     const uint32_t adv = iss_g < G ? row0 * HD : OOB;
     const uint32_t radv = iss_g < G ? row0 * 4 : OOB;
     const uint32_t base = (uint32_t)decltype(stg)::value * KV_STAGE;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NP; ++j) {
       load16_to_lds(rsrc_q, off[j] + adv, lds_w + base + 1024u * j);
       load16_to_lds(rsrc_do, off[j] + adv, lds_w + base + TILE + 1024u * j);
     }
     load4_to_lds(rows_d ? rsrc_d : rsrc_lse, (uint32_t)(4 * l) + radv, lds0 + base + 2 * TILE + (rows_d ? 256u : 0u));
-    if (++iss_i == nqb) { iss_i = 0; ++iss_g; }
+#pragma unroll
+    for (int n = 0; n < TURNS; ++n) next_block(iss_i, iss_g);
   };
   // fragment addresses: rows of this wave's 32 queries; columns of its half of the head dimension, read r of the transposing
   // read covering queries 16 r + 8 g .. + 7 (the swizzle does not change from read to read); the exchange tiles in that order
@@ -284,12 +302,12 @@ __global__ __launch_bounds__(PAIR_THREADS, 3) void attn_bwd_dkdv_kernel(BwdArgs 
   uint32_t ca[2];
 #pragma unroll
   for (int d = 0; d < 2; ++d) ca[d] = (uint32_t)(crow * HD + (((4 * half + 2 * d + ((l & 16) >> 4)) ^ swz(crow)) << 4) + 8 * (l & 1));
-  const uint8_t* xbase = smem + PAIR_STAGES * KV_STAGE + pair * XCHG;   // + 2048 for dS
+  const uint8_t* xbase = smem + TURNS * RING + pair * XCHG;   // + 2048 for dS
   // (the 16-byte halves of an exchange row trade places with bit 3 of the row: one read touches rows 0..7 and 8..15 together)
   const uint8_t* xread = xbase + crow * 32 + ((l & 16) ^ (16 * g)) + 8 * (l & 1);
   uint8_t* xwrite = const_cast<uint8_t*>(xbase) + (32 * half + (l & 31)) * 32 + ((16 * g) ^ (2 * (l & 8)));
   const uint32_t row_const = 2 * TILE + 4 * (32 * half + (l & 31));           // lse - log2 rho_p; + 256: D rho_ds / rho_p
-  const int q_rel = 32 * half + (l & 31) - 32 * pair - 4 * g;                 // this lane's query of the diagonal block against key register 0
+  const int q_rel = qb_first * STEP + 32 * half + (l & 31) - key0 - 4 * g;    // this lane's query of the diagonal block against key register 0
 
   FOG_SETTLE(kf[0]); FOG_SETTLE(kf[1]); FOG_SETTLE(vf[0]); FOG_SETTLE(vf[1]);
   issue(Stg<0>{});
@@ -320,12 +338,11 @@ __global__ __launch_bounds__(PAIR_THREADS, 3) void attn_bwd_dkdv_kernel(BwdArgs 
     for (int r = 0; r < 16; ++r) x[r] = 0.0f;
   };
 
-  __builtin_amdgcn_s_waitcnt(0x0F75);   // vmcnt = 5: block 0 has landed (5 direct loads per thread and block)
+  __builtin_amdgcn_s_waitcnt(0x0F70 | LOADS);   // vmcnt = LOADS: block 0 has landed
   __syncthreads();
-  int cur_i = 0;
   auto block = [&](const bool CLAMP, auto stg, int it) __attribute__((always_inline)) {
     constexpr int STG = decltype(stg)::value;
-    const uint8_t* sq = smem + STG * KV_STAGE;
+    const uint8_t* sq = ring + STG * KV_STAGE;
     const uint8_t* sdo = sq + TILE;
     const float lse = *reinterpret_cast<const float*>(sq + row_const);
     const float Dq = *reinterpret_cast<const float*>(sq + row_const + 256);
@@ -352,7 +369,7 @@ __global__ __launch_bounds__(PAIR_THREADS, 3) void attn_bwd_dkdv_kernel(BwdArgs 
       dsk[qd] = __builtin_amdgcn_cvt_pk_bf8_f32(s[2], s[3], slo, true);
     }
     if (CAUSAL && cur_i == 0) {
-      // The first query block of every head is the diagonal one (PAIR_KEYS == STEP): a query sees nothing of the keys after it.
+      // The first query block of every head is the diagonal one (KEYS divides STEP): a query sees nothing of the keys after it.
       // The codes of those are cleared here, whatever the exponential of a score that has no place in its row became.
       int q = q_rel;
       asm volatile("" : "+v"(q));           // the masks are made here, not kept in registers over the loop
@@ -364,7 +381,8 @@ __global__ __launch_bounds__(PAIR_THREADS, 3) void attn_bwd_dkdv_kernel(BwdArgs 
         dsk[qd] &= m;
       }
     }
-    cur_i = cur_i + 1 == nqb ? 0 : cur_i + 1;
+#pragma unroll
+    for (int n = 0; n < TURNS; ++n) cur_i = cur_i + 1 == nqb ? 0 : cur_i + 1;
     *reinterpret_cast<uint4*>(xwrite) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
     *reinterpret_cast<uint4*>(xwrite + 2048) = make_uint4(dsk[0], dsk[1], dsk[2], dsk[3]);
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt = 0
@@ -379,17 +397,44 @@ __global__ __launch_bounds__(PAIR_THREADS, 3) void attn_bwd_dkdv_kernel(BwdArgs 
     dv[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(o1, pf, dv[1], 1, 0, 0, 0, 0, 0);
     dk[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(q1, dsf, dk[1], 0, 1, 0, 0, 0, 0);
   };
+  // Blocks of a pair (one past the end is a block of zeros: P is 1 there, but dO, D and dP are 0 and add nothing).
+  const int turns = (total + TURNS - 1) / TURNS;
   // two blocks per trip: the ring stage is a constant in each copy
   auto trips = [&](const bool CLAMP) __attribute__((always_inline)) {
-    for (int it = 0; it < total; it += PAIR_STAGES) {
+    for (int it = 0; it < turns; it += PAIR_STAGES) {
       block(CLAMP, Stg<0>{}, it);
-      if (it + 1 < total) block(CLAMP, Stg<1>{}, it + 1);
+      if (it + 1 < turns) block(CLAMP, Stg<1>{}, it + 1);
     }
   };
   // the converts saturate finite values; only a scale beyond any gradient's range could make rho_ds dS infinite
   if (rho_ds > 1.0e18f) trips(true);
   else                  trips(false);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): no direct load may still be writing LDS when the workgroup retires
+  if (QSPLIT) {
+    // the second pair's sums through LDS (both rings are done with): 16 bytes per lane and instruction
+    float4* part = reinterpret_cast<float4*>(smem) + half * (16 * 64) + l;
+    static_assert(2 * 16 * 64 * 16 <= TURNS * RING || !QSPLIT, "the sums of two waves fit the rings");
+    __syncthreads();
+    if (pair) {
+#pragma unroll
+      for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd) {
+          part[(8 * d + qd) * 64] = make_float4(dv[d][4 * qd], dv[d][4 * qd + 1], dv[d][4 * qd + 2], dv[d][4 * qd + 3]);
+          part[(8 * d + 4 + qd) * 64] = make_float4(dk[d][4 * qd], dk[d][4 * qd + 1], dk[d][4 * qd + 2], dk[d][4 * qd + 3]);
+        }
+    }
+    __syncthreads();
+    if (pair) return;
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        const float4 x = part[(8 * d + qd) * 64], y = part[(8 * d + 4 + qd) * 64];
+        dv[d][4 * qd] += x.x; dv[d][4 * qd + 1] += x.y; dv[d][4 * qd + 2] += x.z; dv[d][4 * qd + 3] += x.w;
+        dk[d][4 * qd] += y.x; dk[d][4 * qd + 1] += y.y; dk[d][4 * qd + 2] += y.z; dk[d][4 * qd + 3] += y.w;
+      }
+  }
   const float sdv = (*a.sinv_do) / rho_p;
   const float sdk = a.softmax_scale * (*a.sinv_q) / rho_ds;
   const int64_t orow = hoff + key0 + key_of_position(l & 31);
@@ -612,8 +657,18 @@ static fog_status bwd_launch(int B, int H, int H_kv, int S, float softmax_scale,
   attn_bwd_rowdot_kernel<<<(int)((rows + 15) / 16), kThreads, 0, s>>>(a.O, a.dO, a.lse, a.scale_p, a.scale_ds, a.Dws, rows,
                                                                       amax_ds ? a.amax_ds : nullptr);
   const int grid = a.BH * a.nblk, grid_kv = a.BHkv * (S / PAIR_KEYS);
-  if (causal) attn_bwd_dkdv_kernel<true><<<grid_kv, PAIR_THREADS, 0, s>>>(a);
-  else        attn_bwd_dkdv_kernel<false><<<grid_kv, PAIR_THREADS, 0, s>>>(a);
+  // Pairs in turns where the launch is bound by its longest workgroup (the first keys see every query block of every head of the
+  // group): up to half a workgroup per CU always, up to two where that workgroup walks 64 blocks or more.  Backward, us, without ->
+  // with: 36 workgroups of up to 36 blocks 46 -> 37, 68 of 68 74 -> 56, 256 of 64 82 -> 71, 512 of 256 338 -> 319; but 256 of 4
+  // 22 -> 25 and 512 of 32 72 -> 76.
+  const int longest = (S / STEP) * a.G;
+  if (grid_kv <= 128 || (grid_kv <= 512 && longest >= 64)) {
+    if (causal) attn_bwd_dkdv_kernel<true, true><<<2 * grid_kv, PAIR_THREADS, 0, s>>>(a);
+    else        attn_bwd_dkdv_kernel<false, true><<<2 * grid_kv, PAIR_THREADS, 0, s>>>(a);
+  } else {
+    if (causal) attn_bwd_dkdv_kernel<true, false><<<grid_kv, PAIR_THREADS, 0, s>>>(a);
+    else        attn_bwd_dkdv_kernel<false, false><<<grid_kv, PAIR_THREADS, 0, s>>>(a);
+  }
   if (causal) { if (amax_ds) attn_bwd_dq_kernel<true, true><<<grid, kThreads, 0, s>>>(a); else attn_bwd_dq_kernel<true, false><<<grid, kThreads, 0, s>>>(a); }
   else        { if (amax_ds) attn_bwd_dq_kernel<false, true><<<grid, kThreads, 0, s>>>(a); else attn_bwd_dq_kernel<false, false><<<grid, kThreads, 0, s>>>(a); }
   return fog_launch_status();

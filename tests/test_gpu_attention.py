@@ -451,3 +451,14 @@ def test_failing_attention_calls_leave_device_memory_untouched():
     assert fwd(p) == 0                                   # the same arguments, valid: the call runs and zeroes the abs-max first
     torch.cuda.synchronize()
     assert am.item() != -7.0
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,H,Hkv,S", [(3, 45, 45, 64), (2, 33, 33, 128), (1, 6, 2, 64), (1, 3, 1, 192)])
+def test_backward_workgroup_shapes(B, H, Hkv, S, causal):
+    """dK/dV with 64 keys per workgroup (more than 128 of them) and with 32 keys and two pairs that take the query blocks in
+    turns (few workgroups; an odd number of blocks leaves one turn empty): first, last and middle heads against the oracle."""
+    c, do = gqa_case(3400 + S + H, B, H, Hkv, S)
+    G = H // Hkv
+    heads = sorted({(b, h) for b in (0, B - 1) for hk in (0, Hkv // 2, Hkv - 1) for h in range(hk * G, hk * G + G)})
+    run_bwd(c, B, H, S, 1 / math.sqrt(128), causal, heads, do)
