@@ -89,10 +89,17 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without building a torch.cuda.Stream object around it: 0.5 us a call instead of 3.1 us, on calls
+# whose kernels take 5 us.  (Builds of torch without the getter take the object.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(code, where):
