@@ -56,14 +56,6 @@ FOG_DEVICE v4i make_rsrc(const void* base, uint32_t bytes) {
   return r;
 }
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-// Two floats -> packed bf16 with the hardware convert (round to nearest even).
-FOG_DEVICE uint32_t cvt_pk_bf16(float lo, float hi) {
-  f32x2 v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
 // Eight consecutive elements of row m of C from column n (< N) on: one 16-byte store where C allows it, element-wise at the
 // right edge and where C is not aligned.
 FOG_DEVICE void store_row_piece(const GemmArgs& g, int m, int n, uint4 v) {

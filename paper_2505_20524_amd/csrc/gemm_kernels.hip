@@ -407,7 +407,7 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
             for (int qd = 0; qd < 4; ++qd) {
               const float v0 = acc[i][j][4 * qd + 0] * alpha, v1 = acc[i][j][4 * qd + 1] * alpha;
               const float v2 = acc[i][j][4 * qd + 2] * alpha, v3 = acc[i][j][4 * qd + 3] * alpha;
-              *reinterpret_cast<uint2*>(epi + (l & 31) * WIDE + 64 * jj + 16 * qd + 8 * (l >> 5)) = make_uint2(cvt_pk_bf16(v0, v1), cvt_pk_bf16(v2, v3));
+              *reinterpret_cast<uint2*>(epi + (l & 31) * WIDE + 64 * jj + 16 * qd + 8 * (l >> 5)) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
             }
           }
 #pragma unroll
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
           for (int qd = 0; qd < 4; ++qd) {
             const float v0 = acc[i][j][4 * qd + 0] * alpha, v1 = acc[i][j][4 * qd + 1] * alpha;
             const float v2 = acc[i][j][4 * qd + 2] * alpha, v3 = acc[i][j][4 * qd + 3] * alpha;
-            *reinterpret_cast<uint2*>(buf + (l & 31) * EPI_STRIDE + 16 * qd + 8 * (l >> 5)) = make_uint2(cvt_pk_bf16(v0, v1), cvt_pk_bf16(v2, v3));
+            *reinterpret_cast<uint2*>(buf + (l & 31) * EPI_STRIDE + 16 * qd + 8 * (l >> 5)) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
           }
 #pragma unroll
           for (int t = 0; t < 2; ++t) {
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
           for (int qd = 0; qd < 4; ++qd) {
             const float v0 = acc[i][j][4 * qd + 0] * alpha, v1 = acc[i][j][4 * qd + 1] * alpha;
             const float v2 = acc[i][j][4 * qd + 2] * alpha, v3 = acc[i][j][4 * qd + 3] * alpha;
-            *reinterpret_cast<uint2*>(buf + (l & 31) * EPI_STRIDE + 16 * qd + 8 * (l >> 5)) = make_uint2(cvt_pk_bf16(v0, v1), cvt_pk_bf16(v2, v3));
+            *reinterpret_cast<uint2*>(buf + (l & 31) * EPI_STRIDE + 16 * qd + 8 * (l >> 5)) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
           }
 #pragma unroll
           for (int t = 0; t < 2; ++t) {

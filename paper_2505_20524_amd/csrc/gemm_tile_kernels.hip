@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kThreads, WPS) void fp8_gemm_tile_kernel(GemmArgs g
         for (int qd = 0; qd < 4; ++qd) {
           const v16f& x = acc[i][jp * JW + jj];
           *reinterpret_cast<uint2*>(epi + (l & 31) * STRIDE + 64 * jj + 16 * qd + 8 * (l >> 5)) =
-              make_uint2(cvt_pk_bf16(x[4 * qd + 0] * alpha, x[4 * qd + 1] * alpha), cvt_pk_bf16(x[4 * qd + 2] * alpha, x[4 * qd + 3] * alpha));
+              make_uint2(pack_bf16x2(x[4 * qd + 0] * alpha, x[4 * qd + 1] * alpha), pack_bf16x2(x[4 * qd + 2] * alpha, x[4 * qd + 3] * alpha));
         }
 #pragma unroll
       for (int t = 0; t < 32 / RPS; ++t) {
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kThreads) void gemm_tile_reduce_kernel(GemmArgs g, 
   }
   const float alpha = (*g.sinv_a) * (*g.sinv_b);
   *reinterpret_cast<uint2*>(blk + (l & 31) * STRIDE + 16 * qd + 8 * (l >> 5)) =
-      make_uint2(cvt_pk_bf16(acc.x * alpha, acc.y * alpha), cvt_pk_bf16(acc.z * alpha, acc.w * alpha));
+      make_uint2(pack_bf16x2(acc.x * alpha, acc.y * alpha), pack_bf16x2(acc.z * alpha, acc.w * alpha));
   __syncthreads();
   if (t < 128) {
     const int m = mb + (t >> 2), n = nb + 8 * (t & 3);

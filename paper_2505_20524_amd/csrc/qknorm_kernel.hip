@@ -3,7 +3,10 @@
 // cast of Appendix E with a caller-provided scale, as under delayed scaling).  The normalised
 // tensor is never stored: every bf16 element is read once and one FP8 byte is written, against
 // 2 + 2 + 2 + 2 + 1 bytes per element for normalise -> abs-max -> cast as separate passes.
-// HBM-bound.  A row of D elements is handled by D / 8 adjacent lanes (16 for the head size 128,
+// Bound by HBM, with the vector ALU close behind: the square root and the divisions of a row are computed by one lane of four (each
+// takes one of the four rows in flight), row sums are exchanged inside the vector ALU, and the casts go without clamp and NaN test
+// where the row's sum of squares and the scale say so (262144 x 128: 27.1 -> 24.1 us with the launch that clears the abs-max).
+// A row of D elements is handled by D / 8 adjacent lanes (16 for the head size 128,
 // four rows per wave); longer or odd rows take one wave per row and read the row twice.
 #include "common.h"
 #include "launch.h"
@@ -34,6 +37,26 @@ FOG_DEVICE void block_amax(float m, bool nan, uint32_t* amax_out) {
   }
 }
 
+// Sum over the LPR adjacent lanes of a row, in every lane: exchanges inside the vector ALU (quad permutes and mirrors within rows of
+// 16 lanes) where a shuffle goes through LDS; the partners hold the same partial sums as under an xor shuffle, so the bits agree.
+template <int CTRL>
+FOG_DEVICE float dpp_add(float s) {
+  return s + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), CTRL, 0xF, 0xF, false));
+}
+template <int LPR>
+FOG_DEVICE float row_sum(float s) {
+  s = dpp_add<0xB1>(s);                  // lane ^ 1
+  s = dpp_add<0x4E>(s);                  // lane ^ 2
+  s = dpp_add<0x141>(s);                 // the other four of eight (half-row mirror)
+  if (LPR >= 16) s = dpp_add<0x140>(s);  // the other eight of sixteen (row mirror)
+  if (LPR >= 32) s += __shfl_xor(s, 16, 64);
+  if (LPR >= 64) s += __shfl_xor(s, 32, 64);
+  return s;
+}
+// Value of lane u of every four.
+template <int U>
+FOG_DEVICE float quad_lane(float v) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x55 * U, 0xF, 0xF, false)); }
+
 // LPR lanes per row, each holding 8 consecutive elements (cols = 8 LPR); 64 / LPR rows per wave.
 template <int FMT, int LPR>
 __global__ __launch_bounds__(kThreads) void qknorm_rows_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t ldx, float gain,
@@ -43,6 +66,10 @@ __global__ __launch_bounds__(kThreads) void qknorm_rows_kernel(const uint16_t* _
   constexpr int U = 4;                  // rows per lane group and trip: four loads in flight
   const float rho = *scale;
   const int sub = threadIdx.x % LPR, rloc = threadIdx.x / LPR;
+  // |y| <= gain sqrt(cols) in rows with a finite sum of squares: with such a scale no product overflows, and the saturating converts
+  // need neither a clamp nor a NaN test
+  const bool plain = fabsf(rho) * gain <= 1.0e30f;
+  saturating_converts();
   float m = 0.0f;
   bool nan = false;
   auto fetch = [&](int64_t r0, uint4 (&v)[U]) {
@@ -54,16 +81,26 @@ __global__ __launch_bounds__(kThreads) void qknorm_rows_kernel(const uint16_t* _
     }
   };
   auto process = [&](int64_t r0, const uint4 (&v)[U]) {
+    float sum[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t r = r0 + u * RPB + rloc;
-      float f[8] = {bf16lo(v[u].x), bf16hi(v[u].x), bf16lo(v[u].y), bf16hi(v[u].y), bf16lo(v[u].z), bf16hi(v[u].z), bf16lo(v[u].w), bf16hi(v[u].w)};
+      const float f[8] = {bf16lo(v[u].x), bf16hi(v[u].x), bf16lo(v[u].y), bf16hi(v[u].y), bf16lo(v[u].z), bf16hi(v[u].z), bf16lo(v[u].w), bf16hi(v[u].w)};
       float s = 0.0f;
 #pragma unroll
       for (int k = 0; k < 8; ++k) s = __builtin_fmaf(f[k], f[k], s);
+      sum[u] = row_sum<LPR>(s);
+    }
+    // The square root and the two divisions cost as much as the rest of a row: of every four lanes each takes one of the four rows.
+    static_assert(U == 4, "one row per lane of a quad");
+    const float mine = sub & 2 ? (sub & 1 ? sum[3] : sum[2]) : (sub & 1 ? sum[1] : sum[0]);
+    const float inv_mine = inv_rms(mine, (float)(8 * LPR), gain);
+    const float invs[U] = {quad_lane<0>(inv_mine), quad_lane<1>(inv_mine), quad_lane<2>(inv_mine), quad_lane<3>(inv_mine)};
+    const bool all_plain = plain && sum[0] < INFINITY && sum[1] < INFINITY && sum[2] < INFINITY && sum[3] < INFINITY;
 #pragma unroll
-      for (int o = 1; o < LPR; o <<= 1) s += __shfl_xor(s, o, 64);
-      const float inv = inv_rms(s, (float)(8 * LPR), gain);
+    for (int u = 0; u < U; ++u) {
+      const int64_t r = r0 + u * RPB + rloc;
+      const float f[8] = {bf16lo(v[u].x), bf16hi(v[u].x), bf16lo(v[u].y), bf16hi(v[u].y), bf16lo(v[u].z), bf16hi(v[u].z), bf16lo(v[u].w), bf16hi(v[u].w)};
+      const float inv = invs[u];
       float y[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -72,8 +109,13 @@ __global__ __launch_bounds__(kThreads) void qknorm_rows_kernel(const uint16_t* _
       }
       if (r < rows) {
         uint2 o;
-        o.x = cvt4_fp8_nan<FMT>(y[0] * rho, y[1] * rho, y[2] * rho, y[3] * rho, &nan);
-        o.y = cvt4_fp8_nan<FMT>(y[4] * rho, y[5] * rho, y[6] * rho, y[7] * rho, &nan);
+        if (__builtin_expect(all_plain, 1)) {
+          o.x = cvt4_fp8_finite<FMT>(y[0] * rho, y[1] * rho, y[2] * rho, y[3] * rho);
+          o.y = cvt4_fp8_finite<FMT>(y[4] * rho, y[5] * rho, y[6] * rho, y[7] * rho);
+        } else {
+          o.x = cvt4_fp8_nan<FMT>(y[0] * rho, y[1] * rho, y[2] * rho, y[3] * rho, &nan);
+          o.y = cvt4_fp8_nan<FMT>(y[4] * rho, y[5] * rho, y[6] * rho, y[7] * rho, &nan);
+        }
         st_nt8(q + r * ldq + 8 * sub, o);
       }
     }

@@ -100,3 +100,26 @@ def test_in_place_without_codes_and_errors():
     assert call(*t) == 0
     torch.cuda.synchronize()
     assert am.item() == 0.0
+
+
+@pytest.mark.parametrize("fmt", [fp8.E4M3, fp8.E5M2])
+@pytest.mark.parametrize("rho", [0.5, 1.0e-30, 3.0e38, float("inf"), float("nan")])
+def test_special_values_and_scales(rho, fmt):
+    """NaN, infinities and huge values in the residual stream or the sub-layer output, and scales that overflow products or are not
+    finite: the codes are those of the plain cast of the stored tensor, byte for byte (the rows kernel drops clamp and NaN test
+    where the values and the scale allow it, the plain cast never does)."""
+    rows, cols = 33, 1024
+    rng = np.random.default_rng(12)
+    x = synth.f32_to_bf16_bits(rng.standard_normal((rows, cols)).astype(np.float32))
+    y = synth.f32_to_bf16_bits(rng.standard_normal((rows, cols)).astype(np.float32))
+    x[2, 3], x[2, 900], x[5, 0], x[6, 77], x[7, 511], x[8, 512] = 0x7FC1, 0xFFC1, 0x7F80, 0xFF80, 0x7F7F, 0xFF7F
+    y[10, 4], y[11, 6], y[12] = 0x7FC0, 0x7F80, 0
+    xd, yd = dev(x), dev(y)
+    xnew = torch.zeros((rows, cols), dtype=torch.int16, device="cuda")
+    q, want = (torch.zeros((rows, cols), dtype=torch.uint8, device="cuda") for _ in range(2))
+    gamma = torch.full((cols,), 0.25, device="cuda")
+    sc = fscalar(rho)
+    fog.postnorm_residual_quantize(xd, yd, gamma, fmt, sc, xnew, q=q)
+    fog.quantize(xnew, fmt, sc, q=want)
+    torch.cuda.synchronize()
+    assert np.array_equal(q.cpu().numpy(), want.cpu().numpy())

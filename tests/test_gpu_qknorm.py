@@ -105,3 +105,34 @@ def test_qknorm_config_shape_and_errors():
     assert call(None, 0, 128, 128, 1.0, 0, f.data_ptr(), None, 128, f.data_ptr(), st) == 0
     torch.cuda.synchronize()
     assert f.item() == 0.0                                 # the abs-max of an empty tensor is written as 0
+
+
+@pytest.mark.parametrize("fmt", [fp8.E4M3, fp8.E5M2])
+@pytest.mark.parametrize("rho", [39.0, 3.0e38, float("nan")])
+def test_qknorm_special_values_take_the_careful_cast(rho, fmt):
+    """Rows that hold NaN, infinities or values whose squares overflow, and scales that overflow every product or are NaN: the
+    rows kernel (which casts without clamp or NaN test where it can) against the general kernel, which has no such form.  Ordinary
+    rows under an ordinary scale may differ in the last bit of the norm, all others agree to the byte."""
+    D, rows = 128, 70
+    rng = np.random.default_rng(8)
+    x = rng.standard_normal((rows, D)).astype(np.float32)
+    x[3, 5], x[9, 7], x[9, 8], x[20, 1], x[33, 100], x[40] = np.nan, np.inf, 1.0, -np.inf, 3e38, 0.0
+    x[41, :2] = (-np.nan, np.inf)
+    xd = dev(synth.f32_to_bf16_bits(np.where(np.isnan(x), 0, x)))
+    bits = xd.cpu().numpy().view(np.uint16).copy()
+    bits[3, 5], bits[41, 0] = 0x7FC1, 0xFFC1
+    xd = dev(bits)
+    out = []
+    for pad in (0, 1):
+        q = torch.zeros((rows, D + pad), dtype=torch.uint8, device="cuda")[:, :D]
+        am = torch.zeros(1, device="cuda")
+        fog.rmsnorm_quantize(xd, fmt, fscalar(rho), q, amax_out=am)
+        torch.cuda.synchronize()
+        out.append((q.cpu().numpy(), am.item()))
+    special = [3, 9, 20, 33, 40, 41]
+    assert np.array_equal(out[0][0][special], out[1][0][special])
+    if rho == 39.0:
+        assert (out[0][0] != out[1][0]).mean() < 1e-3
+    else:
+        assert np.array_equal(out[0][0], out[1][0])
+    assert np.isnan(out[0][1]) and np.isnan(out[1][1])
