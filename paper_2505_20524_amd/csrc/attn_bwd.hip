@@ -206,8 +206,9 @@ FOG_DEVICE void clamp_block(v16f* x) {
 // cycles); two barriers per block of queries are the price, which three independent workgroups hide.  Tried and slower: eight
 // waves and 128 keys per workgroup (335 us), the products of one block dealt out between the vector work of the next inside the
 // wave (311 us), a three-stage ring with one barrier and two workgroups per CU (318 us).
-// Times of dK and dV, 2 x 32 heads x 4096 causal: 177 + 243 us as two launches -> 292 us; whole backward there 629 -> 530 us, 4 x
-// 16 x 2048 201 -> 171 us, 2 x 32/8 (grouped) x 4096 660 -> 520 us, 1 x 16/4 x 576 80 -> 45 us.
+// Times of dK and dV, 2 x 32 heads x 4096 causal: 177 + 243 us as two launches -> 292 us, 286 us with the
+// gradients stored as whole lines; whole backward there 622 -> 508 us, 4 x 16 x 2048 198 -> 146 us, 1 x 32/8 (grouped) x 4096 511 ->
+// 296 us, 1 x 16/4 x 576 80 -> 33 us.
 //
 // Ring stage: Q tile, dO tile, then 64 lse and 64 D values.  Five direct loads per thread and stage.
 constexpr int KV_STAGE = 2 * TILE + 512;
@@ -437,19 +438,14 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
   }
   const float sdv = (*a.sinv_do) / rho_p;
   const float sdk = a.softmax_scale * (*a.sinv_q) / rho_ds;
-  const int64_t orow = hoff + key0 + key_of_position(l & 31);
-  uint16_t* dvrow = a.dV + orow * HD + 64 * half;
-  uint16_t* dkrow = a.dK + orow * HD + 64 * half;
-#pragma unroll
-  for (int d = 0; d < 2; ++d)
-#pragma unroll
-    for (int qd = 0; qd < 4; ++qd) {
-      const int col = 32 * d + 8 * qd + 4 * g;
-      *reinterpret_cast<uint2*>(dvrow + col) = make_uint2(pack_bf16x2(dv[d][4 * qd] * sdv, dv[d][4 * qd + 1] * sdv),
-                                                          pack_bf16x2(dv[d][4 * qd + 2] * sdv, dv[d][4 * qd + 3] * sdv));
-      *reinterpret_cast<uint2*>(dkrow + col) = make_uint2(pack_bf16x2(dk[d][4 * qd] * sdk, dk[d][4 * qd + 1] * sdk),
-                                                          pack_bf16x2(dk[d][4 * qd + 2] * sdk, dk[d][4 * qd + 3] * sdk));
-    }
+  if (!QSPLIT) __syncthreads();   // every wave's direct loads have landed: the rings become the staging areas
+  uint8_t* stage = QSPLIT ? smem + half * (16 * 64 * 16) : smem + w * (32 * 144);   // split: where this wave has read its partner's sums
+  const int64_t out0 = (hoff + key0) * HD + 64 * half;
+  // Stored as 8-byte pieces straight from the registers, the three gradients (200 MB at 2 x 32 heads x 4096) stay in the caches as
+  // dirty lines that leave them during whatever runs next: the abs-max pass after it took 60 us instead of 50, the forward 180
+  // instead of 172.  Pieces stored past the caches are worse still: a line then goes to memory in parts (this kernel + 100 us).
+  store_tile_rows<2>(stage, dv, sdv, a.dV + out0, HD, [](int pos) { return key_of_position(pos); });
+  store_tile_rows<2>(stage, dk, sdk, a.dK + out0, HD, [](int pos) { return key_of_position(pos); });
 }
 
 // ------------------------------------------------------------------ kernel 2: dQ (and max |dS|)
@@ -578,17 +574,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
     if (kb + 3 < nkb) block(kb + 3, Stg<3>{});
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): no direct load may still be writing LDS when the workgroup retires
+  __syncthreads();                     // ... of any wave: the ring becomes the staging area
   if (!wave_on) return;
   const float sdq = a.softmax_scale * (*a.sinv_k) / rho_ds;
-  uint16_t* dqrow = a.dQ + (hoff + q) * HD;
-#pragma unroll
-  for (int d = 0; d < 4; ++d)
-#pragma unroll
-    for (int qd = 0; qd < 4; ++qd) {
-      const int col = 32 * d + 8 * qd + 4 * g;
-      *reinterpret_cast<uint2*>(dqrow + col) = make_uint2(pack_bf16x2(dq[d][4 * qd] * sdq, dq[d][4 * qd + 1] * sdq),
-                                                          pack_bf16x2(dq[d][4 * qd + 2] * sdq, dq[d][4 * qd + 3] * sdq));
-    }
+  store_tile_rows<4>(smem + w * (32 * 272), dq, sdq, a.dQ + (hoff + q0) * HD, HD, [](int row) { return row; });
   if (AMAX) {
     ds_max = wave_max_f32(ds_max) / rho_ds;   // the running maximum was taken on rho_ds dS
     // only a wave that would raise the maximum pays for the atomic (a stale read can only be too small)

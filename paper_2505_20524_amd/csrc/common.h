@@ -145,6 +145,29 @@ FOG_DEVICE void st_nt8(void* p, uint2 v) {
   __builtin_nontemporal_store(w, reinterpret_cast<u32x2*>(p));
 }
 
+// A wave's result tile of 32 rows x (32 T) columns, from the accumulators of T 32 x 32 matrix tiles (lane & 31 = row, 8 (r / 4) +
+// 4 (lane / 32) + r % 4 = column of a tile): scaled, rounded to bf16, parked in LDS (32 rows of 64 T + 16 bytes, the wave's own) and
+// stored as whole 128-byte lines past the caches.
+template <int T, typename RowOf>
+FOG_DEVICE void store_tile_rows(uint8_t* stage, const v16f* x, float scale, uint16_t* out, int ld, RowOf row_of) {
+  constexpr int STRIDE = 64 * T + 16, LPR = 4 * T, RPS = 64 / LPR;    // bytes of a staged row, lanes per row, rows per store
+  const int l = threadIdx.x & 63;
+#pragma unroll
+  for (int d = 0; d < T; ++d)
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd)
+      *reinterpret_cast<uint2*>(stage + (l & 31) * STRIDE + 64 * d + 16 * qd + 8 * (l >> 5)) =
+          make_uint2(pack_bf16x2(x[d][4 * qd] * scale, x[d][4 * qd + 1] * scale), pack_bf16x2(x[d][4 * qd + 2] * scale, x[d][4 * qd + 3] * scale));
+  // (the wave's LDS instructions complete in order: all that is needed is that the compiler keeps their order)
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int t = 0; t < 32 / RPS; ++t) {
+    const int row = RPS * t + l / LPR, piece = l % LPR;
+    st_nt16(out + (int64_t)row_of(row) * ld + 8 * piece, *reinterpret_cast<const uint4*>(stage + row * STRIDE + 16 * piece));
+  }
+  asm volatile("" ::: "memory");
+}
+
 // Makes the compiler treat `v` as used here.  Kernels that stream tiles into LDS with direct loads
 // issued from inline assembly wait for those loads with explicit s_waitcnt immediates; the
 // compiler does not see them, so any ordinary global load still "outstanding" in its bookkeeping
