@@ -291,20 +291,13 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_kernel(FwdArgs a) {
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): no direct load may still be writing LDS when the workgroup retires
 
+  __syncthreads();                     // ... of any wave: the ring becomes the staging area
   if (!wave_on) return;
   // ---- epilogue: O = sinv_v O^T / (rho_p l);  lse = m + log2 l  (l_run holds rho_p l, split over two lanes)
   const float l_tot = l_run + lane_xor32(l_run);
   const float scale_o = (*a.sinv_v) / l_tot;
-  uint16_t* orow = a.O + ((int64_t)bh * S + q) * HD;
-#pragma unroll
-  for (int d = 0; d < 4; ++d)
-#pragma unroll
-    for (int qd = 0; qd < 4; ++qd) {
-      const int col = 32 * d + 8 * qd + 4 * g;
-      uint2 v = make_uint2(pack_bf16x2(o[d][4 * qd + 0] * scale_o, o[d][4 * qd + 1] * scale_o),
-                           pack_bf16x2(o[d][4 * qd + 2] * scale_o, o[d][4 * qd + 3] * scale_o));
-      *reinterpret_cast<uint2*>(orow + col) = v;
-    }
+  // O as whole lines past the caches: 1 x 32/8 heads x 8192 causal 348 -> 343 us, 4 x 16 x 2048 53 -> 48 us
+  store_tile_rows<4>(smem + w * (32 * 272), o, scale_o, a.O + ((int64_t)bh * S + q0) * HD, HD, [](int row) { return row; });
   if (g == 0) a.lse[(int64_t)bh * S + q] = m_run + (__log2f(l_tot) - lg_rho_p);
   if (a.amax_p) {
     float rm = fmaxf(raw_max, lane_xor32(raw_max));
