@@ -23,9 +23,10 @@ import re
 UNIT_COUNTERS = ("TCP_TCC_READ_REQ_sum TCP_TOTAL_CACHE_ACCESSES_sum TCP_PENDING_STALL_CYCLES_sum TCP_TCC_READ_REQ_LATENCY_sum "
                  "TA_TA_BUSY_sum TA_BUFFER_TOTAL_CYCLES_sum SQ_VALU_MFMA_BUSY_CYCLES SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_ACTIVE_INST_VALU "
                  "SQ_BUSY_CYCLES GRBM_GUI_ACTIVE")
-KERNELS = ("fp8_gemm_kernel", "gemm_split_reduce_kernel", "amax_batch_kernel", "quantize_batch_kernel", "amax_kernel", "quantize_transpose_kernel",
-           "quantize_rows_kernel", "attn_fwd_kernel", "attn_bwd_dkdv_kernel", "attn_bwd_dq_kernel", "kurtosis_kernel", "qknorm_rows_kernel",
-           "copyBuffer")
+GEMMS = ("fp8_gemm_kernel", "fp8_gemm_tile_kernel")   # a product is one launch of either (a split one also runs gemm_tile_reduce_kernel)
+KERNELS = GEMMS + ("gemm_tile_reduce_kernel", "amax_batch_kernel", "quantize_batch_kernel", "amax_kernel", "quantize_transpose_kernel",
+           "quantize_rows_kernel", "attn_fwd_kernel", "attn_bwd_dkdv_kernel", "attn_bwd_dq_kernel", "kurtosis_kernel",
+           "qknorm_rows_kernel", "copyBuffer")
 TRAFFIC_LINE = re.compile(r"= ([0-9.]+e[+-]?[0-9]+) bytes per launch")
 
 
@@ -34,7 +35,7 @@ def traffic_file(out_dir, cid):
 
 
 def read_gemm_traffic(out_dir, cid):
-    """Bytes per fp8_gemm_kernel launch as measured and written by `traffic_summary`, or None when there is no such summary."""
+    """Bytes per GEMM launch as measured and written by `traffic_summary`, or None when there is no such summary."""
     try:
         m = TRAFFIC_LINE.search(open(traffic_file(out_dir, cid)).read())
     except OSError:
@@ -47,6 +48,10 @@ def _find(directory, name):
     if not hits:
         raise FileNotFoundError("%s under %s" % (name, directory))
     return hits[0]
+
+
+def _is_gemm(name):
+    return any(g in name for g in GEMMS)
 
 
 def _pmc(path):
@@ -91,10 +96,10 @@ def stats_summary(cid, d, out_dir, bench_line):
 
     def grp(pred):
         return sum(v[0] for k, v in per.items() if pred(k)), sum(v[1] for k, v in per.items() if pred(k))
-    c, t = grp(lambda k: "fp8_gemm_kernel" in k)
+    c, t = grp(_is_gemm)
     o.append("")
     if c:
-        o.append("All `fp8_gemm_kernel` instantiations together: %d launches, average %.1f us per launch (kernel trace)." % (c, t / c / 1e3))
+        o.append("All GEMM launches (`fp8_gemm_kernel`, `fp8_gemm_tile_kernel`) together: %d launches, average %.1f us per launch (kernel trace)." % (c, t / c / 1e3))
     if bench_line:
         r = bench_line["roofline"]
         o.append("bench.py's own HIP-event figure in the same run: %d launches per step, average %.1f us per launch, %.0f TFLOP/s (%.1f %% of the "
@@ -102,9 +107,9 @@ def stats_summary(cid, d, out_dir, bench_line):
                      r["launches_per_step"], r["avg_launch_ms"] * 1e3, r["achieved"], r["frac"] * 100, r["peak"], bench_line["ms_per_step"], bench_line["value"]))
     o.append("")
     parts = []
-    for name, pred, div in (("GEMM (split reduce included)", lambda k: "fp8_gemm_kernel" in k or "gemm_split_reduce" in k, 24),
+    for name, pred, div in (("GEMM (split reduce included)", lambda k: _is_gemm(k) or "gemm_tile_reduce" in k, 24),
                             ("attention forward", lambda k: "attn_fwd_kernel" in k, 24),
-                            ("attention backward (row constants, dV, dK, dQ)", lambda k: "attn_bwd" in k, 24),
+                            ("attention backward (row constants, dK and dV, dQ)", lambda k: "attn_bwd" in k, 24),
                             ("abs-max pass (just-in-time passes only)", lambda k: "amax_batch_kernel" in k or "amax_kernel" in k, 12),
                             ("cast pass, just-in-time", lambda k: "quantize_batch_kernel" in k or ("quantize_rows_kernel" in k and "false>" in k.split("(")[0]), 12),
                             ("cast pass with abs-max output, delayed", lambda k: "quantize_delayed_batch_kernel" in k or ("quantize_rows_kernel" in k and "true>" in k.split("(")[0]), 12)):
@@ -132,11 +137,12 @@ def traffic_summary(cid, d, out_dir, bench_line):
             continue
         fa, wa = sum(F[k]) / len(F[k]), sum(W[k]) / len(W[k])
         o.append("| `%s` | %d | %.0f | %.0f | %.1f | %.1f |" % (k, len(F[k]), fa, wa, fa * sf * 1024 / 1e6, wa * sw * 1024 / 1e6))
-    if F["fp8_gemm_kernel"]:
-        rd = sum(F["fp8_gemm_kernel"]) / len(F["fp8_gemm_kernel"]) * sf * 1024
-        wr = sum(W["fp8_gemm_kernel"]) / len(W["fp8_gemm_kernel"]) * sw * 1024
+    fg, wg = [x for g in GEMMS for x in F[g]], [x for g in GEMMS for x in W[g]]
+    if fg:
+        rd = sum(fg) / len(fg) * sf * 1024
+        wr = sum(wg) / len(wg) * sw * 1024
         o.append("")
-        o.append("Dominant kernel (`fp8_gemm_kernel`): %.0f MB read + %.0f MB written = %.3e bytes per launch on average." % (rd / 1e6, wr / 1e6, rd + wr))
+        o.append("Dominant kernel (GEMM, both kernels): %.0f MB read + %.0f MB written = %.3e bytes per launch on average." % (rd / 1e6, wr / 1e6, rd + wr))
         if bench_line:
             alg = bench_line.get("gemm_algorithmic_bytes_per_launch")
             if alg:
@@ -148,13 +154,12 @@ def traffic_summary(cid, d, out_dir, bench_line):
 
 def units_summary(cid, d, out_dir):
     acc = _pmc(_find(os.path.join(d, "units"), "b_counter_collection.csv"))
-    kn = ("fp8_gemm_kernel", "attn_fwd_kernel", "dkdv_kernel<true, 1>", "dkdv_kernel<true, 2>", "dkdv_kernel<true, 0>", "attn_bwd_dq_kernel")
-    disp = {"fp8_gemm_kernel": "fp8_gemm_kernel", "attn_fwd_kernel": "attn_fwd_kernel", "dkdv_kernel<true, 1>": "attn_bwd_dkdv (dV)",
-            "dkdv_kernel<true, 2>": "attn_bwd_dkdv (dK)", "dkdv_kernel<true, 0>": "attn_bwd_dkdv (dK + dV)", "attn_bwd_dq_kernel": "attn_bwd_dq_kernel"}
-    A = collections.defaultdict(lambda: collections.defaultdict(list))
+    kn = GEMMS + ("attn_fwd_kernel", "dkdv_kernel<true, false>", "dkdv_kernel<true, true>", "attn_bwd_dq_kernel")
+    disp = {n: n for n in kn}
+    disp.update({"dkdv_kernel<true, false>": "attn_bwd_dkdv", "dkdv_kernel<true, true>": "attn_bwd_dkdv (pairs in turns)"})
     for k, v in acc.items():
         for n in kn:
-            if n in k and "split_reduce" not in k:
+            if n in k:
                 for c, vals in v.items():
                     A[n][c] += vals
     kn = [n for n in kn if A[n]]
@@ -174,7 +179,7 @@ def units_summary(cid, d, out_dir):
     dur = collections.defaultdict(list)
     for r in trace:
         for n in kn:
-            if n in r["Kernel_Name"] and "split_reduce" not in r["Kernel_Name"]:
+            if n in r["Kernel_Name"]:
                 dur[n].append(float(r["End_Timestamp"]) - float(r["Start_Timestamp"]))
     o.append("| | " + " | ".join("`%s`" % disp[n] for n in kn) + " |")
     o.append("|---|" + "---|" * len(kn))
