@@ -157,6 +157,7 @@ def units_summary(cid, d, out_dir):
     kn = GEMMS + ("attn_fwd_kernel", "dkdv_kernel<true, false>", "dkdv_kernel<true, true>", "attn_bwd_dq_kernel")
     disp = {n: n for n in kn}
     disp.update({"dkdv_kernel<true, false>": "attn_bwd_dkdv", "dkdv_kernel<true, true>": "attn_bwd_dkdv (pairs in turns)"})
+    A = collections.defaultdict(lambda: collections.defaultdict(list))
     for k, v in acc.items():
         for n in kn:
             if n in k:
