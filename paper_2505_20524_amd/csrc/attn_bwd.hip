@@ -346,7 +346,10 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
     const uint8_t* sq = ring + STG * KV_STAGE;
     const uint8_t* sdo = sq + TILE;
     const float lse = *reinterpret_cast<const float*>(sq + row_const);
-    const float Dq = *reinterpret_cast<const float*>(sq + row_const + 256);
+    // A row whose output gradient holds an infinity has an infinite D, and the converts saturate finite values only: a bound
+    // that P > 3e-31 takes beyond E5M2, and that no P makes infinite, stands in for it (a NaN stays).
+    const float D_row = *reinterpret_cast<const float*>(sq + row_const + 256);
+    const float Dq = fabsf(D_row) > 2.0e35f ? __builtin_copysignf(2.0e35f, D_row) : D_row;
     v16f st, dp;
     clear(st); clear(dp);
 #pragma unroll
@@ -407,8 +410,8 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
       if (it + 1 < turns) block(CLAMP, Stg<1>{}, it + 1);
     }
   };
-  // the converts saturate finite values; only a scale beyond any gradient's range could make rho_ds dS infinite
-  if (rho_ds > 1.0e18f) trips(true);
+  // the converts saturate finite values; only scales beyond any gradient's range could make rho_ds dS infinite (dP~ is below 4e9)
+  if (rho_ds > 1.0e18f || fabsf(cdpk) > 1.0e24f) trips(true);
   else                  trips(false);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): no direct load may still be writing LDS when the workgroup retires
   if (QSPLIT) {

@@ -192,6 +192,31 @@ def test_backward_with_a_scale_beyond_any_gradient(causal):
     run_bwd(c, B, H, S, 1 / math.sqrt(128), causal, [(b, h) for b in range(B) for h in range(H)], do, ds_scale_factor=2.0 ** 50)
 
 
+@pytest.mark.parametrize("causal", [True, False])
+def test_backward_with_an_infinite_output_gradient(causal):
+    """One element of the bf16 dO is infinite (its code is saturated, as a cast under a delayed scale leaves it): D of that row is
+    infinite and every dS of the row saturates at the largest finite code, exactly as it does for a huge finite element.
+    dK and dV have to be the same bytes in the two cases."""
+    B, H, S = 1, 2, 192
+    q, k, v, do = synth.small_attention(2710, B, H, S)
+    c = cast_all(q, k, v, do)
+    s = 1 / math.sqrt(128)
+    O, lse, _ = gpu_fwd(c, B, H, S, s, causal, want_amax=False)
+    out = []
+    for bits in (0x7F80, 0x7149):                  # +infinity, 1e30
+        d = do.copy()
+        d[0, 0, 100, 5] = bits
+        dQ, dK, dV = (torch.full((B, H, S, 128), 0x7FC0, dtype=torch.int16, device="cuda") for _ in range(3))
+        ws = torch.empty(fog.fp8_attn_workspace(B, H, S, 128, True), dtype=torch.uint8, device="cuda")
+        fog.fp8_attn_bwd(B, H, S, 128, s, causal, dev(c["q"][0]), dev(c["k"][0]), dev(c["v"][0]),
+                         fscalar(c["q"][1]), fscalar(c["k"][1]), fscalar(c["v"][1]), dev(O), dev(d), dev(c["do"][0]),
+                         fscalar(c["do"][1]), dev(lse), fscalar(448.0), fscalar(1024.0), dQ, dK, dV, workspace=ws)
+        torch.cuda.synchronize()
+        out.append((host_u16(dK), host_u16(dV)))
+    assert np.all((out[1][0] & 0x7F80) != 0x7F80)
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
 def gqa_case(seed, B, H, Hkv, S):
     """Grouped-query inputs: Q and dO with H heads, K and V with H_kv heads (same recipe, own seed)."""
     q, _, _, do = synth.small_attention(seed, B, H, S)
