@@ -66,9 +66,10 @@ __global__ __launch_bounds__(kThreads) void qknorm_rows_kernel(const uint16_t* _
   constexpr int U = 4;                  // rows per lane group and trip: four loads in flight
   const float rho = *scale;
   const int sub = threadIdx.x % LPR, rloc = threadIdx.x / LPR;
-  // |y| <= gain sqrt(cols) in rows with a finite sum of squares: with such a scale no product overflows, and the saturating converts
-  // need neither a clamp nor a NaN test
-  const bool plain = fabsf(rho) * gain <= 1.0e30f;
+  // |y| <= 1.5 gain sqrt(cols) in rows whose sum of squares and inverse norm are finite (squares that vanish below the smallest
+  // subnormal included): with such a gain and scale no product overflows, and the saturating converts, which let infinities
+  // through, need neither a clamp nor a NaN test
+  const bool plain = gain <= 1.0e30f && fabsf(rho) * gain <= 1.0e30f;
   saturating_converts();
   float m = 0.0f;
   bool nan = false;
@@ -95,7 +96,8 @@ __global__ __launch_bounds__(kThreads) void qknorm_rows_kernel(const uint16_t* _
     const float mine = sub & 2 ? (sub & 1 ? sum[3] : sum[2]) : (sub & 1 ? sum[1] : sum[0]);
     const float inv_mine = inv_rms(mine, (float)(8 * LPR), gain);
     const float invs[U] = {quad_lane<0>(inv_mine), quad_lane<1>(inv_mine), quad_lane<2>(inv_mine), quad_lane<3>(inv_mine)};
-    const bool all_plain = plain && sum[0] < INFINITY && sum[1] < INFINITY && sum[2] < INFINITY && sum[3] < INFINITY;
+    // (the inverse norm is infinite where the mean of tiny squares rounds to 0 or the gain is large against the norm)
+    const bool all_plain = plain && __all(mine < INFINITY && inv_mine < INFINITY);   // every row of the wave's trip
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t r = r0 + u * RPB + rloc;

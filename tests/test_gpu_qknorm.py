@@ -10,7 +10,7 @@ import torch
 
 from oracle import fp8, qknorm
 from paper_2505_20524_amd import fog, synth
-from parity import dev, fscalar
+from parity import dev, fscalar, host_u16
 
 pytestmark = pytest.mark.gpu
 
@@ -136,3 +136,37 @@ def test_qknorm_special_values_take_the_careful_cast(rho, fmt):
     else:
         assert np.array_equal(out[0][0], out[1][0])
     assert np.isnan(out[0][1]) and np.isnan(out[1][1])
+
+
+@pytest.mark.parametrize("fmt", [fp8.E4M3, fp8.E5M2])
+@pytest.mark.parametrize("cols", [128, 512])
+@pytest.mark.parametrize("gain,rho", [(1.0, 39.0), (1.0e30, 1.0e-30), (3.0e38, 1.0e-10)])
+def test_qknorm_norm_or_product_beyond_binary32(gain, rho, cols, fmt):
+    """Finite rows whose inverse norm is not finite (squares so small that their mean rounds to 0, a gain over a small norm) and
+    gains whose product with an element overflows: the rows kernel gives the bytes and the abs-max of the general kernel, which
+    clamps every element, and what is not zero saturates."""
+    rows = 70
+    rng = np.random.default_rng(9)
+    x = rng.standard_normal((rows, cols)).astype(np.float32)
+    x[2], x[5], x[9] = 0.0, 0.0, 0.0
+    x[2, 17] = 2.0 ** -74                                             # its square / cols is below half the smallest subnormal
+    x[5, 40:80] = 1.25 * 2.0 ** -75 * rng.choice([-1.0, 1.0], 40)     # each square rounds up to one subnormal step
+    x[9, [3, 4, 60, 127]] = (1e-22, -1e-22, 1e-22, 1e-22)
+    x[12] *= np.float32(1e-10)                                        # gain 1e30 over a norm of 1e-10
+    xd = dev(synth.f32_to_bf16_bits(x))
+    nonzero = synth.bf16_bits_to_f32(host_u16(xd)) != 0
+    top = 0x7E if fmt == fp8.E4M3 else 0x7B
+    out = []
+    for pad in (0, 1):                 # an odd ldq takes the general kernel
+        q = torch.zeros((rows, cols + pad), dtype=torch.uint8, device="cuda")[:, :cols]
+        am = torch.zeros(1, device="cuda")
+        fog.rmsnorm_quantize(xd, fmt, fscalar(rho), q, gain=gain, amax_out=am)
+        torch.cuda.synchronize()
+        out.append((q.cpu().numpy(), am.item()))
+    special = [2, 5, 9] if gain == 1.0 else [2, 5, 9, 12] if gain == 1.0e30 else list(range(rows))
+    got, want = out[0][0], out[1][0]
+    assert np.array_equal(got[special], want[special])
+    assert (got != want).mean() < 1e-3                                # ordinary rows: the last bit of the norm, as elsewhere
+    for r in special:
+        assert ((got[r] & 0x7F)[nonzero[r]] == top).all()
+    assert np.isnan(out[0][1]) and np.isnan(out[1][1])                # zero times an infinite inverse norm
