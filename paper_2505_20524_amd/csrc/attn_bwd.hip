@@ -15,6 +15,7 @@
 // products but keeps every accumulator in registers, needs no atomics and is deterministic.
 // Operands whose contraction index is their row index (dO^T, Q^T, K^T) are gathered from the
 // row-major LDS tiles with the byte-transposing read, in the order the packed scores have.
+#include <cfloat>
 #include <mutex>
 
 #include "common.h"
@@ -171,12 +172,13 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_rowdot_kernel(const uint16_
   }
 }
 
-// Largest magnitude among the 32 values of a lane's two score tiles (NaN operands are dropped by the maximum), as four
-// independent chains, and the clamp of those values to the finite range of E5M2.
+// Largest magnitude among the 16 T values of a lane's T score tiles (NaN operands are dropped by the maximum), as 2 T
+// independent chains, and the clamp of two tiles to the finite range of E5M2.
+template <int T>
 FOG_DEVICE float block_absmax(const v16f* x) {
-  float cm[4];
+  float cm[2 * T];
 #pragma unroll
-  for (int ch = 0; ch < 4; ++ch) {
+  for (int ch = 0; ch < 2 * T; ++ch) {
     const v16f& t = x[ch >> 1];
     const int b = 8 * (ch & 1);
     float m = fmaxf(fmaxf(fabsf(t[b]), fabsf(t[b + 1])), fabsf(t[b + 2]));
@@ -184,7 +186,9 @@ FOG_DEVICE float block_absmax(const v16f* x) {
     m = fmaxf(fmaxf(m, fabsf(t[b + 5])), fabsf(t[b + 6]));
     cm[ch] = fmaxf(m, fabsf(t[b + 7]));
   }
-  return fmaxf(fmaxf(fmaxf(cm[0], cm[1]), cm[2]), cm[3]);
+#pragma unroll
+  for (int ch = 1; ch < 2 * T; ++ch) cm[0] = fmaxf(cm[0], cm[ch]);
+  return cm[0];
 }
 FOG_DEVICE void clamp_block(v16f* x) {
 #pragma unroll
@@ -209,6 +213,8 @@ FOG_DEVICE void clamp_block(v16f* x) {
 // Times of dK and dV, 2 x 32 heads x 4096 causal: 177 + 243 us as two launches -> 292 us, 286 us with the
 // gradients stored as whole lines; whole backward there 622 -> 508 us, 4 x 16 x 2048 198 -> 146 us, 1 x 32/8 (grouped) x 4096 511 ->
 // 296 us, 1 x 16/4 x 576 80 -> 33 us.
+// Saturating converts (MODE.FP16_OVFL) would save the search for overflow in front of the cast of dS, 2 % of the backward (508
+// against 518 us), but under that mode matrix instructions drop NaNs, and a diverged gradient left dK and dV finite.
 //
 // Ring stage: Q tile, dO tile, then 64 lse and 64 D values.  Five direct loads per thread and stage.
 constexpr int KV_STAGE = 2 * TILE + 512;
@@ -244,7 +250,6 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
   const float rho_p = *a.scale_p, rho_ds = *a.scale_ds;
   const float c = a.softmax_scale * 1.44269504088896340736f * (*a.sinv_q) * (*a.sinv_k);
   const float cdpk = (*a.sinv_do) * (*a.sinv_v) * (rho_ds / rho_p);   // dP scale times rho_ds / rho_p
-  saturating_converts();
 
   v16f dv[2], dk[2];
 #pragma unroll
@@ -341,15 +346,15 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
 
   __builtin_amdgcn_s_waitcnt(0x0F70 | LOADS);   // vmcnt = LOADS: block 0 has landed
   __syncthreads();
-  auto block = [&](const bool CLAMP, auto stg, int it) __attribute__((always_inline)) {
+  auto block = [&](const bool CLAMP_P, auto stg) __attribute__((always_inline)) {
     constexpr int STG = decltype(stg)::value;
     const uint8_t* sq = ring + STG * KV_STAGE;
     const uint8_t* sdo = sq + TILE;
     const float lse = *reinterpret_cast<const float*>(sq + row_const);
-    // A row whose output gradient holds an infinity has an infinite D, and the converts saturate finite values only: a bound
-    // that P > 3e-31 takes beyond E5M2, and that no P makes infinite, stands in for it (a NaN stays).
+    // A row whose output gradient holds an infinity has an infinite D, and 0 times that is no number: where P is 0 its dS is 0
+    // (a NaN stays).
     const float D_row = *reinterpret_cast<const float*>(sq + row_const + 256);
-    const float Dq = fabsf(D_row) > 2.0e35f ? __builtin_copysignf(2.0e35f, D_row) : D_row;
+    const float Dq = fabsf(D_row) > FLT_MAX ? __builtin_copysignf(FLT_MAX, D_row) : D_row;
     v16f st, dp;
     clear(st); clear(dp);
 #pragma unroll
@@ -361,16 +366,27 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
     uint32_t pk[4], dsk[4];
 #pragma unroll
     for (int qd = 0; qd < 4; ++qd) {
-      float p[4], s[4];
+      float p[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[4 * qd + e], c, -lse));          // rho_p P
-        s[e] = p[e] * __builtin_fmaf(dp[4 * qd + e], cdpk, -Dq);                         // rho_ds dS
-        if (CLAMP) s[e] = __builtin_amdgcn_fmed3f(s[e], -57344.0f, 57344.0f);
+        const int r = 4 * qd + e;
+        p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[r], c, -lse));          // rho_p P
+        dp[r] = p[e] * __builtin_fmaf(dp[r], cdpk, -Dq);                        // rho_ds dS, left in the registers of dP
+        if (CLAMP_P) p[e] = p[e] > 448.0f ? 448.0f : p[e];                      // (a NaN stays)
       }
-      const uint32_t plo = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], any_u32(), false), slo = __builtin_amdgcn_cvt_pk_bf8_f32(s[0], s[1], any_u32(), false);
-      pk[qd] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], plo, true);
-      dsk[qd] = __builtin_amdgcn_cvt_pk_bf8_f32(s[2], s[3], slo, true);
+      const uint32_t lo = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], any_u32(), false);
+      pk[qd] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], lo, true);
+    }
+    // The hardware convert turns overflow into infinity: dS is clamped before its cast where the block holds a magnitude above the
+    // largest finite E5M2 value (finding that out costs half an instruction per value, the clamp three; a NaN stays).
+    if (__builtin_expect(__any(block_absmax<1>(&dp) > 57344.0f), 0)) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dp[r] = fabsf(dp[r]) > 57344.0f ? __builtin_copysignf(57344.0f, dp[r]) : dp[r];
+    }
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd) {
+      const uint32_t lo = __builtin_amdgcn_cvt_pk_bf8_f32(dp[4 * qd], dp[4 * qd + 1], any_u32(), false);
+      dsk[qd] = __builtin_amdgcn_cvt_pk_bf8_f32(dp[4 * qd + 2], dp[4 * qd + 3], lo, true);
     }
     if (CAUSAL && cur_i == 0) {
       // The first query block of every head is the diagonal one (KEYS divides STEP): a query sees nothing of the keys after it.
@@ -404,15 +420,14 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
   // Blocks of a pair (one past the end is a block of zeros: P is 1 there, but dO, D and dP are 0 and add nothing).
   const int turns = (total + TURNS - 1) / TURNS;
   // two blocks per trip: the ring stage is a constant in each copy
-  auto trips = [&](const bool CLAMP) __attribute__((always_inline)) {
+  auto trips = [&](const bool CLAMP_P) __attribute__((always_inline)) {
     for (int it = 0; it < turns; it += PAIR_STAGES) {
-      block(CLAMP, Stg<0>{}, it);
-      if (it + 1 < turns) block(CLAMP, Stg<1>{}, it + 1);
+      block(CLAMP_P, Stg<0>{});
+      if (it + 1 < turns) block(CLAMP_P, Stg<1>{});
     }
   };
-  // the converts saturate finite values; only scales beyond any gradient's range could make rho_ds dS infinite (dP~ is below 4e9)
-  if (rho_ds > 1.0e18f || fabsf(cdpk) > 1.0e24f) trips(true);
-  else                  trips(false);
+  if (!(rho_p <= 448.0f)) trips(true);   // rho_p P <= rho_p: the cast of P only overflows under a scale above the format's maximum
+  else                    trips(false);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): no direct load may still be writing LDS when the workgroup retires
   if (QSPLIT) {
     // the second pair's sums through LDS (both rings are done with): 16 bytes per lane and instruction
@@ -550,7 +565,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
         const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kt][r], c, -lse));   // rho_ds P
         dp[kt][r] = e * __builtin_fmaf(dp[kt][r], cdp, -Dq);
       }
-    const float bm = block_absmax(dp);
+    const float bm = block_absmax<2>(dp);
     ds_max = fmaxf(ds_max, bm);
     // The hardware convert turns overflow into infinity, so magnitudes above the largest finite E5M2 value have to be clamped
     // first; whether any of the block's 32 values per lane needs that is known from the block maximum (which the abs-max of dS

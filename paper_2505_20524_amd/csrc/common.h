@@ -59,6 +59,8 @@ FOG_DEVICE uint32_t cvt4_fp8(float a, float b, float c, float d) {
 
 // Switches the wave's FP8 converts to saturation (MODE.FP16_OVFL): a finite value beyond the format becomes the largest finite
 // code, which makes the clamp above unnecessary; a NaN keeps its NaN code, an infinity is not clamped.
+// Only for kernels that neither convert to bf16 (finite values then round to the largest finite bf16 instead of infinity) nor run
+// matrix instructions (they then drop NaNs and turn infinities into the largest finite float).
 FOG_DEVICE void saturating_converts() { __builtin_amdgcn_s_setreg(1 | (23 << 6) | (0 << 11), 1); }
 
 // The cast without the clamp, for waves that switched saturation on and values that are finite.

@@ -217,6 +217,90 @@ def test_backward_with_an_infinite_output_gradient(causal):
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
 
+def bwd_dkdv(c, O, lse, do_bits, s, causal, rho_p, rho_ds):
+    """dK and dV of one backward call with the scales given (the other outputs are covered elsewhere)."""
+    B, H, S = lse.shape
+    dQ, dK, dV = (torch.full((B, H, S, 128), 0x7FC0, dtype=torch.int16, device="cuda") for _ in range(3))
+    ws = torch.empty(fog.fp8_attn_workspace(B, H, S, 128, True), dtype=torch.uint8, device="cuda")
+    fog.fp8_attn_bwd(B, H, S, 128, s, causal, dev(c["q"][0]), dev(c["k"][0]), dev(c["v"][0]),
+                     fscalar(c["q"][1]), fscalar(c["k"][1]), fscalar(c["v"][1]), dev(O), dev(do_bits), dev(c["do"][0]),
+                     fscalar(c["do"][1]), dev(lse), fscalar(rho_p), fscalar(rho_ds), dQ, dK, dV, workspace=ws)
+    torch.cuda.synchronize()
+    return host_u16(dK), host_u16(dV)
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("rho_p", [1000.0, 4096.0, 2.0 ** 40])
+def test_backward_with_an_infinite_output_gradient_and_a_large_scale_of_p(rho_p, causal):
+    """As above with a probability scale of 448 and beyond: rho_p P times the stand-in of an infinite D must not reach infinity
+    in the casts.  dK and dV have to be those of a huge finite element, byte for byte."""
+    B, H, S = 1, 2, 192
+    q, k, v, do = synth.small_attention(2720, B, H, S)
+    c = cast_all(q, k, v, do)
+    s = 1 / math.sqrt(128)
+    O, lse, _ = gpu_fwd(c, B, H, S, s, causal, want_amax=False)
+    out = []
+    for bits in (0x7F80, 0x7149):                  # +infinity, 1e30
+        d = do.copy()
+        d[0, 0, 100, 5] = bits
+        out.append(bwd_dkdv(c, O, lse, d, s, causal, rho_p, 1024.0))
+    assert np.all((out[0][0] & 0x7F80) != 0x7F80)
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("causal", [True, False])
+def test_backward_dk_under_a_tiny_scale_of_p(causal):
+    """dK does not depend on the scale of P but for rounding: under a scale of 2^-100 the row constant D rho_ds / rho_p is huge for
+    ordinary gradients, and dK is that of scale 448 (which the oracle checks).  The two differ in the last bit of products taken
+    in another order: codes of dS flip on rounding ties, at most one E5M2 step (an eighth to a quarter of the value) each."""
+    B, H, S = 1, 2, 192
+    q, k, v, do = synth.small_attention(2730, B, H, S)
+    c = cast_all(q, k, v, do)
+    s = 1 / math.sqrt(128)
+    O, lse, _ = gpu_fwd(c, B, H, S, s, causal, want_amax=False)
+    a, b = (synth.bf16_bits_to_f32(bwd_dkdv(c, O, lse, do, s, causal, rho_p, 2.0 ** 20)[0]).astype(np.float64) for rho_p in (448.0, 2.0 ** -100))
+    assert np.isfinite(a).all() and np.abs(a).max() > 0
+    assert np.linalg.norm(a - b) <= 5e-3 * np.linalg.norm(a)
+
+
+@pytest.mark.parametrize("rho_ds", [1024.0, 2.0 ** 62])
+def test_backward_keeps_a_nan_of_the_output_gradient(rho_ds):
+    """A NaN in dO makes D of its row NaN: dK is NaN for every key that the row attends to, under a scale of dS that saturates
+    everything else too, and for no other key."""
+    B, H, S = 1, 2, 192
+    q, k, v, do = synth.small_attention(2740, B, H, S)
+    c = cast_all(q, k, v, do)
+    s = 1 / math.sqrt(128)
+    O, lse, _ = gpu_fwd(c, B, H, S, s, True, want_amax=False)
+    d = do.copy()
+    d[0, 1, 100, 5] = 0x7FC0
+    dK, _ = bwd_dkdv(c, O, lse, d, s, True, 448.0, rho_ds)
+    nan = (dK & 0x7FFF) > 0x7F80
+    assert nan[0, 1, :101].all() and not nan[0, 1, 101:].any() and not nan[0, 0].any()
+
+
+@pytest.mark.parametrize("name", ["q", "k", "v", "do"])
+def test_backward_keeps_nan_codes_of_the_operands(name):
+    """A NaN code in an operand reaches dK and dV wherever its row or column takes part, and no other head."""
+    B, H, S = 1, 2, 192
+    q, k, v, do = synth.small_attention(2750, B, H, S)
+    c = cast_all(q, k, v, do)
+    s = 1 / math.sqrt(128)
+    c[name][0][0, 1, 100, 5] = 0x7F
+    O, lse, _ = gpu_fwd(c, B, H, S, s, True, want_amax=False)
+    dK, dV = ((x & 0x7FFF) > 0x7F80 for x in bwd_dkdv(c, O, lse, do, s, True, 448.0, 1024.0))
+    assert not dK[0, 0].any() and not dV[0, 0].any()
+    if name == "q":                    # scores of query 100
+        assert dK[0, 1, :101].all() and dV[0, 1, :101].all()
+    elif name == "k":                  # scores of key 100, and through lse every key of the queries from 100 on
+        assert dK[0, 1].all() and dV[0, 1].all()
+    elif name == "v":                  # dP of key 100, and through O (one column of it) D of the queries from 100 on
+        assert dK[0, 1].all() and not dV[0, 1].any()
+    else:                              # dP of query 100; dV in the element's own column
+        assert dK[0, 1, :101].all()
+        assert dV[0, 1, :101, 5].all() and not np.delete(dV[0, 1], 5, axis=1).any()
+
+
 def gqa_case(seed, B, H, Hkv, S):
     """Grouped-query inputs: Q and dO with H heads, K and V with H_kv heads (same recipe, own seed)."""
     q, _, _, do = synth.small_attention(seed, B, H, S)
