@@ -6,6 +6,8 @@
 // One pass: y and x are read once (2 + 2 B per element), the new stream is written as bf16 (2 B) and
 // as FP8 codes (1 B); the abs-max of the stored bf16 tensor comes with it.  Done as separate passes
 // the same work moves 2+2 (norm) + 2+2+2 (add) + 2 (abs-max) + 2+1 (cast) bytes.  HBM-bound.
+#include <cfloat>
+
 #include "common.h"
 #include "launch.h"
 
@@ -39,7 +41,7 @@ FOG_DEVICE void block_amax_bits(uint32_t m, uint32_t* amax_out) {
 FOG_DEVICE float residual(float x, float y, float g, float inv) { return __builtin_fmaf(g * y, inv, x); }
 
 // Bound by HBM (7 bytes per element): 8192 x 4096 55.2 -> 50.1 us and 777 x 8192 18.6 -> 15.2 us when the bf16 rounding moved to the
-// hardware convert and the casts lost their clamp and NaN test (a third of the vector instructions).
+// hardware convert and the casts lost their NaN test (a third of the vector instructions).
 // One wave per row; a lane owns C <= CMAX chunks of 8 consecutive elements (chunk c of lane l is
 // elements [8 (64 c + l), +8): consecutive lanes read consecutive 16 bytes).  All loads of y and x
 // of a row are issued before the first is used.
@@ -49,10 +51,10 @@ __global__ __launch_bounds__(kThreads) void postnorm_rows_kernel(const uint16_t*
                                                                  const float* __restrict__ scale, uint16_t* out, int64_t ldo,
                                                                  uint8_t* __restrict__ q, int64_t ldq, uint32_t* __restrict__ amax_out) {
   const float rho = *scale;
-  // values whose bf16 magnitude pattern lies below `limit` stay finite when scaled: no clamp and no NaN test for them
-  // (0: a scale that is not a number, nothing is)
-  const uint32_t limit = fabsf(rho) <= 1.0e38f ? min(0x7F80u, __float_as_uint(1.0e38f / fmaxf(fabsf(rho), 0.01f)) >> 16) : 0u;
-  saturating_converts();
+  // Finite values under a finite scale give no NaN (products that overflow are clamped): a lane that has met another value, and
+  // every lane under another scale, casts its rows a second time with the NaN test.  (Saturating converts would spare the clamp,
+  // but the same mode rounds bf16 sums beyond the largest finite value down to it.)
+  const uint32_t limit = fabsf(rho) <= FLT_MAX ? 0x7F80u : 0u;
   const float cols = (float)(C * 512);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t m = 0u;
@@ -87,22 +89,23 @@ __global__ __launch_bounds__(kThreads) void postnorm_rows_kernel(const uint16_t*
             pack_bf16x2(residual(bf16lo(vx[c].w), bf16lo(vy[c].w), g1.z, inv), residual(bf16hi(vx[c].w), bf16hi(vy[c].w), g1.w, inv)));
         m = pkmax_abs_bf16(m, o.x); m = pkmax_abs_bf16(m, o.y); m = pkmax_abs_bf16(m, o.z); m = pkmax_abs_bf16(m, o.w);
         st_nt16(out + r * ldo + col, o);
-        if (q) {
-          uint2 c8;
-          if (__builtin_expect(max_of_pair(m) < limit, 1)) {   // the running maximum: nothing this lane has seen needs the careful form
-            c8.x = cvt4_fp8_finite<FMT>(bf16lo(o.x) * rho, bf16hi(o.x) * rho, bf16lo(o.y) * rho, bf16hi(o.y) * rho);
-            c8.y = cvt4_fp8_finite<FMT>(bf16lo(o.z) * rho, bf16hi(o.z) * rho, bf16lo(o.w) * rho, bf16hi(o.w) * rho);
-          } else {
-            c8.x = cvt4_fp8_nan<FMT>(bf16lo(o.x) * rho, bf16hi(o.x) * rho, bf16lo(o.y) * rho, bf16hi(o.y) * rho);
-            c8.y = cvt4_fp8_nan<FMT>(bf16lo(o.z) * rho, bf16hi(o.z) * rho, bf16lo(o.w) * rho, bf16hi(o.w) * rho);
-          }
-          st_nt8(q + r * ldq + col, c8);
-        }
+        if (q)
+          st_nt8(q + r * ldq + col, make_uint2(cvt4_fp8<FMT>(bf16lo(o.x) * rho, bf16hi(o.x) * rho, bf16lo(o.y) * rho, bf16hi(o.y) * rho),
+                                               cvt4_fp8<FMT>(bf16lo(o.z) * rho, bf16hi(o.z) * rho, bf16lo(o.w) * rho, bf16hi(o.w) * rho)));
+        vx[c] = o;
       }
+    if (__builtin_expect(q && max_of_pair(m) >= limit, 0)) {
+#pragma unroll
+      for (int c = 0; c < CMAX; ++c)
+        if (c < C) {
+          const uint4 o = vx[c];
+          st_nt8(q + r * ldq + 8 * (64 * c + lane), make_uint2(cvt4_fp8_nan<FMT>(bf16lo(o.x) * rho, bf16hi(o.x) * rho, bf16lo(o.y) * rho, bf16hi(o.y) * rho),
+                                                               cvt4_fp8_nan<FMT>(bf16lo(o.z) * rho, bf16hi(o.z) * rho, bf16lo(o.w) * rho, bf16hi(o.w) * rho)));
+        }
+    }
   }
   if (amax_out) {
-    const uint32_t mm = (m & 0xFFFFu) > (m >> 16) ? (m & 0xFFFFu) : (m >> 16);
-    block_amax_bits(mm, amax_out);
+    block_amax_bits(max_of_pair(m), amax_out);
   }
 }
 

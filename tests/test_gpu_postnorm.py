@@ -11,7 +11,7 @@ import torch
 
 from oracle import bf16, fp8, postnorm, scaling
 from paper_2505_20524_amd import fog, synth
-from parity import dev, fscalar
+from parity import dev, fscalar, host_u16
 
 pytestmark = pytest.mark.gpu
 
@@ -123,3 +123,27 @@ def test_special_values_and_scales(rho, fmt):
     fog.quantize(xnew, fmt, sc, q=want)
     torch.cuda.synchronize()
     assert np.array_equal(q.cpu().numpy(), want.cpu().numpy())
+
+
+@pytest.mark.parametrize("fmt", [fp8.E4M3, fp8.E5M2])
+def test_sums_beyond_the_largest_bf16(fmt):
+    """Finite binary32 sums on both sides of the point where the rounding to bf16 goes to infinity: stored as infinities (the rows
+    kernel converts to bf16 with saturating FP8 converts switched on), the same tensor, codes and abs-max as the general kernel."""
+    rows, cols = 5, 1024
+    x = np.full((rows, cols), 0x7F7F, np.uint16)                     # the largest finite bf16; half a step above it is 6.6e35
+    x[1::2] |= 0x8000
+    y = np.full((rows, cols), 0x3F80, np.uint16)                     # 1: rms 1, so the sum is x + gamma
+    y[1::2] |= 0x8000
+    gamma = np.tile(np.float32([0.5e36, 0.66e36, 0.67e36, 1.0e36, 1.3e36, 2.0e36, 0.0, -1.0e36]), cols // 8)
+    want = postnorm.residual_bf16(x, y, gamma)
+    assert ((want & 0x7FFF) == 0x7F80).any() and ((want & 0x7FFF) == 0x7F7F).any()
+    out = []
+    for pad in (0, 1):                                               # an odd ldq takes the general kernel
+        xnew = torch.zeros((rows, cols), dtype=torch.int16, device="cuda")
+        q = torch.zeros((rows, cols + pad), dtype=torch.uint8, device="cuda")[:, :cols]
+        am = torch.zeros(1, device="cuda")
+        fog.postnorm_residual_quantize(dev(x), dev(y), torch.from_numpy(gamma).cuda(), fmt, fscalar(1.0e-36), xnew, q=q, amax_out=am)
+        torch.cuda.synchronize()
+        out.append((host_u16(xnew), q.cpu().numpy(), am.item()))
+    assert np.array_equal(out[0][0], want) and np.array_equal(out[1][0], want)
+    assert np.array_equal(out[0][1], out[1][1]) and out[0][2] == out[1][2] == float("inf")
