@@ -148,14 +148,19 @@ void launch_postnorm(const uint16_t* x, int64_t ldx, const uint16_t* y, int64_t 
   const bool vec = cols % 512 == 0 && cols <= 8192 && al(x, 16) && al(y, 16) && al(out, 16) && al(gamma, 16) && (!q || al(q, 8)) &&
                    ldx % 8 == 0 && ldy % 8 == 0 && ldo % 8 == 0 && ldq % 8 == 0;
   int64_t blocks = (rows + 3) / 4;
-  if (blocks > 8192) blocks = 8192;
   if (vec) {
+    // Two workgroups per CU that walk the rows, whatever the registers allow: with more waves in flight the streams past the caches get
+    // in each other's way.  us with up to 8192 workgroups -> 1024 -> 512 -> 256, other buffers each pass: 4096 x 1024 20.0 -> 20.0 ->
+    // 13.6 -> 14.7, 8192 x 1024 26.3 -> 25.5 -> 19.2 -> 22.9, 4096 x 2048 23.1 -> 22.5 -> 18.3 -> 18.8, 8192 x 4096 49.7 -> 46.8 ->
+    // 47.0 -> 53.2, 16384 x 512 25.5 -> 23.1 -> 21.9 -> 32.3, 8192 x 8192 103 -> 100 -> 100 -> 100.
+    if (blocks > 512) blocks = 512;
     const int C = (int)(cols / 512);
     if (C <= 4)      postnorm_rows_kernel<FMT, 4><<<(int)blocks, kThreads, 0, s>>>(x, ldx, y, ldy, rows, C, gamma, scale, out, ldo, q, ldq, amax_out);
     else if (C <= 8) postnorm_rows_kernel<FMT, 8><<<(int)blocks, kThreads, 0, s>>>(x, ldx, y, ldy, rows, C, gamma, scale, out, ldo, q, ldq, amax_out);
     else             postnorm_rows_kernel<FMT, 16><<<(int)blocks, kThreads, 0, s>>>(x, ldx, y, ldy, rows, C, gamma, scale, out, ldo, q, ldq, amax_out);
     return;
   }
+  if (blocks > 8192) blocks = 8192;
   postnorm_general_kernel<FMT><<<(int)blocks, kThreads, 0, s>>>(x, ldx, y, ldy, rows, cols, gamma, scale, out, ldo, q, ldq, amax_out);
 }
 
