@@ -66,7 +66,9 @@ struct LoadPlan {
 
 // K-contiguous operand: piece j covers tile rows 64 w + 8 j .. + 7; lane -> (row, LDS chunk position).
 FOG_DEVICE LoadPlan plan_kc(int64_t ld, int row0, int rows, int K) {
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int l = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  asm volatile("" : "+v"(l));    // made anew for every tile
   const int r8 = l >> 3, pos = l & 7;
   LoadPlan p;
   p.step = PAIR_K;
@@ -85,7 +87,9 @@ FOG_DEVICE LoadPlan plan_kc(int64_t ld, int row0, int rows, int K) {
 }
 // K-major operand: piece j covers contraction rows 32 w + 4 j .. + 3 of the pair; lane -> (k, LDS chunk position).
 FOG_DEVICE LoadPlan plan_km(int64_t ld, int col0, int cols, int K) {
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int l = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  asm volatile("" : "+v"(l));
   LoadPlan p;
   p.step = (uint32_t)(PAIR_K * ld);
   p.stride2 = (uint32_t)(8 * ld);
@@ -211,17 +215,24 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
   const TileWalk walk = tile_walk(ntiles);
   if (walk.first >= walk.end) return;
 
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
   const int wm = (w >> 1) * 128, wn = (w & 1) * 128;
 
   const v4i rsrc_a = make_rsrc(g.A, g.a_bytes), rsrc_b = make_rsrc(g.B, g.b_bytes);
   // LDS byte address of this wave's first piece in stage 0 (wave-uniform, kept in a scalar register)
   const uint32_t lds_w = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(uintptr_t)smem + 8192u * w));
-  const FragAddr fa_addr = A_KM ? fragaddr_km(wm) : fragaddr_kc(wm);
-  const FragAddr fb_addr = B_KM ? fragaddr_km(wn) : fragaddr_kc(wn);
-  const uint8_t* ring_a = smem + RING_A;
-  const uint8_t* ring_b = smem + RING_B;
-  const float alpha = (*g.sinv_a) * (*g.sinv_b);
+  FragAddr fa_addr = A_KM ? fragaddr_km(wm) : fragaddr_kc(wm), fb_addr = B_KM ? fragaddr_km(wn) : fragaddr_kc(wn);
+  // Eight LDS addresses, and nothing else, serve every fragment read through immediate offsets.  Left to itself the compiler keeps
+  // sums of them with the ring's bases as well and spills them; the wait for a reload from scratch is a wait for the whole prefetch
+  // stream.  (Without any spill, this way and with the lane hidden from it in plan_kc, plan_km and the epilogue: 4096 x 8192 x 2048
+  // NT 60.7 -> 58.2 us, 7936 x 6400 x 1280 NN 72.7 -> 63.8, 8192 x 14336 x 4096 NN 361 -> 350, 1280 x 11264 x 1280 TN 27.2 -> 24.6.)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    fa_addr.a[i] += RING_A;
+    fb_addr.a[i] += RING_B;
+    asm volatile("" : "+v"(fa_addr.a[i]), "+v"(fb_addr.a[i]));
+  }
+  const float alpha = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int((*g.sinv_a) * (*g.sinv_b))));
 
   v16f acc[4][4];   // written by the first K-step of every tile (zero accumulator input), never cleared
   v16f zero16;
@@ -241,8 +252,8 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
     }                                                         \
     advance(pa); advance(pb);                                 \
   } while (0)
-#define FOG_RA(i, ST, H) read_frag<A_KM>(ring_a + (ST) * OPERAND_BYTES, fa_addr, i, H)
-#define FOG_RB(j, ST, H) read_frag<B_KM>(ring_b + (ST) * OPERAND_BYTES, fb_addr, j, H)
+#define FOG_RA(i, ST, H) read_frag<A_KM>(smem + (ST) * OPERAND_BYTES, fa_addr, i, H)
+#define FOG_RB(j, ST, H) read_frag<B_KM>(smem + (ST) * OPERAND_BYTES, fb_addr, j, H)
 #define FOG_MFMA(j, FAI_, FB_, i) \
   acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(FB_[j], FAI_, acc[i][j], FB, FA, 0, 0, 0, 0)
   // first K-step of a tile: the accumulator input is the constant 0, so the 256 accumulator registers
@@ -387,14 +398,17 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
       stores_pending = false;
       continue;
     }
-    const int prow = l >> 2, piece = l & 3;   // this lane's row (+ 16 t) and 16-byte piece of a staged block
+    // the addresses below are made here, once per tile, and cost the K loop no registers
+    int el = l;
+    asm volatile("" : "+v"(el));
+    const int prow = el >> 2, piece = el & 3;   // this lane's row (+ 16 t) and 16-byte piece of a staged block
     if (fast && g.wide_store) {
       // Launches in which a workgroup computes several tiles: two neighbouring 32 x 32 blocks are staged together, so that a
       // store instruction covers 8 rows of 128 bytes (whole lines of C) instead of 16 rows of 64 bytes.  One staging buffer per
       // wave (LDS operations of a wave execute in order, so refilling it needs no wait); the longer dependency chain per block
       // is hidden by the next tile's products, which is why single-tile launches keep the narrow form below.
       constexpr int WIDE = 128 + 8;   // row stride of the staged 32 x 64 block: rows 34 banks apart
-      const int row8 = l >> 3, piece8 = l & 7;
+      const int row8 = el >> 3, piece8 = el & 7;
       uint16_t* cbase = g.C + (int64_t)(m_cur + wm + row8) * g.ldc + (n_cur + wn + 8 * piece8);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -407,7 +421,7 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
             for (int qd = 0; qd < 4; ++qd) {
               const float v0 = acc[i][j][4 * qd + 0] * alpha, v1 = acc[i][j][4 * qd + 1] * alpha;
               const float v2 = acc[i][j][4 * qd + 2] * alpha, v3 = acc[i][j][4 * qd + 3] * alpha;
-              *reinterpret_cast<uint2*>(epi + (l & 31) * WIDE + 64 * jj + 16 * qd + 8 * (l >> 5)) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
+              *reinterpret_cast<uint2*>(epi + (el & 31) * WIDE + 64 * jj + 16 * qd + 8 * (el >> 5)) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
             }
           }
 #pragma unroll
@@ -429,7 +443,7 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
           for (int qd = 0; qd < 4; ++qd) {
             const float v0 = acc[i][j][4 * qd + 0] * alpha, v1 = acc[i][j][4 * qd + 1] * alpha;
             const float v2 = acc[i][j][4 * qd + 2] * alpha, v3 = acc[i][j][4 * qd + 3] * alpha;
-            *reinterpret_cast<uint2*>(buf + (l & 31) * EPI_STRIDE + 16 * qd + 8 * (l >> 5)) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
+            *reinterpret_cast<uint2*>(buf + (el & 31) * EPI_STRIDE + 16 * qd + 8 * (el >> 5)) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
           }
 #pragma unroll
           for (int t = 0; t < 2; ++t) {
@@ -449,7 +463,7 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
           for (int qd = 0; qd < 4; ++qd) {
             const float v0 = acc[i][j][4 * qd + 0] * alpha, v1 = acc[i][j][4 * qd + 1] * alpha;
             const float v2 = acc[i][j][4 * qd + 2] * alpha, v3 = acc[i][j][4 * qd + 3] * alpha;
-            *reinterpret_cast<uint2*>(buf + (l & 31) * EPI_STRIDE + 16 * qd + 8 * (l >> 5)) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
+            *reinterpret_cast<uint2*>(buf + (el & 31) * EPI_STRIDE + 16 * qd + 8 * (el >> 5)) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
           }
 #pragma unroll
           for (int t = 0; t < 2; ++t) {
