@@ -333,10 +333,11 @@ fog_status fog_kurtosis(const void* x_bf16, int64_t rows, int64_t cols, int64_t 
  *   workspace : NULL, or fog_fp8_gemm_workspace(layout, M, N, K) bytes, 16-byte aligned.  The query returns 0
  *            for most shapes.  For products with fewer output tiles (256 x 256) than the GPU has compute
  *            units and a long contraction (the weight gradient of a small projection over many tokens) it
- *            returns room for binary32 partial tiles: the call then cuts the contraction into chunks that
- *            run side by side and adds them in a fixed order in a second kernel (deterministic; against the
- *            unsplit kernel only the order of binary32 additions differs).  Without a workspace, or with a
- *            smaller one, the unsplit kernel runs: never an error.
+ *            returns room for binary32 partial tiles, an upper bound: where it expects a gain the call cuts the
+ *            contraction into chunks that run side by side and adds them in a fixed order in a second kernel
+ *            (deterministic; against an unsplit kernel only the order of binary32 additions differs), and where
+ *            smaller output tiles fill the GPU as well it leaves the room alone.  Without a workspace, or with a
+ *            smaller one, the contraction stays whole: never an error.
  * Requirements: A, B 16-byte aligned, lda, ldb multiples of 16; C 2-byte aligned, any ldc >= N (a
  * 16-byte aligned C with ldc a multiple of 8 takes 16-byte stores, anything else element-wise ones);
  * the contiguous dimension of each operand a multiple of 16 (K for row-major-in-K operands,

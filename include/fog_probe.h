@@ -98,6 +98,18 @@ fog_status fog_probe_mfma_cross_wave(int op, int vector_ops, int iters_matrix, i
 fog_status fog_probe_gemm_products_only(int64_t M, int64_t N, int64_t K, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
                                         const float* scale_inv_A, const float* scale_inv_B, void* C_bf16, int64_t ldc, void* stream);
 
+/*
+ * Which kernel fog_fp8_gemm takes for a product: host arithmetic only, no device is needed.  For tests, which have to
+ * know that the kernel they mean to cover is the one that runs.
+ *   with_workspace : whether the caller brings fog_fp8_gemm_workspace(layout, M, N, K) bytes.
+ *   compute_units  : of the device in mind; 0 = the current device's (256 where there is none).
+ *   tile_m, tile_n, workgroups_per_cu : the output tile and how many workgroups the kernel keeps on a compute unit.
+ *   splits, k_chunk : chunks of the contraction (1 = not split) and contraction indices per chunk.   All HOST pointers.
+ * Errors: NULL, SHAPE (sizes not positive or too large), UNSUPPORTED.
+ */
+fog_status fog_probe_gemm_plan(fog_layout layout, int64_t M, int64_t N, int64_t K, int with_workspace, int compute_units,
+                               int* tile_m, int* tile_n, int* workgroups_per_cu, int* splits, int* k_chunk);
+
 #ifdef __cplusplus
 }
 #endif

@@ -15,7 +15,7 @@ struct GemmArgs {
   int vec_store;  // C rows allow 16-byte stores
   int wide_store; // interior tiles are stored as whole 128-byte lines (launches of several tiles per workgroup)
   uint32_t a_bytes, b_bytes;  // addressable span of each operand
-  // contraction split of the small-tile kernels (splits == 1: none): work item = chunk * tiles + tile, chunk c covers
+  // contraction split (splits == 1: none): work item = chunk * tiles + tile, chunk c covers
   // contraction indices [c * k_chunk, min(K, (c + 1) * k_chunk)); partial holds splits * tiles blocks of a tile's
   // floats in the register order of the accumulators
   int splits, k_chunk;
@@ -25,6 +25,8 @@ struct GemmArgs {
 // Launches one of the small-tile kernels (gemm_tile_kernels.hip) on checked arguments.
 enum GemmTile { TILE_256x128, TILE_128x128, TILE_128x128_2WG, TILE_64x64 };
 __attribute__((visibility("hidden"))) fog_status gemm_tile_launch(GemmTile tile, fog_layout layout, fog_fp8 fmt_a, fog_fp8 fmt_b, GemmArgs g, hipStream_t s);
+// Adds up the partial tiles of a split product whose tiles are 64 ti x 64 tj.
+__attribute__((visibility("hidden"))) void gemm_reduce_launch(const GemmArgs& g, int ti, int tj, hipStream_t s);
 
 namespace {
 

@@ -31,7 +31,9 @@
 // consecutive output columns per register quad and can store 8 bytes of bf16 at a time.
 //
 // Launches whose 256 x 256 tiles would leave much of the chip idle (few tiles, or a nearly empty last round) take the
-// kernels of gemm_tile_kernels.hip: see plan_product below.
+// kernels of gemm_tile_kernels.hip, or these tiles with the contraction split: see plan_product below.  The split wins on long
+// contractions of a fifth to two fifths of the chip in tiles: 400 x 9920 x 11712 NN 70 us on 256 x 128 tiles, 62 split in three,
+// 1744 x 2480 x 9296 NN 65 and 58, 752 x 6960 x 13808 NN 94 and 80.
 #include "gemm_common.h"
 #include "../../include/fog_probe.h"
 
@@ -65,7 +67,8 @@ struct LoadPlan {
 };
 
 // K-contiguous operand: piece j covers tile rows 64 w + 8 j .. + 7; lane -> (row, LDS chunk position).
-FOG_DEVICE LoadPlan plan_kc(int64_t ld, int row0, int rows, int K) {
+// The plans cover contraction indices kb .. kb + K - 1 of the operand (a chunk of a split product, or all of it).
+FOG_DEVICE LoadPlan plan_kc(int64_t ld, int row0, int rows, int kb, int K) {
   int l = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   asm volatile("" : "+v"(l));    // made anew for every tile
@@ -81,12 +84,12 @@ FOG_DEVICE LoadPlan plan_kc(int64_t ld, int row0, int rows, int K) {
     // row = 64 w + 8 j + r8: the swizzle key (row >> 1) & 7 is (r8 >> 1) ^ 4 (j & 1)
     const int c = pos ^ (r8 >> 1) ^ (4 * par);  // global chunk that lives at LDS position pos of this row
     p.klim[par] = K - 16 * c;
-    p.off[par] = (uint32_t)((int64_t)(first + 8 * par) * ld + 16 * c);
+    p.off[par] = (uint32_t)((int64_t)(first + 8 * par) * ld + 16 * c + kb);
   }
   return p;
 }
 // K-major operand: piece j covers contraction rows 32 w + 4 j .. + 3 of the pair; lane -> (k, LDS chunk position).
-FOG_DEVICE LoadPlan plan_km(int64_t ld, int col0, int cols, int K) {
+FOG_DEVICE LoadPlan plan_km(int64_t ld, int col0, int cols, int kb, int K) {
   int l = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   asm volatile("" : "+v"(l));
@@ -100,7 +103,7 @@ FOG_DEVICE LoadPlan plan_km(int64_t ld, int col0, int cols, int K) {
     // k + 4 j: the swizzle key (k + 4 j) & 7 is ((l >> 4) & 7) ^ 4 (j & 1)
     const int c = (l & 15) ^ (l >> 4) ^ (4 * par);
     p.klim[par] = K - k;
-    p.off[par] = (col0 + 16 * c < cols) ? (uint32_t)((int64_t)(k + 4 * par) * ld + col0 + 16 * c) : OOB;  // cols % 16 == 0
+    p.off[par] = (col0 + 16 * c < cols) ? (uint32_t)((int64_t)(kb + k + 4 * par) * ld + col0 + 16 * c) : OOB;  // cols % 16 == 0
   }
   return p;
 }
@@ -205,14 +208,15 @@ FOG_DEVICE void tile_origin(int logical, int tiles_m, int tiles_n, int& m0, int&
 
 // PRODUCTS_ONLY (measurement helper fog_probe_gemm_products_only, never the product path): interior tiles skip
 // their epilogue, so that the launch shows what the conversion, staging and stores of the finished tiles cost.
-template <int LAYOUT, int FA, int FB, bool PRODUCTS_ONLY = false>
+// SPLIT: the work items are (tile, contraction chunk) pairs, and the epilogue leaves the binary32 accumulators in the workspace.
+template <int LAYOUT, int FA, int FB, bool SPLIT, bool PRODUCTS_ONLY = false>
 __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   constexpr bool A_KM = LAYOUT == FOG_TN;
   constexpr bool B_KM = LAYOUT != FOG_NT;
 
   const int ntiles = g.tiles_m * g.tiles_n;
-  const TileWalk walk = tile_walk(ntiles);
+  const TileWalk walk = tile_walk(SPLIT ? ntiles * g.splits : ntiles);
   if (walk.first >= walk.end) return;
 
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
@@ -239,8 +243,16 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) zero16[r] = 0.0f;
 
-  const int nk = (g.K + BK - 1) / BK;
+  const int nk = ((SPLIT ? g.k_chunk : g.K) + BK - 1) / BK;   // every chunk of a split takes the steps of a full chunk
   const int nk4 = (nk + 3) & ~3;  // steps are handled four at a time (two pair stages); steps past K multiply zeros
+  // work item -> origin of its tile, first contraction index, number of contraction indices
+  int m0, n0, kb, klen;
+  auto item_range = [&](int item) {
+    const int c = SPLIT ? item / ntiles : 0;
+    kb = SPLIT ? c * g.k_chunk : 0;
+    klen = SPLIT ? min(g.K - kb, g.k_chunk) : g.K;
+    tile_origin(item - c * ntiles, g.tiles_m, g.tiles_n, m0, n0);
+  };
 
 #define FOG_LOAD_A(j, k0, ST) issue_piece<A_KM>(pa, j, rsrc_a, k0, lds_w + RING_A + (ST) * OPERAND_BYTES + 1024u * (j))
 #define FOG_LOAD_B(j, k0, ST) issue_piece<B_KM>(pb, j, rsrc_b, k0, lds_w + RING_B + (ST) * OPERAND_BYTES + 1024u * (j))
@@ -334,10 +346,9 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
   // tile the first two pairs of the workgroup's next tile are already being fetched, so a new tile
   // starts with its data in LDS and its first fragments in registers, and the epilogue's stores
   // drain while the next tile computes.
-  int m0, n0;
-  tile_origin(walk.first, g.tiles_m, g.tiles_n, m0, n0);
-  LoadPlan pa = A_KM ? plan_km(g.lda, m0, g.M, g.K) : plan_kc(g.lda, m0, g.M, g.K);
-  LoadPlan pb = B_KM ? plan_km(g.ldb, n0, g.N, g.K) : plan_kc(g.ldb, n0, g.N, g.K);
+  item_range(walk.first);
+  LoadPlan pa = A_KM ? plan_km(g.lda, m0, g.M, kb, klen) : plan_kc(g.lda, m0, g.M, kb, klen);
+  LoadPlan pb = B_KM ? plan_km(g.ldb, n0, g.N, kb, klen) : plan_kc(g.ldb, n0, g.N, kb, klen);
   v8i fa[4], fa3, xb[4], yb[4];   // A fragments (row 3 twice), B fragments twice
   FOG_ISSUE_PAIR(0, 0);
   FOG_ISSUE_PAIR(PAIR_K, 1);
@@ -361,9 +372,9 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
       /* last four steps of this tile: the loads issued now belong to the next tile (all zero-fill  \
          if there is none, which keeps the outstanding-load count the waits assume) */              \
       if (next < walk.end) {                                                                         \
-        tile_origin(next, g.tiles_m, g.tiles_n, m0, n0);                                             \
-        pa = A_KM ? plan_km(g.lda, m0, g.M, g.K) : plan_kc(g.lda, m0, g.M, g.K);                     \
-        pb = B_KM ? plan_km(g.ldb, n0, g.N, g.K) : plan_kc(g.ldb, n0, g.N, g.K);                     \
+        item_range(next);                                                                            \
+        pa = A_KM ? plan_km(g.lda, m0, g.M, kb, klen) : plan_kc(g.lda, m0, g.M, kb, klen);           \
+        pb = B_KM ? plan_km(g.ldb, n0, g.N, kb, klen) : plan_kc(g.ldb, n0, g.N, kb, klen);           \
       } else {                                                                                       \
         pa.off[0] = pa.off[1] = pb.off[0] = pb.off[1] = OOB;                                         \
       }                                                                                              \
@@ -389,6 +400,20 @@ __global__ __launch_bounds__(kThreads) void fp8_gemm_kernel(GemmArgs g) {
     // stored as 16-byte pieces, four lanes per 64-byte row segment: 32 coalesced stores per lane.  The stores are
     // non-temporal: a result of 100 to 235 MB cannot stay in the caches anyway, and as ordinary stores its dirty lines
     // were written back during whatever kernel came next (the abs-max pass of the next layer ran a third slower).
+    if (SPLIT) {
+      // The accumulators as they are, 1 KB per wave and store: float4 number (((tile * 4 + w) * 16 + 4 i + j) * 4 + qd) * 64 + l.
+      // Waited for at once, and with them the next item's prefetch.
+      float4* dst = reinterpret_cast<float4*>(g.partial) + (int64_t)(tile * 4 + w) * (16 * 256) + l;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int qd = 0; qd < 4; ++qd)
+            dst[((4 * i + j) * 4 + qd) * 64] = make_float4(acc[i][j][4 * qd + 0], acc[i][j][4 * qd + 1], acc[i][j][4 * qd + 2], acc[i][j][4 * qd + 3]);
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      continue;
+    }
     const bool fast = g.vec_store != 0 && m_cur + BM <= g.M && n_cur + BN <= g.N;
     if (PRODUCTS_ONLY && fast) {
 #pragma unroll
@@ -520,8 +545,8 @@ int compute_units() {
 // whatever happens; the smallest grid that still needs that many rounds leaves no workgroup idle in the last
 // one and, on a power-limited part, lets the busy CUs clock higher (896 tiles: 224 workgroups x 4 rounds
 // instead of 256 x 3.5).
-int persistent_grid(int64_t total, int* rounds_out = nullptr) {
-  int grid = (compute_units() / 8) * 8;
+int persistent_grid(int64_t total, int cus, int* rounds_out = nullptr) {
+  int grid = (cus / 8) * 8;
   if (grid < 8) grid = 8;
   const int64_t rounds = (total + grid - 1) / grid;
   const int64_t need = (((total + rounds - 1) / rounds + 7) / 8) * 8;
@@ -534,12 +559,12 @@ int persistent_grid(int64_t total, int* rounds_out = nullptr) {
 // tiles of C, from a cost model in shader cycles of such a split (a K-step about 1100, the bf16 epilogue 9000, the binary32 one
 // twice that, the reduce pass 2000 bytes per cycle plus a launch); 0 where it promises less than 7 %.  plan_product decides
 // what the room is used for.
-size_t split_room(int64_t M, int64_t N, int64_t K) {
+size_t split_room(int64_t M, int64_t N, int64_t K, int cus) {
   const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  if (tiles >= compute_units() || K < 1024) return 0;
+  if (tiles >= cus || K < 1024) return 0;
   auto cost = [&](int splits, int64_t k_chunk) {
     int rounds = 0;
-    persistent_grid(tiles * splits, &rounds);
+    persistent_grid(tiles * splits, cus, &rounds);
     const int64_t steps = ((k_chunk + BK - 1) / BK + 3) & ~(int64_t)3;
     double c = (double)rounds * (steps * 1100.0 + (splits > 1 ? 18000.0 : 9000.0));
     if (splits > 1) c += ((double)tiles * splits * BM * BN * 4 + 2.0 * M * N) / 2000.0 + 6000.0;
@@ -560,63 +585,86 @@ size_t split_room(int64_t M, int64_t N, int64_t K) {
 
 // Which kernel computes a product.  The 256 x 256 kernel moves the fewest operand bytes per matrix instruction and is the
 // fastest wherever its tiles fill the chip; every smaller tile costs more per flop (operand bytes from L2) and fills it with
-// less work: 46 -> 21 us on 1777 x 3088 x 2064 (91 tiles), 14.6 -> 4.7 us on 512 x 1024 x 1024 (8 tiles), but 98 -> 109 us on
-// 8192 x 4096 x 4096.  The estimate in microseconds, fitted to the kernel times of 110 shapes in the three layouts (M 64 to
-// 16384, N and K 256 to 14336; rms error 12 to 20 %, the chosen kernel is on average within 1 % of the fastest one):
+// less work: 46 -> 21 us on 1777 x 3088 x 2064 (91 tiles), 14.6 -> 4.7 us on 512 x 1024 x 1024 (8 tiles), but 102 -> 117 us on
+// 8192 x 4096 x 4096.  The estimate in microseconds, fitted to the times of 646 shapes in the three layouts (M, N and K 64 to 16384,
+// profiles/gemm_tile_times.md; rms error 8 to 14 % per kernel, the chosen one is on average within 2 % of the fastest):
 //   2 + sum over rounds of (stages * s(n) + epilogue),  stage = 128 contraction bytes, n = workgroups resident in the round,
-//   s(n) = s_few + (s_full - s_few) n / 256 up to one workgroup per compute unit, rising to s_two with two;
-//   a contraction split adds 6 us (second launch) and its partial tiles, written and read, at 16 TB/s (they stay in the caches).
-struct TileCost { int bm, bn, resident; double epilogue, s_few, s_full, s_two; };
+//   s(n) = s_few + (s_full - s_few) n / CUs up to one workgroup per compute unit, from s_one_more to s_two with two;
+//   operands whose rows are not whole 128-byte lines cost `ragged` more per stage if both are;
+//   a contraction split adds a second launch and its partial tiles, written and read.
+struct TileCost { int bm, bn, per_cu; double epilogue, s_few, s_full, s_one_more, s_two, ragged, launch2, tb_per_s; };
 constexpr TileCost kTileCost[] = {
-    {256, 128, 256, 4.27, 0.52, 0.81, 0.81},   // TILE_256x128
-    {128, 128, 256, 2.77, 0.39, 0.53, 0.53},   // TILE_128x128
-    {128, 128, 512, 1.88, 0.53, 0.92, 1.09},   // TILE_128x128_2WG
-    {64, 64, 512, 1.48, 0.12, 0.37, 0.41},     // TILE_64x64
+    {256, 128, 1, 4.36, 0.42, 0.77, 0.77, 0.77, 0.155, 3.4, 10.4},   // TILE_256x128
+    {128, 128, 1, 2.68, 0.25, 0.46, 0.46, 0.46, 0.30, 3.5, 8.9},     // TILE_128x128
+    {128, 128, 2, 2.53, 0.40, 0.70, 0.66, 0.91, 0.29, 0.0, 0.0},     // TILE_128x128_2WG: not split
+    {64, 64, 2, 1.40, 0.107, 0.206, 0.33, 0.383, 0.26, 4.3, 13.4},   // TILE_64x64
 };
 struct ProductPlan { int tile, splits, k_chunk; };   // tile: GemmTile, or -1 for the 256 x 256 kernel
-ProductPlan plan_product(fog_layout layout, int64_t M, int64_t N, int64_t K, size_t room) {
+ProductPlan plan_product(fog_layout layout, int64_t M, int64_t N, int64_t K, size_t room, int cus) {
   ProductPlan best{-1, 1, (int)K};
   const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  int rounds = 0;
-  const int grid = persistent_grid(tiles, &rounds);
-  const double stages = 2.0 * ((K + 4 * BK - 1) / (4 * BK));     // four K-steps per trip
-  // a smaller tile has to promise 10 %: where the chip is full the estimates lie closer together than their error
-  double best_cost = 0.9 * (2.0 + rounds * (stages * (1.03 + 0.47 * (grid < 256 ? grid / 256.0 : 1.0)) + 6.62));
+  const double ragged = 0.5 * (((layout == FOG_TN ? M : K) % 128 != 0) + ((layout == FOG_NT ? K : N) % 128 != 0));
+  // 256 x 256 tiles: four K-steps per trip
+  auto big_cost = [&](int64_t items, int64_t k_chunk, double epilogue) {
+    int rounds = 0;
+    const int grid = persistent_grid(items, cus, &rounds);
+    const double stages = 2.0 * ((k_chunk + 4 * BK - 1) / (4 * BK)), full = grid < cus ? grid / (double)cus : 1.0;
+    return 2.5 + rounds * (stages * (1.0 + 0.047 * ragged) * (0.836 + 0.512 * full) + epilogue);
+  };
+  double best_cost = big_cost(tiles, K, M % BM || N % BN ? 6.87 : 5.45);
+  for (int want = 2; room > 0 && want <= 16; ++want) {
+    const int64_t k_chunk = ((K + want - 1) / want + 255) / 256 * 256;
+    if (k_chunk < 512) break;
+    const int splits = (int)((K + k_chunk - 1) / k_chunk);
+    if (splits != want) continue;
+    if (tiles * splits * BM * BN * sizeof(float) > room) break;
+    // smaller tiles have to promise 5 % over a split of these: on long contractions they run up to 15 % over their estimate
+    const double cost = 0.95 * (big_cost(tiles * splits, k_chunk, 0.34) + 7.2 + (double)(tiles * splits) * BM * BN * 8.0 / 9.7e6);
+    if (cost < best_cost) { best_cost = cost; best = ProductPlan{-1, splits, (int)k_chunk}; }
+  }
   for (int t = 0; t < 4; ++t) {
     const TileCost& c = kTileCost[t];
-    const int64_t n_tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    const int64_t n_tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), resident = (int64_t)c.per_cu * cus;
     if (n_tiles > (1 << 24)) continue;
     // pieces of a 64-byte wide tile of a K-major operand are half lines
-    const double half_lines = c.bn != 64 || layout == FOG_NT ? 1.0 : layout == FOG_NN ? 1.3 : 1.5;
-    for (int want = 1; want <= 16; ++want) {
+    const double lines = (c.bn != 64 || layout == FOG_NT ? 1.0 : layout == FOG_NN ? 1.3 : 1.5) * (1.0 + c.ragged * ragged);
+    const int most = room > 0 && t != TILE_128x128_2WG ? 16 : 1;
+    for (int want = 1; want <= most; ++want) {
       const int64_t k_chunk = ((K + want - 1) / want + PAIR_K - 1) / PAIR_K * PAIR_K;
+      if (want > 1 && k_chunk < 512) break;
       const int splits = (int)((K + k_chunk - 1) / k_chunk);
-      if (want > 1 && (splits != want || k_chunk < 512)) continue;
+      if (splits != want) continue;
       const int64_t items = n_tiles * splits;
-      if (splits > 1 && (items * c.bm * c.bn * sizeof(float) > room || items > 2 * c.resident)) break;
-      const double n_st = (double)(k_chunk / PAIR_K);
+      if (splits > 1 && (items * c.bm * c.bn * sizeof(float) > room || items > 2 * resident)) break;
+      const double n_st = (double)((k_chunk + PAIR_K - 1) / PAIR_K) * lines;
       auto round_cost = [&](int64_t n) {
-        const double s = n <= 256 ? c.s_few + (c.s_full - c.s_few) * (n / 256.0) : c.s_full + (c.s_two - c.s_full) * ((n - 256) / 256.0);
-        return n > 0 ? n_st * s * half_lines + c.epilogue : 0.0;
+        const double x = n / (double)cus;
+        const double s = x <= 1.0 ? c.s_few + (c.s_full - c.s_few) * x : c.s_one_more + (c.s_two - c.s_one_more) * (x - 1.0);
+        return n > 0 ? n_st * s + c.epilogue : 0.0;
       };
-      double cost = 2.0 + (double)(items / c.resident) * round_cost(c.resident) + round_cost(items % c.resident);
-      if (splits > 1) cost += 6.0 + (double)items * c.bm * c.bn * 8.0 / 16e6;
+      double cost = 2.0 + (double)(items / resident) * round_cost(resident) + round_cost(items % resident);
+      if (splits > 1) cost += c.launch2 + (double)items * c.bm * c.bn * 8.0 / (c.tb_per_s * 1e6);
       if (cost < best_cost) { best_cost = cost; best = ProductPlan{t, splits, splits > 1 ? (int)k_chunk : (int)K}; }
     }
   }
   return best;
 }
 
-template <int LAYOUT, int FA, int FB>
+template <int LAYOUT, int FA, int FB, bool SPLIT>
 fog_status launch(const GemmArgs& g, hipStream_t s) {
   static bool configured = false;  // per instantiation; the attribute is sticky for the process
   if (!configured) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(fp8_gemm_kernel<LAYOUT, FA, FB>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess)
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(fp8_gemm_kernel<LAYOUT, FA, FB, SPLIT>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess)
       return FOG_ERR_HIP;
     configured = true;
   }
-  fp8_gemm_kernel<LAYOUT, FA, FB><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n), kThreads, LDS_BYTES, s>>>(g);
+  fp8_gemm_kernel<LAYOUT, FA, FB, SPLIT><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n * g.splits, compute_units()), kThreads, LDS_BYTES, s>>>(g);
+  if (SPLIT) gemm_reduce_launch(g, 4, 4, s);
   return fog_launch_status();
+}
+template <int LAYOUT, int FA, int FB>
+fog_status launch(const GemmArgs& g, hipStream_t s) {
+  return g.splits > 1 ? launch<LAYOUT, FA, FB, true>(g, s) : launch<LAYOUT, FA, FB, false>(g, s);
 }
 
 template <int LAYOUT>
@@ -631,7 +679,7 @@ inline bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintp
 
 extern "C" size_t fog_fp8_gemm_workspace(fog_layout, int64_t M, int64_t N, int64_t K) {
   if (M <= 0 || N <= 0 || K <= 0 || M > 0x7FFFFF00 || N > 0x7FFFFF00 || K > 0x7FFFFF00) return 0;
-  return split_room(M, N, K);
+  return split_room(M, N, K, compute_units());
 }
 
 extern "C" fog_status fog_fp8_gemm(fog_layout layout, int64_t M, int64_t N, int64_t K,
@@ -679,20 +727,35 @@ extern "C" fog_status fog_fp8_gemm(fog_layout layout, int64_t M, int64_t N, int6
   // the contraction is only split when the caller brought the room that the workspace query names
   size_t room = 0;
   if (workspace && aligned(workspace, 16)) {
-    room = split_room(M, N, K);
+    room = split_room(M, N, K, compute_units());
     if (workspace_bytes < room) room = 0;
   }
-  const ProductPlan plan = plan_product(layout, M, N, K, room);
-  if (plan.tile >= 0) {
-    g.splits = plan.splits; g.k_chunk = plan.k_chunk;
-    if (plan.splits > 1) g.partial = reinterpret_cast<float*>(workspace);
-    return gemm_tile_launch((GemmTile)plan.tile, layout, fmtA, fmtB, g, s);
-  }
+  const ProductPlan plan = plan_product(layout, M, N, K, room, compute_units());
+  g.splits = plan.splits;
+  g.k_chunk = plan.k_chunk;
+  if (plan.splits > 1) g.partial = reinterpret_cast<float*>(workspace);
+  if (plan.tile >= 0) return gemm_tile_launch((GemmTile)plan.tile, layout, fmtA, fmtB, g, s);
   switch (layout) {
     case FOG_NT: return launch_fmt<FOG_NT>(g, fmtA, fmtB, s);
     case FOG_NN: return launch_fmt<FOG_NN>(g, fmtA, fmtB, s);
     default: return launch_fmt<FOG_TN>(g, fmtA, fmtB, s);
   }
+}
+
+// Host-only helper (include/fog_probe.h): the choice above without a launch.
+extern "C" fog_status fog_probe_gemm_plan(fog_layout layout, int64_t M, int64_t N, int64_t K, int with_workspace, int compute_units_or_0,
+                                          int* tile_m, int* tile_n, int* workgroups_per_cu, int* splits, int* k_chunk) {
+  if (!tile_m || !tile_n || !workgroups_per_cu || !splits || !k_chunk) return FOG_ERR_NULL;
+  if (M <= 0 || N <= 0 || K <= 0 || M > 0x7FFFFF00 || N > 0x7FFFFF00 || K > 0x7FFFFF00) return FOG_ERR_SHAPE;
+  if ((layout != FOG_NT && layout != FOG_NN && layout != FOG_TN) || compute_units_or_0 < 0) return FOG_ERR_UNSUPPORTED;
+  const int cus = compute_units_or_0 > 0 ? compute_units_or_0 : compute_units();
+  const ProductPlan plan = plan_product(layout, M, N, K, with_workspace ? split_room(M, N, K, cus) : 0, cus);
+  *tile_m = plan.tile < 0 ? BM : kTileCost[plan.tile].bm;
+  *tile_n = plan.tile < 0 ? BN : kTileCost[plan.tile].bn;
+  *workgroups_per_cu = plan.tile < 0 ? 1 : kTileCost[plan.tile].per_cu;
+  *splits = plan.splits;
+  *k_chunk = plan.k_chunk;
+  return FOG_OK;
 }
 
 // Measurement helper (include/fog_probe.h): the NT product of E4M3 operands with the epilogue of every tile left out.
@@ -717,10 +780,10 @@ extern "C" fog_status fog_probe_gemm_products_only(int64_t M, int64_t N, int64_t
   g.splits = 1; g.k_chunk = (int)K; g.partial = nullptr;
   static bool configured = false;
   if (!configured) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(fp8_gemm_kernel<FOG_NT, 0, 0, true>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess)
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(fp8_gemm_kernel<FOG_NT, 0, 0, false, true>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess)
       return FOG_ERR_HIP;
     configured = true;
   }
-  fp8_gemm_kernel<FOG_NT, 0, 0, true><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n), kThreads, LDS_BYTES, (hipStream_t)stream>>>(g);
+  fp8_gemm_kernel<FOG_NT, 0, 0, false, true><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n, compute_units()), kThreads, LDS_BYTES, (hipStream_t)stream>>>(g);
   return fog_launch_status();
 }

@@ -4,15 +4,16 @@
 // One workgroup of 4 waves per tile, no persistence: with few tiles there is nothing to walk.  Operand stages of 128 contraction
 // bytes go straight into an LDS ring of two to four stages (buffer_load ... lds); the fragments of a whole stage are read into
 // registers one stage ahead, under the matrix instructions of the current one, so that a stage costs one barrier and no wait
-// for LDS.  What bounds these kernels is the rate at which a compute unit gets its operand stages: 50 to 60 GB/s whatever the
-// tile (16, 32 and 48 KB per stage of 64 x 64, 128 x 128 and 256 x 128 take 0.31, 0.57 and 0.86 us with few workgroups on the
-// chip; deeper rings, and fragments read later or earlier, change nothing).  Hence the rule of plan_product: the largest tile
-// that still spreads the product over the chip, and where even 64 x 64 leaves it idle, a split of the contraction.
+// for LDS.  A stage of 64 x 64, 128 x 128 and 256 x 128 (16, 32 and 48 KB of operands) takes 0.11, 0.25 and 0.42 us with few
+// workgroups on the chip, i.e. 150, 130 and 115 GB/s a compute unit, and 0.21, 0.46 and 0.77 us with one on each, 80, 70 and 62 GB/s
+// (fits of plan_product); deeper rings, and fragments read later or earlier, change nothing.  Hence its rule: the largest tile that
+// still spreads the product over the chip, and where even 64 x 64 leaves it idle, a split of the contraction.
 // Kernel times (256 x 256 kernel before, with its own contraction split where it had one -> now), us:
 //   512 x 1024 x 1024 NT  14.6 -> 4.7     1777 x 3088 x 2064 NT  46.9 -> 20.6    1777 x 2064 x 3088 NN  54.1 -> 20.2
 //   4096 x 2048 x 8192 NN  69.5 -> 53.4   754 x 432 x 12832 NT   27.2 -> 18.2    8192 x 2048 x 4096 TN  55 -> 59 (not taken)
 //
-// Contraction split.  With a caller workspace a product of few tiles and a long contraction is cut along K into chunks: the unit
+// Contraction split, of these kernels and of the 256 x 256 one.  With a caller workspace a product of few tiles and a long
+// contraction is cut along K into chunks: the unit
 // of work becomes (tile, chunk), every unit leaves its binary32 accumulators in the workspace, and a second kernel adds the
 // chunks of a tile in ascending order, applies the scales and rounds once to bf16.  Deterministic (no atomics); the sums differ
 // from the unsplit kernel's only in the order of binary32 additions.
@@ -322,7 +323,7 @@ fog_status launch(GemmArgs g, hipStream_t s) {
   }
   const int grid = 8 * ((g.tiles_m * g.tiles_n * g.splits + 7) / 8);
   fp8_gemm_tile_kernel<LAYOUT, FA, FB, TI, TJ, NST, WPS><<<grid, kThreads, LDS, s>>>(g);
-  if (g.splits > 1) gemm_tile_reduce_kernel<<<g.tiles_m * g.tiles_n * 4 * TI * TJ, kThreads, 0, s>>>(g, TI, TJ);
+  if (g.splits > 1) gemm_reduce_launch(g, TI, TJ, s);
   return fog_launch_status();
 }
 
@@ -343,6 +344,10 @@ fog_status launch_fmt(GemmTile tile, int fa, int fb, const GemmArgs& g, hipStrea
 }
 
 }  // namespace
+
+void gemm_reduce_launch(const GemmArgs& g, int ti, int tj, hipStream_t s) {
+  gemm_tile_reduce_kernel<<<g.tiles_m * g.tiles_n * 4 * ti * tj, kThreads, 0, s>>>(g, ti, tj);
+}
 
 fog_status gemm_tile_launch(GemmTile tile, fog_layout layout, fog_fp8 fmt_a, fog_fp8 fmt_b, GemmArgs g, hipStream_t s) {
   switch (layout) {

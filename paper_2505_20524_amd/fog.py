@@ -59,6 +59,7 @@ PROBE_SIGNATURES = {
     "fog_probe_attention_loop": (_I, [_I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _P]),
     "fog_probe_mfma_coissue": (_I, [_I, _I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _P]),
     "fog_probe_mfma_cross_wave": (_I, [_I, _I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _c.POINTER(_c.c_double), _P]),
+    "fog_probe_gemm_plan": (_I, [_I, _I64, _I64, _I64, _I, _I] + [_c.POINTER(_I)] * 5),
     "fog_probe_gemm_products_only": (_I, [_I64, _I64, _I64, _P, _I64, _P, _I64, _P, _P, _P, _I64, _P]),
 }
 
@@ -325,6 +326,13 @@ def probe_mfma_cross_wave(op, vector_ops, iters_matrix, iters_vector, sink, stre
     _check(load().fog_probe_mfma_cross_wave(op, vector_ops, iters_matrix, iters_vector, _ptr(sink), sink.numel() * sink.element_size(),
                                             _c.byref(cm), _c.byref(cv), _stream(stream)), "fog_probe_mfma_cross_wave")
     return cm.value, cv.value
+
+
+def probe_gemm_plan(layout, M, N, K, with_workspace=False, compute_units=0):
+    """(tile_m, tile_n, workgroups per CU, splits, k_chunk) of the kernel that fp8_gemm takes (fog_probe.h; no device needed)."""
+    out = [_I(0) for _ in range(5)]
+    _check(load().fog_probe_gemm_plan(layout, M, N, K, int(with_workspace), compute_units, *[_c.byref(o) for o in out]), "fog_probe_gemm_plan")
+    return tuple(o.value for o in out)
 
 
 def probe_gemm_products_only(M, N, K, A, sinv_a, B, sinv_b, C, stream=None):

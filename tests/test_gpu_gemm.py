@@ -199,7 +199,7 @@ def run_gemm_ws(layout, a, fa, sa, b, fb, sb, M, N, K, ws_bytes=None):
     return host_u16(C), need
 
 
-SPLIT_SHAPES = [   # few output tiles, long contraction: the launches the split is for
+SPLIT_SHAPES = [   # few output tiles, long contraction: the query names room on all of them, five are split (PLANNED_SPLITS names the kernels)
     (gemm.TN, 2048, 2048, 16384),     # config 4: weight gradient of the output projection (64 tiles)
     (gemm.NN, 4096, 2048, 8192),      # config 2: data gradient (128 tiles)
     (gemm.NT, 256, 256, 32768),       # one tile
@@ -251,18 +251,19 @@ def test_gemm_split_exact_integers_and_query():
         assert fog.fp8_gemm_workspace(layout, m, n, k) == 0
 
 
-TILE_SHAPES = [   # (layout, M, N, K, padding of C's rows): products of few 256 x 256 tiles, one of each smaller tile per layout
-    (gemm.NT, 65, 63, 16, 1), (gemm.NT, 500, 776, 1040, 8), (gemm.NN, 129, 80, 272, 3), (gemm.TN, 64, 144, 5, 0),      # 64 x 64
-    (gemm.NT, 1900, 1500, 3088, 8), (gemm.NN, 1777, 2064, 3088, 0), (gemm.TN, 1296, 1040, 2001, 5),                      # 128 x 128
-    (gemm.NT, 7900, 1184, 384, 0), (gemm.NN, 2050, 3216, 144, 8), (gemm.TN, 6336, 1104, 155, 0),                        # 128 x 128, two per CU
-    (gemm.NT, 1777, 3088, 2064, 0), (gemm.NN, 4000, 1808, 2064, 3), (gemm.TN, 3088, 2064, 1777, 8),                     # 256 x 128
+TILE_SHAPES = [   # (layout, M, N, K, padding of C's rows, tile, workgroups per CU): products of few 256 x 256 tiles, each smaller tile per layout
+    (gemm.NT, 65, 63, 16, 1, 64, 64, 2), (gemm.NT, 500, 776, 1040, 8, 64, 64, 2), (gemm.NN, 129, 80, 272, 3, 64, 64, 2), (gemm.TN, 64, 144, 5, 0, 64, 64, 2),
+    (gemm.NT, 1900, 1500, 3088, 8, 128, 128, 1), (gemm.NN, 1777, 2064, 3088, 0, 128, 128, 1), (gemm.TN, 1296, 1040, 2001, 5, 128, 128, 1),
+    (gemm.NT, 7900, 1184, 384, 0, 128, 128, 2), (gemm.NN, 2050, 3216, 144, 8, 128, 128, 2), (gemm.TN, 6336, 1104, 155, 0, 128, 128, 2),
+    (gemm.NT, 1777, 3088, 2064, 0, 256, 128, 1), (gemm.NN, 4000, 1808, 2064, 3, 256, 128, 1), (gemm.TN, 3088, 2064, 1777, 8, 256, 128, 1),
 ]
 
 
-@pytest.mark.parametrize("layout,M,N,K,pad", TILE_SHAPES)
-def test_gemm_small_tiles(layout, M, N, K, pad):
+@pytest.mark.parametrize("layout,M,N,K,pad,tile_m,tile_n,per_cu", TILE_SHAPES)
+def test_gemm_small_tiles(layout, M, N, K, pad, tile_m, tile_n, per_cu):
     """Products whose 256 x 256 tiles would leave most of the chip idle run on smaller tiles: edges of the tiles, contractions
     that end inside a stage, padded and unaligned C, against the oracle; nothing outside C's rows is written."""
+    assert fog.probe_gemm_plan(layout, M, N, K)[:4] == (tile_m, tile_n, per_cu, 1), "another kernel runs on this shape"
     fa, fb = (fp8.E5M2, fp8.E4M3) if layout != gemm.NT else (fp8.E4M3, fp8.E4M3)
     A8, sa, B8, sb = quantized_layer(M + 5 * N + K, M, N, K, fa, fb)
     a, b = lay(layout, A8, B8)
@@ -281,8 +282,8 @@ def test_gemm_small_tiles(layout, M, N, K, pad):
 @pytest.mark.parametrize("layout,M,N,K", [(gemm.NT, 66, 1936, 9520), (gemm.NN, 80, 368, 11520), (gemm.TN, 304, 272, 8200), (gemm.NT, 328, 1584, 6000),
                                           (gemm.NN, 2339, 400, 9616)])
 def test_gemm_small_tile_split(layout, M, N, K):
-    """The contraction split on smaller tiles: partial tiles that reach past C, a last chunk shorter than the others, the
-    workspace full of NaN patterns beforehand and its end untouched; the same bits on a second call."""
+    """With room for a split on smaller tiles (the fourth shape is left whole all the same): partial tiles that reach past C, a last chunk
+    shorter than the others, the workspace full of NaN patterns beforehand and its end untouched; the same bits on a second call."""
     fa, fb = (fp8.E5M2, fp8.E4M3) if layout != gemm.NT else (fp8.E4M3, fp8.E4M3)
     A8, sa, B8, sb = quantized_layer(M + 7 * N + K, M, N, K, fa, fb)
     a, b = lay(layout, A8, B8)
@@ -301,3 +302,75 @@ def test_gemm_small_tile_split(layout, M, N, K):
     what = "split tiles %d %dx%dx%d" % (layout, M, N, K)
     check_bf16(got[0], ref, what=what)
     check_gemm_elementwise(got[0], ref, absdot(layout, a, fa, sa, b, fb, sb), what=what)
+
+
+def wide(a, pad):
+    """The matrix as a view of a wider buffer whose padding holds 0x7E (the largest E4M3 code, a NaN in E5M2): a leak would show."""
+    buf = torch.full((a.shape[0], a.shape[1] + pad), 0x7E, dtype=torch.uint8, device="cuda")
+    buf[:, :a.shape[1]] = dev(a)
+    return buf[:, :a.shape[1]]
+
+
+E4, E5 = fp8.E4M3, fp8.E5M2
+BIG_EDGE_SHAPES = [   # (layout, M, N, K, formats, padding of A's, B's and C's rows): 256 x 256 tiles, one and two rounds of them
+    (gemm.NT, 911, 8860, 432, E4, E5, 16, 0, 0),          # C's rows allow no 16-byte store (8860 = 4 mod 8)
+    (gemm.NT, 5889, 4104, 400, E5, E5, 0, 48, 8),
+    (gemm.NN, 2706, 3376, 400, E5, E4, 48, 16, 3),
+    (gemm.NN, 6935, 3504, 400, E4, E5, 16, 0, 0),
+    (gemm.TN, 5296, 1712, 390, E5, E5, 0, 16, 8),
+    (gemm.TN, 6704, 3648, 385, E4, E4, 32, 16, 5),
+]
+
+
+@pytest.mark.parametrize("layout,M,N,K,fa,fb,pa,pb,pc", BIG_EDGE_SHAPES)
+def test_gemm_big_tile_edges(layout, M, N, K, fa, fb, pa, pb, pc):
+    """The 256 x 256 kernel away from its home ground: edge tiles in both directions, contractions that end inside a K-step,
+    padded operands, padded and unaligned C, the format pairs; nothing outside C's rows is written."""
+    assert fog.probe_gemm_plan(layout, M, N, K)[:4] == (256, 256, 1, 1), "another kernel runs on this shape"
+    A8, sa, B8, sb = quantized_layer(M + 11 * N + K, M, N, K, fa, fb)
+    a, b = lay(layout, A8, B8)
+    ref = gemm.fp8_gemm(layout, a, fa, sa, b, fb, sb)
+    store = torch.full((M + 1, N + pc), 0x7FC0, dtype=torch.int16, device="cuda")
+    fog.fp8_gemm(layout, M, N, K, wide(a, pa), fa, fscalar(sa), wide(b, pb), fb, fscalar(sb), store[:M, :N])
+    torch.cuda.synchronize()
+    got = host_u16(store)
+    assert (got[M] == 0x7FC0).all() and (got[:, N:] == 0x7FC0).all()
+    what = "edges %d %dx%dx%d" % (layout, M, N, K)
+    check_bf16(got[:M, :N], ref, what=what)
+    check_gemm_elementwise(got[:M, :N], ref, absdot(layout, a, fa, sa, b, fb, sb), what=what)
+
+
+PLANNED_SPLITS = [   # (layout, M, N, K, formats, padding of C's rows, tile): every kernel that splits, per layout, ragged
+    (gemm.NT, 73, 77, 4848, E4, E4, 3, 64, 64), (gemm.NN, 87, 112, 4592, E5, E4, 0, 64, 64), (gemm.TN, 64, 80, 4909, E4, E5, 8, 64, 64),
+    (gemm.NT, 2321, 65, 12608, E5, E4, 7, 128, 128), (gemm.NN, 69, 1168, 13456, E4, E5, 8, 128, 128), (gemm.TN, 80, 1392, 6508, E5, E5, 0, 128, 128),
+    (gemm.NT, 5987, 136, 7472, E4, E4, 8, 256, 128), (gemm.NN, 130, 5552, 7664, E5, E5, 1, 256, 128), (gemm.TN, 8592, 80, 10583, E5, E4, 0, 256, 128),
+    (gemm.NT, 8274, 136, 12480, E4, E5, 0, 256, 256), (gemm.NN, 1744, 2480, 9296, E5, E4, 5, 256, 256), (gemm.TN, 6432, 144, 13908, E5, E4, 8, 256, 256),
+]
+
+
+@pytest.mark.parametrize("layout,M,N,K,fa,fb,pc,tile_m,tile_n", PLANNED_SPLITS)
+def test_gemm_split_kernels(layout, M, N, K, fa, fb, pc, tile_m, tile_n):
+    """The contraction split on each tile, partial tiles that reach past C, a shorter last chunk: the workspace is full of NaN patterns
+    beforehand, is used, and its end is not touched; nothing outside C's rows is written; the same bits on a second call."""
+    plan = fog.probe_gemm_plan(layout, M, N, K, True)
+    assert plan[:2] == (tile_m, tile_n) and plan[3] > 1, "another kernel runs on this shape"
+    assert K % plan[4] != 0
+    A8, sa, B8, sb = quantized_layer(M + 13 * N + K, M, N, K, fa, fb)
+    a, b = lay(layout, A8, B8)
+    ref = gemm.fp8_gemm(layout, a, fa, sa, b, fb, sb)
+    need = fog.fp8_gemm_workspace(layout, M, N, K)
+    used = plan[3] * -(-M // tile_m) * -(-N // tile_n) * tile_m * tile_n * 4
+    assert 0 < used <= need
+    got = []
+    for _ in range(2):
+        ws = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+        store = torch.full((M + 1, N + pc), 0x7FC0, dtype=torch.int16, device="cuda")
+        fog.fp8_gemm(layout, M, N, K, dev(a), fa, fscalar(sa), dev(b), fb, fscalar(sb), store[:M, :N], workspace=ws[:need])
+        torch.cuda.synchronize()
+        assert not (ws[:used].view(torch.int32) == -1).any() and (ws[used:] == 0xFF).all()
+        got.append(host_u16(store))
+    assert np.array_equal(got[0], got[1])
+    assert (got[0][M] == 0x7FC0).all() and (got[0][:, N:] == 0x7FC0).all()
+    what = "split %dx%d %d %dx%dx%d" % (tile_m, tile_n, layout, M, N, K)
+    check_bf16(got[0][:M, :N], ref, what=what)
+    check_gemm_elementwise(got[0][:M, :N], ref, absdot(layout, a, fa, sa, b, fb, sb), what=what)
