@@ -668,8 +668,8 @@ static fog_status bwd_launch(int B, int H, int H_kv, int S, float softmax_scale,
   // group): up to half a workgroup per CU always, up to two where that workgroup walks 64 blocks or more.  Backward, us, without ->
   // with: 36 workgroups of up to 36 blocks 46 -> 37, 68 of 68 74 -> 56, 256 of 64 82 -> 71, 512 of 256 338 -> 319; but 256 of 4
   // 22 -> 25 and 512 of 32 72 -> 76.
-  const int longest = (S / STEP) * a.G;
-  if (grid_kv <= 128 || (grid_kv <= 512 && longest >= 64)) {
+  const int longest = (S / STEP) * a.G, cus = fog_compute_units();
+  if (2 * grid_kv <= cus || (grid_kv <= 2 * cus && longest >= 64)) {
     if (causal) attn_bwd_dkdv_kernel<true, true><<<2 * grid_kv, PAIR_THREADS, 0, s>>>(a);
     else        attn_bwd_dkdv_kernel<false, true><<<2 * grid_kv, PAIR_THREADS, 0, s>>>(a);
   } else {

@@ -528,18 +528,6 @@ __global__ __launch_bounds__(256) void gemm_zero_kernel(uint16_t* C, int64_t ldc
     C[(i / N) * ldc + (i % N)] = 0;
 }
 
-// Number of compute units of the current device (the persistent grid size), queried once per process.
-int compute_units() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-      n = 256;
-    cus = n;
-  }
-  return cus;
-}
-
 // Persistent grid for `total` work items: one workgroup per compute unit (a multiple of 8 so that every XCD
 // gets the same number), fewer when there are fewer items.  The launch takes ceil(total / grid) rounds
 // whatever happens; the smallest grid that still needs that many rounds leaves no workgroup idle in the last
@@ -658,7 +646,7 @@ fog_status launch(const GemmArgs& g, hipStream_t s) {
       return FOG_ERR_HIP;
     configured = true;
   }
-  fp8_gemm_kernel<LAYOUT, FA, FB, SPLIT><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n * g.splits, compute_units()), kThreads, LDS_BYTES, s>>>(g);
+  fp8_gemm_kernel<LAYOUT, FA, FB, SPLIT><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n * g.splits, fog_compute_units()), kThreads, LDS_BYTES, s>>>(g);
   if (SPLIT) gemm_reduce_launch(g, 4, 4, s);
   return fog_launch_status();
 }
@@ -679,7 +667,7 @@ inline bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintp
 
 extern "C" size_t fog_fp8_gemm_workspace(fog_layout, int64_t M, int64_t N, int64_t K) {
   if (M <= 0 || N <= 0 || K <= 0 || M > 0x7FFFFF00 || N > 0x7FFFFF00 || K > 0x7FFFFF00) return 0;
-  return split_room(M, N, K, compute_units());
+  return split_room(M, N, K, fog_compute_units());
 }
 
 extern "C" fog_status fog_fp8_gemm(fog_layout layout, int64_t M, int64_t N, int64_t K,
@@ -710,7 +698,7 @@ extern "C" fog_status fog_fp8_gemm(fog_layout layout, int64_t M, int64_t N, int6
   g.tiles_n = (int)((N + BN - 1) / BN);
   if ((int64_t)g.tiles_m * g.tiles_n > 0x7FFFFFF0) return FOG_ERR_UNSUPPORTED;
   g.vec_store = aligned(C_bf16, 16) && ldc % 8 == 0;
-  g.wide_store = (int64_t)g.tiles_m * g.tiles_n >= 2 * (int64_t)compute_units();
+  g.wide_store = (int64_t)g.tiles_m * g.tiles_n >= 2 * (int64_t)fog_compute_units();
   // addressable span of each operand (last row may be shorter than the leading dimension)
   const int64_t a_rows = layout == FOG_TN ? K : M, b_rows = layout == FOG_NT ? N : K;
   const int64_t a_span = K > 0 ? (a_rows - 1) * lda + a_cols : 0, b_span = K > 0 ? (b_rows - 1) * ldb + b_cols : 0;
@@ -727,10 +715,10 @@ extern "C" fog_status fog_fp8_gemm(fog_layout layout, int64_t M, int64_t N, int6
   // the contraction is only split when the caller brought the room that the workspace query names
   size_t room = 0;
   if (workspace && aligned(workspace, 16)) {
-    room = split_room(M, N, K, compute_units());
+    room = split_room(M, N, K, fog_compute_units());
     if (workspace_bytes < room) room = 0;
   }
-  const ProductPlan plan = plan_product(layout, M, N, K, room, compute_units());
+  const ProductPlan plan = plan_product(layout, M, N, K, room, fog_compute_units());
   g.splits = plan.splits;
   g.k_chunk = plan.k_chunk;
   if (plan.splits > 1) g.partial = reinterpret_cast<float*>(workspace);
@@ -748,7 +736,7 @@ extern "C" fog_status fog_probe_gemm_plan(fog_layout layout, int64_t M, int64_t 
   if (!tile_m || !tile_n || !workgroups_per_cu || !splits || !k_chunk) return FOG_ERR_NULL;
   if (M <= 0 || N <= 0 || K <= 0 || M > 0x7FFFFF00 || N > 0x7FFFFF00 || K > 0x7FFFFF00) return FOG_ERR_SHAPE;
   if ((layout != FOG_NT && layout != FOG_NN && layout != FOG_TN) || compute_units_or_0 < 0) return FOG_ERR_UNSUPPORTED;
-  const int cus = compute_units_or_0 > 0 ? compute_units_or_0 : compute_units();
+  const int cus = compute_units_or_0 > 0 ? compute_units_or_0 : fog_compute_units();
   const ProductPlan plan = plan_product(layout, M, N, K, with_workspace ? split_room(M, N, K, cus) : 0, cus);
   *tile_m = plan.tile < 0 ? BM : kTileCost[plan.tile].bm;
   *tile_n = plan.tile < 0 ? BN : kTileCost[plan.tile].bn;
@@ -784,6 +772,6 @@ extern "C" fog_status fog_probe_gemm_products_only(int64_t M, int64_t N, int64_t
       return FOG_ERR_HIP;
     configured = true;
   }
-  fp8_gemm_kernel<FOG_NT, 0, 0, false, true><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n, compute_units()), kThreads, LDS_BYTES, (hipStream_t)stream>>>(g);
+  fp8_gemm_kernel<FOG_NT, 0, 0, false, true><<<persistent_grid((int64_t)g.tiles_m * g.tiles_n, fog_compute_units()), kThreads, LDS_BYTES, (hipStream_t)stream>>>(g);
   return fog_launch_status();
 }
