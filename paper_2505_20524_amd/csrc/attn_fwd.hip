@@ -68,8 +68,8 @@ FOG_DEVICE float pair_max32(float v) {
 
 // LDS chunk swizzles (16-byte chunks inside a 128-byte row), applied by choosing which global chunk
 // a lane of the direct load fetches.  K rows are read 32 consecutive rows at a time (same chunk):
-// key (row >> 1) & 7 (with row & 7 rows r and r + 8 of a 16-byte read share their banks: 1-4 % of the kernel).  V rows are read by the transposing read 8 rows {r..r+3, r+8..r+11} at a time:
-// key (row & 3) | ((row >> 3) & 1) << 2.
+// key (row >> 1) & 7 (with row & 7 rows r and r + 8 of a 16-byte read share their banks: 1-4 % of the kernel).  V rows are
+// read by the transposing read 8 rows {r..r+3, r+8..r+11} at a time: key (row & 3) | ((row >> 3) & 1) << 2.
 FOG_DEVICE int swz_k(int row) { return (row >> 1) & 7; }
 FOG_DEVICE int swz_v(int row) { return (row & 3) | (((row >> 3) & 1) << 2); }
 

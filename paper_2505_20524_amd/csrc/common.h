@@ -154,13 +154,15 @@ template <int T, typename RowOf>
 FOG_DEVICE void store_tile_rows(uint8_t* stage, const v16f* x, float scale, uint16_t* out, int ld, RowOf row_of) {
   constexpr int STRIDE = 64 * T + 16, LPR = 4 * T, RPS = 64 / LPR;    // bytes of a staged row, lanes per row, rows per store
   const int l = threadIdx.x & 63;
+  // (the wave's LDS instructions complete in order: all that is needed is that the compiler keeps their order, here against what
+  // the wave has read from the area before, and between the two halves below)
+  asm volatile("" ::: "memory");
 #pragma unroll
   for (int d = 0; d < T; ++d)
 #pragma unroll
     for (int qd = 0; qd < 4; ++qd)
       *reinterpret_cast<uint2*>(stage + (l & 31) * STRIDE + 64 * d + 16 * qd + 8 * (l >> 5)) =
           make_uint2(pack_bf16x2(x[d][4 * qd] * scale, x[d][4 * qd + 1] * scale), pack_bf16x2(x[d][4 * qd + 2] * scale, x[d][4 * qd + 3] * scale));
-  // (the wave's LDS instructions complete in order: all that is needed is that the compiler keeps their order)
   asm volatile("" ::: "memory");
 #pragma unroll
   for (int t = 0; t < 32 / RPS; ++t) {

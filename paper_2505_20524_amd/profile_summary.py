@@ -185,11 +185,13 @@ def units_summary(cid, d, out_dir):
     o.append("| | " + " | ".join("`%s`" % disp[n] for n in kn) + " |")
     o.append("|---|" + "---|" * len(kn))
     o.append("| launch duration under the counters, us | " + " | ".join("%.1f" % (sum(dur[n]) / len(dur[n]) / 1e3) for n in kn) + " |")
-    o.append("| shader clock = cycles / duration, GHz | " + " | ".join("%.2f" % (avg(n, "GRBM_GUI_ACTIVE") / 8 / (sum(dur[n]) / len(dur[n]))) for n in kn) + " |")
-    o.append("| matrix-core busy fraction of those cycles | " + " | ".join("%.1f %%" % (100 * avg(n, "SQ_VALU_MFMA_BUSY_CYCLES") / 1024 / (avg(n, "GRBM_GUI_ACTIVE") / 8)) for n in kn) + " |")
+    # around a launch of a few microseconds the chip is active for longer than the launch: nothing is derived from those cycles
+    cyc = lambda n, s: s if sum(dur[n]) / len(dur[n]) >= 20e3 else "-"
+    o.append("| shader clock = cycles / duration, GHz | " + " | ".join(cyc(n, "%.2f" % (avg(n, "GRBM_GUI_ACTIVE") / 8 / (sum(dur[n]) / len(dur[n])))) for n in kn) + " |")
+    o.append("| matrix-core busy fraction of those cycles | " + " | ".join(cyc(n, "%.1f %%" % (100 * avg(n, "SQ_VALU_MFMA_BUSY_CYCLES") / 1024 / (avg(n, "GRBM_GUI_ACTIVE") / 8))) for n in kn) + " |")
     o.append("| wave time waiting on s_waitcnt (SQ_WAIT_ANY / SQ_WAVE_CYCLES) | " + " | ".join("%.0f %%" % (100 * avg(n, "SQ_WAIT_ANY") / avg(n, "SQ_WAVE_CYCLES")) for n in kn) + " |")
     o.append("| wave time issuing vector ALU incl. matrix instructions (SQ_ACTIVE_INST_VALU / SQ_WAVE_CYCLES) | " + " | ".join("%.0f %%" % (100 * avg(n, "SQ_ACTIVE_INST_VALU") / avg(n, "SQ_WAVE_CYCLES")) for n in kn) + " |")
-    o.append("| resident waves per SIMD (4 SQ_WAVE_CYCLES / (1024 x cycles)) | " + " | ".join("%.2f" % (4 * avg(n, "SQ_WAVE_CYCLES") / (1024 * avg(n, "GRBM_GUI_ACTIVE") / 8)) for n in kn) + " |")
+    o.append("| resident waves per SIMD (4 SQ_WAVE_CYCLES / (1024 x cycles)) | " + " | ".join(cyc(n, "%.2f" % (4 * avg(n, "SQ_WAVE_CYCLES") / (1024 * avg(n, "GRBM_GUI_ACTIVE") / 8))) for n in kn) + " |")
     o.append("| bytes per L2 read request (16 B x 64 lanes x TA wavefronts / requests) | " + " | ".join("%.0f" % (avg(n, "TA_BUFFER_TOTAL_CYCLES_sum") / 16 * 1024 / avg(n, "TCP_TCC_READ_REQ_sum")) for n in kn) + " |")
     o.append("| mean L2 read latency seen by the vector cache, cycles | " + " | ".join("%.0f" % (avg(n, "TCP_TCC_READ_REQ_LATENCY_sum") / avg(n, "TCP_TCC_READ_REQ_sum")) for n in kn) + " |")
     open(os.path.join(out_dir, "bench_config%d_unit_counters.md" % cid), "w").write("\n".join(o) + "\n")
