@@ -184,8 +184,8 @@ def test_backward_with_a_stale_ds_scale_saturates_like_the_oracle(factor):
 
 @pytest.mark.parametrize("causal", [True, False])
 def test_backward_with_a_scale_beyond_any_gradient(causal):
-    """A scale of dS so large (above 1e18) that rho_ds dS may leave binary32: the dK/dV kernel clamps before its casts, which
-    saturate finite values only.  Every dS that is not tiny saturates, in the oracle too."""
+    """A scale of dS so large (above 1e18) that rho_ds dS may leave binary32: the dK/dV kernel clamps infinities too before its
+    casts.  Every dS that is not tiny saturates, in the oracle too."""
     B, H, S = 1, 2, 192
     q, k, v, do = synth.small_attention(2700, B, H, S)
     c = cast_all(q, k, v, do)

@@ -106,8 +106,8 @@ def test_in_place_without_codes_and_errors():
 @pytest.mark.parametrize("rho", [0.5, 1.0e-30, 3.0e38, float("inf"), float("nan")])
 def test_special_values_and_scales(rho, fmt):
     """NaN, infinities and huge values in the residual stream or the sub-layer output, and scales that overflow products or are not
-    finite: the codes are those of the plain cast of the stored tensor, byte for byte (the rows kernel drops clamp and NaN test
-    where the values and the scale allow it, the plain cast never does)."""
+    finite: the codes are those of the plain cast of the stored tensor, byte for byte (the rows kernel casts without a NaN test
+    first and once more with it where a value or the scale asks for it, the plain cast always tests)."""
     rows, cols = 33, 1024
     rng = np.random.default_rng(12)
     x = synth.f32_to_bf16_bits(rng.standard_normal((rows, cols)).astype(np.float32))
@@ -127,8 +127,8 @@ def test_special_values_and_scales(rho, fmt):
 
 @pytest.mark.parametrize("fmt", [fp8.E4M3, fp8.E5M2])
 def test_sums_beyond_the_largest_bf16(fmt):
-    """Finite binary32 sums on both sides of the point where the rounding to bf16 goes to infinity: stored as infinities (the rows
-    kernel converts to bf16 with saturating FP8 converts switched on), the same tensor, codes and abs-max as the general kernel."""
+    """Finite binary32 sums on both sides of the point where the rounding to bf16 goes to infinity: stored as infinities (under the
+    hardware's saturating mode the convert would round them down), the same tensor, codes and abs-max as the general kernel."""
     rows, cols = 5, 1024
     x = np.full((rows, cols), 0x7F7F, np.uint16)                     # the largest finite bf16; half a step above it is 6.6e35
     x[1::2] |= 0x8000
