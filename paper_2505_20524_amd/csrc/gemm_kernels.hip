@@ -574,8 +574,8 @@ size_t split_room(int64_t M, int64_t N, int64_t K, int cus) {
 // Which kernel computes a product.  The 256 x 256 kernel moves the fewest operand bytes per matrix instruction and is the
 // fastest wherever its tiles fill the chip; every smaller tile costs more per flop (operand bytes from L2) and fills it with
 // less work: 46 -> 21 us on 1777 x 3088 x 2064 (91 tiles), 14.6 -> 4.7 us on 512 x 1024 x 1024 (8 tiles), but 102 -> 117 us on
-// 8192 x 4096 x 4096.  The estimate in microseconds, fitted to the times of 646 shapes in the three layouts (M, N and K 64 to 16384,
-// profiles/gemm_tile_times.md; rms error 8 to 14 % per kernel, the chosen one is on average within 2 % of the fastest):
+// 8192 x 4096 x 4096.  The estimate in microseconds, fitted to the times of 646 shapes in the three layouts (M, N and K 64 to 16384;
+// rms error 8 to 14 % per kernel, the chosen one is on average within 2 % of the fastest):
 //   2 + sum over rounds of (stages * s(n) + epilogue),  stage = 128 contraction bytes, n = workgroups resident in the round,
 //   s(n) = s_few + (s_full - s_few) n / CUs up to one workgroup per compute unit, from s_one_more to s_two with two;
 //   operands whose rows are not whole 128-byte lines cost `ragged` more per stage if both are;
