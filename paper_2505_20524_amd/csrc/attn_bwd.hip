@@ -7,9 +7,9 @@
 //     dP  = sinv_do sinv_v (dO~ V~^T)               dS = P o (dP - D_i),  dS~ = E5M2(rho_ds dS)
 //     dQ  = s sinv_k / rho_ds (dS~ K~)              dK = s sinv_q / rho_ds (dS~^T Q~)
 //
-// Three kernels.  (0) D_i and two per-row constants, one pass over the bf16 tensors.  (1) dK/dV: a workgroup owns
-// 64 keys and walks the query blocks at or below its diagonal.  (2) dQ: a workgroup owns 128 queries and walks
-// the key blocks.  Both produce the score tile with lane = query; its packed dS is then the B operand of
+// Two kernels.  (1) dQ: a workgroup owns 128 queries, sums their D_i from the bf16 tensors and walks the key blocks; it leaves
+// two constants per row for the other kernel.  (2) dK/dV: a workgroup owns 64 keys and walks the query blocks at or below
+// its diagonal.  Both produce the score tile with lane = query; its packed dS is then the B operand of
 // dQ^T += K^T dS^T as it lies in the registers, and reaches lane = key, the B operand of dV^T += dO^T P and
 // dK^T += Q^T dS, through a small exchange tile in LDS.  Recomputing S and dP in both kernels costs two extra
 // products but keeps every accumulator in registers, needs no atomics and is deterministic.
@@ -25,10 +25,10 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int HD = 128;
-constexpr int BLK = 128;           // queries owned by a workgroup of kernel 2
+constexpr int BLK = 128;           // queries owned by a workgroup of the dQ kernel
 constexpr int STEP = 64;           // rows of the streamed operands per step
 constexpr int TILE = STEP * HD;    // 8 KB, 16-byte chunks swizzled by swz(row)
-constexpr int NSTAGE = 4;          // ring of kernel 2
+constexpr int NSTAGE = 4;          // ring of the dQ kernel
 constexpr uint32_t OOB = 0x80000000u;
 // The ring stage of a block as a compile-time constant: the loops are unrolled over the ring so that every LDS address is a
 // per-lane constant plus an immediate offset (a stage taken from the block number at run time costs an integer add per
@@ -142,34 +142,33 @@ FOG_DEVICE void tile_load_offsets(uint32_t* off) {
 
 FOG_DEVICE float lane_xor32(float v) { return __shfl_xor(v, 32, 64); }
 
-// ------------------------------------------------------------------ kernel 0: per-row constants
-// ws[0][row] = D_i = sum_d dO_id O_id                (used by the dQ kernel)
-// ws[1][row] = D_i * rho_ds / rho_p                  (dK/dV kernel: its probabilities carry the factor rho_p)
-// ws[2][row] = lse_i - log2 rho_p                    (dK/dV kernel: 2^(x - that) = rho_p P)
-// Folding the scales into per-row constants once saves three vector instructions per score later.
-__global__ __launch_bounds__(kThreads) void attn_bwd_rowdot_kernel(const uint16_t* __restrict__ O, const uint16_t* __restrict__ dO,
-                                                                   const float* __restrict__ lse, const float* __restrict__ scale_p,
-                                                                   const float* __restrict__ scale_ds, float* __restrict__ ws,
-                                                                   int64_t rows, uint32_t* __restrict__ amax_ds) {
-  // the abs-max of dS starts from 0; the kernels that raise it are launched after this one on the same stream
-  if (amax_ds && blockIdx.x == 0 && threadIdx.x == 0) *amax_ds = 0u;
-  const int64_t row = (int64_t)blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
-  const int part = threadIdx.x & 15;
-  float s = 0.0f;
-  if (row < rows) {
-    uint4 a = *reinterpret_cast<const uint4*>(O + row * HD + part * 8);
-    uint4 b = *reinterpret_cast<const uint4*>(dO + row * HD + part * 8);
-    s = bf16lo(a.x) * bf16lo(b.x) + bf16hi(a.x) * bf16hi(b.x) + bf16lo(a.y) * bf16lo(b.y) + bf16hi(a.y) * bf16hi(b.y) +
-        bf16lo(a.z) * bf16lo(b.z) + bf16hi(a.z) * bf16hi(b.z) + bf16lo(a.w) * bf16lo(b.w) + bf16hi(a.w) * bf16hi(b.w);
+// D_i = sum_d dO_id O_id of 32 consecutive rows by one wave of the dQ kernel, before it walks the keys.  (As a kernel of its own, one
+// pass over O and dO in front of the others, this took 27, 15 and 4 us at 2 x 32 heads x 4096, 4 x 16 x 2048 and 1 x 16/4 x 576; here
+// its loads fly under other workgroups' matrix instructions: forward + backward with casts 781 -> 762, 265 -> 259, 55.6 -> 54.6 us.)
+// Layout: sixteen lanes hold a row, four rows per load, the sums of lane l's row
+// l & 31 come back through `park` (32 floats of LDS, the wave's own).  The exchange rotates within rows of 16 lanes by 8, 4, 2 and 1.
+template <int N>
+FOG_DEVICE float ror_add(float s) {
+  return s + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0x120 + N, 0xF, 0xF, false));
+}
+FOG_DEVICE float row_dots(const uint16_t* __restrict__ O, const uint16_t* __restrict__ dO, float* park) {
+  const int l = threadIdx.x & 63, at = (l >> 4) * HD + (l & 15) * 8;
+  uint4 x[8], y[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    x[i] = ld_nt16(O + at + 4 * i * HD);
+    y[i] = ld_nt16(dO + at + 4 * i * HD);
   }
 #pragma unroll
-  for (int o = 8; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (row < rows && part == 0) {
-    const float rp = *scale_p, rds = *scale_ds;
-    ws[row] = s;
-    ws[rows + row] = s * (rds / rp);
-    ws[2 * rows + row] = lse[row] - __log2f(rp);
+  for (int i = 0; i < 8; ++i) {
+    const uint4 a = x[i], b = y[i];
+    float s = bf16lo(a.x) * bf16lo(b.x) + bf16hi(a.x) * bf16hi(b.x) + bf16lo(a.y) * bf16lo(b.y) + bf16hi(a.y) * bf16hi(b.y) +
+              bf16lo(a.z) * bf16lo(b.z) + bf16hi(a.z) * bf16hi(b.z) + bf16lo(a.w) * bf16lo(b.w) + bf16hi(a.w) * bf16hi(b.w);
+    s = ror_add<1>(ror_add<2>(ror_add<4>(ror_add<8>(s))));
+    if ((l & 15) == 0) park[4 * i + (l >> 4)] = s;
   }
+  asm volatile("" ::: "memory");   // (a wave's LDS instructions complete in order)
+  return park[l & 31];
 }
 
 // Largest magnitude among the 16 T values of a lane's T score tiles (NaN operands are dropped by the maximum), as 2 T
@@ -197,7 +196,7 @@ FOG_DEVICE void clamp_block(v16f* x) {
     for (int r = 0; r < 16; ++r) x[kt][r] = __builtin_amdgcn_fmed3f(x[kt][r], -57344.0f, 57344.0f);
 }
 
-// ------------------------------------------------------------------ kernel 1: dK, dV
+// ------------------------------------------------------------------ dK, dV
 // A workgroup of four waves owns 64 keys, a pair of waves 32 of them.  Of every block of 64 queries each wave of a pair takes 32
 // through scores, dP, softmax and the casts (lane = query, so the row constants are one register per lane), and sums dV and dK
 // over all 64 for its half of the head dimension.  The packed probabilities and dS travel between the two, and from lane = query
@@ -464,9 +463,23 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
   // instead of 172.  Pieces stored past the caches are worse still: a line then goes to memory in parts (this kernel + 100 us).
   store_tile_rows<2>(stage, dv, sdv, a.dV + out0, HD, [](int pos) { return key_of_position(pos); });
   store_tile_rows<2>(stage, dk, sdk, a.dK + out0, HD, [](int pos) { return key_of_position(pos); });
+  if (a.amax_ds && w == 0) {
+    // this workgroup's share of the maxima that the dQ kernel left, one per 32 rows
+    const int64_t n = nrows / 32, per = (n + gridDim.x - 1) / gridDim.x, first = per * blockIdx.x, last = first + per < n ? first + per : n;
+    float m = 0.0f;
+    for (int64_t i = first + l; i < last; i += 64) m = fmaxf(m, a.Dws[i]);
+    m = wave_max_f32(m);
+    // only a wave that would raise the maximum pays for the atomic (a stale read can only be too small)
+    if (l == 0 && m > 0.0f && __float_as_uint(m) > __hip_atomic_load(a.amax_ds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(a.amax_ds, __float_as_uint(m));
+  }
 }
 
-// ------------------------------------------------------------------ kernel 2: dQ (and max |dS|)
+// ------------------------------------------------------------------ dQ (and max |dS|), and the constants of its rows
+// ws[1][row] = D_i * rho_ds / rho_p    (for the dK/dV kernel: its probabilities carry the factor rho_p)
+// ws[2][row] = lse_i - log2 rho_p      (for the dK/dV kernel: 2^(x - that) = rho_p P)
+// ws[0][n]   = max |dS| of the n-th 32 rows, for the dK/dV kernel to reduce (one word raised by every wave of this launch would have
+//              to be cleared by a launch before it)
+// Folding the scales into per-row constants once saves three vector instructions per score.
 template <bool CAUSAL, bool AMAX>
 __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[NSTAGE * 2 * TILE];     // {K, V} x 4 stages
@@ -485,9 +498,9 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
     qf[h] = frag_global(a.Q + hoff * HD, wave_on ? q : 0, h);
     dof[h] = frag_global(a.dO8 + hoff * HD, wave_on ? q : 0, h);
   }
-  const float rho_ds = *a.scale_ds;
-  const float lse = (wave_on ? a.lse[hoff + q] : 0.0f) - __log2f(rho_ds);   // 2^(x - this) = rho_ds P
-  const float Dq = wave_on ? a.Dws[hoff + q] : 0.0f;
+  const float rho_ds = *a.scale_ds, rho_p = *a.scale_p;
+  const float lse_row = wave_on ? a.lse[hoff + q] : 0.0f;
+  const float lse = lse_row - __log2f(rho_ds);   // 2^(x - this) = rho_ds P
   const float c = a.softmax_scale * 1.44269504088896340736f * (*a.sinv_q) * (*a.sinv_k);
   const float cdp = (*a.sinv_do) * (*a.sinv_v);
 
@@ -520,10 +533,21 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
   const RowFrag rf = rowfrag_addr();
   const ColFrag cf = colfrag_addr();
 
-  FOG_SETTLE(qf[0]); FOG_SETTLE(qf[1]); FOG_SETTLE(dof[0]); FOG_SETTLE(dof[1]); FOG_SETTLE(lse); FOG_SETTLE(Dq);
   issue(0, Stg<0>{});
   issue(1, Stg<1>{});
   issue(2, Stg<2>{});
+  // The rows' D, under the flight of the first key blocks (stage 3 of the ring is free until the barrier below).
+  float Dq = 0.0f;
+  if (wave_on) {
+    Dq = row_dots(a.O + (hoff + q0) * HD, a.dO + (hoff + q0) * HD, reinterpret_cast<float*>(smem + 3 * 2 * TILE) + 32 * w);
+    if (g == 0) {
+      const int64_t nrows = (int64_t)a.BH * S;
+      a.Dws[nrows + hoff + q] = Dq * (rho_ds / rho_p);
+      a.Dws[2 * nrows + hoff + q] = lse_row - __log2f(rho_p);
+    }
+  }
+  if (AMAX && blockIdx.x == 0 && t == 0) *a.amax_ds = 0u;   // raised by the dK/dV kernel, from the maxima left below
+  FOG_SETTLE(qf[0]); FOG_SETTLE(qf[1]); FOG_SETTLE(dof[0]); FOG_SETTLE(dof[1]); FOG_SETTLE(lse); FOG_SETTLE(Dq);
   __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt = 8: block 0 has landed (4 direct loads per thread and block)
   __syncthreads();
 
@@ -598,8 +622,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
   store_tile_rows<4>(smem + w * (32 * 272), dq, sdq, a.dQ + (hoff + q0) * HD, HD, [](int row) { return row; });
   if (AMAX) {
     ds_max = wave_max_f32(ds_max) / rho_ds;   // the running maximum was taken on rho_ds dS
-    // only a wave that would raise the maximum pays for the atomic (a stale read can only be too small)
-    if (l == 0 && ds_max > 0.0f && __float_as_uint(ds_max) > __hip_atomic_load(a.amax_ds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(a.amax_ds, __float_as_uint(ds_max));
+    if (l == 0) a.Dws[(hoff + q0) / 32] = ds_max;
   }
 }
 
@@ -660,10 +683,10 @@ static fog_status bwd_launch(int B, int H, int H_kv, int S, float softmax_scale,
   a.softmax_scale = softmax_scale;
   a.BH = B * H; a.S = S; a.nblk = (S + BLK - 1) / BLK;
   a.BHkv = B * H_kv; a.G = H / H_kv;
-  const int64_t rows = (int64_t)a.BH * S;
-  attn_bwd_rowdot_kernel<<<(int)((rows + 15) / 16), kThreads, 0, s>>>(a.O, a.dO, a.lse, a.scale_p, a.scale_ds, a.Dws, rows,
-                                                                      amax_ds ? a.amax_ds : nullptr);
   const int grid = a.BH * a.nblk, grid_kv = a.BHkv * (S / PAIR_KEYS);
+  // the dQ kernel first: it leaves the row constants that the dK/dV kernel reads
+  if (causal) { if (amax_ds) attn_bwd_dq_kernel<true, true><<<grid, kThreads, 0, s>>>(a); else attn_bwd_dq_kernel<true, false><<<grid, kThreads, 0, s>>>(a); }
+  else        { if (amax_ds) attn_bwd_dq_kernel<false, true><<<grid, kThreads, 0, s>>>(a); else attn_bwd_dq_kernel<false, false><<<grid, kThreads, 0, s>>>(a); }
   // Pairs in turns where the launch is bound by its longest workgroup (the first keys see every query block of every head of the
   // group): up to half a workgroup per CU always, up to two where that workgroup walks 64 blocks or more.  Backward, us, without ->
   // with: 36 workgroups of up to 36 blocks 46 -> 37, 68 of 68 74 -> 56, 256 of 64 82 -> 71, 512 of 256 338 -> 319; but 256 of 4
@@ -676,8 +699,6 @@ static fog_status bwd_launch(int B, int H, int H_kv, int S, float softmax_scale,
     if (causal) attn_bwd_dkdv_kernel<true, false><<<grid_kv, PAIR_THREADS, 0, s>>>(a);
     else        attn_bwd_dkdv_kernel<false, false><<<grid_kv, PAIR_THREADS, 0, s>>>(a);
   }
-  if (causal) { if (amax_ds) attn_bwd_dq_kernel<true, true><<<grid, kThreads, 0, s>>>(a); else attn_bwd_dq_kernel<true, false><<<grid, kThreads, 0, s>>>(a); }
-  else        { if (amax_ds) attn_bwd_dq_kernel<false, true><<<grid, kThreads, 0, s>>>(a); else attn_bwd_dq_kernel<false, false><<<grid, kThreads, 0, s>>>(a); }
   return fog_launch_status();
 }
 
