@@ -521,3 +521,25 @@ def test_quantize_delayed_batch_equals_the_calls_one_by_one_and_the_oracle():
     assert call(C.cast(bad, C.c_void_p), 1, 6, st) == 1
     torch.cuda.synchronize()
     assert all(torch.equal(a, t["q"]) for a, t in zip(before, T))
+
+
+@pytest.mark.parametrize("chunks", [[5 * 2 ** 20 + 1], [2 ** 20 + 257, 3], [3 * 2 ** 18 + 1, 1, 2 ** 19 - 1], [2 ** 18 + 1] * 5])
+def test_jit_batch_several_trips_per_workgroup(chunks):
+    """Tensors of n chunks of 16 elements around whole trips of all workgroups (2048, 1024 and 512 a tensor, two chunks per thread and
+    trip) and smaller than one workgroup."""
+    items, xs = [], []
+    for j, n in enumerate(chunks):
+        g = torch.Generator(device="cuda").manual_seed(n)
+        x = torch.randn((n, 16), device="cuda", generator=g).to(torch.bfloat16)
+        x[n // 2, 3] = 100.0 + j
+        xs.append(x)
+        items.append((x, j % 2, torch.full((n, 16), 0x55, dtype=torch.uint8, device="cuda"), *(torch.zeros(1, device="cuda") for _ in range(3))))
+    ws = torch.empty(fog.quantize_jit_batch_workspace(len(items)), dtype=torch.uint8, device="cuda")
+    fog.quantize_jit_batch(fog.make_cast_jobs(items), ws)
+    for x, fmt, q, amax, scale, sinv in items:
+        largest = x.abs().max().float()
+        mx = (448.0, 57344.0)[fmt]
+        rho = torch.tensor(mx, device="cuda") / largest
+        assert amax.item() == largest.item() and scale.item() == rho.item() and sinv.item() == (1.0 / rho).item()
+        want = (x.float() * rho).clamp_(-mx, mx).to((torch.float8_e4m3fn, torch.float8_e5m2)[fmt]).view(torch.uint8)
+        assert torch.equal(q, want)
