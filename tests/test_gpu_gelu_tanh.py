@@ -126,3 +126,32 @@ def test_nan_inputs_reach_the_codes_and_the_abs_max(kind):
             assert nan_codes[0, 0] and nan_codes[rows - 1, cols - 1] and nan_codes[rows // 2, 5]
             assert nan_codes.sum() == 3
             assert np.isnan(am)
+
+
+@pytest.mark.parametrize("pad", [0, 16])
+@pytest.mark.parametrize("kind,p0,p1", [("gelu", 0.0, 0.0), ("xielu", 0.8, 0.7), ("xielu", 0.0, 0.5), ("tanh", 0.5, 0.0), ("tanh", -1.25, 0.0), ("tanh", 0.0, 0.0),
+                                        ("tanh", 1e-39, 0.0), ("tanh", -3e-20, 0.0), ("tanh", 700.0, 0.0), ("tanh", 3e38, 0.0)])
+def test_large_tensors_give_the_codes_of_small_ones(kind, p0, p1, pad):
+    """Every bf16 pattern through the kernel of large tensors (the function from a table) and through that of small ones (the function
+    evaluated): the same codes and the same abs-max.  A NaN's sign is not defined."""
+    def call(x, fmt, rho):
+        q, am = torch.zeros((x.shape[0], x.shape[1] + pad), dtype=torch.uint8, device="cuda")[:, :x.shape[1]], torch.full((1,), -1.0, device="cuda")
+        if kind == "gelu":
+            fog.gelu_quantize(x, fmt, fscalar(rho), q, amax_out=am)
+        elif kind == "xielu":
+            fog.xielu_quantize(x, p0, p1, fmt, fscalar(rho), q, amax_out=am)
+        else:
+            fog.tanh_quantize(x, p0, fmt, fscalar(rho), q, amax_out=am)
+        return q, am
+    rows, cols, copies = 32, 2048, 65
+    patterns = torch.arange(rows * cols, dtype=torch.int32, device="cuda").to(torch.int16).view(torch.bfloat16).view(rows, cols)
+    finite = torch.where(patterns.isfinite(), patterns, 0.0)
+    for fmt, rho in ((fp8.E4M3, 1.0), (fp8.E5M2, 2.0 ** 30), (fp8.E5M2, 2.0 ** -20)):
+        for values in (patterns, finite):
+            small = torch.empty((rows, cols + pad), dtype=torch.bfloat16, device="cuda")[:, :cols].copy_(values)
+            large = torch.empty((copies * rows, cols + pad), dtype=torch.bfloat16, device="cuda")[:, :cols].copy_(values.repeat(copies, 1))
+            (qs, ms), (ql, ml) = call(small, fmt, rho), call(large, fmt, rho)
+            qs, ql = qs.repeat(copies, 1), ql.clone()
+            nan = (qs & 0x7F) == 0x7F
+            assert torch.equal(nan, (ql & 0x7F) == 0x7F) and torch.equal(qs[~nan], ql[~nan])
+            assert torch.equal(ms.view(torch.int32), ml.view(torch.int32))
