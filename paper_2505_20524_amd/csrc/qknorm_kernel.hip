@@ -5,7 +5,8 @@
 // 2 + 2 + 2 + 2 + 1 bytes per element for normalise -> abs-max -> cast as separate passes.
 // Bound by HBM, with the vector ALU close behind: the square root and the divisions of a row are computed by one lane of four (each
 // takes one of the four rows in flight), row sums are exchanged inside the vector ALU, and the casts go without clamp and NaN test
-// where the row's norm, the gain and the scale say so (262144 x 128, whole call: 26.1 -> 23.9 us).
+// where the row's norm, the gain and the scale say so (262144 x 128, whole call: 26.1 -> 23.9 us, 19.2 with one workgroup per
+// compute unit and ordinary loads).
 // A row of D elements is handled by D / 8 adjacent lanes (16 for the head size 128,
 // four rows per wave); longer or odd rows take one wave per row and read the row twice.
 #include "common.h"
@@ -13,7 +14,11 @@
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 256;          // general kernel
+// Rows kernel: one workgroup per compute unit.  Every workgroup raises the one abs-max word when it ends, nearly all at the same time,
+// and same-address atomics are served one after the other: 2048 workgroups of 256 threads took 8 us for the abs-max, 256 of 1024
+// take 2-3, its clearing launch included.
+constexpr int kRowThreads = 1024;
 
 __global__ void zero_u32q(uint32_t* p) { *p = 0u; }
 
@@ -24,15 +29,16 @@ FOG_DEVICE float inv_rms(float sumsq, float cols, float gain) {
 
 // Workgroup maximum raised into *amax_out; reduced on bit patterns (non-negative floats order like them,
 // and the NaN pattern of a thread that saw a NaN orders above everything).
+template <int THREADS>
 FOG_DEVICE void block_amax(float m, bool nan, uint32_t* amax_out) {
   const uint32_t h = wave_max_u32(amax_bits(m, nan));
-  __shared__ uint32_t part[kThreads / 64];
+  __shared__ uint32_t part[THREADS / 64];
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = h;
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t b = part[0];
 #pragma unroll
-    for (int w = 1; w < kThreads / 64; ++w) b = b > part[w] ? b : part[w];
+    for (int w = 1; w < THREADS / 64; ++w) b = b > part[w] ? b : part[w];
     if (b > __hip_atomic_load(amax_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(amax_out, b);
   }
 }
@@ -58,11 +64,12 @@ template <int U>
 FOG_DEVICE float quad_lane(float v) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x55 * U, 0xF, 0xF, false)); }
 
 // LPR lanes per row, each holding 8 consecutive elements (cols = 8 LPR); 64 / LPR rows per wave.
-template <int FMT, int LPR>
-__global__ __launch_bounds__(kThreads) void qknorm_rows_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t ldx, float gain,
+// REREAD: ordinary loads, for tensors that may still lie in the memory-side cache (non-temporal ones find them there less often).
+template <int FMT, int LPR, bool REREAD>
+__global__ __launch_bounds__(kRowThreads) void qknorm_rows_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t ldx, float gain,
                                                                const float* __restrict__ scale, uint8_t* __restrict__ q, int64_t ldq,
                                                                uint32_t* __restrict__ amax_out) {
-  constexpr int RPB = kThreads / LPR;   // rows per workgroup and load
+  constexpr int RPB = kRowThreads / LPR;   // rows per workgroup and load
   constexpr int U = 4;                  // rows per lane group and trip: four loads in flight
   const float rho = *scale;
   const int sub = threadIdx.x % LPR, rloc = threadIdx.x / LPR;
@@ -78,7 +85,8 @@ __global__ __launch_bounds__(kThreads) void qknorm_rows_kernel(const uint16_t* _
     for (int u = 0; u < U; ++u) {
       const int64_t r = r0 + u * RPB + rloc;
       v[u] = make_uint4(0u, 0u, 0u, 0u);
-      if (r < rows) v[u] = ld_nt16(x + r * ldx + 8 * sub);
+      const uint16_t* p = x + r * ldx + 8 * sub;
+      if (r < rows) v[u] = REREAD ? *reinterpret_cast<const uint4*>(p) : ld_nt16(p);
     }
   };
   auto process = [&](int64_t r0, const uint4 (&v)[U]) {
@@ -137,7 +145,7 @@ __global__ __launch_bounds__(kThreads) void qknorm_rows_kernel(const uint16_t* _
     process(r1, vb);
     r0 = r2;
   }
-  if (amax_out) block_amax(m, nan, amax_out);
+  if (amax_out) block_amax<kRowThreads>(m, nan, amax_out);
 }
 
 // Any row length: one wave per row, two passes over the row (the second is served from cache).
@@ -165,19 +173,24 @@ __global__ __launch_bounds__(kThreads) void qknorm_general_kernel(const uint16_t
       q[r * ldq + i] = (uint8_t)(cvt4_fp8_nan<FMT>(t, t, t, t, &nan) & 0xFFu);
     }
   }
-  if (amax_out) block_amax(m, nan, amax_out);
+  if (amax_out) block_amax<kThreads>(m, nan, amax_out);
 }
 
 template <int FMT>
 void launch_qknorm(const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx, float gain, const float* scale, uint8_t* q, int64_t ldq,
                    uint32_t* amax_out, hipStream_t s) {
   const bool vec = (reinterpret_cast<uintptr_t>(x) & 15u) == 0 && (reinterpret_cast<uintptr_t>(q) & 7u) == 0 && ldx % 8 == 0 && ldq % 8 == 0;
-#define FOG_QKN(LPR)                                                                                            \
-  do {                                                                                                          \
-    int64_t blocks = (rows + 4 * (kThreads / LPR) - 1) / (4 * (kThreads / LPR));                                \
-    if (blocks > 2048) blocks = 2048;                                                                           \
-    qknorm_rows_kernel<FMT, LPR><<<(int)blocks, kThreads, 0, s>>>(x, rows, ldx, gain, scale, q, ldq, amax_out); \
-    return;                                                                                                     \
+  // Up to half of the 256 MB memory-side cache the input is read with ordinary loads (262144 x 128, 67 MB: 21.6 -> 19.2 us; 900000 x
+  // 128, 230 MB: 62.8 -> 66.7).
+  const bool reread = rows * cols <= (int64_t)64 << 20;
+#define FOG_QKN(LPR)                                                                                                          \
+  do {                                                                                                                        \
+    constexpr int ROWS = 4 * (kRowThreads / LPR);   /* of a workgroup and trip */                                             \
+    int64_t blocks = (rows + ROWS - 1) / ROWS;                                                                                \
+    if (blocks > fog_compute_units()) blocks = fog_compute_units();                                                           \
+    if (reread) qknorm_rows_kernel<FMT, LPR, true><<<(int)blocks, kRowThreads, 0, s>>>(x, rows, ldx, gain, scale, q, ldq, amax_out);  \
+    else        qknorm_rows_kernel<FMT, LPR, false><<<(int)blocks, kRowThreads, 0, s>>>(x, rows, ldx, gain, scale, q, ldq, amax_out); \
+    return;                                                                                                                   \
   } while (0)
   if (vec && cols == 128) FOG_QKN(16);
   if (vec && cols == 64) FOG_QKN(8);
