@@ -14,6 +14,7 @@
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kWideThreads = 1024;
 
 __global__ void zero_u32p(uint32_t* p) { *p = 0u; }
 
@@ -23,30 +24,35 @@ FOG_DEVICE float inv_rms(float sumsq, float cols) {
 }
 
 // abs-max of bf16 values kept as their 15-bit magnitude patterns (ordered like the values)
+template <int THREADS>
 FOG_DEVICE void block_amax_bits(uint32_t m, uint32_t* amax_out) {
   m = wave_max_u32(m);
-  __shared__ uint32_t part[kThreads / 64];
+  __shared__ uint32_t part[THREADS / 64];
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t r = part[0];
 #pragma unroll
-    for (int w = 1; w < kThreads / 64; ++w) r = r > part[w] ? r : part[w];
+    for (int w = 1; w < THREADS / 64; ++w) r = r > part[w] ? r : part[w];
     r <<= 16;   // the float with that bf16 pattern
     if (r > __hip_atomic_load(amax_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(amax_out, r);
   }
 }
 
+template <bool REREAD>
+FOG_DEVICE uint4 fetch(const uint16_t* p) { return REREAD ? *reinterpret_cast<const uint4*>(p) : ld_nt16(p); }
+
 // One element before its one rounding to bf16.
 FOG_DEVICE float residual(float x, float y, float g, float inv) { return __builtin_fmaf(g * y, inv, x); }
 
 // Bound by HBM (7 bytes per element).  Whole calls, other buffers each time, with the bf16 rounding in integers, the NaN test in every
-// cast and a workgroup for every four rows -> now: 8192 x 4096 54.7 -> 47.0 us, 777 x 8192 19.4 -> 15.9 us.
+// cast and a workgroup for every four rows -> now: 8192 x 4096 54.7 -> 44.1 us, 777 x 8192 19.4 -> 15.9 us.
 // One wave per row; a lane owns C <= CMAX chunks of 8 consecutive elements (chunk c of lane l is
 // elements [8 (64 c + l), +8): consecutive lanes read consecutive 16 bytes).  All loads of y and x
 // of a row are issued before the first is used.
-template <int FMT, int CMAX>
-__global__ __launch_bounds__(kThreads) void postnorm_rows_kernel(const uint16_t* x, int64_t ldx, const uint16_t* __restrict__ y,
+// REREAD: 1 y, 2 y and x with ordinary loads, which find a tensor in the memory-side cache more often than non-temporal ones.
+template <int FMT, int CMAX, int THREADS, int REREAD>
+__global__ __launch_bounds__(THREADS) void postnorm_rows_kernel(const uint16_t* x, int64_t ldx, const uint16_t* __restrict__ y,
                                                                  int64_t ldy, int64_t rows, int C, const float* __restrict__ gamma,
                                                                  const float* __restrict__ scale, uint16_t* out, int64_t ldo,
                                                                  uint8_t* __restrict__ q, int64_t ldq, uint32_t* __restrict__ amax_out) {
@@ -58,14 +64,14 @@ __global__ __launch_bounds__(kThreads) void postnorm_rows_kernel(const uint16_t*
   const float cols = (float)(C * 512);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t m = 0u;
-  for (int64_t r = (int64_t)blockIdx.x * 4 + w; r < rows; r += (int64_t)gridDim.x * 4) {
+  for (int64_t r = (int64_t)blockIdx.x * (THREADS / 64) + w; r < rows; r += (int64_t)gridDim.x * (THREADS / 64)) {
     uint4 vy[CMAX], vx[CMAX];
 #pragma unroll
     for (int c = 0; c < CMAX; ++c)
-      if (c < C) vy[c] = ld_nt16(y + r * ldy + 8 * (64 * c + lane));
+      if (c < C) vy[c] = fetch<REREAD >= 1>(y + r * ldy + 8 * (64 * c + lane));
 #pragma unroll
     for (int c = 0; c < CMAX; ++c)
-      if (c < C) vx[c] = ld_nt16(x + r * ldx + 8 * (64 * c + lane));
+      if (c < C) vx[c] = fetch<REREAD >= 2>(x + r * ldx + 8 * (64 * c + lane));
     float s = 0.0f;
 #pragma unroll
     for (int c = 0; c < CMAX; ++c)
@@ -105,7 +111,7 @@ __global__ __launch_bounds__(kThreads) void postnorm_rows_kernel(const uint16_t*
     }
   }
   if (amax_out) {
-    block_amax_bits(max_of_pair(m), amax_out);
+    block_amax_bits<THREADS>(max_of_pair(m), amax_out);
   }
 }
 
@@ -138,7 +144,7 @@ __global__ __launch_bounds__(kThreads) void postnorm_general_kernel(const uint16
       }
     }
   }
-  if (amax_out) block_amax_bits(m, amax_out);
+  if (amax_out) block_amax_bits<kThreads>(m, amax_out);
 }
 
 template <int FMT>
@@ -149,15 +155,29 @@ void launch_postnorm(const uint16_t* x, int64_t ldx, const uint16_t* y, int64_t 
                    ldx % 8 == 0 && ldy % 8 == 0 && ldo % 8 == 0 && ldq % 8 == 0;
   int64_t blocks = (rows + 3) / 4;
   if (vec) {
-    // Two workgroups per CU that walk the rows, whatever the registers allow: with more waves in flight the streams past the caches get
-    // in each other's way.  us with up to 8192 workgroups -> 1024 -> 512 -> 256, other buffers each pass: 4096 x 1024 20.0 -> 20.0 ->
-    // 13.6 -> 14.7, 8192 x 1024 26.3 -> 25.5 -> 19.2 -> 22.9, 4096 x 2048 23.1 -> 22.5 -> 18.3 -> 18.8, 8192 x 4096 49.7 -> 46.8 ->
-    // 47.0 -> 53.2, 16384 x 512 25.5 -> 23.1 -> 21.9 -> 32.3, 8192 x 8192 103 -> 100 -> 100 -> 100.
-    if (blocks > 512) blocks = 512;
-    const int C = (int)(cols / 512);
-    if (C <= 4)      postnorm_rows_kernel<FMT, 4><<<(int)blocks, kThreads, 0, s>>>(x, ldx, y, ldy, rows, C, gamma, scale, out, ldo, q, ldq, amax_out);
-    else if (C <= 8) postnorm_rows_kernel<FMT, 8><<<(int)blocks, kThreads, 0, s>>>(x, ldx, y, ldy, rows, C, gamma, scale, out, ldo, q, ldq, amax_out);
-    else             postnorm_rows_kernel<FMT, 16><<<(int)blocks, kThreads, 0, s>>>(x, ldx, y, ldy, rows, C, gamma, scale, out, ldo, q, ldq, amax_out);
+    // Few workgroups that walk the rows, whatever the registers allow: with more waves in flight the streams past the caches get in
+    // each other's way, and every workgroup raises the abs-max word when it ends.  Two of 256 threads per CU, or, for rows of up to
+    // 1024 elements and small tensors of up to 2048, one of 1024.  us, other buffers each pass, 512 x 256 threads -> 256 x 1024:
+    // 16384 x 512 18.4 -> 14.5, 65536 x 1024 96.9 -> 83.9, 4096 x 2048 15.2 -> 13.8; 65536 x 2048 168 -> 174, 4096 x 4096 24 -> 35.
+    // (512 workgroups of 256 threads against up to 8192: 4096 x 1024 20.0 -> 13.6, 8192 x 4096 49.7 -> 47.0.)
+    // Ordinary loads where the tensors may still be in the memory-side cache: of both up to 16 M elements (8192 x 1024 20.0 -> 14.3,
+    // 6000 x 3072 28.5 -> 25.0), of y alone up to 48 M (8192 x 4096 47.0 -> 44.1; both 48.7), of none beyond (65536 x 2048 168; both 170).
+    const int C = (int)(cols / 512), cus = fog_compute_units();
+    const int64_t n = rows * cols;
+    const int reread = n <= (int64_t)16 << 20 ? 2 : n <= (int64_t)48 << 20 ? 1 : 0;
+    const bool wide = C <= 2 || (C <= 4 && n <= (int64_t)16 << 20);
+    const int threads = wide ? kWideThreads : kThreads;
+    const int64_t most = wide ? cus : 2 * cus;
+    blocks = (rows + threads / 64 - 1) / (threads / 64);
+    if (blocks > most) blocks = most;
+#define FOG_PN(CM, T, RE) postnorm_rows_kernel<FMT, CM, T, RE><<<(int)blocks, T, 0, s>>>(x, ldx, y, ldy, rows, C, gamma, scale, out, ldo, q, ldq, amax_out)
+#define FOG_PN3(CM, T) do { if (reread == 2) FOG_PN(CM, T, 2); else if (reread == 1) FOG_PN(CM, T, 1); else FOG_PN(CM, T, 0); } while (0)
+    if (wide)        FOG_PN3(4, kWideThreads);
+    else if (C <= 4) FOG_PN3(4, kThreads);
+    else if (C <= 8) FOG_PN3(8, kThreads);
+    else             FOG_PN3(16, kThreads);
+#undef FOG_PN3
+#undef FOG_PN
     return;
   }
   if (blocks > 8192) blocks = 8192;

@@ -147,3 +147,26 @@ def test_sums_beyond_the_largest_bf16(fmt):
         out.append((host_u16(xnew), q.cpu().numpy(), am.item()))
     assert np.array_equal(out[0][0], want) and np.array_equal(out[1][0], want)
     assert np.array_equal(out[0][1], out[1][1]) and out[0][2] == out[1][2] == float("inf")
+
+
+@pytest.mark.parametrize("rows,cols", [(4097, 512), (9001, 1024), (8193, 1536), (8200, 2048), (16500, 2048), (4100, 4096), (24700, 2048), (6200, 8192)])
+def test_every_form_gives_the_rows_of_small_calls(rows, cols):
+    """Workgroups of 1024 and of 256 threads with several rows a wave, the three ways of loading x and y, in place and not: the bytes
+    and the abs-max that calls of 64 rows give."""
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x, y = (torch.randn((rows, cols), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    gamma, rho = torch.rand(cols, device="cuda", generator=g), fscalar(20.0)
+    def call(xs, ys, out):
+        q, am = torch.zeros(xs.shape, dtype=torch.uint8, device="cuda"), torch.full((1,), -1.0, device="cuda")
+        fog.postnorm_residual_quantize(xs, ys, gamma, fp8.E4M3, rho, out, q=q, amax_out=am)
+        return q, am
+    out = torch.empty_like(x)
+    q, am = call(x, y, out)
+    assert am.item() == out.abs().max().float().item()
+    for first in (0, 64 * 20, (rows - 1) // 64 * 64):
+        part = slice(first, min(first + 64, rows))
+        want = torch.empty_like(x[part])
+        wq, _ = call(x[part], y[part], want)
+        assert torch.equal(out[part].view(torch.int16), want.view(torch.int16)) and torch.equal(q[part], wq)
+    qi, ami = call(x, y, x)
+    assert torch.equal(x.view(torch.int16), out.view(torch.int16)) and torch.equal(qi, q) and ami.item() == am.item()
