@@ -4,7 +4,8 @@
 // FP8cast(rho X); Section 2 calls the two-pass flow (abs-max, then cast) just-in-time scaling
 // and the one-pass flow (cast with last iteration's scale, abs-max as a by-product) delayed
 // scaling.  All of these are HBM-bound: every element is read once with 16-byte loads and
-// every output byte is written once with 8- or 16-byte stores.
+// every output byte is written once with 8- or 16-byte stores.  Casts alone run at the copy rate; what their memory accesses do to the
+// kernels around them counts as much.
 #include "common.h"
 #include "launch.h"
 
@@ -293,6 +294,9 @@ FOG_DEVICE uint2 cast8(uint4 v, float rho) {
 // holds it or its end.  Ordinary loads find it there, non-temporal ones less often, and the next abs-max pass is slower after them:
 // abs-max + cast of a linear layer's 31 MB 20.9 -> 18.2 us, of 84 MB 39.6 -> 36.4, of 268 MB 119.7 -> 116 (other tensors each time).
 // A tensor read for the first time keeps the non-temporal loads (512 MB read and 256 written: 5.9 TB/s against 4.6-5.1).
+// The codes are stored with ordinary stores: the products that follow find them in the caches (past them, linear layers forward + backward:
+// 1777 x 3088 x 2064 83.1 -> 77.3 us, 8192 x 4096 x 14336 delayed 1151 -> 1127; with the transposed copies of 4096 x 8192 x 2048 251.7 ->
+// 246.6; feed-forward half 205 -> 200).
 // Workgroup `bid` of `nb` over one tensor (a whole launch, or one job's share of a batched launch).
 template <int FMT, bool AMAX, bool REREAD>
 FOG_DEVICE void quantize_rows_body(const uint16_t* __restrict__ x, int64_t rows, int64_t chunks_per_row, int64_t ldx,
@@ -333,7 +337,7 @@ FOG_DEVICE void quantize_rows_body(const uint16_t* __restrict__ x, int64_t rows,
       m = pkmax_abs_bf16(pkmax_abs_bf16(pkmax_abs_bf16(pkmax_abs_bf16(m, b.x), b.y), b.z), b.w);
     }
     uint2 lo = cast8<FMT>(a, rho), hi = cast8<FMT>(b, rho);
-    st_nt16(dst, make_uint4(lo.x, lo.y, hi.x, hi.y));
+    *reinterpret_cast<uint4*>(dst) = make_uint4(lo.x, lo.y, hi.x, hi.y);
   };
   while (i < total) {
     const int64_t n = i + 2 * stride;
@@ -503,7 +507,7 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint
         const uint4 w = v[it][k];
         if (AMAX) m = pkmax_abs_bf16(pkmax_abs_bf16(pkmax_abs_bf16(pkmax_abs_bf16(m, w.x), w.y), w.z), w.w);
         code[k] = cast8<FMT>(w, rho);
-        if (WRITE_Q) st_nt8(q + (r + k) * ldq + c, code[k]);
+        if (WRITE_Q) *reinterpret_cast<uint2*>(q + (r + k) * ldq + c) = code[k];
       }
     } else {
 #pragma unroll
@@ -527,7 +531,7 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint
     const int64_t c = c0 + col, r = r0 + ch * 16;
     if (c < cols && r < rows) {  // rows % 16 == 0 on this path
       uint4 v = *reinterpret_cast<const uint4*>(tile + col * kTile + ((ch ^ ((col >> 3) & 7)) * 16));
-      st_nt16(qT + c * ldqT + r, v);
+      *reinterpret_cast<uint4*>(qT + c * ldqT + r) = v;
     }
   }
   if (AMAX) {
@@ -570,6 +574,21 @@ __global__ __launch_bounds__(kThreads) void quantize_general_kernel(const uint16
     if ((threadIdx.x & 63) == 0 && m) atomicMax(js.cur ? js.cur + (blockIdx.x & (kDelayedSlots - 1)) : amax_out, m << 16);
   }
 }
+
+// Workgroups that cast `chunks` chunks of 16 elements as one of `count` tensors of a launch: all of them resident at once (2048, eight
+// per CU), since one that starts later first waits for the scale again, and two per CU where each has several trips to make.  Just-in-time
+// batches, 2048 a tensor -> 512, us: 134 MB in four tensors 58 -> 51.5, 84 MB in three 38 -> 34.4, 268 MB equal; one tensor of 34 MB
+// 15.2 -> 14.1, but of 17 MB 8.7 -> 9.4.
+// A power of two for each tensor, whatever its size: shares of 2048 in proportion (84 MB in 16, 34 and 34 MB) take 37 us.
+inline int cast_workgroups(int64_t chunks, int count) {
+  const int64_t need = (chunks + 2 * kThreads - 1) / (2 * kThreads), most = count >= 3 || chunks >= (int64_t)1 << 20 ? 512 : count == 2 ? 1024 : 2048;
+  return (int)(need < 1 ? 1 : need < most ? need : most);
+}
+// The same under delayed scaling, where the maxima a tensor's workgroups leave are the same words in a batch as alone (us, 2048 -> 512:
+// batches of 31 MB 15.0 -> 13.5, 84 MB 28.8 -> 25.1, 101 MB 34.7 -> 29.4, 419 MB 118.5 -> 113.7) ...
+inline int delayed_workgroups(int64_t chunks) { return cast_workgroups(chunks, kBatchMax); }
+// ... and where every workgroup raises the one abs-max word when it ends, one after the other (4096 x 4096 29.8 -> 16.4 us).
+inline int one_word_workgroups(int64_t chunks) { return cast_workgroups(chunks, kBatchMax); }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -619,11 +638,8 @@ static void launch_quantize(const uint16_t* x, int64_t rows, int64_t cols, int64
   if (!qT && base_ok) {
     int64_t r = rows, cpr = cols / 16, lx = ldx, lq = ldq;
     if (ldx == cols && ldq == cols) { cpr = rows * cpr; r = 1; }  // contiguous: one long row
-    int64_t total = r * cpr;
-    int64_t blocks = (total + 2 * kThreads - 1) / (2 * kThreads);
-    if (blocks > 2048) blocks = 2048;
-    if (blocks < 1) blocks = 1;
-#define FOG_QR(AM, RE) quantize_rows_kernel<FMT, AM, RE><<<(int)blocks, kThreads, 0, s>>>(x, r, cpr, lx, scale, q, lq, amax_out, js)
+    const int blocks = js.cur ? delayed_workgroups(r * cpr) : amax_out ? one_word_workgroups(r * cpr) : cast_workgroups(r * cpr, 1);
+#define FOG_QR(AM, RE) quantize_rows_kernel<FMT, AM, RE><<<blocks, kThreads, 0, s>>>(x, r, cpr, lx, scale, q, lq, amax_out, js)
     if (amax_out)     FOG_QR(true, false);
     else if (js.part) FOG_QR(false, true);     // just-in-time scaling: the abs-max pass has just read the tensor
     else              FOG_QR(false, false);
@@ -793,15 +809,10 @@ extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count
     b.scale_inv[j] = t.scale_inv;
   }
   b.cast_first[0] = 0;
-  // Cast workgroups: all of them resident at once (2048, eight per CU), each walking its part, since a workgroup that starts later
-  // first waits for the scale again: 512 for each of four tensors against 2048, 134 MB 58 -> 51.5 us, 84 MB 38 -> 34.4, 268 MB equal.
-  // A power of two for each tensor, whatever its size: shares of 2048 in proportion (84 MB in 16, 34 and 34 MB) take 37 us.
-  const int cast_cap = count == 1 ? 2048 : count == 2 ? 1024 : 512;
   for (int p = 0; p < count; ++p) {   // launch position p casts job count - 1 - p
     const int64_t chunks = b.n[count - 1 - p] / 16;
-    int64_t cb = (chunks + 2 * kThreads - 1) / (2 * kThreads);
-    if (cb > cast_cap) cb = cast_cap;
-    b.cast_first[p + 1] = b.cast_first[p] + (int)cb;
+    const int cb = cast_workgroups(chunks, count);
+    b.cast_first[p + 1] = b.cast_first[p] + cb;
   }
   for (int j = count; j < kBatchMax; ++j) {
     b.amax_first[j + 1] = b.amax_first[count];
@@ -835,9 +846,8 @@ extern "C" fog_status fog_quantize_delayed_batch(const fog_delayed_job* jobs, in
     if (t.state_bytes < fog_quantize_delayed_state()) return FOG_ERR_WORKSPACE;
     const int64_t n = t.rows * t.cols;
     if (n % 16 != 0) return FOG_ERR_UNSUPPORTED;
-    int64_t cb = (n / 16 + 2 * kThreads - 1) / (2 * kThreads);
-    if (cb > 2048) cb = 2048;
-    b.first[j + 1] = b.first[j] + (int)cb;
+    const int cb = delayed_workgroups(n / 16);
+    b.first[j + 1] = b.first[j] + cb;
     b.x[j] = reinterpret_cast<const uint16_t*>(t.x_bf16);
     b.n[j] = n;
     b.q[j] = t.q;
