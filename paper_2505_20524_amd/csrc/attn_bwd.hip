@@ -47,6 +47,8 @@ struct BwdArgs {
   float softmax_scale;
   int BH, S, nblk;
   int BHkv, G;   // key/value heads in all, query heads per key/value head (grouped-query attention)
+  int splits;    // dK/dV in turns: parts that a key block's stream of query blocks is cut into, each a workgroup's
+  float4* partial;   // ... and where they leave their sums (splits > 1)
 };
 
 // LDS tiles are [64 rows][128 bytes]; the 16-byte chunks of a row sit at position chunk ^ swz(row).
@@ -232,10 +234,12 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
   constexpr int KEYS = QSPLIT ? 32 : PAIR_KEYS, TURNS = QSPLIT ? 2 : 1;   // keys of a workgroup, pairs that share them
   constexpr int RING = PAIR_STAGES * KV_STAGE;                            // bytes of one ring
   __shared__ __attribute__((aligned(1024))) uint8_t smem[TURNS * RING + 2 * XCHG];
-  const int bhk = blockIdx.x % a.BHkv;                 // key/value head; its query heads are bhk * G .. + G - 1
-  const int kblk = blockIdx.x / a.BHkv;                // early key blocks see the most queries: launched first
-  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, g = l >> 5, pair = w >> 1, half = w & 1;
   const int S = a.S, G = a.G;
+  const int wgs = a.BHkv * (S / KEYS);                 // workgroups of a part
+  const int part = QSPLIT ? blockIdx.x / wgs : 0, bid = blockIdx.x - part * wgs;
+  const int bhk = bid % a.BHkv;                        // key/value head; its query heads are bhk * G .. + G - 1
+  const int kblk = bid / a.BHkv;                       // early key blocks see the most queries: launched first
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, g = l >> 5, pair = w >> 1, half = w & 1;
   const int64_t hoff = (int64_t)bhk * S;               // rows of this K/V head
   const int64_t qoff = hoff * G;                       // first row of the group's first query head
   const int key0 = kblk * KEYS + (QSPLIT ? 0 : 32 * pair);
@@ -258,7 +262,8 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
 
   const int qb_first = CAUSAL ? key0 / STEP : 0;       // the diagonal block comes first
   const int nqb = S / STEP - qb_first;                 // query blocks of one head this workgroup walks
-  const int total = nqb * G;                           // ... and of the whole group: head after head, one stream
+  // ... and of the whole group: head after head, one stream, of which this workgroup takes blocks `begin` to `end`
+  const int begin = QSPLIT ? nqb * G * part / a.splits : 0, end = QSPLIT ? nqb * G * (part + 1) / a.splits : nqb * G;
 
   const uint32_t group_bytes = (uint32_t)G * S * HD;
   const v4i rsrc_q = make_rsrc(a.Q + qoff * HD, group_bytes), rsrc_do = make_rsrc(a.dO8 + qoff * HD, group_bytes);
@@ -280,14 +285,14 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
   const bool rows_d = w & 1;
   // query block and head of the next block to issue (issue() is called once per block, in order); a pair that takes turns starts
   // at its own and skips the other's
-  int iss_i = 0, iss_g = 0;
+  int iss_i = QSPLIT ? begin % nqb : 0, iss_g = QSPLIT ? begin / nqb : 0, iss_at = begin + (QSPLIT ? pair : 0);
   auto next_block = [&](int& i, int& head) { if (++i == nqb) { i = 0; ++head; } };
   if (QSPLIT && pair) next_block(iss_i, iss_g);
   int cur_i = iss_i;          // query block (within its head) of the block in hand
   auto issue = [&](auto stg) {  // the next block of the stream -> stage stg; blocks past the end fetch zeros
     const uint32_t row0 = (uint32_t)(iss_g * S + (qb_first + iss_i) * STEP);
-    const uint32_t adv = iss_g < G ? row0 * HD : OOB;
-    const uint32_t radv = iss_g < G ? row0 * 4 : OOB;
+    const uint32_t adv = iss_at < end ? row0 * HD : OOB;
+    const uint32_t radv = iss_at < end ? row0 * 4 : OOB;
     const uint32_t base = (uint32_t)decltype(stg)::value * KV_STAGE;
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
@@ -297,6 +302,7 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
     load4_to_lds(rows_d ? rsrc_d : rsrc_lse, (uint32_t)(4 * l) + radv, lds0 + base + 2 * TILE + (rows_d ? 256u : 0u));
 #pragma unroll
     for (int n = 0; n < TURNS; ++n) next_block(iss_i, iss_g);
+    iss_at += TURNS;
   };
   // fragment addresses: rows of this wave's 32 queries; columns of its half of the head dimension, read r of the transposing
   // read covering queries 16 r + 8 g .. + 7 (the swizzle does not change from read to read); the exchange tiles in that order
@@ -417,7 +423,7 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
     dk[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(q1, dsf, dk[1], 0, 1, 0, 0, 0, 0);
   };
   // Blocks of a pair (one past the end is a block of zeros: P is 1 there, but dO, D and dP are 0 and add nothing).
-  const int turns = (total + TURNS - 1) / TURNS;
+  const int turns = (end - begin + TURNS - 1) / TURNS;
   // two blocks per trip: the ring stage is a constant in each copy
   auto trips = [&](const bool CLAMP_P) __attribute__((always_inline)) {
     for (int it = 0; it < turns; it += PAIR_STAGES) {
@@ -458,11 +464,22 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
   if (!QSPLIT) __syncthreads();   // every wave's direct loads have landed: the rings become the staging areas
   uint8_t* stage = QSPLIT ? smem + half * (16 * 64 * 16) : smem + w * (32 * 144);   // split: where this wave has read its partner's sums
   const int64_t out0 = (hoff + key0) * HD + 64 * half;
+  if (QSPLIT && a.splits > 1) {   // binary32, as they are: attn_bwd_dkdv_sum_kernel adds the parts
+    float4* part_sums = a.partial + ((int64_t)blockIdx.x * 2 + half) * (16 * 64) + l;
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        part_sums[(4 * d + qd) * 64] = make_float4(dv[d][4 * qd], dv[d][4 * qd + 1], dv[d][4 * qd + 2], dv[d][4 * qd + 3]);
+        part_sums[(8 + 4 * d + qd) * 64] = make_float4(dk[d][4 * qd], dk[d][4 * qd + 1], dk[d][4 * qd + 2], dk[d][4 * qd + 3]);
+      }
+  } else {
   // Stored as 8-byte pieces straight from the registers, the three gradients (200 MB at 2 x 32 heads x 4096) stay in the caches as
   // dirty lines that leave them during whatever runs next: the abs-max pass after it took 60 us instead of 50, the forward 180
   // instead of 172.  Pieces stored past the caches are worse still: a line then goes to memory in parts (this kernel + 100 us).
   store_tile_rows<2>(stage, dv, sdv, a.dV + out0, HD, [](int pos) { return key_of_position(pos); });
   store_tile_rows<2>(stage, dk, sdk, a.dK + out0, HD, [](int pos) { return key_of_position(pos); });
+  }
   if (a.amax_ds && w == 0) {
     // this workgroup's share of the maxima that the dQ kernel left, one per 32 rows
     const int64_t n = nrows / 32, per = (n + gridDim.x - 1) / gridDim.x, first = per * blockIdx.x, last = first + per < n ? first + per : n;
@@ -472,6 +489,35 @@ __global__ __launch_bounds__(PAIR_THREADS, QSPLIT ? 2 : 3) void attn_bwd_dkdv_ke
     // only a wave that would raise the maximum pays for the atomic (a stale read can only be too small)
     if (l == 0 && m > 0.0f && __float_as_uint(m) > __hip_atomic_load(a.amax_ds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(a.amax_ds, __float_as_uint(m));
   }
+}
+
+// The sums of a split dK/dV launch: workgroup n adds the parts of 32 keys in ascending order, scales and rounds once; a wave has one
+// half of the head dimension of dV (waves 0, 1) or dK (2, 3), in the layout of the accumulators.
+__global__ __launch_bounds__(256) void attn_bwd_dkdv_sum_kernel(BwdArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[4 * 32 * 144];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, half = w & 1, which = w >> 1;
+  const int wgs = (int)gridDim.x, bid = (int)blockIdx.x;
+  const float4* src = a.partial + ((int64_t)bid * 2 + half) * (16 * 64) + which * (8 * 64) + l;
+  v16f x[2];
+  float4 v[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = src[64 * i];
+  for (int n = 1; n < a.splits; ++n) {
+    src += (int64_t)wgs * (2 * 16 * 64);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float4 y = src[64 * i];
+      v[i].x += y.x; v[i].y += y.y; v[i].z += y.z; v[i].w += y.w;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    x[i >> 2][4 * (i & 3)] = v[i].x; x[i >> 2][4 * (i & 3) + 1] = v[i].y;
+    x[i >> 2][4 * (i & 3) + 2] = v[i].z; x[i >> 2][4 * (i & 3) + 3] = v[i].w;
+  }
+  const float scale = which ? a.softmax_scale * (*a.sinv_q) / (*a.scale_ds) : (*a.sinv_do) / (*a.scale_p);
+  const int64_t out0 = ((int64_t)(bid % a.BHkv) * a.S + 32 * (bid / a.BHkv)) * HD + 64 * half;
+  store_tile_rows<2>(smem + w * (32 * 144), x, scale, (which ? a.dK : a.dV) + out0, HD, [](int pos) { return key_of_position(pos); });
 }
 
 // ------------------------------------------------------------------ dQ (and max |dS|), and the constants of its rows
@@ -632,10 +678,26 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 }  // namespace
 
+// Parts that the query blocks of every 32 keys are cut into for the dK/dV kernel in turns: as many as one workgroup per CU allows,
+// each of kSplitBlocks blocks or more where the stream is longest, because the sums of the parts cost a launch and a pass over memory.
+// A launch of few workgroups takes what its longest one takes, 0.43 us a block, while other CUs idle.  Backward of B x H/H_kv heads x S,
+// us, whole streams -> parts: 1 x 16/4 x 576 32.8 -> 28.9 (two parts; three of 12 blocks 32.9), 1 x 8/2 x 1024 50.0 -> 36.5, 1 x 4/1 x 2048
+// 87.6 -> 56.4, 1 x 2/2 x 2048 50.0 -> 48.2, 1 x 1/1 x 4096 not causal 84.6 -> 77.2; two parts of 8 blocks each lose: 1 x 4/4 x 1024
+// 30.5 -> 31.6.  (Four pairs in turns inside one workgroup instead gain nothing: two waves on a SIMD take twice the time for a block each.)
+constexpr int kSplitBlocks = 16, kSplitsMost = 8;
+static int kv_splits(int64_t BHkv, int S, int G, int cus) {
+  const int64_t wgs = BHkv * (S / 32), longest = (int64_t)(S / STEP) * G;
+  const int64_t p = cus / wgs < longest / kSplitBlocks ? cus / wgs : longest / kSplitBlocks;
+  return p < 2 ? 1 : p < kSplitsMost ? (int)p : kSplitsMost;
+}
+// Bytes of the three constants per row, and of the parts' sums behind them.
+static size_t rows_bytes(int B, int H, int S) { return (size_t)3 * B * H * S * sizeof(float); }
+static size_t parts_bytes(int splits, int B, int H_kv, int S) { return splits > 1 ? (size_t)splits * 2 * B * H_kv * S * HD * sizeof(float) : 0; }
+
 extern "C" size_t fog_fp8_attn_workspace(int B, int H, int H_kv, int S, int D, int is_bwd) {
-  (void)D; (void)H_kv;
   if (!is_bwd || B <= 0 || H <= 0 || S <= 0) return 0;
-  return (size_t)3 * B * H * S * sizeof(float);
+  if (D != HD || S % STEP != 0 || H_kv <= 0 || H % H_kv != 0) return rows_bytes(B, H, S);   // refused by the call
+  return rows_bytes(B, H, S) + parts_bytes(kv_splits((int64_t)B * H_kv, S, H / H_kv, fog_compute_units()), B, H_kv, S);
 }
 
 // Argument checks shared by the two entry points (everything but the workspace); FOG_OK with *empty set
@@ -666,13 +728,13 @@ static fog_status bwd_checks(int B, int H, int H_kv, int S, int D, float softmax
   return FOG_OK;
 }
 
-// The launches of the backward, on checked arguments; `ws` holds three floats per row.
+// The launches of the backward, on checked arguments; `ws` holds three floats per row, and the sums of split launches if it has the room.
 static fog_status bwd_launch(int B, int H, int H_kv, int S, float softmax_scale, int causal,
                              const uint8_t* Q, const uint8_t* K, const uint8_t* V,
                              const float* sinv_q, const float* sinv_k, const float* sinv_v,
                              const void* O_bf16, const void* dO_bf16, const uint8_t* dO_e5m2, const float* sinv_do,
                              const float* lse, const float* scale_p, const float* scale_ds,
-                             void* dQ_bf16, void* dK_bf16, void* dV_bf16, float* amax_ds, float* ws, hipStream_t s) {
+                             void* dQ_bf16, void* dK_bf16, void* dV_bf16, float* amax_ds, float* ws, size_t ws_bytes, hipStream_t s) {
   BwdArgs a;
   a.Q = Q; a.K = K; a.V = V; a.dO8 = dO_e5m2;
   a.O = reinterpret_cast<const uint16_t*>(O_bf16); a.dO = reinterpret_cast<const uint16_t*>(dO_bf16);
@@ -683,6 +745,7 @@ static fog_status bwd_launch(int B, int H, int H_kv, int S, float softmax_scale,
   a.softmax_scale = softmax_scale;
   a.BH = B * H; a.S = S; a.nblk = (S + BLK - 1) / BLK;
   a.BHkv = B * H_kv; a.G = H / H_kv;
+  a.splits = 1; a.partial = nullptr;
   const int grid = a.BH * a.nblk, grid_kv = a.BHkv * (S / PAIR_KEYS);
   // the dQ kernel first: it leaves the row constants that the dK/dV kernel reads
   if (causal) { if (amax_ds) attn_bwd_dq_kernel<true, true><<<grid, kThreads, 0, s>>>(a); else attn_bwd_dq_kernel<true, false><<<grid, kThreads, 0, s>>>(a); }
@@ -693,8 +756,14 @@ static fog_status bwd_launch(int B, int H, int H_kv, int S, float softmax_scale,
   // 22 -> 25 and 512 of 32 72 -> 76.
   const int longest = (S / STEP) * a.G, cus = fog_compute_units();
   if (2 * grid_kv <= cus || (grid_kv <= 2 * cus && longest >= 64)) {
-    if (causal) attn_bwd_dkdv_kernel<true, true><<<2 * grid_kv, PAIR_THREADS, 0, s>>>(a);
-    else        attn_bwd_dkdv_kernel<false, true><<<2 * grid_kv, PAIR_THREADS, 0, s>>>(a);
+    const int splits = kv_splits(a.BHkv, S, a.G, cus);
+    if (splits > 1 && aligned16(ws) && ws_bytes >= rows_bytes(B, H, S) + parts_bytes(splits, B, H_kv, S)) {
+      a.splits = splits;
+      a.partial = reinterpret_cast<float4*>(ws + (int64_t)3 * B * H * S);
+    }
+    if (causal) attn_bwd_dkdv_kernel<true, true><<<2 * grid_kv * a.splits, PAIR_THREADS, 0, s>>>(a);
+    else        attn_bwd_dkdv_kernel<false, true><<<2 * grid_kv * a.splits, PAIR_THREADS, 0, s>>>(a);
+    if (a.splits > 1) attn_bwd_dkdv_sum_kernel<<<2 * grid_kv, 256, 0, s>>>(a);
   } else {
     if (causal) attn_bwd_dkdv_kernel<true, false><<<grid_kv, PAIR_THREADS, 0, s>>>(a);
     else        attn_bwd_dkdv_kernel<false, false><<<grid_kv, PAIR_THREADS, 0, s>>>(a);
@@ -718,10 +787,10 @@ extern "C" fog_status fog_fp8_attn_bwd(int B, int H, int H_kv, int S, int D, flo
     if (amax_ds) zero_u32b<<<1, 1, 0, s>>>(reinterpret_cast<uint32_t*>(amax_ds));
     return fog_launch_status();
   }
-  if (!workspace || workspace_bytes < fog_fp8_attn_workspace(B, H, H_kv, S, D, 1) || (reinterpret_cast<uintptr_t>(workspace) & 3u))
+  if (!workspace || workspace_bytes < rows_bytes(B, H, S) || (reinterpret_cast<uintptr_t>(workspace) & 3u))
     return FOG_ERR_WORKSPACE;
   return bwd_launch(B, H, H_kv, S, softmax_scale, causal, Q, K, V, sinv_q, sinv_k, sinv_v, O_bf16, dO_bf16, dO_e5m2, sinv_do, lse,
-                    scale_p, scale_ds, dQ_bf16, dK_bf16, dV_bf16, amax_ds, reinterpret_cast<float*>(workspace), s);
+                    scale_p, scale_ds, dQ_bf16, dK_bf16, dV_bf16, amax_ds, reinterpret_cast<float*>(workspace), workspace_bytes, s);
 }
 
 // ------------------------------------------------------------------ the backward without a caller workspace
@@ -774,5 +843,5 @@ extern "C" fog_status fog_fp8_attn_bwd_static(int B, int H, int H_kv, int S, int
   if (sw != FOG_OK) return sw;
   // Nothing in the array has to start at zero: the first kernel overwrites the 3 * B * H * S floats the others read.
   return bwd_launch(B, H, H_kv, S, softmax_scale, causal, Q, K, V, sinv_q, sinv_k, sinv_v, O_bf16, dO_bf16, dO_e5m2, sinv_do, lse,
-                    scale_p, scale_ds, dQ_bf16, dK_bf16, dV_bf16, amax_ds, ws, s);
+                    scale_p, scale_ds, dQ_bf16, dK_bf16, dV_bf16, amax_ds, ws, 0, s);
 }

@@ -600,3 +600,35 @@ def test_backward_abs_max_sees_every_row(B, H, Hkv, S):
         p = torch.softmax(s * (kk @ f64(q[row])), dim=0)
         want = (p * (vv @ d - (d * O[row].double()).sum())).abs().max().item()
         assert abs(am.item() - want) <= 1e-4 * want      # binary32 sums of 128 terms and one exponential: 1e-5 at most
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,H,Hkv,S", [(1, 4, 1, 512), (1, 4, 1, 768), (1, 34, 2, 128), (1, 16, 1, 192), (1, 130, 1, 64)])
+def test_backward_in_parts(B, H, Hkv, S, causal):
+    """Few keys and long streams of query blocks: dK and dV summed in two, three, two, three and eight parts (parts that end inside a
+    head, odd numbers of blocks, streams of late keys that are shorter than the parts are many), against the oracle and against the
+    sums in one piece."""
+    rows = 3 * B * H * S * 4
+    assert fog.fp8_attn_workspace(B, H, S, 128, True, H_kv=Hkv) > rows
+    c, do = gqa_case(3900 + S + H, B, H, Hkv, S)
+    s = 1 / math.sqrt(128)
+    if H // Hkv <= 4:   # the slacks of a group's casts add up: without a mask, those of 8 heads exceed what the oracle's check allows a group
+        run_bwd(c, B, H, S, s, causal, [(b, h) for b in range(B) for h in range(H // Hkv)], do)
+    # the smaller workspace and one that is not 16-byte aligned keep working; the sums then differ in the order of binary32 additions
+    O, lse, _ = gpu_fwd(c, B, H, S, s, causal, want_amax=False)
+    args = (dev(c["q"][0]), dev(c["k"][0]), dev(c["v"][0]), fscalar(c["q"][1]), fscalar(c["k"][1]), fscalar(c["v"][1]), dev(O), dev(do),
+            dev(c["do"][0]), fscalar(c["do"][1]), dev(lse), fscalar(448.0), fscalar(64.0))
+    full = torch.empty(fog.fp8_attn_workspace(B, H, S, 128, True, H_kv=Hkv) + 16, dtype=torch.uint8, device="cuda")
+    out = []
+    for ws in (full, full[:rows], full[4:]):
+        o = [torch.full((B, h, S, 128), float("nan"), dtype=torch.bfloat16, device="cuda") for h in (H, Hkv, Hkv)] + [torch.zeros(1, device="cuda")]
+        fog.fp8_attn_bwd(B, H, S, 128, s, causal, *args, *o[:3], amax_ds=o[3], workspace=ws, H_kv=Hkv)
+        torch.cuda.synchronize()
+        out.append(o)
+    for o in out[1:]:
+        assert torch.equal(o[0], out[0][0]) and torch.equal(o[3], out[0][3])
+        for a, b in zip(o[1:3], out[0][1:3]):
+            # one bf16 step where the sums straddle a rounding boundary, and binary32 sums of up to 8320 terms where they cancel
+            a, b = a.double(), b.double()
+            assert ((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5 * b.abs().max()).all()
+    assert torch.equal(out[1][1], out[2][1]) and torch.equal(out[1][2], out[2][2])
