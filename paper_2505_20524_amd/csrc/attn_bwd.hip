@@ -678,16 +678,16 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 }  // namespace
 
-// Parts that the query blocks of every 32 keys are cut into for the dK/dV kernel in turns: as many as one workgroup per CU allows,
+// Parts that the query blocks of every 32 keys are cut into for the dK/dV kernel in turns: as many as two workgroups per CU allow,
 // each of kSplitBlocks blocks or more where the stream is longest, because the sums of the parts cost a launch and a pass over memory.
 // A launch of few workgroups takes what its longest one takes, 0.43 us a block, while other CUs idle.  Backward of B x H/H_kv heads x S,
 // us, whole streams -> parts: 1 x 16/4 x 576 32.8 -> 28.9 (two parts; three of 12 blocks 32.9), 1 x 8/2 x 1024 50.0 -> 36.5, 1 x 4/1 x 2048
 // 87.6 -> 56.4, 1 x 2/2 x 2048 50.0 -> 48.2, 1 x 1/1 x 4096 not causal 84.6 -> 77.2; two parts of 8 blocks each lose: 1 x 4/4 x 1024
-// 30.5 -> 31.6.  (Four pairs in turns inside one workgroup instead gain nothing: two waves on a SIMD take twice the time for a block each.)
+// 30.5 -> 31.6.  Two workgroups per CU against one: 1 x 4/1 x 4096 119.0 -> 110.6, 1 x 16/4 x 2048 89.7 -> 83.7.  (Four pairs in turns inside one workgroup instead gain nothing: two waves on a SIMD take twice the time for a block each.)
 constexpr int kSplitBlocks = 16, kSplitsMost = 8;
 static int kv_splits(int64_t BHkv, int S, int G, int cus) {
   const int64_t wgs = BHkv * (S / 32), longest = (int64_t)(S / STEP) * G;
-  const int64_t p = cus / wgs < longest / kSplitBlocks ? cus / wgs : longest / kSplitBlocks;
+  const int64_t room = 2 * cus / wgs, p = room < longest / kSplitBlocks ? room : longest / kSplitBlocks;
   return p < 2 ? 1 : p < kSplitsMost ? (int)p : kSplitsMost;
 }
 // Bytes of the three constants per row, and of the parts' sums behind them.
