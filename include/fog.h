@@ -413,9 +413,9 @@ size_t fog_fp8_attn_workspace(int B, int H, int H_kv, int S, int D, int is_bwd);
 /*
  * fog_fp8_attn_bwd for callers that cannot allocate device memory or pass a workspace (code under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation): the same kernels and the same
- * results, bit for bit, with the per-row constants (three floats per query row) kept in a device array
- * that is part of the library instead of a caller workspace.  The call allocates nothing.
- *   Limit: B * H * S <= FOG_ATTN_BWD_STATIC_MAX_ROWS (the array is 6 MB per GPU the library is used on and
+ * results, bit for bit, as with a workspace of fog_fp8_attn_workspace bytes, 16-byte aligned; what that
+ * would hold lies in a device array that is part of the library.  The call allocates nothing.
+ *   Limit: B * H * S <= FOG_ATTN_BWD_STATIC_MAX_ROWS (the array is 22 MB per GPU the library is used on and
  *   stays until the process ends); a larger problem returns FOG_ERR_WORKSPACE and takes fog_fp8_attn_bwd.
  *   All calls on one GPU share that GPU's array: calls that may overlap in time on one GPU (different
  *   streams) race; serialise them or use fog_fp8_attn_bwd with a workspace each.  Nothing in the array has

@@ -795,11 +795,14 @@ extern "C" fog_status fog_fp8_attn_bwd(int B, int H, int H_kv, int S, int D, flo
 
 // ------------------------------------------------------------------ the backward without a caller workspace
 // For callers that cannot allocate device memory (code under HIP graph capture, serving loops, harnesses
-// that forbid it): the three per-row constants live in a file-scope device array instead of a caller
-// workspace.  Every GPU the library runs on holds its own copy of the array, at its own address, until the
-// process ends; the address is looked up once per device, with that device current, and kept.
+// that forbid it): what the workspace holds lives in a file-scope device array instead.  Every GPU the
+// library runs on holds its own copy of the array, at its own address, until the process ends; the address
+// is looked up once per device, with that device current, and kept.
 constexpr int64_t kStaticRows = FOG_ATTN_BWD_STATIC_MAX_ROWS;          // B * H * S of a call, at most (6 MB of floats)
-static __device__ __align__(256) float scratch[3 * kStaticRows];
+// The parts' sums behind them: kv_splits() launches at most two workgroups per CU of the part's 256, each leaving 32 KB (16 MB).
+// The same parts as with a workspace make the same order of additions, so the same bytes, and the same times.
+constexpr int64_t kStaticPartFloats = (int64_t)2 * 256 * 32 * 2 * HD;
+static __device__ __align__(256) float scratch[3 * kStaticRows + kStaticPartFloats];
 constexpr int kMaxDevices = 64;
 static float* g_scratch_ptr[kMaxDevices];                             // device address of `scratch`, per device
 static std::mutex g_scratch_mutex;
@@ -841,7 +844,7 @@ extern "C" fog_status fog_fp8_attn_bwd_static(int B, int H, int H_kv, int S, int
   float* ws = nullptr;
   const fog_status sw = static_scratch(&ws);
   if (sw != FOG_OK) return sw;
-  // Nothing in the array has to start at zero: the first kernel overwrites the 3 * B * H * S floats the others read.
+  // Nothing in the array has to start at zero: every word that a kernel reads has been written by a kernel of this call before it.
   return bwd_launch(B, H, H_kv, S, softmax_scale, causal, Q, K, V, sinv_q, sinv_k, sinv_v, O_bf16, dO_bf16, dO_e5m2, sinv_do, lse,
-                    scale_p, scale_ds, dQ_bf16, dK_bf16, dV_bf16, amax_ds, ws, 0, s);
+                    scale_p, scale_ds, dQ_bf16, dK_bf16, dV_bf16, amax_ds, ws, sizeof(scratch), s);
 }

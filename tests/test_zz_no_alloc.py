@@ -1,7 +1,8 @@
 """GPU: the attention backward that takes no workspace (fog_fp8_attn_bwd_static) against fog_fp8_attn_bwd.
 
-The two entry points run the same kernels; the only difference is where the per-row constants live (the
-library's own device array instead of a caller workspace), so every output must agree bit for bit.
+The two entry points run the same kernels; the only difference is where the per-row constants and the partial
+sums of dK and dV live (the library's own device array instead of a caller workspace of the size that
+fog_fp8_attn_workspace names), so every output must agree bit for bit.
 Two calls in a row on the same GPU share the array: the second, smaller, call must not see anything of
 the first.  Each call goes through the C ABI (ctypes), with every buffer allocated beforehand.
 """
@@ -67,6 +68,20 @@ def test_static_scratch_backward_equals_the_workspace_backward_on_two_calls_in_a
         for name, t, ref in zip(("dQ", "dK", "dV"), outs[:3], w[:3]):
             assert np.array_equal(host_u16(t), ref), "%s differs (B=%d H=%d S=%d)" % (name, k["B"], k["H"], k["S"])
         assert outs[3].item() == w[3]
+
+
+@pytest.mark.parametrize("B,H,Hkv,S", [(1, 16, 4, 576), (1, 4, 1, 2048), (1, 8, 2, 1024), (1, 8, 1, 4096)])
+def test_static_scratch_backward_in_parts_equals_the_workspace_backward(B, H, Hkv, S):
+    """Shapes whose streams of query blocks are cut into parts (the second and the last with as many sums as the array has room for): the same cuts."""
+    assert fog.fp8_attn_workspace(B, H, S, 128, True, H_kv=Hkv) > 3 * B * H * S * 4
+    k = _case(7400 + H + S, B, H, Hkv, S)
+    want, got = _outputs(k), _outputs(k)
+    ws = torch.empty(fog.fp8_attn_workspace(B, H, S, 128, True, H_kv=Hkv), dtype=torch.uint8, device="cuda")
+    fog.fp8_attn_bwd(*_args(k, want), amax_ds=want[3], workspace=ws, H_kv=Hkv)
+    fog.fp8_attn_bwd_static(*_args(k, got), amax_ds=got[3], H_kv=Hkv)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("dQ", "dK", "dV", "amax_ds"), want, got):
+        assert torch.equal(a, b), name
 
 
 def test_static_scratch_backward_against_the_oracle_and_its_size_limit():
