@@ -8,6 +8,7 @@
 // kernels around them counts as much.
 #include "common.h"
 #include "launch.h"
+#include "words.h"
 
 namespace {
 
@@ -181,27 +182,13 @@ struct ScaleSource {
   uint32_t* next;         // delayed scaling only: cleared by workgroup 0
 };
 constexpr int kDelayedSlots = 1024;
-// Words threadIdx.x, + kThreads, ... of `n` words in batches of independent loads (in a plain loop each waits for the one before it).
-template <typename T, typename F>
-FOG_DEVICE void for_words(const T* __restrict__ p, int n, F take) {
-  for (int base = 0; base < n; base += 4 * kThreads) {
-    T v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = base + k * kThreads + (int)threadIdx.x;
-      v[k] = i < n ? p[i] : T(0);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) take(base + k * kThreads + (int)threadIdx.x, v[k]);
-  }
-}
 FOG_DEVICE float scale_from_partials(const ScaleSource& js, bool publisher) {
   uint32_t m = 0;
-  for_words(js.part, js.n, [&](int, uint32_t v) { m = m > v ? m : v; });
+  for_words<kThreads>(js.part, js.n, -1, (int)threadIdx.x, [&](int, uint32_t v) { m = m > v ? m : v; });
   uint32_t h = 0;   // maximum of the history entries that stay
   if (js.hist) {
-    for_words(js.hist, js.hlen, [&](int i, float f) {
-      const uint32_t v = i == js.slot ? 0u : __float_as_uint(f);   // abs-maxes: non-negative floats order like their bits
+    for_words<kThreads>((const float*)js.hist, js.hlen, js.slot, (int)threadIdx.x, [&](int, float f) {
+      const uint32_t v = __float_as_uint(f);   // abs-maxes: non-negative floats order like their bits
       h = h > v ? h : v;
     });
     if (publisher)
