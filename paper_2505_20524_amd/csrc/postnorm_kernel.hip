@@ -39,19 +39,18 @@ FOG_DEVICE void block_amax_bits(uint32_t m, uint32_t* amax_out) {
   }
 }
 
-template <bool REREAD>
-FOG_DEVICE uint4 fetch(const uint16_t* p) { return REREAD ? *reinterpret_cast<const uint4*>(p) : ld_nt16(p); }
-
 // One element before its one rounding to bf16.
 FOG_DEVICE float residual(float x, float y, float g, float inv) { return __builtin_fmaf(g * y, inv, x); }
 
 // Bound by HBM (7 bytes per element).  Whole calls, other buffers each time, with the bf16 rounding in integers, the NaN test in every
-// cast and a workgroup for every four rows -> now: 8192 x 4096 54.7 -> 44.1 us, 777 x 8192 19.4 -> 15.9 us.
+// cast and a workgroup for every four rows -> now: 8192 x 4096 54.7 -> 46.5 us, 777 x 8192 19.4 -> 15.9 us.
 // One wave per row; a lane owns C <= CMAX chunks of 8 consecutive elements (chunk c of lane l is
 // elements [8 (64 c + l), +8): consecutive lanes read consecutive 16 bytes).  All loads of y and x
 // of a row are issued before the first is used.
-// REREAD: 1 y, 2 y and x with ordinary loads, which find a tensor in the memory-side cache more often than non-temporal ones.
-template <int FMT, int CMAX, int THREADS, int REREAD>
+// Non-temporal loads at every size: ordinary ones find a tensor in the memory-side cache more often where the same few are used over
+// and over (8192 x 4096 46.8 -> 45.0 us), but lose everywhere else: on tensors that no call has just read 46.8 -> 50.8, 2048 x 4096
+// 17.3 -> 21.3, 1024 x 8192 17.0 -> 28.1, and behind the product that writes y, feed-forward half of 4096 x 4096 98.5 -> 105.0.
+template <int FMT, int CMAX, int THREADS>
 __global__ __launch_bounds__(THREADS) void postnorm_rows_kernel(const uint16_t* x, int64_t ldx, const uint16_t* __restrict__ y,
                                                                  int64_t ldy, int64_t rows, int C, const float* __restrict__ gamma,
                                                                  const float* __restrict__ scale, uint16_t* out, int64_t ldo,
@@ -68,10 +67,10 @@ __global__ __launch_bounds__(THREADS) void postnorm_rows_kernel(const uint16_t* 
     uint4 vy[CMAX], vx[CMAX];
 #pragma unroll
     for (int c = 0; c < CMAX; ++c)
-      if (c < C) vy[c] = fetch<REREAD >= 1>(y + r * ldy + 8 * (64 * c + lane));
+      if (c < C) vy[c] = ld_nt16(y + r * ldy + 8 * (64 * c + lane));
 #pragma unroll
     for (int c = 0; c < CMAX; ++c)
-      if (c < C) vx[c] = fetch<REREAD >= 2>(x + r * ldx + 8 * (64 * c + lane));
+      if (c < C) vx[c] = ld_nt16(x + r * ldx + 8 * (64 * c + lane));
     float s = 0.0f;
 #pragma unroll
     for (int c = 0; c < CMAX; ++c)
@@ -157,26 +156,20 @@ void launch_postnorm(const uint16_t* x, int64_t ldx, const uint16_t* y, int64_t 
   if (vec) {
     // Few workgroups that walk the rows, whatever the registers allow: with more waves in flight the streams past the caches get in
     // each other's way, and every workgroup raises the abs-max word when it ends.  Two of 256 threads per CU, or, for rows of up to
-    // 1024 elements and small tensors of up to 2048, one of 1024.  us, other buffers each pass, 512 x 256 threads -> 256 x 1024:
-    // 16384 x 512 18.4 -> 14.5, 65536 x 1024 96.9 -> 83.9, 4096 x 2048 15.2 -> 13.8; 65536 x 2048 168 -> 174, 4096 x 4096 24 -> 35.
+    // 1024 elements and small tensors of up to 2048, one of 1024.  us, 512 x 256 threads -> 256 x 1024: 16384 x 512 18.4 -> 14.5,
+    // 65536 x 1024 97.1 -> 83.5, 2048 x 512 11.2 -> 7.4, 4096 x 2048 18.2 -> 15.2; 65536 x 2048 168 -> 174, 4096 x 4096 24 -> 35.
     // (512 workgroups of 256 threads against up to 8192: 4096 x 1024 20.0 -> 13.6, 8192 x 4096 49.7 -> 47.0.)
-    // Ordinary loads where the tensors may still be in the memory-side cache: of both up to 16 M elements (8192 x 1024 20.0 -> 14.3,
-    // 6000 x 3072 28.5 -> 25.0), of y alone up to 48 M (8192 x 4096 47.0 -> 44.1; both 48.7), of none beyond (65536 x 2048 168; both 170).
     const int C = (int)(cols / 512), cus = fog_compute_units();
-    const int64_t n = rows * cols;
-    const int reread = n <= (int64_t)16 << 20 ? 2 : n <= (int64_t)48 << 20 ? 1 : 0;
-    const bool wide = C <= 2 || (C <= 4 && n <= (int64_t)16 << 20);
+    const bool wide = C <= 2 || (C <= 4 && rows * cols <= (int64_t)16 << 20);
     const int threads = wide ? kWideThreads : kThreads;
     const int64_t most = wide ? cus : 2 * cus;
     blocks = (rows + threads / 64 - 1) / (threads / 64);
     if (blocks > most) blocks = most;
-#define FOG_PN(CM, T, RE) postnorm_rows_kernel<FMT, CM, T, RE><<<(int)blocks, T, 0, s>>>(x, ldx, y, ldy, rows, C, gamma, scale, out, ldo, q, ldq, amax_out)
-#define FOG_PN3(CM, T) do { if (reread == 2) FOG_PN(CM, T, 2); else if (reread == 1) FOG_PN(CM, T, 1); else FOG_PN(CM, T, 0); } while (0)
-    if (wide)        FOG_PN3(4, kWideThreads);
-    else if (C <= 4) FOG_PN3(4, kThreads);
-    else if (C <= 8) FOG_PN3(8, kThreads);
-    else             FOG_PN3(16, kThreads);
-#undef FOG_PN3
+#define FOG_PN(CM, T) postnorm_rows_kernel<FMT, CM, T><<<(int)blocks, T, 0, s>>>(x, ldx, y, ldy, rows, C, gamma, scale, out, ldo, q, ldq, amax_out)
+    if (wide)        FOG_PN(4, kWideThreads);
+    else if (C <= 4) FOG_PN(4, kThreads);
+    else if (C <= 8) FOG_PN(8, kThreads);
+    else             FOG_PN(16, kThreads);
 #undef FOG_PN
     return;
   }

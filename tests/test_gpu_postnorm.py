@@ -151,8 +151,8 @@ def test_sums_beyond_the_largest_bf16(fmt):
 
 @pytest.mark.parametrize("rows,cols", [(4097, 512), (9001, 1024), (8193, 1536), (8200, 2048), (16500, 2048), (4100, 4096), (24700, 2048), (6200, 8192)])
 def test_every_form_gives_the_rows_of_small_calls(rows, cols):
-    """Workgroups of 1024 and of 256 threads with several rows a wave, the three ways of loading x and y, in place and not: the bytes
-    and the abs-max that calls of 64 rows give."""
+    """Workgroups of 1024 and of 256 threads with several rows a wave, in place and not: the bytes and the abs-max that calls of 64 rows
+    give."""
     g = torch.Generator(device="cuda").manual_seed(rows)
     x, y = (torch.randn((rows, cols), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
     gamma, rho = torch.rand(cols, device="cuda", generator=g), fscalar(20.0)
