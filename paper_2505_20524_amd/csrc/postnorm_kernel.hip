@@ -159,8 +159,10 @@ void launch_postnorm(const uint16_t* x, int64_t ldx, const uint16_t* y, int64_t 
     // 1024 elements and small tensors of up to 2048, one of 1024.  us, 512 x 256 threads -> 256 x 1024: 16384 x 512 18.4 -> 14.5,
     // 65536 x 1024 97.1 -> 83.5, 2048 x 512 11.2 -> 7.4, 4096 x 2048 18.2 -> 15.2; 65536 x 2048 168 -> 174, 4096 x 4096 24 -> 35.
     // (512 workgroups of 256 threads against up to 8192: 4096 x 1024 20.0 -> 13.6, 8192 x 4096 49.7 -> 47.0.)
+    // At fewer rows than columns the 16 rows of a wide workgroup leave it too few workgroups: 64 x 512 5.5 -> 6.0, 512 x 2048 7.7 -> 8.2,
+    // feed-forward half of 1024 x 2048 41.9 -> 42.6; 2048 x 2048 52.4 -> 52.0.
     const int C = (int)(cols / 512), cus = fog_compute_units();
-    const bool wide = C <= 2 || (C <= 4 && rows * cols <= (int64_t)16 << 20);
+    const bool wide = rows >= cols && (C <= 2 || (C <= 4 && rows * cols <= (int64_t)16 << 20));
     const int threads = wide ? kWideThreads : kThreads;
     const int64_t most = wide ? cus : 2 * cus;
     blocks = (rows + threads / 64 - 1) / (threads / 64);
