@@ -14,8 +14,8 @@
 
 namespace {
 
-constexpr int kThreads = 256;          // general kernel
-// Rows kernel: one workgroup per compute unit.  Every workgroup raises the one abs-max word when it ends, nearly all at the same time,
+constexpr int kThreads = 256;          // general kernel, and the rows kernel on few rows
+// Rows kernel otherwise: one workgroup per compute unit.  Every workgroup raises the one abs-max word when it ends, nearly all at the same time,
 // and same-address atomics are served one after the other: 2048 workgroups of 256 threads took 8 us for the abs-max, 256 of 1024
 // take 2-3, its clearing launch included.
 constexpr int kRowThreads = 1024;
@@ -65,11 +65,11 @@ FOG_DEVICE float quad_lane(float v) { return __int_as_float(__builtin_amdgcn_mov
 
 // LPR lanes per row, each holding 8 consecutive elements (cols = 8 LPR); 64 / LPR rows per wave.
 // REREAD: ordinary loads, for tensors that may still lie in the memory-side cache (non-temporal ones find them there less often).
-template <int FMT, int LPR, bool REREAD>
-__global__ __launch_bounds__(kRowThreads) void qknorm_rows_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t ldx, float gain,
-                                                               const float* __restrict__ scale, uint8_t* __restrict__ q, int64_t ldq,
-                                                               uint32_t* __restrict__ amax_out) {
-  constexpr int RPB = kRowThreads / LPR;   // rows per workgroup and load
+template <int FMT, int LPR, int THREADS, bool REREAD>
+__global__ __launch_bounds__(THREADS) void qknorm_rows_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t ldx, float gain,
+                                                              const float* __restrict__ scale, uint8_t* __restrict__ q, int64_t ldq,
+                                                              uint32_t* __restrict__ amax_out) {
+  constexpr int RPB = THREADS / LPR;   // rows per workgroup and load
   constexpr int U = 4;                  // rows per lane group and trip: four loads in flight
   const float rho = *scale;
   const int sub = threadIdx.x % LPR, rloc = threadIdx.x / LPR;
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kRowThreads) void qknorm_rows_kernel(const uint16_t
     process(r1, vb);
     r0 = r2;
   }
-  if (amax_out) block_amax<kRowThreads>(m, nan, amax_out);
+  if (amax_out) block_amax<THREADS>(m, nan, amax_out);
 }
 
 // Any row length: one wave per row, two passes over the row (the second is served from cache).
@@ -183,20 +183,29 @@ void launch_qknorm(const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx, f
   // Up to half of the 256 MB memory-side cache the input is read with ordinary loads (262144 x 128, 67 MB: 21.6 -> 19.2 us; 900000 x
   // 128, 230 MB: 62.8 -> 66.7).
   const bool reread = rows * cols <= (int64_t)64 << 20;
-#define FOG_QKN(LPR)                                                                                                          \
+  // A workgroup of 1024 threads takes 4096 / LPR rows: below 1 M elements these are too few workgroups, and the smaller form is the faster
+  // (1024 x 128 6.5 -> 5.5 us, 6000 x 128 6.6 -> 6.2; 9216 x 128 6.9 against 6.8, 16384 x 128 7.2 against 8.0).
+  const bool few = rows * cols < (int64_t)1 << 20;
+#define FOG_QKT(LPR, T, RE)                                                                                                   \
   do {                                                                                                                        \
-    constexpr int ROWS = 4 * (kRowThreads / LPR);   /* of a workgroup and trip */                                             \
+    constexpr int ROWS = 4 * (T / LPR);   /* of a workgroup and trip */                                                       \
     int64_t blocks = (rows + ROWS - 1) / ROWS;                                                                                \
     if (blocks > fog_compute_units()) blocks = fog_compute_units();                                                           \
-    if (reread) qknorm_rows_kernel<FMT, LPR, true><<<(int)blocks, kRowThreads, 0, s>>>(x, rows, ldx, gain, scale, q, ldq, amax_out);  \
-    else        qknorm_rows_kernel<FMT, LPR, false><<<(int)blocks, kRowThreads, 0, s>>>(x, rows, ldx, gain, scale, q, ldq, amax_out); \
+    qknorm_rows_kernel<FMT, LPR, T, RE><<<(int)blocks, T, 0, s>>>(x, rows, ldx, gain, scale, q, ldq, amax_out);               \
     return;                                                                                                                   \
+  } while (0)
+#define FOG_QKN(LPR)                                                                                                          \
+  do {                                                                                                                        \
+    if (few) FOG_QKT(LPR, kThreads, true);                                                                                    \
+    if (reread) FOG_QKT(LPR, kRowThreads, true);                                                                              \
+    FOG_QKT(LPR, kRowThreads, false);                                                                                         \
   } while (0)
   if (vec && cols == 128) FOG_QKN(16);
   if (vec && cols == 64) FOG_QKN(8);
   if (vec && cols == 256) FOG_QKN(32);
   if (vec && cols == 512) FOG_QKN(64);
 #undef FOG_QKN
+#undef FOG_QKT
   int64_t blocks = (rows + 3) / 4;
   if (blocks > 4096) blocks = 4096;
   qknorm_general_kernel<FMT><<<(int)blocks, kThreads, 0, s>>>(x, rows, cols, ldx, gain, scale, q, ldq, amax_out);

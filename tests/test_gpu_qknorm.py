@@ -74,8 +74,8 @@ def test_qknorm_special_rows_and_saturation():
 
 
 def test_qknorm_several_trips_per_workgroup():
-    """More rows than one trip of the largest grid covers (2048 workgroups x 64 rows at D = 128): the pipelined
-    loop runs two to four trips with a ragged last one; config 5's Q has 262144 rows."""
+    """More rows than one trip of the largest grid covers (256 workgroups x 256 rows at D = 128): the pipelined
+    loop runs several trips with a ragged last one; config 5's Q has 262144 rows."""
     rng = np.random.default_rng(11)
     rows = 3 * 131072 + 77
     xb = synth.f32_to_bf16_bits(rng.standard_normal((rows, 128)).astype(np.float32))
@@ -170,3 +170,20 @@ def test_qknorm_norm_or_product_beyond_binary32(gain, rho, cols, fmt):
     for r in special:
         assert ((got[r] & 0x7F)[nonzero[r]] == top).all()
     assert np.isnan(out[0][1]) and np.isnan(out[1][1])                # zero times an infinite inverse norm
+
+
+@pytest.mark.parametrize("rows,cols", [(8191, 128), (8192, 128), (16383, 64), (4097, 256), (2047, 512), (262145, 128), (524289, 128)])
+def test_every_form_gives_the_rows_of_small_calls(rows, cols):
+    """Workgroups of 256 and of 1024 threads, ordinary and non-temporal loads: the bytes and the abs-max that calls of 96 rows give."""
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x, rho = torch.randn((rows, cols), device="cuda", generator=g).to(torch.bfloat16), fscalar(39.0)
+    q, am, largest = torch.zeros((rows, cols), dtype=torch.uint8, device="cuda"), torch.full((1,), -1.0, device="cuda"), 0.0
+    fog.rmsnorm_quantize(x, fp8.E4M3, rho, q, amax_out=am)
+    top = int((x.abs().amax(dim=1).float() / x.float().square().mean(dim=1).sqrt()).argmax())   # the row that holds the largest result
+    for first in sorted({0, 96 * 20, top // 96 * 96, (rows - 1) // 96 * 96}):
+        part = slice(first, min(first + 96, rows))
+        want, wam = torch.zeros((part.stop - first, cols), dtype=torch.uint8, device="cuda"), torch.zeros(1, device="cuda")
+        fog.rmsnorm_quantize(x[part], fp8.E4M3, rho, want, amax_out=wam)
+        assert torch.equal(q[part], want)
+        largest = max(largest, wam.item())
+    assert am.item() == largest
