@@ -180,9 +180,11 @@ template <int FMT>
 void launch_qknorm(const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx, float gain, const float* scale, uint8_t* q, int64_t ldq,
                    uint32_t* amax_out, hipStream_t s) {
   const bool vec = (reinterpret_cast<uintptr_t>(x) & 15u) == 0 && (reinterpret_cast<uintptr_t>(q) & 7u) == 0 && ldx % 8 == 0 && ldq % 8 == 0;
-  // Up to half of the 256 MB memory-side cache the input is read with ordinary loads (262144 x 128, 67 MB: 21.6 -> 19.2 us; 900000 x
-  // 128, 230 MB: 62.8 -> 66.7).
-  const bool reread = rows * cols <= (int64_t)64 << 20;
+  // Up to a quarter of the 256 MB memory-side cache the input is read with ordinary loads.  us, non-temporal -> ordinary, the same three
+  // tensors in turn and tensors that no call has just read: 131072 x 128 14.5 -> 14.2 and 14.2 -> 15.6, 262144 x 128 21.8 -> 19.3 and
+  // 21.7 -> 22.7; 400000 x 128 31.6 -> 33.4 and 31.9 -> 33.8, 900000 x 128 63.5 -> 67.2 and 62.9 -> 67.2.  In front of the attention
+  // forward: 1 x 16 x 1024 41.9 -> 40.6, 1 x 32/8 x 4096 121.5 -> 119.4, 2 x 32 x 4096 242.7 -> 244.3, 4 x 32 x 4096 476 -> 483.
+  const bool reread = rows * cols <= (int64_t)32 << 20;
   // A workgroup of 1024 threads takes 4096 / LPR rows: below 1 M elements these are too few workgroups, and the smaller form is the faster
   // (1024 x 128 6.5 -> 5.5 us, 6000 x 128 6.6 -> 6.2; 9216 x 128 6.9 against 6.8, 16384 x 128 7.2 against 8.0).
   const bool few = rows * cols < (int64_t)1 << 20;
