@@ -281,9 +281,12 @@ FOG_DEVICE uint2 cast8(uint4 v, float rho) {
 // holds it or its end.  Ordinary loads find it there, non-temporal ones less often, and the next abs-max pass is slower after them:
 // abs-max + cast of a linear layer's 31 MB 20.9 -> 18.2 us, of 84 MB 39.6 -> 36.4, of 268 MB 119.7 -> 116 (other tensors each time).
 // A tensor read for the first time keeps the non-temporal loads (512 MB read and 256 written: 5.9 TB/s against 4.6-5.1).
-// The codes are stored with ordinary stores: the products that follow find them in the caches (past them, linear layers forward + backward:
-// 1777 x 3088 x 2064 83.1 -> 77.3 us, 8192 x 4096 x 14336 delayed 1151 -> 1127; with the transposed copies of 4096 x 8192 x 2048 251.7 ->
-// 246.6; feed-forward half 205 -> 200).
+// The codes are written through: the products that follow find them in the caches, and no dirty lines are left to the kernels that run
+// meanwhile.  Linear layers forward + backward, us, past the caches -> ordinary stores -> written through: 2048 x 2048 x 2048 48.8 -> 45.8
+// -> 44.8, 1777 x 3088 x 2064 80.7 -> 74.5 -> 74.3, 4096 x 4096 x 4096 203.4 -> 197.0 -> 196.5, 8192 x 4096 x 14336 delayed 1111 -> 1090
+// -> 1092.  The price is paid by casts that no product follows: codes take room from the bf16 tensors that the second pass reads again.
+// Batches back to back on tensors that nothing has just read, us: 3 + 6 + 6 M elements 17.3 -> 20.5 -> 19.1, 8 + 16 + 16 M 37.1 -> 41.3 ->
+// 41.0, 3 x 32 M 84.8 -> 97.9 -> 97.3; half or less of what the products gain.
 // Workgroup `bid` of `nb` over one tensor (a whole launch, or one job's share of a batched launch).
 template <int FMT, bool AMAX, bool REREAD>
 FOG_DEVICE void quantize_rows_body(const uint16_t* __restrict__ x, int64_t rows, int64_t chunks_per_row, int64_t ldx,
@@ -324,7 +327,7 @@ FOG_DEVICE void quantize_rows_body(const uint16_t* __restrict__ x, int64_t rows,
       m = pkmax_abs_bf16(pkmax_abs_bf16(pkmax_abs_bf16(pkmax_abs_bf16(m, b.x), b.y), b.z), b.w);
     }
     uint2 lo = cast8<FMT>(a, rho), hi = cast8<FMT>(b, rho);
-    *reinterpret_cast<uint4*>(dst) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    st_through16(dst, make_uint4(lo.x, lo.y, hi.x, hi.y));
   };
   while (i < total) {
     const int64_t n = i + 2 * stride;
@@ -494,7 +497,7 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint
         const uint4 w = v[it][k];
         if (AMAX) m = pkmax_abs_bf16(pkmax_abs_bf16(pkmax_abs_bf16(pkmax_abs_bf16(m, w.x), w.y), w.z), w.w);
         code[k] = cast8<FMT>(w, rho);
-        if (WRITE_Q) *reinterpret_cast<uint2*>(q + (r + k) * ldq + c) = code[k];
+        if (WRITE_Q) st_through8(q + (r + k) * ldq + c, code[k]);
       }
     } else {
 #pragma unroll
@@ -518,7 +521,7 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint
     const int64_t c = c0 + col, r = r0 + ch * 16;
     if (c < cols && r < rows) {  // rows % 16 == 0 on this path
       uint4 v = *reinterpret_cast<const uint4*>(tile + col * kTile + ((ch ^ ((col >> 3) & 7)) * 16));
-      *reinterpret_cast<uint4*>(qT + c * ldqT + r) = v;
+      st_through16(qT + c * ldqT + r, v);
     }
   }
   if (AMAX) {

@@ -128,10 +128,11 @@ def test_nan_inputs_reach_the_codes_and_the_abs_max(kind):
             assert np.isnan(am)
 
 
+@pytest.mark.parametrize("copies", [65, 129])   # a few more chunks than one and than two for each thread: half of a trip, and a second trip
 @pytest.mark.parametrize("pad", [0, 16])
 @pytest.mark.parametrize("kind,p0,p1", [("gelu", 0.0, 0.0), ("xielu", 0.8, 0.7), ("xielu", 0.0, 0.5), ("tanh", 0.5, 0.0), ("tanh", -1.25, 0.0), ("tanh", 0.0, 0.0),
                                         ("tanh", 1e-39, 0.0), ("tanh", -3e-20, 0.0), ("tanh", 700.0, 0.0), ("tanh", 3e38, 0.0)])
-def test_large_tensors_give_the_codes_of_small_ones(kind, p0, p1, pad):
+def test_large_tensors_give_the_codes_of_small_ones(kind, p0, p1, pad, copies):
     """Every bf16 pattern through the kernel of large tensors (the function from a table) and through that of small ones (the function
     evaluated): the same codes and the same abs-max.  A NaN's sign is not defined."""
     def call(x, fmt, rho):
@@ -143,7 +144,7 @@ def test_large_tensors_give_the_codes_of_small_ones(kind, p0, p1, pad):
         else:
             fog.tanh_quantize(x, p0, fmt, fscalar(rho), q, amax_out=am)
         return q, am
-    rows, cols, copies = 32, 2048, 65
+    rows, cols = 32, 2048
     patterns = torch.arange(rows * cols, dtype=torch.int32, device="cuda").to(torch.int16).view(torch.bfloat16).view(rows, cols)
     finite = torch.where(patterns.isfinite(), patterns, 0.0)
     for fmt, rho in ((fp8.E4M3, 1.0), (fp8.E5M2, 2.0 ** 30), (fp8.E5M2, 2.0 ** -20)):
