@@ -277,10 +277,9 @@ FOG_DEVICE uint2 cast8(uint4 v, float rho) {
 // Each thread turns 16 bf16 (two 16-byte loads) into 16 FP8 codes (one 16-byte store), two such
 // chunks per trip so that four loads are in flight; the first trip's are requested before the scale is known, later ones before the
 // chunks in hand are cast.
-// REREAD: the abs-max pass of just-in-time scaling has read the tensor just before, and the memory-side cache (256 MB) still
-// holds it or its end.  Ordinary loads find it there, non-temporal ones less often, and the next abs-max pass is slower after them:
-// abs-max + cast of a linear layer's 31 MB 20.9 -> 18.2 us, of 84 MB 39.6 -> 36.4, of 268 MB 119.7 -> 116 (other tensors each time).
-// A tensor read for the first time keeps the non-temporal loads (512 MB read and 256 written: 5.9 TB/s against 4.6-5.1).
+// REREAD: the abs-max pass of just-in-time scaling has read the tensors just before, and the memory-side cache (256 MB) holds them
+// beside their codes (reread_stays below).  A tensor read for the first time keeps the non-temporal loads (512 MB read and 256 written:
+// 5.9 TB/s against 4.6-5.1).
 // The codes are written through: the products that follow find them in the caches, and no dirty lines are left to the kernels that run
 // meanwhile.  Linear layers forward + backward, us, past the caches -> ordinary stores -> written through: 2048 x 2048 x 2048 48.8 -> 45.8
 // -> 44.8, 1777 x 3088 x 2064 80.7 -> 74.5 -> 74.3, 4096 x 4096 x 4096 203.4 -> 197.0 -> 196.5, 8192 x 4096 x 14336 delayed 1111 -> 1090
@@ -390,6 +389,7 @@ __global__ __launch_bounds__(kThreads) void amax_batch_kernel(BatchJobs b, uint3
   amax_span<true>(reinterpret_cast<const uint4*>(b.x[j]), b.n[j] / 8, nullptr, 0, ws + j * kJitSlots, (int)blockIdx.x - b.amax_first[j], nb);
 }
 
+template <bool REREAD>
 __global__ __launch_bounds__(kThreads) void quantize_batch_kernel(BatchJobs b, const uint32_t* __restrict__ ws) {
   // position p in the launch order is job count - 1 - p: the tensor whose abs-max pass ran last is cast first
   int p = 0;
@@ -400,8 +400,8 @@ __global__ __launch_bounds__(kThreads) void quantize_batch_kernel(BatchJobs b, c
   const ScaleSource js{ws + j * kJitSlots, b.amax_first[j + 1] - b.amax_first[j], b.fmt[j], b.margin[j], b.amax[j], b.scale[j], b.scale_inv[j],
                     nullptr, 0, 0, nullptr, nullptr};
   const int64_t chunks = b.n[j] / 16;
-  if (b.fmt[j] == FOG_E4M3) quantize_rows_body<FOG_E4M3, false, true>(b.x[j], 1, chunks, chunks * 16, nullptr, b.q[j], chunks * 16, nullptr, js, bid, nb);
-  else                      quantize_rows_body<FOG_E5M2, false, true>(b.x[j], 1, chunks, chunks * 16, nullptr, b.q[j], chunks * 16, nullptr, js, bid, nb);
+  if (b.fmt[j] == FOG_E4M3) quantize_rows_body<FOG_E4M3, false, REREAD>(b.x[j], 1, chunks, chunks * 16, nullptr, b.q[j], chunks * 16, nullptr, js, bid, nb);
+  else                      quantize_rows_body<FOG_E5M2, false, REREAD>(b.x[j], 1, chunks, chunks * 16, nullptr, b.q[j], chunks * 16, nullptr, js, bid, nb);
 }
 
 // ---------------------------------------------------------------- several tensors per launch (delayed scaling)
@@ -457,7 +457,7 @@ FOG_DEVICE void transpose4x4(uint32_t r0, uint32_t r1, uint32_t r2, uint32_t r3,
   t[3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
 }
 
-template <int FMT, bool AMAX, bool WRITE_Q, bool REREAD>
+template <int FMT, bool AMAX, bool WRITE_Q, bool REREAD, bool THROUGH>
 __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                                       int64_t cols, int64_t ldx,
                                                                       const float* __restrict__ scale,
@@ -497,7 +497,10 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint
         const uint4 w = v[it][k];
         if (AMAX) m = pkmax_abs_bf16(pkmax_abs_bf16(pkmax_abs_bf16(pkmax_abs_bf16(m, w.x), w.y), w.z), w.w);
         code[k] = cast8<FMT>(w, rho);
-        if (WRITE_Q) st_through8(q + (r + k) * ldq + c, code[k]);
+        if (WRITE_Q) {
+          if (THROUGH) st_through8(q + (r + k) * ldq + c, code[k]);
+          else *reinterpret_cast<uint2*>(q + (r + k) * ldq + c) = code[k];
+        }
       }
     } else {
 #pragma unroll
@@ -521,7 +524,8 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint
     const int64_t c = c0 + col, r = r0 + ch * 16;
     if (c < cols && r < rows) {  // rows % 16 == 0 on this path
       uint4 v = *reinterpret_cast<const uint4*>(tile + col * kTile + ((ch ^ ((col >> 3) & 7)) * 16));
-      st_through16(qT + c * ldqT + r, v);
+      if (THROUGH) st_through16(qT + c * ldqT + r, v);
+      else *reinterpret_cast<uint4*>(qT + c * ldqT + r) = v;
     }
   }
   if (AMAX) {
@@ -564,6 +568,16 @@ __global__ __launch_bounds__(kThreads) void quantize_general_kernel(const uint16
     if ((threadIdx.x & 63) == 0 && m) atomicMax(js.cur ? js.cur + (blockIdx.x & (kDelayedSlots - 1)) : amax_out, m << 16);
   }
 }
+
+// Whether `n` elements of bf16 that the abs-max pass has just read, and their codes, fit the memory-side cache together: the cast then
+// reads with ordinary loads, which find more of them there.  Beyond, these keep lines that nobody reads again, at the cost of the codes that
+// the products read next.  Linear layers forward + backward, us, three sets of tensors in turn, non-temporal -> ordinary loads: 12 M elements
+// cast 46.0 -> 44.8, 16 M 77.2 -> 74.3, 48 M 196.0 -> 196.5, 80 M 349.7 -> 348.5; but 96 M 374.7 -> 379.9, 128 M 652 -> 662, 144 M
+// 669 -> 692, 232 M 1102 -> 1140.
+// With transposed copies, whose cast takes one tensor of a layer at a time, only up to 8 M elements: layers of 208 x 816 x 5008 62.5 ->
+// 59.3, 1456 x 3088 x 1888 89.0 -> 86.5, 2048 x 2048 x 2048 61.3 -> 60.4, 4096 x 2048 x 2048 85.9 -> 85.0; but 4096 x 4096 x 4096
+// 210.1 -> 211.0, 4096 x 8192 x 2048 226.5 -> 238.7, 16384 x 4096 x 4096 723 -> 762.
+inline bool reread_stays(int64_t n, bool transposed) { return transposed ? n <= (int64_t)8 << 20 : 3 * n <= (int64_t)256 << 20; }
 
 // Workgroups that cast `chunks` chunks of 16 elements as one of `count` tensors of a launch: all of them resident at once (2048, eight
 // per CU), since one that starts later first waits for the scale again, and two per CU where each has several trips to make.  Just-in-time
@@ -630,9 +644,9 @@ static void launch_quantize(const uint16_t* x, int64_t rows, int64_t cols, int64
     if (ldx == cols && ldq == cols) { cpr = rows * cpr; r = 1; }  // contiguous: one long row
     const int blocks = js.cur ? delayed_workgroups(r * cpr) : amax_out ? one_word_workgroups(r * cpr) : cast_workgroups(r * cpr, 1);
 #define FOG_QR(AM, RE) quantize_rows_kernel<FMT, AM, RE><<<blocks, kThreads, 0, s>>>(x, r, cpr, lx, scale, q, lq, amax_out, js)
-    if (amax_out)     FOG_QR(true, false);
-    else if (js.part) FOG_QR(false, true);     // just-in-time scaling: the abs-max pass has just read the tensor
-    else              FOG_QR(false, false);
+    if (amax_out)                                   FOG_QR(true, false);
+    else if (js.part && reread_stays(r * cpr * 16, false)) FOG_QR(false, true);
+    else                                            FOG_QR(false, false);
 #undef FOG_QR
     return;
   }
@@ -640,10 +654,15 @@ static void launch_quantize(const uint16_t* x, int64_t rows, int64_t cols, int64
     const int64_t tr = (rows + kTile - 1) / kTile, tc = (cols + kTile - 1) / kTile;
     if (tr * tc <= 0x7FFFFFFF) {
       const int grid = (int)(tr * tc);
-#define FOG_QT(AM, WQ, RE) quantize_transpose_kernel<FMT, AM, WQ, RE><<<grid, kThreads, 0, s>>>(x, rows, cols, ldx, scale, q, ldq, qT, ldqT, amax_out, (int)tc, js)
-      if (amax_out)     { if (q) FOG_QT(true, true, false);  else FOG_QT(true, false, false); }
-      else if (js.part) { if (q) FOG_QT(false, true, true);  else FOG_QT(false, false, true); }
-      else              { if (q) FOG_QT(false, true, false); else FOG_QT(false, false, false); }
+      // Small tensors: writing through takes a microsecond at the end of the launch, more than the lines left dirty cost the next one (layers
+      // of 240 x 384 x 320 30.1 -> 32.3 us, 512 x 512 x 512 32.6 -> 34.6; 208 x 816 x 5008 59.1 -> 59.5, 1456 x 3088 x 1888 85.9 -> 85.1).
+      const bool through = rows * cols >= (int64_t)2 << 20;
+#define FOG_QT(AM, WQ, RE, TH) quantize_transpose_kernel<FMT, AM, WQ, RE, TH><<<grid, kThreads, 0, s>>>(x, rows, cols, ldx, scale, q, ldq, qT, ldqT, amax_out, (int)tc, js)
+#define FOG_QT2(AM, WQ, RE) do { if (through) FOG_QT(AM, WQ, RE, true); else FOG_QT(AM, WQ, RE, false); } while (0)
+      if (amax_out)                                        { if (q) FOG_QT2(true, true, false);  else FOG_QT2(true, false, false); }
+      else if (js.part && reread_stays(rows * cols, true)) { if (q) FOG_QT2(false, true, true);  else FOG_QT2(false, false, true); }
+      else                                                 { if (q) FOG_QT2(false, true, false); else FOG_QT2(false, false, false); }
+#undef FOG_QT2
 #undef FOG_QT
       return;
     }
@@ -778,6 +797,7 @@ extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count
   BatchJobs b;
   b.count = count;
   b.amax_first[0] = 0;
+  int64_t total = 0;
   for (int j = 0; j < count; ++j) {
     const fog_cast_job& t = jobs[j];
     if (!t.x_bf16 || !t.q || !t.amax || !t.scale) return FOG_ERR_NULL;
@@ -789,6 +809,7 @@ extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count
     int64_t ab = (n / 8 + kThreads * 8 - 1) / (kThreads * 8);
     if (ab > kJitSlots) ab = kJitSlots;
     b.amax_first[j + 1] = b.amax_first[j] + (int)ab;
+    total += n;
     b.x[j] = reinterpret_cast<const uint16_t*>(t.x_bf16);
     b.n[j] = n;
     b.q[j] = t.q;
@@ -813,7 +834,8 @@ extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count
   hipStream_t s = (hipStream_t)stream;
   uint32_t* ws = reinterpret_cast<uint32_t*>(workspace);
   amax_batch_kernel<<<b.amax_first[count], kThreads, 0, s>>>(b, ws);
-  quantize_batch_kernel<<<b.cast_first[count], kThreads, 0, s>>>(b, ws);
+  if (reread_stays(total, false)) quantize_batch_kernel<true><<<b.cast_first[count], kThreads, 0, s>>>(b, ws);
+  else                     quantize_batch_kernel<false><<<b.cast_first[count], kThreads, 0, s>>>(b, ws);
   return fog_launch_status();
 }
 
