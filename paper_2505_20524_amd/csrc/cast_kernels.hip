@@ -579,20 +579,26 @@ __global__ __launch_bounds__(kThreads) void quantize_general_kernel(const uint16
 // 210.1 -> 211.0, 4096 x 8192 x 2048 226.5 -> 238.7, 16384 x 4096 x 4096 723 -> 762.
 inline bool reread_stays(int64_t n, bool transposed) { return transposed ? n <= (int64_t)8 << 20 : 3 * n <= (int64_t)256 << 20; }
 
-// Workgroups that cast `chunks` chunks of 16 elements as one of `count` tensors of a launch: all of them resident at once (2048, eight
-// per CU), since one that starts later first waits for the scale again, and two per CU where each has several trips to make.  Just-in-time
-// batches, 2048 a tensor -> 512, us: 134 MB in four tensors 58 -> 51.5, 84 MB in three 38 -> 34.4, 268 MB equal; one tensor of 34 MB
-// 15.2 -> 14.1, but of 17 MB 8.7 -> 9.4.
-// A power of two for each tensor, whatever its size: shares of 2048 in proportion (84 MB in 16, 34 and 34 MB) take 37 us.
-inline int cast_workgroups(int64_t chunks, int count) {
-  const int64_t need = (chunks + 2 * kThreads - 1) / (2 * kThreads), most = count >= 3 || chunks >= (int64_t)1 << 20 ? 512 : count == 2 ? 1024 : 2048;
+// Workgroups that cast `chunks` chunks of 16 elements (two a thread and trip), `most` at most.
+inline int workgroups(int64_t chunks, int most) {
+  const int64_t need = (chunks + 2 * kThreads - 1) / (2 * kThreads);
   return (int)(need < 1 ? 1 : need < most ? need : most);
 }
-// The same under delayed scaling, where the maxima a tensor's workgroups leave are the same words in a batch as alone (us, 2048 -> 512:
+// As one of `count` tensors of a just-in-time launch.  Every workgroup waits for the scale before it casts, so up to four tensors get
+// what is resident at once (the batch kernel eight a CU, the one-tensor kernel seven), and where each workgroup has several trips to
+// make, fewer.  us, 2048 a tensor -> 512: 134 MB in four tensors 58 -> 51.5, 84 MB in three 38 -> 34.4, 268 MB equal (shares of 2048
+// by size: 84 MB 37).  One tensor, 2048 -> 1024 -> 512: 16 M elements 16.1 -> 16.0 -> 17.0, 32 M 28.5 -> 28.4 -> 29.5, 112 M
+// 113.0 -> 109.7 -> 109.2.
+inline int cast_workgroups(int64_t chunks, int count) {
+  return workgroups(chunks, count == 1 || (count == 2 && chunks < (int64_t)1 << 20) ? 1024 : 512);
+}
+// With a scale that is there: nothing to wait for.  us, 2048 -> 512: 16 M elements 10.6 -> 11.4, 32 M 20.0 -> 19.4, 112 M 68.5 -> 62.8.
+inline int plain_workgroups(int64_t chunks) { return workgroups(chunks, chunks < (int64_t)2 << 20 ? 2048 : 512); }
+// Under delayed scaling, where the maxima a tensor's workgroups leave are the same words in a batch as alone (us, 2048 -> 512:
 // batches of 31 MB 15.0 -> 13.5, 84 MB 28.8 -> 25.1, 101 MB 34.7 -> 29.4, 419 MB 118.5 -> 113.7) ...
-inline int delayed_workgroups(int64_t chunks) { return cast_workgroups(chunks, kBatchMax); }
+inline int delayed_workgroups(int64_t chunks) { return workgroups(chunks, 512); }
 // ... and where every workgroup raises the one abs-max word when it ends, one after the other (4096 x 4096 29.8 -> 16.4 us).
-inline int one_word_workgroups(int64_t chunks) { return cast_workgroups(chunks, kBatchMax); }
+inline int one_word_workgroups(int64_t chunks) { return workgroups(chunks, 512); }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -642,11 +648,12 @@ static void launch_quantize(const uint16_t* x, int64_t rows, int64_t cols, int64
   if (!qT && base_ok) {
     int64_t r = rows, cpr = cols / 16, lx = ldx, lq = ldq;
     if (ldx == cols && ldq == cols) { cpr = rows * cpr; r = 1; }  // contiguous: one long row
-    const int blocks = js.cur ? delayed_workgroups(r * cpr) : amax_out ? one_word_workgroups(r * cpr) : cast_workgroups(r * cpr, 1);
+    const int64_t n = r * cpr;
+    const int blocks = js.cur ? delayed_workgroups(n) : amax_out ? one_word_workgroups(n) : js.part ? cast_workgroups(n, 1) : plain_workgroups(n);
 #define FOG_QR(AM, RE) quantize_rows_kernel<FMT, AM, RE><<<blocks, kThreads, 0, s>>>(x, r, cpr, lx, scale, q, lq, amax_out, js)
-    if (amax_out)                                   FOG_QR(true, false);
-    else if (js.part && reread_stays(r * cpr * 16, false)) FOG_QR(false, true);
-    else                                            FOG_QR(false, false);
+    if (amax_out)                                     FOG_QR(true, false);
+    else if (js.part && reread_stays(n * 16, false))  FOG_QR(false, true);
+    else                                              FOG_QR(false, false);
 #undef FOG_QR
     return;
   }

@@ -523,10 +523,10 @@ def test_quantize_delayed_batch_equals_the_calls_one_by_one_and_the_oracle():
     assert all(torch.equal(a, t["q"]) for a, t in zip(before, T))
 
 
-@pytest.mark.parametrize("chunks", [[5 * 2 ** 20 + 1], [2 ** 20 + 257, 3], [3 * 2 ** 18 + 1, 1, 2 ** 19 - 1], [2 ** 18 + 1] * 5])
+@pytest.mark.parametrize("chunks", [[5 * 2 ** 20 + 1], [6 * 2 ** 20 + 1], [2 ** 20 + 257, 3], [3 * 2 ** 18 + 1, 1, 2 ** 19 - 1], [2 ** 18 + 1] * 5])
 def test_jit_batch_several_trips_per_workgroup(chunks):
-    """Tensors of n chunks of 16 elements around whole trips of all workgroups (2048, 1024 and 512 a tensor, two chunks per thread and
-    trip) and smaller than one workgroup."""
+    """Tensors of n chunks of 16 elements around whole trips of all workgroups (1024 and 512 a tensor, two chunks per thread and
+    trip) and smaller than one workgroup; the second too large to stay in the memory-side cache with its codes."""
     items, xs = [], []
     for j, n in enumerate(chunks):
         g = torch.Generator(device="cuda").manual_seed(n)
@@ -543,3 +543,22 @@ def test_jit_batch_several_trips_per_workgroup(chunks):
         assert amax.item() == largest.item() and scale.item() == rho.item() and sinv.item() == (1.0 / rho).item()
         want = (x.float() * rho).clamp_(-mx, mx).to((torch.float8_e4m3fn, torch.float8_e5m2)[fmt]).view(torch.uint8)
         assert torch.equal(q, want)
+
+
+@pytest.mark.parametrize("rows,cols,transpose", [(1008, 2048, True), (1024, 2048, True), (4096, 2048, True), (4112, 2048, True),
+                                                 (5456, 16384, False), (5472, 16384, False)])
+def test_jit_forms_by_size(rows, cols, transpose):
+    """Both sides of the sizes at which the second pass changes its loads (8 M elements with a transposed copy, a third of 256 MB without)
+    and its stores (2 M elements with a transposed copy)."""
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x = torch.randn((rows, cols), device="cuda", generator=g).to(torch.bfloat16)
+    x[rows // 2, 3] = -100.0
+    q = torch.full((rows, cols), 0x55, dtype=torch.uint8, device="cuda")
+    qT = torch.full((cols, rows), 0x55, dtype=torch.uint8, device="cuda") if transpose else None
+    amax, scale, sinv = (torch.zeros(1, device="cuda") for _ in range(3))
+    fog.quantize_jit(x, fp8.E4M3, amax, scale, sinv, torch.empty(fog.quantize_jit_workspace(), dtype=torch.uint8, device="cuda"), q=q, qT=qT)
+    rho = torch.tensor(448.0, device="cuda") / 100.0
+    assert amax.item() == 100.0 and scale.item() == rho.item() and sinv.item() == (1.0 / rho).item()
+    want = (x.float() * rho).clamp_(-448.0, 448.0).to(torch.float8_e4m3fn).view(torch.uint8)
+    assert torch.equal(q, want)
+    assert not transpose or torch.equal(qT, want.t())
