@@ -161,8 +161,14 @@ void launch_postnorm(const uint16_t* x, int64_t ldx, const uint16_t* y, int64_t 
     // (512 workgroups of 256 threads against up to 8192: 4096 x 1024 20.0 -> 13.6, 8192 x 4096 49.7 -> 47.0.)
     // At fewer rows than columns the 16 rows of a wide workgroup leave it too few workgroups: 64 x 512 5.5 -> 6.0, 512 x 2048 7.7 -> 8.2,
     // feed-forward half of 1024 x 2048 41.9 -> 42.6; 2048 x 2048 52.4 -> 52.0.
+    // A trip of the wide form takes 16 rows per CU, of the narrow one 8, and a trip that is nearly empty takes as long as a full one: over
+    // several trips the wide form has to fill them, the more the longer its rows (tensors that no call has just read, narrow -> wide:
+    // 4926 x 512 11.1 -> 11.4, 9000 x 512 14.2 -> 12.8; 4926 x 1024 13.0 -> 14.7, 5500 x 1024 15.4 -> 14.7, 9000 x 1024 18.4 -> 18.8, 9800 x
+    // 1024 20.5 -> 18.9; 4926 x 2048 18.5 -> 21.0, 6144 x 2048 22.0 -> 22.3, 8192 x 2048 27.2 -> 25.9, 8400 x 2048 28.2 -> 30.5).
     const int C = (int)(cols / 512), cus = fog_compute_units();
-    const bool wide = rows >= cols && (C <= 2 || (C <= 4 && rows * cols <= (int64_t)16 << 20));
+    const int64_t trip = (int64_t)(kWideThreads / 64) * cus, trips = (rows + trip - 1) / trip;
+    const bool filled = trips <= 1 || 20 * rows >= (C <= 2 ? 13 : 16) * trips * trip;
+    const bool wide = rows >= cols && filled && (C <= 2 || (C <= 4 && rows * cols <= (int64_t)16 << 20));
     const int threads = wide ? kWideThreads : kThreads;
     const int64_t most = wide ? cus : 2 * cus;
     blocks = (rows + threads / 64 - 1) / (threads / 64);

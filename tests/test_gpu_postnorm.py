@@ -150,7 +150,8 @@ def test_sums_beyond_the_largest_bf16(fmt):
 
 
 @pytest.mark.parametrize("rows,cols", [(4097, 512), (9001, 1024), (8193, 1536), (8200, 2048), (16500, 2048), (4100, 4096), (24700, 2048), (6200, 8192),
-                                       (511, 512), (512, 512), (1023, 1024), (2047, 2048), (2048, 2048)])
+                                       (511, 512), (512, 512), (1023, 1024), (2047, 2048), (2048, 2048),
+                                       (4097, 512), (5324, 1024), (5325, 1024), (6553, 1536), (6554, 1536), (4097, 2048)])
 def test_every_form_gives_the_rows_of_small_calls(rows, cols):
     """Workgroups of 1024 and of 256 threads with several rows a wave, in place and not: the bytes and the abs-max that calls of 64 rows
     give."""
