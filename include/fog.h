@@ -394,8 +394,9 @@ fog_status fog_fp8_attn_fwd(int B, int H, int H_kv, int S, int D, float softmax_
  *   dQ : [B, H, S, D], dK, dV : [B, H_kv, S, D] bfloat16, overwritten; under grouped-query attention
  *        dK and dV of a key/value head are the sums over its H / H_kv query heads, accumulated
  *        in binary32 and rounded once.   amax_ds : NULL or one float, max |dS|.
- *   workspace : fog_fp8_attn_workspace(B, H, H_kv, S, D, 1) bytes, 4-byte aligned: three floats per row of
- *               Q (D_i and two per-row constants with the scales folded in) and, for shapes of few key/value
+ *   workspace : fog_fp8_attn_workspace(B, H, H_kv, S, D, 1) bytes, 4-byte aligned: room for three floats per
+ *               row of Q (two constants of the row with D_i, lse and the scales folded in; the first third holds
+ *               only one max |dS| per 32 rows, and that where amax_ds is given) and, for shapes of few key/value
  *               rows and long streams of queries, binary32 partial sums of dK and dV.  Three floats per row
  *               are enough for the call; with less than the query says, or a workspace that is not 16-byte
  *               aligned, dK and dV are summed in one piece (slower; only the order of binary32 additions differs).

@@ -109,10 +109,10 @@ def stats_summary(cid, d, out_dir, bench_line):
     parts = []
     for name, pred, div in (("GEMM (split reduce included)", lambda k: _is_gemm(k) or "gemm_tile_reduce" in k, 24),
                             ("attention forward", lambda k: "attn_fwd_kernel" in k, 24),
-                            ("attention backward (row constants, dK and dV, dQ)", lambda k: "attn_bwd" in k, 24),
+                            ("attention backward (dQ with the row constants, dK and dV)", lambda k: "attn_bwd" in k, 24),
                             ("abs-max pass (just-in-time passes only)", lambda k: "amax_batch_kernel" in k or "amax_kernel" in k, 12),
-                            ("cast pass, just-in-time", lambda k: "quantize_batch_kernel" in k or ("quantize_rows_kernel" in k and "false>" in k.split("(")[0]), 12),
-                            ("cast pass with abs-max output, delayed", lambda k: "quantize_delayed_batch_kernel" in k or ("quantize_rows_kernel" in k and "true>" in k.split("(")[0]), 12)):
+                            ("cast pass, just-in-time", lambda k: "quantize_batch_kernel" in k or re.search(r"quantize_rows_kernel<\d+, false", k), 12),
+                            ("cast pass with abs-max output, delayed", lambda k: "quantize_delayed_batch_kernel" in k or re.search(r"quantize_rows_kernel<\d+, true", k), 12)):
         c, t = grp(pred)
         if c:
             parts.append("%s %.3f ms" % (name, t / div / 1e6))

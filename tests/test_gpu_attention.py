@@ -576,7 +576,9 @@ def test_backward_workgroup_shapes(B, H, Hkv, S, causal):
 @pytest.mark.parametrize("B,H,Hkv,S", [(1, 1, 1, 64), (2, 3, 3, 192), (1, 8, 1, 320), (1, 72, 1, 64)])
 def test_backward_abs_max_sees_every_row(B, H, Hkv, S):
     """max |dS| wherever its row lies: the dQ kernel leaves one maximum per 32 rows, workgroups of the dK/dV kernel reduce shares of
-    them (the last case: more than a wave holds).  Only one row has an output gradient, so every other row contributes 0."""
+    them.  Only one row has an output gradient, so every other row contributes 0.  With the smaller workspace dK and dV are summed in one
+    piece, by fewer workgroups: the last case has two then, whose shares of 72 maxima are more than a wave holds, and rows among the last
+    eight of both."""
     g = torch.Generator().manual_seed(H * S)
     codes = lambda rows: torch.randint(0x28, 0x40, (rows, 128), generator=g, dtype=torch.uint8) | (torch.randint(0, 2, (rows, 128), generator=g, dtype=torch.uint8) << 7)
     q, k, v = (codes(B * h * S).cuda() for h in (H, Hkv, Hkv))
@@ -588,18 +590,21 @@ def test_backward_abs_max_sees_every_row(B, H, Hkv, S):
     dQ, dK, dV = (torch.empty((B * h * S, 128), dtype=torch.bfloat16, device="cuda") for h in (H, Hkv, Hkv))
     ws = torch.empty(fog.fp8_attn_workspace(B, H, S, 128, True, H_kv=Hkv), dtype=torch.uint8, device="cuda")
     groups = B * H * S // 32
+    rows_only = ws[:3 * B * H * S * 4]
     for n in range(0, groups, max(1, groups // 24)):
         row = 32 * n + (7 * n + 3) % 32
         do = torch.zeros((B * H * S, 128), dtype=torch.bfloat16, device="cuda")
         do[row] = (torch.arange(128, device="cuda") % 7 - 3).to(torch.bfloat16)      # values that E5M2 holds exactly
-        am = torch.full((1,), 9.0, device="cuda")
-        fog.fp8_attn_bwd(B, H, S, 128, s, False, q, k, v, one, one, one, O, do, do.to(torch.float8_e5m2).view(torch.uint8), one, lse,
-                         fscalar(448.0), one, dQ, dK, dV, amax_ds=am, workspace=ws, H_kv=Hkv)
+        am = torch.full((2,), 9.0, device="cuda")
+        for i, room in enumerate((ws, rows_only)):
+            fog.fp8_attn_bwd(B, H, S, 128, s, False, q, k, v, one, one, one, O, do, do.to(torch.float8_e5m2).view(torch.uint8), one, lse,
+                             fscalar(448.0), one, dQ, dK, dV, amax_ds=am[i:], workspace=room, H_kv=Hkv)
         kv = row // S // (H // Hkv) * S
         kk, vv, d = f64(k[kv:kv + S]), f64(v[kv:kv + S]), do[row].double()
         p = torch.softmax(s * (kk @ f64(q[row])), dim=0)
         want = (p * (vv @ d - (d * O[row].double()).sum())).abs().max().item()
-        assert abs(am.item() - want) <= 1e-4 * want      # binary32 sums of 128 terms and one exponential: 1e-5 at most
+        assert abs(am[0].item() - want) <= 1e-4 * want      # binary32 sums of 128 terms and one exponential: 1e-5 at most
+        assert am[1].item() == am[0].item()
 
 
 @pytest.mark.parametrize("causal", [True, False])
