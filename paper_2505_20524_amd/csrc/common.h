@@ -148,15 +148,16 @@ FOG_DEVICE void st_nt8(void* p, uint2 v) {
 }
 
 // Stores written through: the lines stay in the caches for the next kernel, but clean, so that nothing is left to write back when the
-// kernel ends or while the next one runs.  (The wait state covers the rule that the data registers of a store of more than 8 bytes must
-// not be written by the very next vector instruction; the compiler does not see the store inside the assembly.)
+// kernel ends or while the next one runs.  (The two wait states cover the rule that the data registers of a store of more than 8 bytes
+// must not be written by the next two vector instructions; the compiler, which keeps it for its own stores, does not see the one inside
+// the assembly.)
 FOG_DEVICE void st_through16(void* p, uint4 v) {
   u32x4 w = {v.x, v.y, v.z, v.w};
-  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(w) : "memory");
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(w) : "memory");
 }
 FOG_DEVICE void st_through8(void* p, uint2 v) {
   u32x2 w = {v.x, v.y};
-  asm volatile("global_store_dwordx2 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(w) : "memory");
+  asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(w) : "memory");
 }
 
 // A wave's result tile of 32 rows x (32 T) columns, from the accumulators of T 32 x 32 matrix tiles (lane & 31 = row, 8 (r / 4) +
