@@ -38,7 +38,7 @@ constexpr int HD = 128;        // head dimension
 constexpr int TILE_BYTES = BKV * HD;         // 8 KB: one K or V block, 16-byte chunks swizzled (see below)
 constexpr int STAGE = 2 * TILE_BYTES;        // K then V
 constexpr int NSTAGE = 3;
-constexpr uint32_t OOB = 0x80000000u;
+constexpr float kLag = 32.0f;   // sums of 448^2 x 2^32 over the keys of a row stay far inside binary32
 template <int N> struct Stg { static constexpr int value = N; };
 
 typedef __attribute__((address_space(3))) v2i* lds_v2i_ptr;
@@ -73,10 +73,11 @@ FOG_DEVICE float pair_max32(float v) {
 FOG_DEVICE int swz_k(int row) { return (row >> 1) & 7; }
 FOG_DEVICE int swz_v(int row) { return (row & 3) | (((row >> 3) & 1) << 2); }
 
-FOG_DEVICE void load_to_lds(v4i rsrc, uint32_t voff, uint32_t lds_addr_uniform) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+// 16 bytes per lane from byte voff + soff of the buffer.
+FOG_DEVICE void load_to_lds(v4i rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr_uniform) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
                :
-               : "v"(voff), "s"(rsrc), "s"(lds_addr_uniform)
+               : "v"(voff), "s"(rsrc), "s"(soff), "s"(lds_addr_uniform)
                : "memory", "m0");
 }
 FOG_DEVICE v4i make_rsrc(const void* base, uint32_t bytes) {
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_kernel(FwdArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[NSTAGE * STAGE];
   const int bh = blockIdx.x % a.BH;
   const int qb = a.nqb - 1 - blockIdx.x / a.BH;   // long rows (late query blocks) are launched first
-  const int t = threadIdx.x, w = t >> 6, l = t & 63, g = l >> 5;
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, g = l >> 5;
   const int S = a.S;
   const uint8_t* Qh = a.Q + (int64_t)bh * S * HD;
   const int q0 = qb * BQ + 32 * w;           // first query of this wave
@@ -141,13 +142,13 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_kernel(FwdArgs a) {
   // The ring stage of a block is a compile-time constant (the loop below is unrolled over the ring), so that every LDS
   // address is a per-lane constant plus an immediate offset: a stage taken from kb at run time costs an integer add per
   // fragment read, a sixth of the loop's vector instructions.
-  auto issue = [&](int kb, auto stg) {   // block kb -> stage kb % NSTAGE = stg; blocks past the end fetch zeros (keeps the wait counts uniform)
-    const uint32_t adv = kb < nkb ? (uint32_t)kb * (BKV * HD) : OOB;
+  auto issue = [&](int kb, auto stg) {   // block kb -> stage kb % NSTAGE = stg; past the end the last block once more (keeps the wait counts uniform)
+    const uint32_t adv = (uint32_t)(kb < nkb ? kb : nkb - 1) * (BKV * HD);
     const uint32_t base = lds_w + (uint32_t)decltype(stg)::value * STAGE;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      load_to_lds(rsrc_k, off_k[j] + adv, base + 1024u * j);
-      load_to_lds(rsrc_v, off_v[j] + adv, base + TILE_BYTES + 1024u * j);
+      load_to_lds(rsrc_k, off_k[j], adv, base + 1024u * j);
+      load_to_lds(rsrc_v, off_v[j], adv, base + TILE_BYTES + 1024u * j);
     }
   };
 
@@ -176,8 +177,17 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_kernel(FwdArgs a) {
   for (int d = 0; d < 4; ++d)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
+  // The row reference of the block in hand, and the one that O and l are kept in.  A block's probabilities enter O with the factor 2^(m_run - m_acc),
+  // which the matrix instruction takes as the E8M0 scale of its operand, and l with the same factor; only a reference that has grown by more than
+  // kLag makes O move.  Powers of two: the same bits as moving O along with the reference.  Moving O takes 64 multiplications, a third of a
+  // block's vector instructions, and one of a wave's 32 rows asks for it in every second block of a 4096-key walk: with the loads' uniform offset in a scalar
+  // register as well (8 additions less), 1 x 32/8 heads x 8192 causal 339 -> 326 us with its producers, forward of 2 x 32 x 4096 166 -> 156 us,
+  // 4 x 16 x 2048 50.3 -> 46.0.
   float m_run = -INFINITY;    // integer-valued row reference (log2 domain)
-  float l_run = 0.0f;         // this lane's share of sum_j rho_p p_ij
+  float m_acc = -INFINITY;
+  int e_blk = 127;            // 127 + m_run - m_acc, and the float 2^(m_run - m_acc)
+  float w_blk = 1.0f;
+  float l_run = 0.0f;         // this lane's share of sum_j rho_p p_ij, relative to m_acc
   float raw_max = -INFINITY;  // this lane's share of max_j (Q K^T)_ij, before scaling
 
   auto scores = [&](v16f* st, auto stg) {   // st[kt][r] = sum_d K[key][d] Q[q][d], key = 64 kb + 32 kt + 8 (r/4) + 4 g + (r%4)
@@ -237,13 +247,18 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_kernel(FwdArgs a) {
       bm = pair_max32(bm);
       const float m_new = vmax(m_run, ceilf(bm * c));
       if (__any(m_new != m_run)) {
-        const float alpha = exp2f(m_run - m_new);   // exact power of two (0 on the first block)
-        l_run *= alpha;
+        if (__any(m_new - m_acc > kLag)) {
+          const float alpha = exp2f(m_acc - m_new);   // exact power of two (0 on the first block)
+          l_run *= alpha;
 #pragma unroll
-        for (int d = 0; d < 4; ++d)
+          for (int d = 0; d < 4; ++d)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
+            for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
+          m_acc = m_new;
+        }
         m_run = m_new;
+        e_blk = 127 + (int)(m_run - m_acc);
+        w_blk = __int_as_float(e_blk << 23);
       }
       // t = rho_p 2^(x - m) <= 448 (1 + eps): summed in binary32 and cast to E4M3 (no clamp needed: values
       // up to 464 round to 448); 32 codes per lane = one B operand.
@@ -257,7 +272,7 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_kernel(FwdArgs a) {
           const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kt][4 * qd + 1], c, shift));
           const float e2 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kt][4 * qd + 2], c, shift));
           const float e3 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kt][4 * qd + 3], c, shift));
-          l_run += (e0 + e1) + (e2 + e3);
+          l_run = __builtin_fmaf((e0 + e1) + (e2 + e3), w_blk, l_run);
           uint32_t pk = __builtin_amdgcn_cvt_pk_fp8_f32(e0, e1, any_u32(), false);
           pf[4 * kt + qd] = (int)__builtin_amdgcn_cvt_pk_fp8_f32(e2, e3, pk, true);
         }
@@ -274,7 +289,7 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_kernel(FwdArgs a) {
           vf[2 * r] = v[0];
           vf[2 * r + 1] = v[1];
         }
-        o[d] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf, pf, o[d], 0, 0, 0, 0, 0, 0);
+        o[d] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf, pf, o[d], 0, 0, 0, 127, 0, e_blk);
       }
     }
   };
@@ -294,11 +309,11 @@ __global__ __launch_bounds__(kThreads, 3) void attn_fwd_kernel(FwdArgs a) {
   __syncthreads();                     // ... of any wave: the ring becomes the staging area
   if (!wave_on) return;
   // ---- epilogue: O = sinv_v O^T / (rho_p l);  lse = m + log2 l  (l_run holds rho_p l, split over two lanes)
-  const float l_tot = l_run + lane_xor32(l_run);
-  const float scale_o = (*a.sinv_v) / l_tot;
+  const float l_acc = l_run + lane_xor32(l_run);
+  const float scale_o = (*a.sinv_v) / l_acc;
   // O as whole lines past the caches: 1 x 32/8 heads x 8192 causal 348 -> 343 us, 4 x 16 x 2048 53 -> 48 us
   store_tile_rows<4>(smem + w * (32 * 272), o, scale_o, a.O + ((int64_t)bh * S + q0) * HD, HD, [](int row) { return row; });
-  if (g == 0) a.lse[(int64_t)bh * S + q] = m_run + (__log2f(l_tot) - lg_rho_p);
+  if (g == 0) a.lse[(int64_t)bh * S + q] = m_run + (__log2f(l_acc * exp2f(m_acc - m_run)) - lg_rho_p);
   if (a.amax_p) {
     float rm = fmaxf(raw_max, lane_xor32(raw_max));
     float pm = exp2f(rm * c - m_run);                 // largest p of this row, in (1/2, 1]

@@ -637,3 +637,31 @@ def test_backward_in_parts(B, H, Hkv, S, causal):
             a, b = a.double(), b.double()
             assert ((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5 * b.abs().max()).all()
     assert torch.equal(out[1][1], out[2][1]) and torch.equal(out[1][2], out[2][2])
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("steps", [(1, 2, 3, 5, 6), (0, 14, 16, 30, 32), (0, 16, 18, 64, 72), (0, 32, 128, 256, 448), (448, 128, 32, 1, 0)])
+def test_forward_with_growing_row_references(steps, causal):
+    """O stays relative to an earlier row reference until the reference has grown by more than 32.  Integer logits (as above) that grow from key
+    block to key block: by little, to 32 and 64 (rows of q = 1 and 2 share a wave, so one moves O and the other has to follow), by more than
+    32 at every block, and not at all."""
+    H, S = 2, 320
+    rng = np.random.default_rng(sum(steps))
+    Q8 = np.zeros((1, H, S, 128), np.uint8)
+    one, two = int(fp8.encode_sat(np.float32(1.0), fp8.E4M3)), int(fp8.encode_sat(np.float32(2.0), fp8.E4M3))
+    for h in range(H):
+        for i in range(S):
+            Q8[0, h, i, i % 128] = one if rng.random() < 0.5 else two
+    k = np.repeat(np.array(steps, np.float32), 64)[None, None, :, None] - rng.integers(0, 3, size=(1, H, S, 128)).astype(np.float32)
+    K8 = fp8.encode_sat(k, fp8.E4M3)                       # integers on the E4M3 grid
+    _, _, v, _ = synth.small_attention(97, 1, H, S)
+    rho_v, vinv = scaling.compute_scale(scaling.amax(v), fp8.E4M3)
+    V8 = scaling.quantize(v.reshape(-1, 128), rho_v, fp8.E4M3).reshape(v.shape)
+    c = {"q": (Q8, np.float32(1.0)), "k": (K8, np.float32(1.0)), "v": (V8, vinv)}
+    s = float(np.float32(np.log(2.0)))
+    O, lse, am = gpu_fwd(c, 1, H, S, s, causal)
+    for h in range(H):
+        Or, lr, _ = attention.attn_fwd_head(Q8[0, h], K8[0, h], V8[0, h], 1.0, 1.0, vinv, s, 448.0, causal)
+        check_bf16(O[0, h], Or, what="O, growing references", max_flip_frac=0.1)
+        # s is ln 2 in binary32 (2^-25 relative) and so is its product with log2 e: at 896 the logits are 1e-4 off integers
+        assert np.all(np.abs(lse[0, h] - lr) <= 2e-5 + 2.0 ** -22 * np.abs(lr))
