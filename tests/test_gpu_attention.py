@@ -665,3 +665,20 @@ def test_forward_with_growing_row_references(steps, causal):
         check_bf16(O[0, h], Or, what="O, growing references", max_flip_frac=0.1)
         # s is ln 2 in binary32 (2^-25 relative) and so is its product with log2 e: at 896 the logits are 1e-4 off integers
         assert np.all(np.abs(lse[0, h] - lr) <= 2e-5 + 2.0 ** -22 * np.abs(lr))
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("S", [512, 576, 640, 1088])
+def test_forward_of_few_workgroups_equals_that_of_many(S, causal):
+    """Launches of up to two workgroups per CU produce scores a block ahead, larger ones do not: the same operations in the same order, so one head
+    by itself has the bytes it has among 300 copies (S = 512 is the shortest of the first kind; block counts of every remainder by four)."""
+    g = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v = ((torch.randn((1, S, 128), device="cuda", generator=g) * 64).to(torch.float8_e4m3fn).view(torch.uint8) for _ in range(3))
+    inv, out = fscalar(2.0 ** -6), []
+    for H in (1, 300):
+        O, lse, am = torch.empty((H, S, 128), dtype=torch.bfloat16, device="cuda"), torch.empty((H, S), device="cuda"), fscalar(-1.0)
+        rep = [x.expand(H, S, 128).contiguous() for x in (q, k, v)]
+        fog.fp8_attn_fwd(1, H, S, 128, 1 / math.sqrt(128), causal, *rep, inv, inv, inv, fscalar(448.0), O, lse, amax_p=am)
+        out.append((O, lse, am))
+    assert torch.isfinite(out[0][0]).all() and out[0][0].abs().max() > 0
+    assert (out[1][0] == out[0][0]).all() and (out[1][1] == out[0][1]).all() and torch.equal(out[1][2], out[0][2])
