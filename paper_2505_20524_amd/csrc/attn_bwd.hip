@@ -63,6 +63,13 @@ FOG_DEVICE void load16_to_lds(v4i rsrc, uint32_t voff, uint32_t lds_addr_uniform
                : "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane((int)lds_addr_uniform))
                : "memory", "m0");
 }
+// ... from byte voff + soff
+FOG_DEVICE void load16_to_lds(v4i rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr_uniform) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               :
+               : "v"(voff), "s"(rsrc), "s"(soff), "s"(lds_addr_uniform)
+               : "memory", "m0");
+}
 FOG_DEVICE void load4_to_lds(v4i rsrc, uint32_t voff, uint32_t lds_addr_uniform) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds"
                :
@@ -531,7 +538,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[NSTAGE * 2 * TILE];     // {K, V} x 4 stages
   const int bh = blockIdx.x % a.BH;
   const int qblk = a.nblk - 1 - blockIdx.x / a.BH;
-  const int t = threadIdx.x, w = t >> 6, l = t & 63, g = l >> 5;
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, g = l >> 5;
   const int S = a.S;
   const int64_t hoff = (int64_t)bh * S;
   const int q0 = qblk * BLK + 32 * w;
@@ -568,12 +575,12 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
   tile_load_offsets(off);
   const uint32_t lds_w = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(uintptr_t)smem + 2048u * w));
   auto issue = [&](int kb, auto stg) {   // block kb -> stage kb % NSTAGE = stg
-    const uint32_t adv = kb < nkb ? (uint32_t)kb * (STEP * HD) : OOB;
+    const uint32_t adv = (uint32_t)(kb < nkb ? kb : nkb - 1) * (STEP * HD);   // (past the end the last block once more: nothing reads it)
     const uint32_t base = lds_w + (uint32_t)decltype(stg)::value * (2 * TILE);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      load16_to_lds(rsrc_k, off[j] + adv, base + 1024u * j);
-      load16_to_lds(rsrc_v, off[j] + adv, base + TILE + 1024u * j);
+      load16_to_lds(rsrc_k, off[j], adv, base + 1024u * j);
+      load16_to_lds(rsrc_v, off[j], adv, base + TILE + 1024u * j);
     }
   };
   const RowFrag rf = rowfrag_addr();
@@ -597,29 +604,29 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
   __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt = 8: block 0 has landed (4 direct loads per thread and block)
   __syncthreads();
 
-  auto block = [&](int kb, auto stg) __attribute__((always_inline)) {
+  // One of the four matrix instructions of a block's scores (or, on V and dO, of its dP): tile n / 2, half n % 2 of the head dimension.
+  auto clear16 = [&](v16f& x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = 0.0f;
+  };
+  auto score = [&](v16f* st, int n, v8i f) __attribute__((always_inline)) {
+    if ((n & 1) == 0) clear16(st[n >> 1]);
+    st[n >> 1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f, qf[n & 1], st[n >> 1], 0, 0, 0, 0, 0, 0);
+  };
+  // The wave overlaps the two units by itself as well: dP of block kb is produced under its exponentials, the scores of block kb + 1 while its dS are
+  // formed, and every operand is read from LDS one matrix instruction ahead.  (All eight products in front of the vector part before, and
+  // uniform load offsets in vector registers: 4 x 16 x 2048 73.5 -> 69.2 us, backward of 1 x 4 x 8192 219 -> 210; 2 x 32 x 4096 level at 225, where the clock
+  // is what gives.)
+  auto block = [&](int kb, v16f* st, v16f* next, auto stg) __attribute__((always_inline)) {
     constexpr int STG = decltype(stg)::value;
-    if (kb > 0) {
-      __builtin_amdgcn_s_waitcnt(0x0078);  // vmcnt = 8: block kb landed (two younger blocks may be in flight); lgkmcnt = 0
-      __syncthreads();
-    }
+    __builtin_amdgcn_s_waitcnt(0x0074);  // vmcnt = 4: block kb + 1 landed (block kb + 2 may be in flight); lgkmcnt = 0
+    __syncthreads();
     issue(kb + 3, Stg<(STG + 3) % NSTAGE>{});   // into the stage of block kb - 1
     if (kb >= nkb_wave) return;
     const uint8_t* sk = smem + STG * (2 * TILE);
     const uint8_t* sv = sk + TILE;
     const int kbase = kb * STEP;
     // transposed tiles, lane = query: element r of tile kt is key kbase + 32 kt + 8 (r/4) + 4 g + (r%4)
-    v16f st[2], dp[2];
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { st[kt][r] = 0.0f; dp[kt][r] = 0.0f; }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        st[kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(read_rowfrag(sk, rf, kt, h), qf[h], st[kt], 0, 0, 0, 0, 0, 0);
-        dp[kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(read_rowfrag(sv, rf, kt, h), dof[h], dp[kt], 0, 1, 0, 0, 0, 0);
-      }
-    }
     if (CAUSAL && kbase + STEP - 1 > q0) {   // diagonal blocks: keys after the query are masked
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
@@ -627,14 +634,33 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
         for (int r = 0; r < 16; ++r)
           if (kbase + 32 * kt + 8 * (r >> 2) + 4 * g + (r & 3) > q) st[kt][r] = -INFINITY;
     }
-    // rho_ds dS = (rho_ds P) (dP - D), left in the registers of dP
+    v16f dp[2];
+    const uint8_t* sn = smem + (STG + 1) % NSTAGE * (2 * TILE);
+    auto frag = [&](int n) __attribute__((always_inline)) {   // operands in the order of the matrix instructions below, each read one of them ahead
+      return n < 4 ? read_rowfrag(sv, rf, n >> 1, n & 1) : n < 8 ? read_rowfrag(sn, rf, (n >> 1) & 1, n & 1) : read_colfrag(sk, cf, n & 3);
+    };
+    v8i f[2];
+    f[0] = frag(0);
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kt][r], c, -lse));   // rho_ds P
-        dp[kt][r] = e * __builtin_fmaf(dp[kt][r], cdp, -Dq);
+    for (int n = 0; n < 8; ++n) {
+      const int kt = (n >> 1) & 1, h = n & 1;
+      __builtin_amdgcn_sched_barrier(0);
+      if (n < 4) {
+        if (h == 0) clear16(dp[kt]);
+        dp[kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[n & 1], dof[h], dp[kt], 0, 1, 0, 0, 0, 0);
+      } else {
+        score(next, n & 3, f[n & 1]);   // (past the wave's last block: of no use, and nothing reads it)
       }
+      f[(n + 1) & 1] = frag(n + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      // rho_ds P under the products of dP, then rho_ds dS = (rho_ds P) (dP - D), left in the registers of dP
+#pragma unroll
+      for (int r = 8 * h; r < 8 * h + 8; ++r) {
+        if (n < 4) st[kt][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kt][r], c, -lse));
+        else       dp[kt][r] = st[kt][r] * __builtin_fmaf(dp[kt][r], cdp, -Dq);
+      }
+    }
+    f[1] = frag(9);
     const float bm = block_absmax<2>(dp);
     ds_max = fmaxf(ds_max, bm);
     // The hardware convert turns overflow into infinity, so magnitudes above the largest finite E5M2 value have to be clamped
@@ -651,15 +677,20 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
       }
     // dQ^T += K^T dS~^T  (contraction over the 64 keys of this step)
 #pragma unroll
-    for (int d = 0; d < 4; ++d)
-      dq[d] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(read_colfrag(sk, cf, d), dsf, dq[d], 0, 1, 0, 0, 0, 0);
+    for (int d = 0; d < 4; ++d) {
+      dq[d] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[d & 1], dsf, dq[d], 0, 1, 0, 0, 0, 0);
+      if (d < 2) f[d & 1] = frag(10 + d);
+    }
   };
   static_assert(NSTAGE == 4, "the loops are unrolled over a ring of four stages");
+  v16f sa[2], sb[2];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) score(sa, n, read_rowfrag(smem, rf, n >> 1, n & 1));
   for (int kb = 0; kb < nkb; kb += NSTAGE) {
-    block(kb, Stg<0>{});
-    if (kb + 1 < nkb) block(kb + 1, Stg<1>{});
-    if (kb + 2 < nkb) block(kb + 2, Stg<2>{});
-    if (kb + 3 < nkb) block(kb + 3, Stg<3>{});
+    block(kb, sa, sb, Stg<0>{});
+    if (kb + 1 < nkb) block(kb + 1, sb, sa, Stg<1>{});
+    if (kb + 2 < nkb) block(kb + 2, sa, sb, Stg<2>{});
+    if (kb + 3 < nkb) block(kb + 3, sb, sa, Stg<3>{});
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): no direct load may still be writing LDS when the workgroup retires
   __syncthreads();                     // ... of any wave: the ring becomes the staging area
