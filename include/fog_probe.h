@@ -110,6 +110,15 @@ fog_status fog_probe_gemm_products_only(int64_t M, int64_t N, int64_t K, const u
 fog_status fog_probe_gemm_plan(fog_layout layout, int64_t M, int64_t N, int64_t K, int with_workspace, int compute_units,
                                int* tile_m, int* tile_n, int* workgroups_per_cu, int* splits, int* k_chunk);
 
+/*
+ * fog_quantize_jit_batch in its one-launch form whatever the sizes (2^30 elements in all at most).  For tests, of its edges and of what
+ * a workgroup does when another one's maximum is late:
+ *   patience : ticks of 10 ns before a waiting workgroup claims a share whose maximum is missing; 0 makes every workgroup claim
+ *              what it does not find at once.
+ * Errors: as fog_quantize_jit_batch; SHAPE for a negative patience or more elements.
+ */
+fog_status fog_probe_quantize_held(const fog_cast_job* jobs, int count, void* workspace, size_t workspace_bytes, int64_t patience, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

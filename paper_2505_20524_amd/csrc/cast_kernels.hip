@@ -9,6 +9,7 @@
 #include "common.h"
 #include "launch.h"
 #include "words.h"
+#include "../../include/fog_probe.h"
 
 namespace {
 
@@ -404,6 +405,177 @@ __global__ __launch_bounds__(kThreads) void quantize_batch_kernel(BatchJobs b, c
   else                      quantize_rows_body<FOG_E5M2, false, REREAD>(b.x[j], 1, chunks, chunks * 16, nullptr, b.q[j], chunks * 16, nullptr, js, bid, nb);
 }
 
+// ---------------------------------------------------------------- abs-max and cast in one launch
+// Two passes read every tensor twice over the fabric (neither L2, invalid at a kernel's start, nor the memory-side cache, which is no faster,
+// helps the second), 5 bytes an element in all where 3 have to move.  Here one workgroup per compute unit reads its share once, keeps 22 x 512 chunks
+// of 16 elements of it in registers (46 M elements on the chip), leaves its maximum in a word of the workspace, gathers those
+// of the tensor's other workgroups and casts what it holds; of a larger share the rest is read twice, as before.  A small launch in front clears the words.
+// No workgroup depends on another one being resident: a word that stays empty for `patience` is claimed by a waiting workgroup, which takes that share's
+// maximum itself (whoever is late publishes the same value), so every wait ends by the work of workgroups that are running.
+constexpr int kHeldThreads = 512, kHeldRegs = 21;
+constexpr uint32_t kMaxIsIn = 0x80000000u, kMaxIsClaimed = 0x40000000u;
+struct HeldJobs {
+  int first[kBatchMax + 1];   // first workgroup of each job
+  int64_t patience;           // ticks of 10 ns
+};
+__global__ __launch_bounds__(256) void clear_maxima_kernel(HeldJobs h, uint32_t* __restrict__ ws) {
+  const int j = blockIdx.x, n = h.first[j + 1] - h.first[j];
+  for (int i = threadIdx.x; i < n; i += 256) ws[j * kJitSlots + i] = 0u;
+}
+// Raw buffer over a workgroup's share: loads past its end return zeros and stores there are dropped, so the unrolled code below needs few branches
+// (the compiler waits for everything in flight behind one).  The bounds check covers the vector offset, not the scalar one, which stays 0.
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+FOG_DEVICE __amdgpu_buffer_rsrc_t span(const void* base, int64_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+struct HeldShared {
+  uint32_t part[kHeldThreads / 64], open_word;
+};
+struct Plain { static constexpr int value = 0; };
+struct Stream { static constexpr int value = 2; };   // non-temporal
+template <int FMT>
+FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, int64_t patience, uint32_t* __restrict__ words, int j, int bid, int nb) {
+  constexpr int STEP = kHeldThreads;                                     // chunks that the workgroup takes at a time
+  constexpr int REGS = kHeldRegs * STEP;                                 // chunks of the share that stay in registers
+  constexpr int NL = 8, GRP = 7;
+  const int tid = threadIdx.x;
+  const int64_t chunks = b.n[j] / 16, per = (chunks + nb - 1) / nb;
+  auto begin = [&](int i) { return per * i < chunks ? per * i : chunks; };
+  const int64_t c0 = begin(bid);
+  const int mine = (int)(begin(bid + 1) - c0);                           // chunks of this workgroup's share
+  const auto src = span(b.x[j] + c0 * 16, (int64_t)mine * 32), dst = span(b.q[j] + c0 * 16, (int64_t)mine * 16);
+  uint32_t m[4] = {0, 0, 0, 0};
+  auto take = [&](const v4u* a) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      m[0] = pkmax_abs_bf16(m[0], a[k][0]); m[1] = pkmax_abs_bf16(m[1], a[k][1]);
+      m[2] = pkmax_abs_bf16(m[2], a[k][2]); m[3] = pkmax_abs_bf16(m[3], a[k][3]);
+    }
+  };
+  auto fetch = [&](decltype(src) from, int c, v4u* to, auto policy) __attribute__((always_inline)) {   // this thread's chunk of those from c on
+    to[0] = __builtin_amdgcn_raw_buffer_load_b128(from, (c + tid) * 32, 0, decltype(policy)::value);
+    to[1] = __builtin_amdgcn_raw_buffer_load_b128(from, (c + tid) * 32 + 16, 0, decltype(policy)::value);
+  };
+  auto walk = [&](decltype(src) from, int c, int n) __attribute__((always_inline)) {
+    for (; c < n; c += NL * STEP) {
+      v4u t[NL][2];
+#pragma unroll
+      for (int k = 0; k < NL; ++k) fetch(from, c + k * STEP, t[k], Plain{});
+#pragma unroll
+      for (int k = 0; k < NL; ++k) take(t[k]);
+    }
+  };
+  auto block_max = [&]() __attribute__((always_inline)) {
+    uint32_t r = wave_max_u32(max_of_pair(pkmax_abs_bf16(pkmax_abs_bf16(m[0], m[1]), pkmax_abs_bf16(m[2], m[3]))));
+    __syncthreads();
+    if ((tid & 63) == 0) sh.part[tid >> 6] = r;
+    __syncthreads();
+    r = sh.part[0];
+#pragma unroll
+    for (int w = 1; w < kHeldThreads / 64; ++w) r = r > sh.part[w] ? r : sh.part[w];
+    return r;
+  };
+  walk(src, REGS, mine);
+  v4u v[kHeldRegs][2];
+#pragma unroll
+  for (int g = 0; g < kHeldRegs; g += GRP)
+    if (g * STEP < mine) {
+#pragma unroll
+      for (int i = g; i < g + GRP && i < kHeldRegs; ++i) fetch(src, i * STEP, v[i], Stream{});
+    }
+#pragma unroll
+  for (int g = 0; g < kHeldRegs; g += GRP)
+    if (g * STEP < mine) {
+#pragma unroll
+      for (int i = g; i < g + GRP && i < kHeldRegs; ++i) take(v[i]);
+    }
+  uint32_t r = block_max();
+  if (tid == 0) __hip_atomic_store(words + bid, kMaxIsIn | r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // Everybody's maxima.  (nb is at most the number of compute units, a word for each thread.)
+  const int64_t t0 = wall_clock64();
+  bool helped = false;
+  uint32_t w;
+  for (;;) {
+    w = tid < nb ? __hip_atomic_load(words + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kMaxIsIn;
+    if (__syncthreads_and(w & kMaxIsIn)) break;
+    if (!__syncthreads_or(wall_clock64() - t0 >= patience)) {   // (the workgroup's decision: its waves read the clock at different times)
+      __builtin_amdgcn_s_sleep(1);
+      continue;
+    }
+    // the first empty word from this workgroup's own on, if it is still empty
+    if (tid == 0) sh.open_word = 0xFFFFFFFFu;
+    __syncthreads();
+    if (w == 0u) atomicMin(&sh.open_word, (uint32_t)(tid >= bid ? tid - bid : tid - bid + nb));
+    __syncthreads();
+    const uint32_t at = sh.open_word;
+    __syncthreads();
+    if (at == 0xFFFFFFFFu) continue;
+    const int i = ((int)at + bid) % nb;
+    if (tid == 0) sh.open_word = atomicCAS(words + i, 0u, kMaxIsClaimed);
+    __syncthreads();
+    const bool claimed = sh.open_word == 0u;
+    __syncthreads();
+    if (claimed) {
+      m[0] = m[1] = m[2] = m[3] = 0u;
+      walk(span(b.x[j] + begin(i) * 16, (begin(i + 1) - begin(i)) * 32), 0, (int)(begin(i + 1) - begin(i)));
+      r = block_max();
+      if (tid == 0) __hip_atomic_store(words + i, kMaxIsIn | r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      helped = true;    // what this workgroup held has made room for that share: it reads its own again below
+    }
+  }
+  m[0] = w & 0x7FFFu;
+  m[1] = m[2] = m[3] = 0u;
+  r = block_max();
+  const float a = __uint_as_float(r << 16);
+  float rho, inv;
+  scale_from_amax(a, FMT, b.margin[j], &rho, &inv);
+  if (bid == 0 && tid == 0) {
+    *b.amax[j] = a;
+    *b.scale[j] = rho;
+    if (b.scale_inv[j]) *b.scale_inv[j] = inv;
+  }
+  auto put = [&](int c, uint2 lo, uint2 hi) __attribute__((always_inline)) {
+    const v4u o = {lo.x, lo.y, hi.x, hi.y};
+    __builtin_amdgcn_raw_buffer_store_b128(o, dst, (c + tid) * 16, 0, 16);   // written through
+  };
+  if (!helped && r < 0x7F80u && a * rho <= (FMT == FOG_E4M3 ? 449.0f : 57400.0f)) {
+    // Finite values that fit: up to a rounding above the format's maximum, which the convert takes back (it overflows from half a step above, 464 and 61440).
+    auto cast = [&](v4u t) __attribute__((always_inline)) {
+      return make_uint2(cvt4_fp8_finite<FMT>(bf16lo(t[0]) * rho, bf16hi(t[0]) * rho, bf16lo(t[1]) * rho, bf16hi(t[1]) * rho),
+                        cvt4_fp8_finite<FMT>(bf16lo(t[2]) * rho, bf16hi(t[2]) * rho, bf16lo(t[3]) * rho, bf16hi(t[3]) * rho));
+    };
+#pragma unroll
+    for (int g = 0; g < kHeldRegs; g += GRP)
+      if (g * STEP < mine) {
+#pragma unroll
+        for (int i = g; i < g + GRP && i < kHeldRegs; ++i) put(i * STEP, cast(v[i][0]), cast(v[i][1]));
+      }
+    for (int c = REGS; c < mine; c += NL * STEP) {
+      v4u t[NL][2];
+#pragma unroll
+      for (int k = 0; k < NL; ++k) fetch(src, c + k * STEP, t[k], Plain{});
+#pragma unroll
+      for (int k = 0; k < NL; ++k) put(c + k * STEP, cast(t[k][0]), cast(t[k][1]));
+    }
+  } else {
+    auto cast = [&](v4u t) { return cast8<FMT>(make_uint4(t[0], t[1], t[2], t[3]), rho); };
+    for (int c = 0; c < mine; c += STEP) {
+      v4u t[2];
+      fetch(src, c, t, Plain{});
+      put(c, cast(t[0]), cast(t[1]));
+    }
+  }
+}
+__global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_kernel(BatchJobs b, HeldJobs h, uint32_t* __restrict__ ws) {
+  __shared__ HeldShared sh;
+  int j = 0;
+  for (int k = 1; k < b.count; ++k)
+    if ((int)blockIdx.x >= h.first[k]) j = k;
+  const int bid = (int)blockIdx.x - h.first[j], nb = h.first[j + 1] - h.first[j];
+  if (b.fmt[j] == FOG_E4M3) held_body<FOG_E4M3>(sh, b, h.patience, ws + j * kJitSlots, j, bid, nb);
+  else                      held_body<FOG_E5M2>(sh, b, h.patience, ws + j * kJitSlots, j, bid, nb);
+}
+
 // ---------------------------------------------------------------- several tensors per launch (delayed scaling)
 // fog_quantize_delayed for up to kBatchMax contiguous tensors in ONE launch: a workgroup finds its job from the prefix
 // sums and does, inside it, exactly what it does in the one-tensor launch (the history update and the scale from the
@@ -602,6 +774,38 @@ inline int one_word_workgroups(int64_t chunks) { return workgroups(chunks, 512);
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Just-in-time casts in one launch (quantize_held_kernel) instead of an abs-max and a cast pass: from 18 M elements (70 K a compute unit) on, where what the
+// second pass reads again is more than the wait for the maxima costs, to 160 M (625 K), beyond which so much is read again after all that the two
+// passes' many workgroups are ahead.  Batches back to back, us, two passes -> one launch: 17 M elements 17.2 -> 18.3, 20 M 21.8 -> 19.4, 25 M 24.9
+// -> 21.7 (in two tensors 22.6 -> 22.3), 42 M in three 39.1 -> 28.7, 67 M in four 62.8 -> 51.4, 82 M 79.2 -> 69.5, 134 M 124 -> 117, 150 M 148.4 -> 133.7, 184 M
+// 172 -> 186.  (Four steps of the shares in LDS besides: a share of 32 steps 51.3 -> 50, all others up to 4 us slower, the registers spill.)
+constexpr int64_t kHeldFrom = 70 << 10, kHeldTo = 625 << 10, kHeldMost = (int64_t)1 << 30, kHeldPatience = 5000;   // elements a compute unit; ...; 50 us
+inline bool held_pays(int64_t n) {
+  const int64_t cus = fog_compute_units();
+  return cus <= kHeldThreads && n >= kHeldFrom * cus && n <= kHeldTo * cus;
+}
+// One workgroup per compute unit, dealt to the tensors by their sizes, at least one each.
+inline fog_status launch_held(const BatchJobs& b, int64_t total, int64_t patience, uint32_t* ws, hipStream_t s) {
+  HeldJobs h;
+  h.patience = patience;
+  h.first[0] = 0;
+  int room = fog_compute_units() < kHeldThreads ? fog_compute_units() : kHeldThreads;
+  for (int j = 0; j < kBatchMax; ++j) {
+    int nb = 0;
+    if (j < b.count) {
+      const int most = room - (b.count - 1 - j);      // the others' one each
+      nb = (int)((b.n[j] * room + total - 1) / total);
+      nb = nb > most ? most : nb < 1 ? 1 : nb;
+      total -= b.n[j];
+      room -= nb;
+    }
+    h.first[j + 1] = h.first[j] + nb;
+  }
+  clear_maxima_kernel<<<b.count, 256, 0, s>>>(h, ws);
+  quantize_held_kernel<<<h.first[b.count], kHeldThreads, 0, s>>>(b, h, ws);
+  return fog_launch_status();
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------- host entry points
@@ -727,6 +931,12 @@ extern "C" fog_status fog_quantize_jit(const void* x_bf16, int64_t rows, int64_t
   const uint16_t* x = reinterpret_cast<const uint16_t*>(x_bf16);
   uint32_t* ws = reinterpret_cast<uint32_t*>(workspace);
   const int64_t n = rows * cols;
+  if (!qT && (rows == 1 || (ldx == cols && ldq == cols)) && n % 16 == 0 && aligned16(x_bf16) && aligned16(q) && held_pays(n)) {
+    BatchJobs b{};
+    b.count = 1;
+    b.x[0] = x; b.n[0] = n; b.q[0] = q; b.fmt[0] = (int)fmt; b.margin[0] = margin; b.amax[0] = amax; b.scale[0] = scale; b.scale_inv[0] = scale_inv;
+    return launch_held(b, n, kHeldPatience, ws, s);
+  }
   int64_t blocks = 0;   // an empty tensor: no partial maxima, abs-max 0, scale 1
   if (n > 0) {
     if ((ldx == cols || rows == 1) && aligned16(x_bf16)) {
@@ -794,17 +1004,15 @@ extern "C" size_t fog_quantize_jit_batch_workspace(int count) {
   return count > 0 ? (size_t)count * kJitSlots * sizeof(uint32_t) : 0;
 }
 
-extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count, void* workspace, size_t workspace_bytes,
-                                             void* stream) {
-  if (count == 0) return FOG_OK;
+// Checks of a batch of casts and its description for the kernels (but for the workgroups of the cast pass); *total is its elements.
+static fog_status batch_jobs(const fog_cast_job* jobs, int count, void* workspace, size_t workspace_bytes, BatchJobs& b, int64_t* total) {
   if (!jobs || !workspace) return FOG_ERR_NULL;
   if (count < 0 || count > kBatchMax) return FOG_ERR_SHAPE;
   if (workspace_bytes < fog_quantize_jit_batch_workspace(count)) return FOG_ERR_WORKSPACE;
   if ((reinterpret_cast<uintptr_t>(workspace) & 3u) != 0) return FOG_ERR_ALIGN;
-  BatchJobs b;
   b.count = count;
   b.amax_first[0] = 0;
-  int64_t total = 0;
+  *total = 0;
   for (int j = 0; j < count; ++j) {
     const fog_cast_job& t = jobs[j];
     if (!t.x_bf16 || !t.q || !t.amax || !t.scale) return FOG_ERR_NULL;
@@ -816,7 +1024,7 @@ extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count
     int64_t ab = (n / 8 + kThreads * 8 - 1) / (kThreads * 8);
     if (ab > kJitSlots) ab = kJitSlots;
     b.amax_first[j + 1] = b.amax_first[j] + (int)ab;
-    total += n;
+    *total += n;
     b.x[j] = reinterpret_cast<const uint16_t*>(t.x_bf16);
     b.n[j] = n;
     b.q[j] = t.q;
@@ -826,6 +1034,19 @@ extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count
     b.scale[j] = t.scale;
     b.scale_inv[j] = t.scale_inv;
   }
+  return FOG_OK;
+}
+
+extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count, void* workspace, size_t workspace_bytes,
+                                             void* stream) {
+  if (count == 0) return FOG_OK;
+  BatchJobs b;
+  int64_t total;
+  const fog_status st = batch_jobs(jobs, count, workspace, workspace_bytes, b, &total);
+  if (st != FOG_OK) return st;
+  hipStream_t s = (hipStream_t)stream;
+  uint32_t* ws = reinterpret_cast<uint32_t*>(workspace);
+  if (held_pays(total)) return launch_held(b, total, kHeldPatience, ws, s);
   b.cast_first[0] = 0;
   for (int p = 0; p < count; ++p) {   // launch position p casts job count - 1 - p
     const int64_t chunks = b.n[count - 1 - p] / 16;
@@ -838,12 +1059,21 @@ extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count
     b.x[j] = nullptr; b.n[j] = 0; b.q[j] = nullptr; b.fmt[j] = 0; b.margin[j] = 0;
     b.amax[j] = b.scale[j] = b.scale_inv[j] = nullptr;
   }
-  hipStream_t s = (hipStream_t)stream;
-  uint32_t* ws = reinterpret_cast<uint32_t*>(workspace);
   amax_batch_kernel<<<b.amax_first[count], kThreads, 0, s>>>(b, ws);
   if (reread_stays(total, false)) quantize_batch_kernel<true><<<b.cast_first[count], kThreads, 0, s>>>(b, ws);
   else                     quantize_batch_kernel<false><<<b.cast_first[count], kThreads, 0, s>>>(b, ws);
   return fog_launch_status();
+}
+
+extern "C" fog_status fog_probe_quantize_held(const fog_cast_job* jobs, int count, void* workspace, size_t workspace_bytes, int64_t patience,
+                                              void* stream) {
+  if (count == 0) return FOG_OK;
+  BatchJobs b;
+  int64_t total;
+  const fog_status st = batch_jobs(jobs, count, workspace, workspace_bytes, b, &total);
+  if (st != FOG_OK) return st;
+  if (patience < 0 || total > kHeldMost) return FOG_ERR_SHAPE;
+  return launch_held(b, total, patience, reinterpret_cast<uint32_t*>(workspace), (hipStream_t)stream);
 }
 
 extern "C" fog_status fog_quantize_delayed_batch(const fog_delayed_job* jobs, int count, int64_t step, void* stream) {

@@ -59,6 +59,7 @@ PROBE_SIGNATURES = {
     "fog_probe_attention_loop": (_I, [_I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _P]),
     "fog_probe_mfma_coissue": (_I, [_I, _I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _P]),
     "fog_probe_mfma_cross_wave": (_I, [_I, _I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _c.POINTER(_c.c_double), _P]),
+    "fog_probe_quantize_held": (_I, [_P, _I, _P, _SZ, _I64, _P]),
     "fog_probe_gemm_plan": (_I, [_I, _I64, _I64, _I64, _I, _I] + [_c.POINTER(_I)] * 5),
     "fog_probe_gemm_products_only": (_I, [_I64, _I64, _I64, _P, _I64, _P, _I64, _P, _P, _P, _I64, _P]),
 }
@@ -326,6 +327,12 @@ def probe_mfma_cross_wave(op, vector_ops, iters_matrix, iters_vector, sink, stre
     _check(load().fog_probe_mfma_cross_wave(op, vector_ops, iters_matrix, iters_vector, _ptr(sink), sink.numel() * sink.element_size(),
                                             _c.byref(cm), _c.byref(cv), _stream(stream)), "fog_probe_mfma_cross_wave")
     return cm.value, cv.value
+
+
+def probe_quantize_held(jobs, workspace, patience, stream=None):
+    """quantize_jit_batch in its one-launch form whatever the sizes (fog_probe.h)."""
+    _check(load().fog_probe_quantize_held(ctypes.cast(jobs, _P), len(jobs), _ptr(workspace), workspace.numel() * workspace.element_size(),
+                                          patience, _stream(stream)), "fog_probe_quantize_held")
 
 
 def probe_gemm_plan(layout, M, N, K, with_workspace=False, compute_units=0):

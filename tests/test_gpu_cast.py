@@ -562,3 +562,108 @@ def test_jit_forms_by_size(rows, cols, transpose):
     want = (x.float() * rho).clamp_(-448.0, 448.0).to(torch.float8_e4m3fn).view(torch.uint8)
     assert torch.equal(q, want)
     assert not transpose or torch.equal(qT, want.t())
+
+
+@pytest.mark.parametrize("patience", [0, 5000])
+@pytest.mark.parametrize("chunks", [[1], [1, 2, 1], [255], [257, 1], [512 * 256], [512 * 256 + 1, 3], [512 * 256 * 7 + 5], [512 * 200, 512 * 30 + 1] * 16,
+                                    [512 * 256 * 21], [512 * 256 * 21 + 1, 17], [512 * 256 * 30 + 333]])
+def test_one_launch_cast_equals_the_separate_calls(chunks, patience):
+    """The cast whose workgroups keep their shares in registers and exchange their maxima: fewer chunks of 16 than workgroups (empty
+    shares), shares that end inside a step of 512 chunks and at its edge, the last step in registers, the first beyond, 32 tensors; and with no
+    patience every workgroup takes other workgroups' maxima itself and reads its own share again."""
+    g = torch.Generator(device="cuda").manual_seed(len(chunks) + chunks[0])
+    jobs, want = [], []
+    for i, c in enumerate(chunks):
+        x = torch.randn((c, 16), device="cuda", generator=g).mul_(3.0 ** (i % 5)).to(torch.bfloat16)
+        x[c // 2, 7] = -20.0 * (i + 1)                              # the abs-max, away from the ends
+        x[-1, 15] = 19.0
+        fmt = (fp8.E4M3, fp8.E5M2)[i % 2]
+        jobs.append((x, fmt, torch.full((c, 16), 0xAA, dtype=torch.uint8, device="cuda"), *(torch.full((1,), -1.0, device="cuda") for _ in range(3))))
+        am, sc, si = (torch.zeros(1, device="cuda") for _ in range(3))
+        q = torch.empty((c, 16), dtype=torch.uint8, device="cuda")
+        fog.amax(x.view(-1), am)
+        fog.scale(am, fmt, sc, si)
+        fog.quantize(x, fmt, sc, q=q)
+        want.append((q, am, sc, si))
+    ws = torch.randint(0, 256, (fog.quantize_jit_batch_workspace(len(jobs)),), dtype=torch.uint8, device="cuda", generator=g)
+    arr = fog.make_cast_jobs(jobs)
+    for _ in range(3):                                              # the words of the call before are no answer
+        for job in jobs:
+            job[2].fill_(0xAA)
+        fog.probe_quantize_held(arr, ws, patience)
+        for job, w in zip(jobs, want):
+            assert all(torch.equal(a, b) for a, b in zip(job[2:], w))
+
+
+@pytest.mark.parametrize("margin", [-3, 0, 2])
+@pytest.mark.parametrize("special", [None, float("inf"), float("nan"), 0.0, 2.0 ** -130, 3.3895e38])
+def test_one_launch_cast_of_special_values(special, margin):
+    """Infinities, NaNs, zeros, the smallest and largest magnitudes, and margins that saturate, through the path that skips the clamp for finite
+    tensors and the one that does not, as the separate calls give them."""
+    for fmt in (fp8.E4M3, fp8.E5M2):
+        x = torch.randn((512 * 16, 16), device="cuda", generator=torch.Generator(device="cuda").manual_seed(5)).to(torch.bfloat16)
+        if special is not None:
+            x[100, 3], x[8000, 9] = special, -special
+            if abs(special) < 1.0:
+                x.mul_(0.0)
+                x[17, 3] = special
+        am, sc, si, am2, sc2, si2 = (torch.full((1,), -1.0, device="cuda") for _ in range(6))
+        q, q2 = (torch.empty((512 * 16, 16), dtype=torch.uint8, device="cuda") for _ in range(2))
+        fog.amax(x.view(-1), am)
+        fog.scale(am, fmt, sc, si, margin=margin)
+        fog.quantize(x, fmt, sc, q=q)
+        ws = torch.empty(fog.quantize_jit_batch_workspace(1), dtype=torch.uint8, device="cuda")
+        fog.probe_quantize_held(fog.make_cast_jobs([(x, fmt, q2, am2, sc2, si2)], margin=margin), ws, 5000)
+        for a, b in ((q, q2), (am, am2), (sc, sc2), (si, si2)):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+def test_large_casts_take_the_one_launch_form_with_the_same_results():
+    """The public calls around the size from which they read a tensor once (70 K elements a compute unit), one tensor and several."""
+    per_cu = (70 << 10) * torch.cuda.get_device_properties(0).multi_processor_count // 16
+    for c in (per_cu - 1, per_cu, per_cu + 1):
+        x = torch.randn((c, 16), device="cuda").to(torch.bfloat16)
+        am, sc, si = (torch.zeros(1, device="cuda") for _ in range(3))
+        q = torch.empty((c, 16), dtype=torch.uint8, device="cuda")
+        fog.amax(x.view(-1), am)
+        fog.scale(am, fp8.E4M3, sc, si)
+        fog.quantize(x, fp8.E4M3, sc, q=q)
+        half = c // 2
+        for parts in ([x], [x[:half], x[half:]]):
+            out = [(p, fp8.E4M3, torch.empty(p.shape, dtype=torch.uint8, device="cuda"), *(torch.zeros(1, device="cuda") for _ in range(3))) for p in parts]
+            fog.quantize_jit_batch(fog.make_cast_jobs(out), torch.empty(fog.quantize_jit_batch_workspace(len(out)), dtype=torch.uint8, device="cuda"))
+            if len(parts) == 1:
+                assert torch.equal(out[0][2], q) and torch.equal(out[0][3], am) and torch.equal(out[0][4], sc) and torch.equal(out[0][5], si)
+                q1 = torch.empty_like(q)
+                fog.quantize_jit(x, fp8.E4M3, am, sc, si, torch.empty(fog.quantize_jit_workspace(), dtype=torch.uint8, device="cuda"), q=q1)
+                assert torch.equal(q1, q) and torch.equal(out[0][3], am) and torch.equal(out[0][4], sc) and torch.equal(out[0][5], si)
+            else:
+                for p, _, qp, a, s, _ in out:
+                    assert a.item() == p.abs().max().item()
+                    r = torch.empty_like(qp)
+                    fog.quantize(p, fp8.E4M3, s, q=r)
+                    assert torch.equal(r, qp)
+
+
+def test_one_launch_casts_on_two_streams_at_once():
+    """Two launches of one workgroup per compute unit each, which share the chip in whatever way they are dealt out: none waits for workgroups
+    that cannot start, and each has its own results."""
+    jobs, want, streams = [], [], [torch.cuda.Stream(), torch.cuda.Stream()]
+    for i in range(2):
+        x = torch.randn((2 ** 21 + 5, 16), device="cuda").mul_(i + 1.0).to(torch.bfloat16)
+        am, sc, si = (torch.zeros(1, device="cuda") for _ in range(3))
+        q = torch.empty(x.shape, dtype=torch.uint8, device="cuda")
+        fog.amax(x.view(-1), am)
+        fog.scale(am, fp8.E4M3, sc, si)
+        fog.quantize(x, fp8.E4M3, sc, q=q)
+        want.append((q, am, sc, si))
+        jobs.append((x, fp8.E4M3, torch.empty_like(q), *(torch.zeros(1, device="cuda") for _ in range(3))))
+    arr = [fog.make_cast_jobs([j]) for j in jobs]
+    ws = [torch.empty(fog.quantize_jit_batch_workspace(1), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for i, s in enumerate(streams):
+            fog.quantize_jit_batch(arr[i], ws[i], stream=s)
+    torch.cuda.synchronize()
+    for j, w in zip(jobs, want):
+        assert all(torch.equal(a, b) for a, b in zip(j[2:], w))
