@@ -119,6 +119,14 @@ fog_status fog_probe_gemm_plan(fog_layout layout, int64_t M, int64_t N, int64_t 
  */
 fog_status fog_probe_quantize_held(const fog_cast_job* jobs, int count, void* workspace, size_t workspace_bytes, int64_t patience, void* stream);
 
+/*
+ * The same of fog_quantize_jit with a transposed copy: rows and cols positive multiples of 16 (2^30 elements in all at most), strides and
+ * addresses multiples of 16, ldx at most 2^20.   Errors: as fog_quantize_jit; ALIGN and SHAPE for what the form does not take, SHAPE for a negative patience.
+ */
+fog_status fog_probe_quantize_held_transpose(const void* x_bf16, int64_t rows, int64_t cols, int64_t ldx, fog_fp8 fmt, int margin,
+                                             uint8_t* q, int64_t ldq, uint8_t* qT, int64_t ldqT, float* amax, float* scale, float* scale_inv,
+                                             void* workspace, size_t workspace_bytes, int64_t patience, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -60,6 +60,7 @@ PROBE_SIGNATURES = {
     "fog_probe_mfma_coissue": (_I, [_I, _I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _P]),
     "fog_probe_mfma_cross_wave": (_I, [_I, _I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _c.POINTER(_c.c_double), _P]),
     "fog_probe_quantize_held": (_I, [_P, _I, _P, _SZ, _I64, _P]),
+    "fog_probe_quantize_held_transpose": (_I, [_P, _I64, _I64, _I64, _I, _I, _P, _I64, _P, _I64, _P, _P, _P, _P, _SZ, _I64, _P]),
     "fog_probe_gemm_plan": (_I, [_I, _I64, _I64, _I64, _I, _I] + [_c.POINTER(_I)] * 5),
     "fog_probe_gemm_products_only": (_I, [_I64, _I64, _I64, _P, _I64, _P, _I64, _P, _P, _P, _I64, _P]),
 }
@@ -333,6 +334,16 @@ def probe_quantize_held(jobs, workspace, patience, stream=None):
     """quantize_jit_batch in its one-launch form whatever the sizes (fog_probe.h)."""
     _check(load().fog_probe_quantize_held(ctypes.cast(jobs, _P), len(jobs), _ptr(workspace), workspace.numel() * workspace.element_size(),
                                           patience, _stream(stream)), "fog_probe_quantize_held")
+
+
+def probe_quantize_held_transpose(x, fmt, amax_out, scale_out, scale_inv_out, workspace, patience, qT, q=None, margin=0, stream=None):
+    """quantize_jit with a transposed copy in its one-launch form whatever the sizes (fog_probe.h)."""
+    rows, cols = x.shape
+    _check(load().fog_probe_quantize_held_transpose(_ptr(x), rows, cols, x.stride(0), fmt, margin,
+                                                    _ptr(q), q.stride(0) if q is not None else 0, _ptr(qT), qT.stride(0),
+                                                    _ptr(amax_out), _ptr(scale_out), _ptr(scale_inv_out),
+                                                    _ptr(workspace), workspace.numel() * workspace.element_size(), patience, _stream(stream)),
+           "fog_probe_quantize_held_transpose")
 
 
 def probe_gemm_plan(layout, M, N, K, with_workspace=False, compute_units=0):

@@ -618,6 +618,35 @@ def test_one_launch_cast_of_special_values(special, margin):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
 
 
+@pytest.mark.parametrize("patience", [5000, 0])
+@pytest.mark.parametrize("rows,cols,pad", [(16, 16, 0), (128, 128, 16), (144, 272, 0), (2064, 2032, 48), (4096, 2064, 0), (5104, 8176, 16), (8208, 9232, 0)])
+def test_one_launch_transposing_cast_equals_the_separate_calls(rows, cols, pad, patience):
+    """One tile, partly filled tiles at both edges, a few tiles a workgroup, the last workgroup with fewer, ten a workgroup, some more than stay in
+    registers; rows apart in all three tensors; without a row-major copy; infinities and a margin that saturates, through the clamp; and with no patience the tiles read again."""
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    whole = torch.randn((rows, cols + pad), device="cuda", generator=g).to(torch.bfloat16)
+    if pad:
+        whole[:, cols:] = 3.0e38                                    # not part of the tensor
+    x = whole[:, :cols]
+    ws = torch.randint(0, 256, (fog.quantize_jit_workspace(),), dtype=torch.uint8, device="cuda", generator=g)
+    for fmt, margin, peak, with_q in ((fp8.E4M3, 0, -77.0, True), (fp8.E5M2, 0, 33.0, False), (fp8.E5M2, -2, 9.0, True), (fp8.E4M3, 0, float("inf"), True)):
+        x[rows // 2, cols - 1] = peak
+        x[rows - 1, cols // 3] = 8.0
+        am, sc, si, am2, sc2, si2 = (torch.full((1,), -1.0, device="cuda") for _ in range(6))
+        q, q2 = (torch.full((rows, cols + pad), 0xAA, dtype=torch.uint8, device="cuda") for _ in range(2))
+        qT, qT2 = (torch.full((cols, rows + pad), 0xAA, dtype=torch.uint8, device="cuda") for _ in range(2))
+        fog.amax(x.contiguous().view(-1), am)
+        fog.scale(am, fmt, sc, si, margin=margin)
+        fog.quantize(x, fmt, sc, q=q[:, :cols] if with_q else None, qT=qT[:, :rows])
+        fog.probe_quantize_held_transpose(x, fmt, am2, sc2, si2, ws, patience, qT2[:, :rows], q=q2[:, :cols] if with_q else None, margin=margin)
+        for a, b in ((q, q2), (qT, qT2), (am, am2), (sc, sc2), (si, si2)):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+        if rows * cols >= (70 << 10) * torch.cuda.get_device_properties(0).multi_processor_count:
+            qT2.fill_(0xAA)
+            fog.quantize_jit(x, fmt, am2, sc2, si2, ws, q=q2[:, :cols] if with_q else None, qT=qT2[:, :rows], margin=margin)
+            assert torch.equal(qT, qT2) and torch.equal(q, q2)
+
+
 def test_large_casts_take_the_one_launch_form_with_the_same_results():
     """The public calls around the size from which they read a tensor once (70 K elements a compute unit), one tensor and several."""
     per_cu = (70 << 10) * torch.cuda.get_device_properties(0).multi_processor_count // 16
