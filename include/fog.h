@@ -118,7 +118,7 @@ fog_status fog_quantize(const void* x_bf16, int64_t rows, int64_t cols, int64_t 
  * its maximum in its own word of the workspace; every workgroup of the cast pass, which follows on
  * the same stream, reduces those words (4 KB at most) and derives the scale itself, and the first
  * one publishes abs-max, scale and 1/scale.  Tensors of 18 to 160 M elements (without a transposed
- * copy: contiguous ones) are read once, but for what exceeds 42 to 46 M: one launch takes the abs-max, exchanges the workgroups' maxima through the
+ * copy: contiguous ones) are read once, but for what exceeds 42 to 44 M: one launch takes the abs-max, exchanges the workgroups' maxima through the
  * workspace and casts what it has kept in registers.
  *   amax, scale : one float each, overwritten.   scale_inv : one float or NULL.
  *   q, qT, x_bf16, leading dimensions, fmt : as in fog_quantize.   margin : as in fog_scale.

@@ -407,8 +407,8 @@ __global__ __launch_bounds__(kThreads) void quantize_batch_kernel(BatchJobs b, c
 
 // ---------------------------------------------------------------- abs-max and cast in one launch
 // Two passes read every tensor twice over the fabric (neither L2, invalid at a kernel's start, nor the memory-side cache, which is no faster,
-// helps the second), 5 bytes an element in all where 3 have to move.  Here one workgroup per compute unit reads its share once, keeps 22 x 512 chunks
-// of 16 elements of it in registers (46 M elements on the chip), leaves its maximum in a word of the workspace, gathers those
+// helps the second), 5 bytes an element in all where 3 have to move.  Here one workgroup per compute unit reads its share once, keeps 21 x 512 chunks
+// of 16 elements of it in registers (44 M elements on the chip), leaves its maximum in a word of the workspace, gathers those
 // of the tensor's other workgroups and casts what it holds; of a larger share the rest is read twice, as before.  A small launch in front clears the words.
 // No workgroup depends on another one being resident: a word that stays empty for `patience` is claimed by a waiting workgroup, which takes that share's
 // maximum itself (whoever is late publishes the same value), so every wait ends by the work of workgroups that are running.
@@ -422,8 +422,8 @@ __global__ __launch_bounds__(256) void clear_maxima_kernel(HeldJobs h, uint32_t*
   const int j = blockIdx.x, n = h.first[j + 1] - h.first[j];
   for (int i = threadIdx.x; i < n; i += 256) ws[j * kJitSlots + i] = 0u;
 }
-// Raw buffer over a workgroup's share: loads past its end return zeros and stores there are dropped, so the unrolled code below needs few branches
-// (the compiler waits for everything in flight behind one).  The bounds check covers the vector offset, not the scalar one, which stays 0.
+// Raw buffer over a workgroup's share: loads past its end return zeros, so the unrolled code below needs few branches (the compiler waits for
+// everything in flight behind one that holds loads).  The bounds check covers the vector offset, not the scalar one, which stays 0.
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 FOG_DEVICE __amdgpu_buffer_rsrc_t span(const void* base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
@@ -489,7 +489,8 @@ FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, int64_t patience, 
   auto begin = [&](int i) { return per * i < chunks ? per * i : chunks; };
   const int64_t c0 = begin(bid);
   const int mine = (int)(begin(bid + 1) - c0);                           // chunks of this workgroup's share
-  const auto src = span(b.x[j] + c0 * 16, (int64_t)mine * 32), dst = span(b.q[j] + c0 * 16, (int64_t)mine * 16);
+  const auto src = span(b.x[j] + c0 * 16, (int64_t)mine * 32);
+  uint8_t* dst = b.q[j] + c0 * 16;
   uint32_t m[4] = {0, 0, 0, 0};
   auto take = [&](const v4u* a) __attribute__((always_inline)) {
 #pragma unroll
@@ -543,8 +544,7 @@ FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, int64_t patience, 
     if (b.scale_inv[j]) *b.scale_inv[j] = inv;
   }
   auto put = [&](int c, uint2 lo, uint2 hi) __attribute__((always_inline)) {
-    const v4u o = {lo.x, lo.y, hi.x, hi.y};
-    __builtin_amdgcn_raw_buffer_store_b128(o, dst, (c + tid) * 16, 0, 16);   // written through
+    if (c + tid < mine) st_through16(dst + (int64_t)(c + tid) * 16, make_uint4(lo.x, lo.y, hi.x, hi.y));
   };
   if (!helped && r < 0x7F80u && a * rho <= (FMT == FOG_E4M3 ? 449.0f : 57400.0f)) {
     // Finite values that fit: up to a rounding above the format's maximum, which the convert takes back (it overflows from half a step above, 464 and 61440).
