@@ -24,7 +24,8 @@ UNIT_COUNTERS = ("TCP_TCC_READ_REQ_sum TCP_TOTAL_CACHE_ACCESSES_sum TCP_PENDING_
                  "TA_TA_BUSY_sum TA_BUFFER_TOTAL_CYCLES_sum SQ_VALU_MFMA_BUSY_CYCLES SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_ACTIVE_INST_VALU "
                  "SQ_BUSY_CYCLES GRBM_GUI_ACTIVE")
 GEMMS = ("fp8_gemm_kernel", "fp8_gemm_tile_kernel")   # a product is one launch of either (a split one also runs gemm_tile_reduce_kernel)
-KERNELS = GEMMS + ("gemm_tile_reduce_kernel", "amax_batch_kernel", "quantize_batch_kernel", "amax_kernel", "quantize_transpose_kernel",
+KERNELS = GEMMS + ("gemm_tile_reduce_kernel", "amax_batch_kernel", "quantize_batch_kernel", "quantize_held_kernel",
+           "quantize_held_transpose_kernel", "clear_maxima_kernel", "amax_kernel", "quantize_transpose_kernel",
            "quantize_rows_kernel", "attn_fwd_kernel", "attn_bwd_dkdv_kernel", "attn_bwd_dq_kernel", "kurtosis_kernel",
            "qknorm_rows_kernel", "copyBuffer")
 TRAFFIC_LINE = re.compile(r"= ([0-9.]+e[+-]?[0-9]+) bytes per launch")
