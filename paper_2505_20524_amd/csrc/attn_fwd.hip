@@ -180,10 +180,11 @@ __global__ __launch_bounds__(kThreads, AHEAD ? 2 : 3) void attn_fwd_kernel(FwdAr
     for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
   // The row reference of the block in hand, and the one that O and l are kept in.  A block's probabilities enter O with the factor 2^(m_run - m_acc),
   // which the matrix instruction takes as the E8M0 scale of its operand, and l with the same factor; only a reference that has grown by more than
-  // kLag makes O move.  Powers of two: the same bits as moving O along with the reference.  Moving O takes 64 multiplications, a third of a
-  // block's vector instructions, and one of a wave's 32 rows asks for it in every second block of a 4096-key walk: with the loads' uniform offset in a scalar
-  // register as well (8 additions less), 1 x 32/8 heads x 8192 causal 339 -> 326 us with its producers, forward of 2 x 32 x 4096 166 -> 156 us,
-  // 4 x 16 x 2048 50.3 -> 46.0.
+  // kLag makes O move.  Powers of two: the same bits as moving O along with the reference (but for a quotient at the end that needs care).  Moving O takes
+  // 64 multiplications, a third of a block's vector instructions, and one of a wave's 32 rows asks for it in every second block of a 4096-key walk: with
+  // the loads' uniform offset in a scalar register as well (8 additions less), 1 x 32/8 heads x 8192 causal 339 -> 326 us with its producers, forward of
+  // 2 x 32 x 4096 166 -> 156 us, 4 x 16 x 2048 50.3 -> 46.0.  One without the other, us, neither / scalar offsets / lag / both: 4 x 16 x 2048 50.8 / 49.8 /
+  // 45.9 / 45.5, 2 x 32 x 4096 168.7 / 163.3 / 153.2 / 153.1, 1 x 32/8 x 8192 300 / 292 / 285 / 283.
   float m_run = -INFINITY;    // integer-valued row reference (log2 domain)
   float m_acc = -INFINITY;
   int e_blk = 127;            // 127 + m_run - m_acc, and the float 2^(m_run - m_acc)
@@ -375,11 +376,22 @@ __global__ __launch_bounds__(kThreads, AHEAD ? 2 : 3) void attn_fwd_kernel(FwdAr
   __syncthreads();                     // ... of any wave: the ring becomes the staging area
   if (!wave_on) return;
   // ---- epilogue: O = sinv_v O^T / (rho_p l);  lse = m + log2 l  (l_run holds rho_p l, split over two lanes)
-  const float l_acc = l_run + lane_xor32(l_run);
-  const float scale_o = (*a.sinv_v) / l_acc;
+  const float l_row = l_run + lane_xor32(l_run);
+  float scale_o = (*a.sinv_v) / l_row;
+  // 2^(m_acc - m_run), exact; from e_blk, because the difference has no value where both references are infinite
+  const float back = __int_as_float((254 - e_blk) << 23);
+  // Relative to an older reference l is up to 2^kLag too large, and the quotient leaves binary32's normal range for a V that is well inside it (abs-max
+  // of 1e-28): such a wave takes O and l to the rows' own references first.  The same bits either way where both are in range.
+  if (__any(scale_o < 0x1p-126f)) {
+    scale_o = (*a.sinv_v) / (l_row * back);
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[d][r] *= back;
+  }
   // O as whole lines past the caches: 1 x 32/8 heads x 8192 causal 348 -> 343 us, 4 x 16 x 2048 53 -> 48 us
   store_tile_rows<4>(smem + w * (32 * 272), o, scale_o, a.O + ((int64_t)bh * S + q0) * HD, HD, [](int row) { return row; });
-  if (g == 0) a.lse[(int64_t)bh * S + q] = m_run + (__log2f(l_acc * exp2f(m_acc - m_run)) - lg_rho_p);
+  if (g == 0) a.lse[(int64_t)bh * S + q] = m_run + (__log2f(l_row * back) - lg_rho_p);
   if (a.amax_p) {
     float rm = fmaxf(raw_max, lane_xor32(raw_max));
     float pm = exp2f(rm * c - m_run);                 // largest p of this row, in (1/2, 1]

@@ -640,19 +640,23 @@ def test_backward_in_parts(B, H, Hkv, S, causal):
 
 
 @pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("S", [320, 576, 704])
 @pytest.mark.parametrize("steps", [(1, 2, 3, 5, 6), (0, 14, 16, 30, 32), (0, 16, 18, 64, 72), (0, 32, 128, 256, 448), (448, 128, 32, 1, 0)])
-def test_forward_with_growing_row_references(steps, causal):
+def test_forward_with_growing_row_references(steps, S, causal):
     """O stays relative to an earlier row reference until the reference has grown by more than 32.  Integer logits (as above) that grow from key
     block to key block: by little, to 32 and 64 (rows of q = 1 and 2 share a wave, so one moves O and the other has to follow), by more than
-    32 at every block, and not at all."""
-    H, S = 2, 320
+    32 at every block, and not at all.  S = 320 takes a block in one go, the longer ones its scores a block ahead and P V a block behind: there the
+    first has the bytes it has among many copies.  A V of 2^-93 times the size gives exactly 2^-93 times the O: nothing on the way
+    leaves binary32's range."""
+    H = 2
     rng = np.random.default_rng(sum(steps))
     Q8 = np.zeros((1, H, S, 128), np.uint8)
     one, two = int(fp8.encode_sat(np.float32(1.0), fp8.E4M3)), int(fp8.encode_sat(np.float32(2.0), fp8.E4M3))
     for h in range(H):
         for i in range(S):
             Q8[0, h, i, i % 128] = one if rng.random() < 0.5 else two
-    k = np.repeat(np.array(steps, np.float32), 64)[None, None, :, None] - rng.integers(0, 3, size=(1, H, S, 128)).astype(np.float32)
+    of_block = np.rint(np.interp(np.linspace(0, 4, S // 64), np.arange(5), steps)).astype(np.float32)
+    k = np.repeat(of_block, 64)[None, None, :, None] - rng.integers(0, 3, size=(1, H, S, 128)).astype(np.float32)
     K8 = fp8.encode_sat(k, fp8.E4M3)                       # integers on the E4M3 grid
     _, _, v, _ = synth.small_attention(97, 1, H, S)
     rho_v, vinv = scaling.compute_scale(scaling.amax(v), fp8.E4M3)
@@ -665,6 +669,12 @@ def test_forward_with_growing_row_references(steps, causal):
         check_bf16(O[0, h], Or, what="O, growing references", max_flip_frac=0.1)
         # s is ln 2 in binary32 (2^-25 relative) and so is its product with log2 e: at 896 the logits are 1e-4 off integers
         assert np.all(np.abs(lse[0, h] - lr) <= 2e-5 + 2.0 ** -22 * np.abs(lr))
+    Os, lses, _ = gpu_fwd({**c, "v": (V8, np.ldexp(vinv, -93))}, 1, H, S, s, causal)
+    assert np.array_equal(bf16.bits_to_f64(Os), np.ldexp(bf16.bits_to_f64(O), -93)) and np.array_equal(lses, lse)
+    if S > 320:
+        many = {n: (np.tile(x, (1, 150, 1, 1)), inv) for n, (x, inv) in c.items()}
+        Om, lm, am_many = gpu_fwd(many, 1, 150 * H, S, s, causal)
+        assert np.array_equal(Om, np.tile(O, (1, 150, 1, 1))) and np.array_equal(lm, np.tile(lse, (1, 150, 1))) and am_many == am
 
 
 @pytest.mark.parametrize("causal", [True, False])
