@@ -112,20 +112,20 @@ fog_status fog_probe_gemm_plan(fog_layout layout, int64_t M, int64_t N, int64_t 
 
 /*
  * fog_quantize_jit_batch in its one-launch form whatever the sizes (2^30 elements in all at most).  For tests, of its edges and of what
- * a workgroup does when another one's maximum is late:
- *   patience : ticks of 10 ns before a waiting workgroup claims a share whose maximum is missing; 0 makes every workgroup claim
- *              what it does not find at once.
- * Errors: as fog_quantize_jit_batch; SHAPE for a negative patience or more elements.
+ * workgroups do when others do not start:
+ *   absent : that many of every absent + 1 workgroups of a tensor end without having begun, and the others have to take their shares.
+ * Errors: as fog_quantize_jit_batch; SHAPE for absent outside 0..65535 or more elements.
  */
-fog_status fog_probe_quantize_held(const fog_cast_job* jobs, int count, void* workspace, size_t workspace_bytes, int64_t patience, void* stream);
+fog_status fog_probe_quantize_held(const fog_cast_job* jobs, int count, void* workspace, size_t workspace_bytes, int64_t absent, void* stream);
 
 /*
  * The same of fog_quantize_jit with a transposed copy: rows and cols positive multiples of 16 (2^30 elements in all at most), strides and
- * addresses multiples of 16, ldx at most 2^20.   Errors: as fog_quantize_jit; ALIGN and SHAPE for what the form does not take, SHAPE for a negative patience.
+ * addresses multiples of 16, ldx at most 2^20.   Errors: as fog_quantize_jit; ALIGN and SHAPE for what the form does not take, SHAPE for absent
+ * outside 0..65535.
  */
 fog_status fog_probe_quantize_held_transpose(const void* x_bf16, int64_t rows, int64_t cols, int64_t ldx, fog_fp8 fmt, int margin,
                                              uint8_t* q, int64_t ldq, uint8_t* qT, int64_t ldqT, float* amax, float* scale, float* scale_inv,
-                                             void* workspace, size_t workspace_bytes, int64_t patience, void* stream);
+                                             void* workspace, size_t workspace_bytes, int64_t absent, void* stream);
 
 #ifdef __cplusplus
 }

@@ -410,13 +410,18 @@ __global__ __launch_bounds__(kThreads) void quantize_batch_kernel(BatchJobs b, c
 // helps the second), 5 bytes an element in all where 3 have to move.  Here one workgroup per compute unit reads its share once, keeps 21 x 512 chunks
 // of 16 elements of it in registers (44 M elements on the chip), leaves its maximum in a word of the workspace, gathers those
 // of the tensor's other workgroups and casts what it holds; of a larger share the rest is read twice, as before.  A small launch in front clears the words.
-// No workgroup depends on another one being resident: a word that stays empty for `patience` is claimed by a waiting workgroup, which takes that share's
-// maximum itself (whoever is late publishes the same value), so every wait ends by the work of workgroups that are running.
+// No workgroup depends on another one being resident, because beside another stream's kernel not all of them are (each fills the registers of a CU): a
+// workgroup takes its share with its first instruction, and one that has its own maximum and finds shares that nobody has taken takes them too,
+// one after the other, and casts them behind its own; a workgroup that starts later and finds its share gone ends.  So every word belongs to a
+// workgroup that is running, and all waits end.  Beside attention forwards of 0 / 16 / 64 / 192 workgroups on another stream, us, two passes: 20 M elements
+// 21 / 26 / 26 / 25, 67 M in four tensors 63 / 64 / 65 / 69, 134 M 124 / 125 / 127 / 131; this: 20 / 34 / 34 / 44, 50 / 56-60 / 63 / 85, 116 / 120 / 138 / 151 (with a
+// wait of 50 us before shares were taken, all workgroups asking for the same one and what a workgroup held given up for it: 19 / 39 / 175 / 105, 50 / 57 / 63 / 85,
+// 117 / 120 / 137 / 151).  Workgroups of 256 threads, two a CU, of which one fits beside a foreign one: 5 us more at every size, for 512 words to gather.
 constexpr int kHeldThreads = 512, kHeldRegs = 21;
-constexpr uint32_t kMaxIsIn = 0x80000000u, kMaxIsClaimed = 0x40000000u;
+constexpr uint32_t kMaxIsIn = 0x80000000u, kShareIsTaken = 0x40000000u;
 struct HeldJobs {
   int first[kBatchMax + 1];   // first workgroup of each job
-  int64_t patience;           // ticks of 10 ns
+  int absent;                 // for tests: that many of every absent + 1 workgroups end without having begun
 };
 __global__ __launch_bounds__(256) void clear_maxima_kernel(HeldJobs h, uint32_t* __restrict__ ws) {
   const int j = blockIdx.x, n = h.first[j + 1] - h.first[j];
@@ -429,7 +434,8 @@ FOG_DEVICE __amdgpu_buffer_rsrc_t span(const void* base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 struct HeldShared {
-  uint32_t part[kHeldThreads / 64], open_word;
+  uint32_t part[kHeldThreads / 64], word;
+  uint16_t extra[kHeldThreads];   // shares taken besides the workgroup's own
 };
 // Maximum over a workgroup's threads of packed pairs.
 FOG_DEVICE uint32_t held_block_max(HeldShared& sh, uint32_t packed) {
@@ -442,45 +448,61 @@ FOG_DEVICE uint32_t held_block_max(HeldShared& sh, uint32_t packed) {
   for (int w = 1; w < kHeldThreads / 64; ++w) r = r > sh.part[w] ? r : sh.part[w];
   return r;
 }
-// Leaves `own`, the maximum of this workgroup's share, in its word and returns that of all `nb` (at most a word for each thread).  share_max(i) is
-// the maximum of share i; a workgroup that has had to call it (*helped) has lost what it held.
+// Takes share i if nobody has: zero, in thread 0, where it was free.
+FOG_DEVICE uint32_t take_share(uint32_t* words, int i) {
+  uint32_t before = 0u;
+  if (threadIdx.x == 0) before = atomicCAS(words + i, 0u, kShareIsTaken);
+  return before;
+}
+// Leaves `own`, the maximum of this workgroup's share, in its word, takes shares that nobody has, and returns the maximum of all `nb` (at most a word for
+// each thread).  share_max(i) is the maximum of share i; the *extra shares taken stand in sh.extra.
 template <typename F>
-FOG_DEVICE uint32_t gather_maxima(HeldShared& sh, uint32_t* __restrict__ words, int bid, int nb, int64_t patience, uint32_t own, bool* helped, F share_max) {
+FOG_DEVICE uint32_t gather_maxima(HeldShared& sh, uint32_t* __restrict__ words, int bid, int nb, uint32_t own, int* extra, F share_max) {
   const int tid = threadIdx.x;
+  *extra = 0;
   if (tid == 0) __hip_atomic_store(words + bid, kMaxIsIn | own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int64_t t0 = wall_clock64();
-  *helped = false;
   for (;;) {
     const uint32_t w = tid < nb ? __hip_atomic_load(words + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kMaxIsIn;
     if (__syncthreads_and(w & kMaxIsIn)) return held_block_max(sh, w & 0x7FFFu);
-    if (!__syncthreads_or(wall_clock64() - t0 >= patience)) {   // (the workgroup's decision: its waves read the clock at different times)
+    if (!__syncthreads_or(w == 0u)) {   // all shares have a workgroup
       __builtin_amdgcn_s_sleep(1);
       continue;
     }
-    // the first empty word from this workgroup's own on, if it is still empty
-    if (tid == 0) sh.open_word = 0xFFFFFFFFu;
+    // One of the shares that have none, if it still has none: number bid of them, so that the workgroups ask for different ones (all asking for
+    // the same one queue up at its word: 100 us for 64 shares).
+    const uint64_t free = __ballot(w == 0u);
+    if ((tid & 63) == 0) sh.part[tid >> 6] = (uint32_t)__popcll(free);
     __syncthreads();
-    if (w == 0u) atomicMin(&sh.open_word, (uint32_t)(tid >= bid ? tid - bid : tid - bid + nb));
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int k = 0; k < kHeldThreads / 64; ++k) {
+      before += k < tid >> 6 ? sh.part[k] : 0u;
+      total += sh.part[k];
+    }
+    before += (uint32_t)__popcll(free & ((1ull << (tid & 63)) - 1u));
+    if (w == 0u && before == (uint32_t)bid % total) sh.word = (uint32_t)tid;
     __syncthreads();
-    const uint32_t at = sh.open_word;
-    __syncthreads();
-    if (at == 0xFFFFFFFFu) continue;
-    const int i = ((int)at + bid) % nb;
-    if (tid == 0) sh.open_word = atomicCAS(words + i, 0u, kMaxIsClaimed);
-    __syncthreads();
-    const bool claimed = sh.open_word == 0u;
-    __syncthreads();
-    if (claimed) {
+    const int i = (int)sh.word;
+    if (!__syncthreads_or(take_share(words, i) != 0u)) {
       const uint32_t r = share_max(i);
-      if (tid == 0) __hip_atomic_store(words + i, kMaxIsIn | r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      *helped = true;
+      if (tid == 0) {
+        __hip_atomic_store(words + i, kMaxIsIn | r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sh.extra[*extra] = (uint16_t)i;
+      }
+      ++*extra;
     }
   }
+}
+// Whether this workgroup is the one that has the first share.
+FOG_DEVICE bool publishes(const HeldShared& sh, int bid, int extra) {
+  for (int k = 0; k < extra; ++k)
+    if (sh.extra[k] == 0) return true;
+  return bid == 0;
 }
 struct Plain { static constexpr int value = 0; };
 struct Stream { static constexpr int value = 2; };   // non-temporal
 template <int FMT>
-FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, int64_t patience, uint32_t* __restrict__ words, int j, int bid, int nb) {
+FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, uint32_t* __restrict__ words, int j, int bid, int nb) {
   constexpr int STEP = kHeldThreads;                                     // chunks that the workgroup takes at a time
   constexpr int REGS = kHeldRegs * STEP;                                 // chunks of the share that stay in registers
   constexpr int NL = 8, GRP = 7;
@@ -489,8 +511,9 @@ FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, int64_t patience, 
   auto begin = [&](int i) { return per * i < chunks ? per * i : chunks; };
   const int64_t c0 = begin(bid);
   const int mine = (int)(begin(bid + 1) - c0);                           // chunks of this workgroup's share
-  const auto src = span(b.x[j] + c0 * 16, (int64_t)mine * 32);
-  uint8_t* dst = b.q[j] + c0 * 16;
+  const uint32_t before = take_share(words, bid);   // (the answer is waited for behind the loads)
+  auto source = [&](int i) { return span(b.x[j] + begin(i) * 16, (begin(i + 1) - begin(i)) * 32); };
+  const auto src = source(bid);
   uint32_t m[4] = {0, 0, 0, 0};
   auto take = [&](const v4u* a) __attribute__((always_inline)) {
 #pragma unroll
@@ -529,50 +552,55 @@ FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, int64_t patience, 
 #pragma unroll
       for (int i = g; i < g + GRP && i < kHeldRegs; ++i) take(v[i]);
     }
-  bool helped;
-  const uint32_t r = gather_maxima(sh, words, bid, nb, patience, block_max(), &helped, [&](int i) {
+  int extra;
+  if (tid == 0) sh.word = before;
+  const uint32_t own = block_max();
+  if (sh.word != 0u) return;   // taken while this workgroup could not start
+  const uint32_t r = gather_maxima(sh, words, bid, nb, own, &extra, [&](int i) {
     m[0] = m[1] = m[2] = m[3] = 0u;
-    walk(span(b.x[j] + begin(i) * 16, (begin(i + 1) - begin(i)) * 32), 0, (int)(begin(i + 1) - begin(i)));
+    walk(source(i), 0, (int)(begin(i + 1) - begin(i)));
     return block_max();
   });
   const float a = __uint_as_float(r << 16);
   float rho, inv;
   scale_from_amax(a, FMT, b.margin[j], &rho, &inv);
-  if (bid == 0 && tid == 0) {
+  if (tid == 0 && publishes(sh, bid, extra)) {
     *b.amax[j] = a;
     *b.scale[j] = rho;
     if (b.scale_inv[j]) *b.scale_inv[j] = inv;
   }
-  auto put = [&](int c, uint2 lo, uint2 hi) __attribute__((always_inline)) {
-    if (c + tid < mine) st_through16(dst + (int64_t)(c + tid) * 16, make_uint4(lo.x, lo.y, hi.x, hi.y));
+  auto put = [&](int64_t at, int c, int n, uint2 lo, uint2 hi) __attribute__((always_inline)) {
+    if (c + tid < n) st_through16(b.q[j] + (at + c + tid) * 16, make_uint4(lo.x, lo.y, hi.x, hi.y));
   };
-  if (!helped && r < 0x7F80u && a * rho <= (FMT == FOG_E4M3 ? 449.0f : 57400.0f)) {
-    // Finite values that fit: up to a rounding above the format's maximum, which the convert takes back (it overflows from half a step above, 464 and 61440).
-    auto cast = [&](v4u t) __attribute__((always_inline)) {
-      return make_uint2(cvt4_fp8_finite<FMT>(bf16lo(t[0]) * rho, bf16hi(t[0]) * rho, bf16lo(t[1]) * rho, bf16hi(t[1]) * rho),
-                        cvt4_fp8_finite<FMT>(bf16lo(t[2]) * rho, bf16hi(t[2]) * rho, bf16lo(t[3]) * rho, bf16hi(t[3]) * rho));
-    };
+  auto cast_all = [&](auto cast) __attribute__((always_inline)) {
 #pragma unroll
     for (int g = 0; g < kHeldRegs; g += GRP)
       if (g * STEP < mine) {
 #pragma unroll
-        for (int i = g; i < g + GRP && i < kHeldRegs; ++i) put(i * STEP, cast(v[i][0]), cast(v[i][1]));
+        for (int i = g; i < g + GRP && i < kHeldRegs; ++i) put(c0, i * STEP, mine, cast(v[i][0]), cast(v[i][1]));
       }
-    for (int c = REGS; c < mine; c += NL * STEP) {
-      v4u t[NL][2];
+    for (int e = -1; e < extra; ++e) {   // what is not held: of this share, and the others that were taken
+      const int i = e < 0 ? bid : sh.extra[e];
+      const auto from = source(i);
+      const int64_t at = begin(i);
+      const int n = (int)(begin(i + 1) - at);
+      for (int c = e < 0 ? REGS : 0; c < n; c += NL * STEP) {
+        v4u t[NL][2];
 #pragma unroll
-      for (int k = 0; k < NL; ++k) fetch(src, c + k * STEP, t[k], Plain{});
+        for (int k = 0; k < NL; ++k) fetch(from, c + k * STEP, t[k], Plain{});
 #pragma unroll
-      for (int k = 0; k < NL; ++k) put(c + k * STEP, cast(t[k][0]), cast(t[k][1]));
+        for (int k = 0; k < NL; ++k) put(at, c + k * STEP, n, cast(t[k][0]), cast(t[k][1]));
+      }
     }
-  } else {
-    auto cast = [&](v4u t) { return cast8<FMT>(make_uint4(t[0], t[1], t[2], t[3]), rho); };
-    for (int c = 0; c < mine; c += STEP) {
-      v4u t[2];
-      fetch(src, c, t, Plain{});
-      put(c, cast(t[0]), cast(t[1]));
-    }
-  }
+  };
+  // Finite values that fit: up to a rounding above the format's maximum, which the convert takes back (it overflows from half a step above, 464 and 61440).
+  if (r < 0x7F80u && a * rho <= (FMT == FOG_E4M3 ? 449.0f : 57400.0f))
+    cast_all([&](v4u t) __attribute__((always_inline)) {
+      return make_uint2(cvt4_fp8_finite<FMT>(bf16lo(t[0]) * rho, bf16hi(t[0]) * rho, bf16lo(t[1]) * rho, bf16hi(t[1]) * rho),
+                        cvt4_fp8_finite<FMT>(bf16lo(t[2]) * rho, bf16hi(t[2]) * rho, bf16lo(t[3]) * rho, bf16hi(t[3]) * rho));
+    });
+  else
+    cast_all([&](v4u t) __attribute__((always_inline)) { return cast8<FMT>(make_uint4(t[0], t[1], t[2], t[3]), rho); });
 }
 __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_kernel(BatchJobs b, HeldJobs h, uint32_t* __restrict__ ws) {
   __shared__ HeldShared sh;
@@ -580,8 +608,9 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_kernel(BatchJob
   for (int k = 1; k < b.count; ++k)
     if ((int)blockIdx.x >= h.first[k]) j = k;
   const int bid = (int)blockIdx.x - h.first[j], nb = h.first[j + 1] - h.first[j];
-  if (b.fmt[j] == FOG_E4M3) held_body<FOG_E4M3>(sh, b, h.patience, ws + j * kJitSlots, j, bid, nb);
-  else                      held_body<FOG_E5M2>(sh, b, h.patience, ws + j * kJitSlots, j, bid, nb);
+  if (h.absent && bid % (h.absent + 1) != 0) return;
+  if (b.fmt[j] == FOG_E4M3) held_body<FOG_E4M3>(sh, b, ws + j * kJitSlots, j, bid, nb);
+  else                      held_body<FOG_E5M2>(sh, b, ws + j * kJitSlots, j, bid, nb);
 }
 
 // ---------------------------------------------------------------- several tensors per launch (delayed scaling)
@@ -726,14 +755,15 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint
 // The same in one launch with the abs-max, bound by the bytes over the fabric as quantize_held_kernel is: a workgroup takes a run of tiles, keeps the
 // first kHeldTiles = 10 of them in registers (one unit of 4 rows x 8 columns a thread and tile, 160 registers; 42 M elements on the chip), reads those
 // beyond twice, and transposes one after the other through two LDS tiles in turn, one barrier each.  Loads go through raw buffers over the tile, so that
-// those of all ten are in flight at once.  Back to back, us, with the row-major copy / without, two passes -> this: 21 M elements 27.0 / 24.1 -> 21.4 /
+// those of all ten are in flight at once (their descriptors do not all fit the scalar registers: 44 wait in lanes of a vector register).  Back to back, us, with the row-major copy / without, two passes -> this: 21 M elements 27.0 / 24.1 -> 21.4 /
 // 19.8, 34 M 34.3 / 29.3 -> 28.0 / 24.4, 42 M 52.8 / 39.7 -> 32.5 / 27.5, 67 M 84.7 / 64.1 -> 76.4 / 60.7, 117 M 145.5 / 112.7 -> 116.7 / 93.1,
-// 151 M 182.5 / 140.8 -> 156.4 / 125.1.
+// 151 M 182.5 / 140.8 -> 156.4 / 125.1.  Beside attention forwards of 0 / 16 / 64 / 192 workgroups on another stream, two passes: 34 M 35 / 39 / 41 / 43, 117 M
+// 150 / 154 / 157 / 158; this: 28 / 46 / 53 / 67, 118 / 126 / 187 / 212.
 constexpr int kHeldTiles = 10;
 struct HeldTranspose {
   const uint16_t* x; uint8_t* q; uint8_t* qT;
-  int64_t rows, cols, ldx, ldq, ldqT, patience;
-  int tiles_c, tiles, margin;
+  int64_t rows, cols, ldx, ldq, ldqT;
+  int tiles_c, tiles, margin, absent;
   float* amax; float* scale; float* scale_inv;
 };
 template <int FMT>
@@ -744,6 +774,8 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_transpose_kerne
   const int per = (a.tiles + nb - 1) / nb;
   auto begin = [&](int i) { return per * i < a.tiles ? per * i : a.tiles; };
   const int t0 = begin(bid), mine = begin(bid + 1) - t0;
+  if (a.absent && bid % (a.absent + 1) != 0) return;
+  const uint32_t before = take_share(words, bid);   // (the answer is waited for behind the loads)
   uint32_t m = 0;
   auto take = [&](const uint4* u) __attribute__((always_inline)) {
 #pragma unroll
@@ -778,9 +810,11 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_transpose_kerne
 #pragma unroll
   for (int i = 0; i < kHeldTiles; ++i)
     take(v[i]);
-  bool helped;
+  int extra;
+  if (tid == 0) sh.word = before;
   const uint32_t own = held_block_max(sh, m);
-  const uint32_t r = gather_maxima(sh, words, bid, nb, a.patience, own, &helped, [&](int i) {
+  if (sh.word != 0u) return;   // taken while this workgroup could not start
+  const uint32_t r = gather_maxima(sh, words, bid, nb, own, &extra, [&](int i) {
     m = 0u;
     walk(begin(i), begin(i + 1));
     return held_block_max(sh, m);
@@ -788,16 +822,17 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_transpose_kerne
   const float am = __uint_as_float(r << 16);
   float rho, inv;
   scale_from_amax(am, FMT, a.margin, &rho, &inv);
-  if (bid == 0 && tid == 0) {
+  if (tid == 0 && publishes(sh, bid, extra)) {
     *a.amax = am;
     *a.scale = rho;
     if (a.scale_inv) *a.scale_inv = inv;
   }
   // codes of a unit -> q, and the tile through LDS -> qT (one barrier a tile: the other buffer has been read before it)
-  auto emit = [&](int i, const uint2* code) __attribute__((always_inline)) {
-    const int t = t0 + i;
+  int side = 0;
+  auto emit = [&](int t, const uint2* code) __attribute__((always_inline)) {
     const int64_t r0 = (int64_t)(t / a.tiles_c) * kTile, c0 = (int64_t)(t % a.tiles_c) * kTile;
-    uint8_t* tile = buf[i & 1];
+    uint8_t* tile = buf[side];
+    side ^= 1;
     if (a.q && r0 + 4 * rg < a.rows && c0 + 8 * cc < a.cols) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) st_through8(a.q + (r0 + 4 * rg + k) * a.ldq + c0 + 8 * cc, code[k]);
@@ -815,20 +850,21 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_transpose_kerne
         st_through16(a.qT + (c0 + col) * a.ldqT + r0 + ch * 16, *reinterpret_cast<const uint4*>(tile + col * kTile + ((ch ^ ((col >> 3) & 7)) * 16)));
     }
   };
-  auto again = [&](int from) __attribute__((always_inline)) {   // tiles that are not held
+  auto again = [&](int from, int to) __attribute__((always_inline)) {   // tiles that are not held
     uint4 u[4], next[4];
-    fetch(t0 + from, from < mine, u);
-    for (int i = from; i < mine; ++i) {
-      fetch(t0 + i + 1, i + 1 < mine, next);
+    fetch(from, from < to, u);
+    for (int t = from; t < to; ++t) {
+      fetch(t + 1, t + 1 < to, next);
       uint2 code[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) code[k] = cast8<FMT>(u[k], rho);
-      emit(i, code);
+      emit(t, code);
 #pragma unroll
       for (int k = 0; k < 4; ++k) u[k] = next[k];
     }
   };
-  if (!helped && r < 0x7F80u && am * rho <= (FMT == FOG_E4M3 ? 449.0f : 57400.0f)) {   // finite and within the format, as in held_body
+  int from = t0;
+  if (r < 0x7F80u && am * rho <= (FMT == FOG_E4M3 ? 449.0f : 57400.0f)) {   // finite and within the format, as in held_body
 #pragma unroll
     for (int i = 0; i < kHeldTiles; ++i)
       if (i < mine) {
@@ -839,12 +875,11 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_transpose_kerne
           code[k] = make_uint2(cvt4_fp8_finite<FMT>(bf16lo(u.x) * rho, bf16hi(u.x) * rho, bf16lo(u.y) * rho, bf16hi(u.y) * rho),
                                cvt4_fp8_finite<FMT>(bf16lo(u.z) * rho, bf16hi(u.z) * rho, bf16lo(u.w) * rho, bf16hi(u.w) * rho));
         }
-        emit(i, code);
+        emit(t0 + i, code);
       }
-    again(kHeldTiles);
-  } else {
-    again(0);
+    from = t0 + kHeldTiles;
   }
+  for (int k = -1; k < extra; ++k) again(k < 0 ? from : begin(sh.extra[k]), k < 0 ? t0 + mine : begin(sh.extra[k] + 1));
 }
 
 // ---------------------------------------------------------------- general shapes (slow, same results)
@@ -911,16 +946,16 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // passes' many workgroups are ahead.  Batches back to back, us, two passes -> one launch: 17 M elements 17.2 -> 18.3, 20 M 21.8 -> 19.4, 25 M 24.9
 // -> 21.7 (in two tensors 22.6 -> 22.3), 42 M in three 39.1 -> 28.7, 67 M in four 62.8 -> 51.4, 82 M 79.2 -> 69.5, 134 M 124 -> 117, 150 M 148.4 -> 133.7, 184 M
 // 172 -> 186.  (Four steps of the shares in LDS besides: a share of 32 steps 51.3 -> 50, all others up to 4 us slower, the registers spill.)
-constexpr int64_t kHeldFrom = 70 << 10, kHeldTo = 625 << 10, kHeldMost = (int64_t)1 << 30, kHeldPatience = 5000;   // elements a compute unit; ...; 50 us
+constexpr int64_t kHeldFrom = 70 << 10, kHeldTo = 625 << 10, kHeldMost = (int64_t)1 << 30;   // elements a compute unit, and in all
 constexpr int64_t kHeldStride = 1 << 20;   // of rows where it transposes: a tile's byte offsets stay below 2^31
 inline bool held_pays(int64_t n) {
   const int64_t cus = fog_compute_units();
   return cus <= kHeldThreads && n >= kHeldFrom * cus && n <= kHeldTo * cus;
 }
 // One workgroup per compute unit, dealt to the tensors by their sizes, at least one each.
-inline fog_status launch_held(const BatchJobs& b, int64_t total, int64_t patience, uint32_t* ws, hipStream_t s) {
+inline fog_status launch_held(const BatchJobs& b, int64_t total, uint32_t* ws, hipStream_t s, int absent = 0) {
   HeldJobs h;
-  h.patience = patience;
+  h.absent = absent;
   h.first[0] = 0;
   int room = fog_compute_units() < kHeldThreads ? fog_compute_units() : kHeldThreads;
   for (int j = 0; j < kBatchMax; ++j) {
@@ -1084,12 +1119,12 @@ extern "C" fog_status fog_quantize_jit(const void* x_bf16, int64_t rows, int64_t
     BatchJobs b{};
     b.count = 1;
     b.x[0] = x; b.n[0] = n; b.q[0] = q; b.fmt[0] = (int)fmt; b.margin[0] = margin; b.amax[0] = amax; b.scale[0] = scale; b.scale_inv[0] = scale_inv;
-    return launch_held(b, n, kHeldPatience, ws, s);
+    return launch_held(b, n, ws, s);
   }
   // The same sizes with a transposed copy: 16.8 M elements 18.7 us in two passes and 19.4 in one launch, 21 M 27.0 and 21.4; ahead at 151 M still
   // (the figures stand at quantize_held_transpose_kernel).
   if (n > 0 && transpose_fits(x, rows, cols, ldx, q, ldq, qT, ldqT) && ldx <= kHeldStride && held_pays(n))
-    return launch_held_transpose({x, q, qT, rows, cols, ldx, ldq, ldqT, kHeldPatience, 0, 0, margin, amax, scale, scale_inv}, (int)fmt, ws, s);
+    return launch_held_transpose({x, q, qT, rows, cols, ldx, ldq, ldqT, 0, 0, margin, 0, amax, scale, scale_inv}, (int)fmt, ws, s);
   int64_t blocks = 0;   // an empty tensor: no partial maxima, abs-max 0, scale 1
   if (n > 0) {
     if ((ldx == cols || rows == 1) && aligned16(x_bf16)) {
@@ -1199,7 +1234,7 @@ extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count
   if (st != FOG_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   uint32_t* ws = reinterpret_cast<uint32_t*>(workspace);
-  if (held_pays(total)) return launch_held(b, total, kHeldPatience, ws, s);
+  if (held_pays(total)) return launch_held(b, total, ws, s);
   b.cast_first[0] = 0;
   for (int p = 0; p < count; ++p) {   // launch position p casts job count - 1 - p
     const int64_t chunks = b.n[count - 1 - p] / 16;
@@ -1218,29 +1253,29 @@ extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count
   return fog_launch_status();
 }
 
-extern "C" fog_status fog_probe_quantize_held(const fog_cast_job* jobs, int count, void* workspace, size_t workspace_bytes, int64_t patience,
+extern "C" fog_status fog_probe_quantize_held(const fog_cast_job* jobs, int count, void* workspace, size_t workspace_bytes, int64_t absent,
                                               void* stream) {
   if (count == 0) return FOG_OK;
   BatchJobs b;
   int64_t total;
   const fog_status st = batch_jobs(jobs, count, workspace, workspace_bytes, b, &total);
   if (st != FOG_OK) return st;
-  if (patience < 0 || total > kHeldMost) return FOG_ERR_SHAPE;
-  return launch_held(b, total, patience, reinterpret_cast<uint32_t*>(workspace), (hipStream_t)stream);
+  if (absent < 0 || absent > 0xFFFF || total > kHeldMost) return FOG_ERR_SHAPE;
+  return launch_held(b, total, reinterpret_cast<uint32_t*>(workspace), (hipStream_t)stream, (int)absent);
 }
 
 extern "C" fog_status fog_probe_quantize_held_transpose(const void* x_bf16, int64_t rows, int64_t cols, int64_t ldx, fog_fp8 fmt, int margin,
                                                         uint8_t* q, int64_t ldq, uint8_t* qT, int64_t ldqT, float* amax, float* scale,
-                                                        float* scale_inv, void* workspace, size_t workspace_bytes, int64_t patience, void* stream) {
+                                                        float* scale_inv, void* workspace, size_t workspace_bytes, int64_t absent, void* stream) {
   if (!amax || !scale || !workspace || !qT) return FOG_ERR_NULL;
   if (workspace_bytes < fog_quantize_jit_workspace()) return FOG_ERR_WORKSPACE;
   if ((reinterpret_cast<uintptr_t>(workspace) & 3u) != 0) return FOG_ERR_ALIGN;
-  if (margin < -64 || margin > 64 || patience < 0 || rows < 1 || cols < 1) return FOG_ERR_SHAPE;
+  if (margin < -64 || margin > 64 || absent < 0 || absent > 0xFFFF || rows < 1 || cols < 1) return FOG_ERR_SHAPE;
   const fog_status st = quantize_checks(x_bf16, rows, cols, ldx, fmt, q, ldq, qT, ldqT);
   if (st != FOG_OK) return st;
   if (!transpose_fits(x_bf16, rows, cols, ldx, q, ldq, qT, ldqT)) return FOG_ERR_ALIGN;
   if (rows > kHeldMost / cols || ldx > kHeldStride) return FOG_ERR_SHAPE;
-  return launch_held_transpose({reinterpret_cast<const uint16_t*>(x_bf16), q, qT, rows, cols, ldx, ldq, ldqT, patience, 0, 0, margin, amax, scale, scale_inv},
+  return launch_held_transpose({reinterpret_cast<const uint16_t*>(x_bf16), q, qT, rows, cols, ldx, ldq, ldqT, 0, 0, margin, (int)absent, amax, scale, scale_inv},
                                (int)fmt, reinterpret_cast<uint32_t*>(workspace), (hipStream_t)stream);
 }
 

@@ -330,19 +330,19 @@ def probe_mfma_cross_wave(op, vector_ops, iters_matrix, iters_vector, sink, stre
     return cm.value, cv.value
 
 
-def probe_quantize_held(jobs, workspace, patience, stream=None):
+def probe_quantize_held(jobs, workspace, absent, stream=None):
     """quantize_jit_batch in its one-launch form whatever the sizes (fog_probe.h)."""
     _check(load().fog_probe_quantize_held(ctypes.cast(jobs, _P), len(jobs), _ptr(workspace), workspace.numel() * workspace.element_size(),
-                                          patience, _stream(stream)), "fog_probe_quantize_held")
+                                          absent, _stream(stream)), "fog_probe_quantize_held")
 
 
-def probe_quantize_held_transpose(x, fmt, amax_out, scale_out, scale_inv_out, workspace, patience, qT, q=None, margin=0, stream=None):
+def probe_quantize_held_transpose(x, fmt, amax_out, scale_out, scale_inv_out, workspace, absent, qT, q=None, margin=0, stream=None):
     """quantize_jit with a transposed copy in its one-launch form whatever the sizes (fog_probe.h)."""
     rows, cols = x.shape
     _check(load().fog_probe_quantize_held_transpose(_ptr(x), rows, cols, x.stride(0), fmt, margin,
                                                     _ptr(q), q.stride(0) if q is not None else 0, _ptr(qT), qT.stride(0),
                                                     _ptr(amax_out), _ptr(scale_out), _ptr(scale_inv_out),
-                                                    _ptr(workspace), workspace.numel() * workspace.element_size(), patience, _stream(stream)),
+                                                    _ptr(workspace), workspace.numel() * workspace.element_size(), absent, _stream(stream)),
            "fog_probe_quantize_held_transpose")
 
 

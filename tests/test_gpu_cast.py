@@ -564,13 +564,13 @@ def test_jit_forms_by_size(rows, cols, transpose):
     assert not transpose or torch.equal(qT, want.t())
 
 
-@pytest.mark.parametrize("patience", [0, 5000])
+@pytest.mark.parametrize("absent", [0, 1, 5000])
 @pytest.mark.parametrize("chunks", [[1], [1, 2, 1], [255], [257, 1], [512 * 256], [512 * 256 + 1, 3], [512 * 256 * 7 + 5], [512 * 200, 512 * 30 + 1] * 16,
                                     [512 * 256 * 21], [512 * 256 * 21 + 1, 17], [512 * 256 * 30 + 333]])
-def test_one_launch_cast_equals_the_separate_calls(chunks, patience):
+def test_one_launch_cast_equals_the_separate_calls(chunks, absent):
     """The cast whose workgroups keep their shares in registers and exchange their maxima: fewer chunks of 16 than workgroups (empty
-    shares), shares that end inside a step of 512 chunks and at its edge, the last step in registers, the first beyond, 32 tensors; and with no
-    patience every workgroup takes other workgroups' maxima itself and reads its own share again."""
+    shares), shares that end inside a step of 512 chunks and at its edge, the last step in registers, the first beyond, 32 tensors; and with
+    every second workgroup absent, or all but a tensor's first, the others take their shares."""
     g = torch.Generator(device="cuda").manual_seed(len(chunks) + chunks[0])
     jobs, want = [], []
     for i, c in enumerate(chunks):
@@ -590,14 +590,15 @@ def test_one_launch_cast_equals_the_separate_calls(chunks, patience):
     for _ in range(3):                                              # the words of the call before are no answer
         for job in jobs:
             job[2].fill_(0xAA)
-        fog.probe_quantize_held(arr, ws, patience)
+        fog.probe_quantize_held(arr, ws, absent)
         for job, w in zip(jobs, want):
             assert all(torch.equal(a, b) for a, b in zip(job[2:], w))
 
 
+@pytest.mark.parametrize("absent", [0, 2])
 @pytest.mark.parametrize("margin", [-3, 0, 2])
 @pytest.mark.parametrize("special", [None, float("inf"), float("nan"), 0.0, 2.0 ** -130, 3.3895e38])
-def test_one_launch_cast_of_special_values(special, margin):
+def test_one_launch_cast_of_special_values(special, margin, absent):
     """Infinities, NaNs, zeros, the smallest and largest magnitudes, and margins that saturate, through the path that skips the clamp for finite
     tensors and the one that does not, as the separate calls give them."""
     for fmt in (fp8.E4M3, fp8.E5M2):
@@ -613,16 +614,17 @@ def test_one_launch_cast_of_special_values(special, margin):
         fog.scale(am, fmt, sc, si, margin=margin)
         fog.quantize(x, fmt, sc, q=q)
         ws = torch.empty(fog.quantize_jit_batch_workspace(1), dtype=torch.uint8, device="cuda")
-        fog.probe_quantize_held(fog.make_cast_jobs([(x, fmt, q2, am2, sc2, si2)], margin=margin), ws, 5000)
+        fog.probe_quantize_held(fog.make_cast_jobs([(x, fmt, q2, am2, sc2, si2)], margin=margin), ws, absent)
         for a, b in ((q, q2), (am, am2), (sc, sc2), (si, si2)):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
 
 
-@pytest.mark.parametrize("patience", [5000, 0])
+@pytest.mark.parametrize("absent", [0, 1, 5000])
 @pytest.mark.parametrize("rows,cols,pad", [(16, 16, 0), (128, 128, 16), (144, 272, 0), (2064, 2032, 48), (4096, 2064, 0), (5104, 8176, 16), (8208, 9232, 0)])
-def test_one_launch_transposing_cast_equals_the_separate_calls(rows, cols, pad, patience):
+def test_one_launch_transposing_cast_equals_the_separate_calls(rows, cols, pad, absent):
     """One tile, partly filled tiles at both edges, a few tiles a workgroup, the last workgroup with fewer, ten a workgroup, some more than stay in
-    registers; rows apart in all three tensors; without a row-major copy; infinities and a margin that saturates, through the clamp; and with no patience the tiles read again."""
+    registers; rows apart in all three tensors; without a row-major copy; infinities and a margin that saturates, through the clamp; and with every second
+    workgroup absent, or all but the first."""
     g = torch.Generator(device="cuda").manual_seed(rows + cols)
     whole = torch.randn((rows, cols + pad), device="cuda", generator=g).to(torch.bfloat16)
     if pad:
@@ -638,7 +640,7 @@ def test_one_launch_transposing_cast_equals_the_separate_calls(rows, cols, pad, 
         fog.amax(x.contiguous().view(-1), am)
         fog.scale(am, fmt, sc, si, margin=margin)
         fog.quantize(x, fmt, sc, q=q[:, :cols] if with_q else None, qT=qT[:, :rows])
-        fog.probe_quantize_held_transpose(x, fmt, am2, sc2, si2, ws, patience, qT2[:, :rows], q=q2[:, :cols] if with_q else None, margin=margin)
+        fog.probe_quantize_held_transpose(x, fmt, am2, sc2, si2, ws, absent, qT2[:, :rows], q=q2[:, :cols] if with_q else None, margin=margin)
         for a, b in ((q, q2), (qT, qT2), (am, am2), (sc, sc2), (si, si2)):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
         if rows * cols >= (70 << 10) * torch.cuda.get_device_properties(0).multi_processor_count:
