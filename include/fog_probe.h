@@ -111,6 +111,14 @@ fog_status fog_probe_gemm_plan(fog_layout layout, int64_t M, int64_t N, int64_t 
                                int* tile_m, int* tile_n, int* workgroups_per_cu, int* splits, int* k_chunk);
 
 /*
+ * Whether fog_quantize_jit casts a dense, 16-byte aligned tensor of [rows, cols] in one launch that keeps it in registers, with a transposed copy or without
+ * (and fog_quantize_jit_batch tensors of rows * cols elements in all): host arithmetic only, no device is needed.  For tests, as fog_probe_gemm_plan.
+ *   compute_units : of the device in mind; 0 = the current device's (256 where there is none).   one_launch : HOST pointer, 0 or 1.
+ * Errors: NULL, SHAPE.
+ */
+fog_status fog_probe_cast_plan(int64_t rows, int64_t cols, int with_transpose, int compute_units, int* one_launch);
+
+/*
  * fog_quantize_jit_batch in its one-launch form whatever the sizes (2^30 elements in all at most).  For tests, of its edges and of what
  * workgroups do when others do not start:
  *   absent : that many of every absent + 1 workgroups of a tensor end without having begun, and the others have to take their shares.

@@ -948,8 +948,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // 172 -> 186.  (Four steps of the shares in LDS besides: a share of 32 steps 51.3 -> 50, all others up to 4 us slower, the registers spill.)
 constexpr int64_t kHeldFrom = 70 << 10, kHeldTo = 625 << 10, kHeldMost = (int64_t)1 << 30;   // elements a compute unit, and in all
 constexpr int64_t kHeldStride = 1 << 20;   // of rows where it transposes: a tile's byte offsets stay below 2^31
-inline bool held_pays(int64_t n) {
-  const int64_t cus = fog_compute_units();
+inline bool held_pays(int64_t n, int64_t cus) {
   return cus <= kHeldThreads && n >= kHeldFrom * cus && n <= kHeldTo * cus;
 }
 // One workgroup per compute unit, dealt to the tensors by their sizes, at least one each.
@@ -978,6 +977,17 @@ inline int64_t tiles_of(int64_t rows, int64_t cols) { return ((rows + kTile - 1)
 inline bool transpose_fits(const void* x, int64_t rows, int64_t cols, int64_t ldx, const void* q, int64_t ldq, const void* qT, int64_t ldqT) {
   return cols % 16 == 0 && rows % 16 == 0 && ldx % 16 == 0 && aligned16(x) && (!q || (ldq % 16 == 0 && aligned16(q))) && qT && ldqT % 16 == 0 &&
          aligned16(qT) && tiles_of(rows, cols) <= 0x7FFFFFFF;
+}
+// With a transposed copy a workgroup's time goes by tiles, filled or not (the two passes have a workgroup for each), so the same sizes (16.8 M elements 18.7
+// us in two passes and 19.4 in one launch, 21 M 27.0 and 21.4; ahead at 151 M still: the figures stand at quantize_held_transpose_kernel) only where all tiles
+// are held, eleven sixteenths of the tiles are tensor, or every workgroup's run has its part of full tiles, as in a tall tensor of more than a tile
+// column (and not in a wide one of more than a tile row).  With the row-major copy / without, us, two passes -> one launch: 16 columns 20 M 55 / 40 -> 87 / 78, 80 M 189 / 148 ->
+// 380 / 303; 64 columns (half filled) 20 M, held, 32 / 25 -> 23 / 22, but 41 M 56 / 39 -> 54 / 50, 77 M 101 / 76 -> 104 / 96; 80 (0.63) 80 M 123 / 85 -> 125 / 88;
+// 96 (0.75) 40 M 55 / 39 -> 41 / 36, 80 M 117 / 83 -> 114 / 79; 176 rows (0.69) 70 M 111 / 83 -> 103 / 77; 144 columns (0.56) 40 M 77 / 51 -> 56 / 48, 144 M
+// 271 / 178 -> 240 / 173; 144 rows 29 M 41 / 35 -> 39 / 36, 101 M 164 / 125 -> 192 / 152.
+inline bool held_transpose_pays(int64_t rows, int64_t cols, int64_t cus) {
+  const int64_t n = rows * cols, tiles = tiles_of(rows, cols);
+  return held_pays(n, cus) && (tiles <= kHeldTiles * cus || (rows > cols && cols > kTile) || 16 * n >= 11 * tiles * kTile * kTile);
 }
 inline fog_status launch_held_transpose(HeldTranspose a, int fmt, uint32_t* ws, hipStream_t s) {
   const int cus = fog_compute_units() < kHeldThreads ? fog_compute_units() : kHeldThreads;
@@ -1115,15 +1125,13 @@ extern "C" fog_status fog_quantize_jit(const void* x_bf16, int64_t rows, int64_t
   const uint16_t* x = reinterpret_cast<const uint16_t*>(x_bf16);
   uint32_t* ws = reinterpret_cast<uint32_t*>(workspace);
   const int64_t n = rows * cols;
-  if (!qT && (rows == 1 || (ldx == cols && ldq == cols)) && n % 16 == 0 && aligned16(x_bf16) && aligned16(q) && held_pays(n)) {
+  if (!qT && (rows == 1 || (ldx == cols && ldq == cols)) && n % 16 == 0 && aligned16(x_bf16) && aligned16(q) && held_pays(n, fog_compute_units())) {
     BatchJobs b{};
     b.count = 1;
     b.x[0] = x; b.n[0] = n; b.q[0] = q; b.fmt[0] = (int)fmt; b.margin[0] = margin; b.amax[0] = amax; b.scale[0] = scale; b.scale_inv[0] = scale_inv;
     return launch_held(b, n, ws, s);
   }
-  // The same sizes with a transposed copy: 16.8 M elements 18.7 us in two passes and 19.4 in one launch, 21 M 27.0 and 21.4; ahead at 151 M still
-  // (the figures stand at quantize_held_transpose_kernel).
-  if (n > 0 && transpose_fits(x, rows, cols, ldx, q, ldq, qT, ldqT) && ldx <= kHeldStride && held_pays(n))
+  if (n > 0 && transpose_fits(x, rows, cols, ldx, q, ldq, qT, ldqT) && ldx <= kHeldStride && held_transpose_pays(rows, cols, fog_compute_units()))
     return launch_held_transpose({x, q, qT, rows, cols, ldx, ldq, ldqT, 0, 0, margin, 0, amax, scale, scale_inv}, (int)fmt, ws, s);
   int64_t blocks = 0;   // an empty tensor: no partial maxima, abs-max 0, scale 1
   if (n > 0) {
@@ -1234,7 +1242,7 @@ extern "C" fog_status fog_quantize_jit_batch(const fog_cast_job* jobs, int count
   if (st != FOG_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   uint32_t* ws = reinterpret_cast<uint32_t*>(workspace);
-  if (held_pays(total)) return launch_held(b, total, ws, s);
+  if (held_pays(total, fog_compute_units())) return launch_held(b, total, ws, s);
   b.cast_first[0] = 0;
   for (int p = 0; p < count; ++p) {   // launch position p casts job count - 1 - p
     const int64_t chunks = b.n[count - 1 - p] / 16;
@@ -1262,6 +1270,16 @@ extern "C" fog_status fog_probe_quantize_held(const fog_cast_job* jobs, int coun
   if (st != FOG_OK) return st;
   if (absent < 0 || absent > 0xFFFF || total > kHeldMost) return FOG_ERR_SHAPE;
   return launch_held(b, total, reinterpret_cast<uint32_t*>(workspace), (hipStream_t)stream, (int)absent);
+}
+
+// Host-only helper (include/fog_probe.h): the choice above without a launch.
+extern "C" fog_status fog_probe_cast_plan(int64_t rows, int64_t cols, int with_transpose, int compute_units_or_0, int* one_launch) {
+  if (!one_launch) return FOG_ERR_NULL;
+  if (rows < 1 || cols < 1 || rows > INT64_MAX / 32 / cols || compute_units_or_0 < 0) return FOG_ERR_SHAPE;
+  const int cus = compute_units_or_0 > 0 ? compute_units_or_0 : fog_compute_units();
+  *one_launch = with_transpose ? rows % 16 == 0 && cols % 16 == 0 && cols <= kHeldStride && held_transpose_pays(rows, cols, cus)
+                               : rows * cols % 16 == 0 && held_pays(rows * cols, cus);
+  return FOG_OK;
 }
 
 extern "C" fog_status fog_probe_quantize_held_transpose(const void* x_bf16, int64_t rows, int64_t cols, int64_t ldx, fog_fp8 fmt, int margin,

@@ -59,6 +59,7 @@ PROBE_SIGNATURES = {
     "fog_probe_attention_loop": (_I, [_I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _P]),
     "fog_probe_mfma_coissue": (_I, [_I, _I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _P]),
     "fog_probe_mfma_cross_wave": (_I, [_I, _I, _I, _I, _P, _SZ, _c.POINTER(_c.c_double), _c.POINTER(_c.c_double), _P]),
+    "fog_probe_cast_plan": (_I, [_I64, _I64, _I, _I, _c.POINTER(_I)]),
     "fog_probe_quantize_held": (_I, [_P, _I, _P, _SZ, _I64, _P]),
     "fog_probe_quantize_held_transpose": (_I, [_P, _I64, _I64, _I64, _I, _I, _P, _I64, _P, _I64, _P, _P, _P, _P, _SZ, _I64, _P]),
     "fog_probe_gemm_plan": (_I, [_I, _I64, _I64, _I64, _I, _I] + [_c.POINTER(_I)] * 5),
@@ -328,6 +329,13 @@ def probe_mfma_cross_wave(op, vector_ops, iters_matrix, iters_vector, sink, stre
     _check(load().fog_probe_mfma_cross_wave(op, vector_ops, iters_matrix, iters_vector, _ptr(sink), sink.numel() * sink.element_size(),
                                             _c.byref(cm), _c.byref(cv), _stream(stream)), "fog_probe_mfma_cross_wave")
     return cm.value, cv.value
+
+
+def probe_cast_plan(rows, cols, with_transpose=False, compute_units=0):
+    """Whether quantize_jit casts such a tensor in one launch (fog_probe.h; no device needed)."""
+    out = _I(0)
+    _check(load().fog_probe_cast_plan(rows, cols, int(with_transpose), compute_units, _c.byref(out)), "fog_probe_cast_plan")
+    return bool(out.value)
 
 
 def probe_quantize_held(jobs, workspace, absent, stream=None):
