@@ -421,6 +421,7 @@ constexpr int kHeldThreads = 512, kHeldRegs = 21;
 constexpr uint32_t kMaxIsIn = 0x80000000u, kShareIsTaken = 0x40000000u;
 struct HeldJobs {
   int first[kBatchMax + 1];   // first workgroup of each job
+  int64_t total;              // elements of all jobs
   int absent;                 // for tests: that many of every absent + 1 workgroups end without having begun
 };
 __global__ __launch_bounds__(256) void clear_maxima_kernel(HeldJobs h, uint32_t* __restrict__ ws) {
@@ -502,7 +503,7 @@ FOG_DEVICE bool publishes(const HeldShared& sh, int bid, int extra) {
 struct Plain { static constexpr int value = 0; };
 struct Stream { static constexpr int value = 2; };   // non-temporal
 template <int FMT>
-FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, uint32_t* __restrict__ words, int j, int bid, int nb) {
+FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, uint32_t* __restrict__ words, int j, int bid, int nb, bool plain) {
   constexpr int STEP = kHeldThreads;                                     // chunks that the workgroup takes at a time
   constexpr int REGS = kHeldRegs * STEP;                                 // chunks of the share that stay in registers
   constexpr int NL = 8, GRP = 7;
@@ -543,8 +544,13 @@ FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, uint32_t* __restri
 #pragma unroll
   for (int g = 0; g < kHeldRegs; g += GRP)
     if (g * STEP < mine) {
+      if (plain) {
 #pragma unroll
-      for (int i = g; i < g + GRP && i < kHeldRegs; ++i) fetch(src, i * STEP, v[i], Stream{});
+        for (int i = g; i < g + GRP && i < kHeldRegs; ++i) fetch(src, i * STEP, v[i], Plain{});
+      } else {
+#pragma unroll
+        for (int i = g; i < g + GRP && i < kHeldRegs; ++i) fetch(src, i * STEP, v[i], Stream{});
+      }
     }
 #pragma unroll
   for (int g = 0; g < kHeldRegs; g += GRP)
@@ -609,8 +615,12 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_kernel(BatchJob
     if ((int)blockIdx.x >= h.first[k]) j = k;
   const int bid = (int)blockIdx.x - h.first[j], nb = h.first[j + 1] - h.first[j];
   if (h.absent && bid % (h.absent + 1) != 0) return;
-  if (b.fmt[j] == FOG_E4M3) held_body<FOG_E4M3>(sh, b, ws + j * kJitSlots, j, bid, nb);
-  else                      held_body<FOG_E5M2>(sh, b, ws + j * kJitSlots, j, bid, nb);
+  // Ordinary loads for tensors that are a small part of the batch: the activations of few tokens beside two weights, say, which a later kernel reads
+  // again and finds in the caches then (feed-forward half of 176 tokens, 2944 x 13696: 172.9 -> 171.4 us; two passes 171.5).  Everything by ordinary
+  // loads is slower: 42 M in three tensors 29.5 -> 37, 67 M in four 52 -> 57; so is every tensor of up to 2 M elements, 47 M in 32 of them 32 -> 38.
+  const bool plain = 64 * b.n[j] <= h.total;
+  if (b.fmt[j] == FOG_E4M3) held_body<FOG_E4M3>(sh, b, ws + j * kJitSlots, j, bid, nb, plain);
+  else                      held_body<FOG_E5M2>(sh, b, ws + j * kJitSlots, j, bid, nb, plain);
 }
 
 // ---------------------------------------------------------------- several tensors per launch (delayed scaling)
@@ -955,6 +965,7 @@ inline bool held_pays(int64_t n, int64_t cus) {
 inline fog_status launch_held(const BatchJobs& b, int64_t total, uint32_t* ws, hipStream_t s, int absent = 0) {
   HeldJobs h;
   h.absent = absent;
+  h.total = total;
   h.first[0] = 0;
   int room = fog_compute_units() < kHeldThreads ? fog_compute_units() : kHeldThreads;
   for (int j = 0; j < kBatchMax; ++j) {
