@@ -437,10 +437,14 @@ extern "C" fog_status fog_fp8_attn_fwd(int B, int H, int H_kv, int S, int D, flo
   a.BH = B * H; a.S = S; a.nqb = (S + BQ - 1) / BQ;
   a.G = H / H_kv;
   const int grid = a.BH * a.nqb;
-  // Scores a block ahead: two waves per SIMD instead of three, for launches that leave two workgroups or fewer to a CU.
-  // Forward, us, without -> with: 1 x 4 x 8192 94 -> 85, 1 x 8 x 4096 49.5 -> 46, 1 x 16 x 4096 (512 workgroups) 54.9 -> 52.5, 1 x 16/8 x 1024 15.6 -> 15.1;
-  // but 2 x 8/2 x 256 7.1 -> 7.3 and 4 x 16 x 2048 (1024 workgroups) 44.5 -> 47.5.
-  if (S >= 512 && grid <= 2 * fog_compute_units()) {
+  // Scores a block ahead: two waves per SIMD instead of three, for launches that leave one workgroup or none to a CU, and longer ones that leave two.
+  // Forward, us, without -> with, causal / not, by heads x S (workgroups on 256 CUs).  One a CU: 8 x 512 (32) 9.6 / 9.3 -> 9.5 / 8.9, 64 x 512 (256) 10.3 / 10.5 ->
+  // 10.3 / 10.4, 16 x 1024 (128) 15.3 / 15.5 -> 14.9 / 14.6, 16 x 2048 26.6 / 27.4 -> 25.2 / 25.7, 4 x 8192 90.2 / 93.8 -> 83.2 / 84.0; but 2 x 8/2 x 256 7.1 -> 7.3.
+  // Two: 128 x 512 (512) 11.8 / 15.1 -> 12.8 / 15.8, 100 x 576 12.8 / 15.8 -> 13.9 / 16.4, 80 x 768 14.7 / 19.3 -> 15.4 / 19.8, 33 x 1024 (264) 16.7 / 22.1 ->
+  // 16.8 / 22.6, 64 x 1024 18.1 / 24.1 -> 18.4 / 24.3, 28 x 1280 (280) 18.8 / 24.9 -> 17.9 / 24.5, 42 x 1408 (462) 21.5 / 30.4 -> 21.1 / 30.5, 40 x 1536
+  // (480) 23.6 / 32.3 -> 23.3 / 32.0, 16 x 4096 53.0 / 78.4 -> 50.7 / 76.3.  Four: 4 x 16 x 2048 44.5 -> 47.5.
+  const int cus = fog_compute_units();
+  if (grid <= cus ? S >= 512 : grid <= 2 * cus && S > 1024) {
     if (causal) attn_fwd_kernel<true, true><<<grid, kThreads, 0, s>>>(a);
     else        attn_fwd_kernel<false, true><<<grid, kThreads, 0, s>>>(a);
   } else {
