@@ -678,10 +678,10 @@ def test_forward_with_growing_row_references(steps, S, causal):
 
 
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("S", [512, 576, 640, 1088])
+@pytest.mark.parametrize("S", [512, 576, 640, 704, 1088])
 def test_forward_of_few_workgroups_equals_that_of_many(S, causal):
-    """Launches of up to two workgroups per CU produce scores a block ahead, larger ones do not: the same operations in the same order, so one head
-    by itself has the bytes it has among 300 copies (S = 512 is the shortest of the first kind; block counts of every remainder by four)."""
+    """Launches of few workgroups produce scores a block ahead, larger ones do not: the same operations in the same order, so one head
+    by itself has the bytes it has among 300 copies (S = 512 is the shortest of the first kind; 8, 9, 10, 11 and 17 blocks: the walk over four stages ends in each)."""
     g = torch.Generator(device="cuda").manual_seed(S)
     q, k, v = ((torch.randn((1, S, 128), device="cuda", generator=g) * 64).to(torch.float8_e4m3fn).view(torch.uint8) for _ in range(3))
     inv, out = fscalar(2.0 ** -6), []

@@ -649,10 +649,13 @@ def test_one_launch_transposing_cast_equals_the_separate_calls(rows, cols, pad, 
             assert torch.equal(qT, qT2) and torch.equal(q, q2)
 
 
-def test_large_casts_take_the_one_launch_form_with_the_same_results():
-    """The public calls around the size from which they read a tensor once (70 K elements a compute unit), one tensor and several."""
-    per_cu = (70 << 10) * torch.cuda.get_device_properties(0).multi_processor_count // 16
-    for c in (per_cu - 1, per_cu, per_cu + 1):
+@pytest.mark.parametrize("limit", [70, 625])
+def test_large_casts_take_the_one_launch_form_with_the_same_results(limit):
+    """The public calls around the sizes between which they keep tensors in registers (70 and 625 K elements a compute unit): the form that the plan
+    names on either side, one tensor and several, with the same results."""
+    at = (limit << 10) * torch.cuda.get_device_properties(0).multi_processor_count // 16
+    for c in (at - 1, at, at + 1):
+        assert fog.probe_cast_plan(c, 16) == (c >= at if limit == 70 else c <= at)
         x = torch.randn((c, 16), device="cuda").to(torch.bfloat16)
         am, sc, si = (torch.zeros(1, device="cuda") for _ in range(3))
         q = torch.empty((c, 16), dtype=torch.uint8, device="cuda")
@@ -665,9 +668,9 @@ def test_large_casts_take_the_one_launch_form_with_the_same_results():
             fog.quantize_jit_batch(fog.make_cast_jobs(out), torch.empty(fog.quantize_jit_batch_workspace(len(out)), dtype=torch.uint8, device="cuda"))
             if len(parts) == 1:
                 assert torch.equal(out[0][2], q) and torch.equal(out[0][3], am) and torch.equal(out[0][4], sc) and torch.equal(out[0][5], si)
-                q1 = torch.empty_like(q)
-                fog.quantize_jit(x, fp8.E4M3, am, sc, si, torch.empty(fog.quantize_jit_workspace(), dtype=torch.uint8, device="cuda"), q=q1)
-                assert torch.equal(q1, q) and torch.equal(out[0][3], am) and torch.equal(out[0][4], sc) and torch.equal(out[0][5], si)
+                q1, am1, sc1, si1 = torch.empty_like(q), *(torch.zeros(1, device="cuda") for _ in range(3))
+                fog.quantize_jit(x, fp8.E4M3, am1, sc1, si1, torch.empty(fog.quantize_jit_workspace(), dtype=torch.uint8, device="cuda"), q=q1)
+                assert torch.equal(q1, q) and torch.equal(am1, am) and torch.equal(sc1, sc) and torch.equal(si1, si)
             else:
                 for p, _, qp, a, s, _ in out:
                     assert a.item() == p.abs().max().item()
@@ -678,23 +681,32 @@ def test_large_casts_take_the_one_launch_form_with_the_same_results():
 
 def test_one_launch_casts_on_two_streams_at_once():
     """Two launches of one workgroup per compute unit each, which share the chip in whatever way they are dealt out: none waits for workgroups
-    that cannot start, and each has its own results."""
+    that cannot start, and every launch has its own results, whatever the one before left in the workspace."""
+    assert fog.probe_cast_plan(2 ** 21 + 5, 16)
     jobs, want, streams = [], [], [torch.cuda.Stream(), torch.cuda.Stream()]
     for i in range(2):
-        x = torch.randn((2 ** 21 + 5, 16), device="cuda").mul_(i + 1.0).to(torch.bfloat16)
-        am, sc, si = (torch.zeros(1, device="cuda") for _ in range(3))
-        q = torch.empty(x.shape, dtype=torch.uint8, device="cuda")
-        fog.amax(x.view(-1), am)
-        fog.scale(am, fp8.E4M3, sc, si)
-        fog.quantize(x, fp8.E4M3, sc, q=q)
-        want.append((q, am, sc, si))
-        jobs.append((x, fp8.E4M3, torch.empty_like(q), *(torch.zeros(1, device="cuda") for _ in range(3))))
-    arr = [fog.make_cast_jobs([j]) for j in jobs]
+        xs = [torch.randn((2 ** 21 + 5, 16), device="cuda").mul_(i + 0.5 * k + 1.0).to(torch.bfloat16) for k in range(2)]   # two inputs in turn
+        want.append([])
+        for x in xs:
+            am, sc, si = (torch.zeros(1, device="cuda") for _ in range(3))
+            q = torch.empty(x.shape, dtype=torch.uint8, device="cuda")
+            fog.amax(x.view(-1), am)
+            fog.scale(am, fp8.E4M3, sc, si)
+            fog.quantize(x, fp8.E4M3, sc, q=q)
+            want[i].append((q, am, sc, si))
+        jobs.append([(x, fp8.E4M3, torch.empty_like(want[i][0][0]), *(torch.zeros(1, device="cuda") for _ in range(3))) for x in xs])
+    arr = [[fog.make_cast_jobs([j]) for j in pair] for pair in jobs]
     ws = [torch.empty(fog.quantize_jit_batch_workspace(1), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    wrong = [torch.zeros((), dtype=torch.int64, device="cuda") for _ in range(2)]
     torch.cuda.synchronize()
-    for _ in range(20):
+    for n in range(20):
         for i, s in enumerate(streams):
-            fog.quantize_jit_batch(arr[i], ws[i], stream=s)
+            with torch.cuda.stream(s):
+                j = jobs[i][n % 2]
+                for t in j[2:]:
+                    t.fill_(0xAA if t.dtype == torch.uint8 else -1.0)
+                fog.quantize_jit_batch(arr[i][n % 2], ws[i])
+                for a, b in zip(j[2:], want[i][n % 2]):
+                    wrong[i] += (a != b).sum()
     torch.cuda.synchronize()
-    for j, w in zip(jobs, want):
-        assert all(torch.equal(a, b) for a, b in zip(j[2:], w))
+    assert all(w.item() == 0 for w in wrong)
