@@ -114,12 +114,15 @@ fog_status fog_quantize(const void* x_bf16, int64_t rows, int64_t cols, int64_t 
 /*
  * Just-in-time scaling in one call (Section 2: abs-max of the tensor being cast, then the cast;
  * Appendix E for the scale): the same results, bit for bit, as fog_amax -> fog_scale -> fog_quantize,
- * in two launches instead of four and without atomics: every workgroup of the abs-max pass leaves
+ * in two launches instead of four.  In general without atomics: every workgroup of the abs-max pass leaves
  * its maximum in its own word of the workspace; every workgroup of the cast pass, which follows on
  * the same stream, reduces those words (4 KB at most) and derives the scale itself, and the first
- * one publishes abs-max, scale and 1/scale.  Tensors of 18 to 160 M elements (without a transposed
- * copy: contiguous ones) are read once, but for what exceeds 42 to 44 M: one launch takes the abs-max, exchanges the workgroups' maxima through the
- * workspace and casts what it has kept in registers.
+ * one publishes abs-max, scale and 1/scale.  Tensors of 70 to 625 K elements per compute unit (18 to 160 M on
+ * 256; without a transposed copy: contiguous ones; with one: not those much narrower than a 128 x 128 tile) take a launch that
+ * clears the workspace and one that reads the tensor, exchanges the workgroups' maxima through the
+ * workspace (with atomics) and casts what it has kept in registers: 42 to 44 M elements on 256 compute units are read once,
+ * what exceeds them twice.  That launch wants a compute unit to itself for each workgroup; beside another stream's kernel
+ * its workgroups wait for none that has not started, and take its share over.
  *   amax, scale : one float each, overwritten.   scale_inv : one float or NULL.
  *   q, qT, x_bf16, leading dimensions, fmt : as in fog_quantize.   margin : as in fog_scale.
  *   workspace : fog_quantize_jit_workspace() bytes (4 KB), 4-byte aligned, owned by the caller; its
@@ -135,8 +138,8 @@ size_t fog_quantize_jit_workspace(void);
 
 /*
  * fog_quantize_jit for up to FOG_CAST_BATCH_MAX tensors in two launches (one abs-max pass over all of them,
- * one cast pass over all of them; or, 18 to 160 M elements in all, one small launch and one that reads them once) instead of two
- * per tensor: a launch costs a few microseconds of ramp and
+ * one cast pass over all of them; or, for the elements in all that fog_quantize_jit names, its clearing launch and
+ * the one that keeps what it can in registers) instead of two per tensor: a launch costs a few microseconds of ramp and
  * tail whatever it does, which is a fifth of either pass over a 100 MB tensor.  Results are those of
  * fog_quantize_jit on each job, bit for bit.
  *   jobs   : HOST array of `count` (0..FOG_CAST_BATCH_MAX) descriptions; the device buffers they name follow the rules
