@@ -411,21 +411,23 @@ __global__ __launch_bounds__(kThreads) void quantize_batch_kernel(BatchJobs b, c
 // of 16 elements of it in registers (44 M elements on the chip), leaves its maximum in a word of the workspace, gathers those
 // of the tensor's other workgroups and casts what it holds; of a larger share the rest is read twice, as before.  A small launch in front clears the words.
 // No workgroup depends on another one being resident, because beside another stream's kernel not all of them are (each fills the registers of a CU): a
-// workgroup takes its share with its first instruction, and one that has its own maximum and finds shares that nobody has taken takes them too,
-// one after the other, and casts them behind its own; a workgroup that starts later and finds its share gone ends.  So every word belongs to a
+// workgroup takes its share, in four pieces with a word each, with its first instruction, and one that has its own maximum and finds pieces that nobody has
+// taken takes them too and casts them behind its own; a workgroup that starts later and finds its share gone ends.  So every word belongs to a
 // workgroup that is running, and all waits end.  Beside attention forwards of 0 / 16 / 64 / 192 workgroups on another stream, us, two passes: 20 M elements
-// 21 / 26 / 26 / 25, 67 M in four tensors 63 / 64 / 65 / 69, 134 M 124 / 125 / 127 / 131; this: 20 / 34 / 34 / 44, 50 / 56-60 / 63 / 85, 116 / 120 / 138 / 151 (with a
+// 22 / 26 / 26 / 25, 67 M in four tensors 63 / 64 / 65 / 68, 134 M 123 / 126 / 127 / 130; this: 18 / 33 / 37 / 44, 48 / 56-59 / 62 / 84, 116 / 117 / 135 / 149.  (With a
 // wait of 50 us before shares were taken, all workgroups asking for the same one and what a workgroup held given up for it: 19 / 39 / 175 / 105, 50 / 57 / 63 / 85,
-// 117 / 120 / 137 / 151).  Workgroups of 256 threads, two a CU, of which one fits beside a foreign one: 5 us more at every size, for 512 words to gather.
+// 117 / 120 / 137 / 151; one word a share: the same times here, 20 M alone 19.4, 117 M with a transposed copy beside 64 workgroups 187 for 151.)
+// Workgroups of 256 threads, two a CU, of which one fits beside a foreign one: 5 us more at every size, for 512 words to gather.
 constexpr int kHeldThreads = 512, kHeldRegs = 21;
-constexpr uint32_t kMaxIsIn = 0x80000000u, kShareIsTaken = 0x40000000u;
+constexpr int kPieces = 4, kHeldShares = kJitSlots / kPieces;   // a share is taken in four pieces, each with its word; shares of a tensor at most
+constexpr uint32_t kMaxIsIn = 0x80000000u, kIsTaken = 0x40000000u;
 struct HeldJobs {
   int first[kBatchMax + 1];   // first workgroup of each job
   int64_t total;              // elements of all jobs
   int absent;                 // for tests: that many of every absent + 1 workgroups end without having begun
 };
 __global__ __launch_bounds__(256) void clear_maxima_kernel(HeldJobs h, uint32_t* __restrict__ ws) {
-  const int j = blockIdx.x, n = h.first[j + 1] - h.first[j];
+  const int j = blockIdx.x, n = kPieces * (h.first[j + 1] - h.first[j]);
   for (int i = threadIdx.x; i < n; i += 256) ws[j * kJitSlots + i] = 0u;
 }
 // Raw buffer over a workgroup's share: loads past its end return zeros, so the unrolled code below needs few branches (the compiler waits for
@@ -435,8 +437,8 @@ FOG_DEVICE __amdgpu_buffer_rsrc_t span(const void* base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 struct HeldShared {
-  uint32_t part[kHeldThreads / 64], word;
-  uint16_t extra[kHeldThreads];   // shares taken besides the workgroup's own
+  uint32_t part[kHeldThreads / 64], free[kJitSlots / 64], word;
+  uint16_t extra[kJitSlots], extra_to[kJitSlots];   // pieces taken besides the workgroup's own share: first, and one past the last, of each take
 };
 // Maximum over a workgroup's threads of packed pairs.
 FOG_DEVICE uint32_t held_block_max(HeldShared& sh, uint32_t packed) {
@@ -449,57 +451,85 @@ FOG_DEVICE uint32_t held_block_max(HeldShared& sh, uint32_t packed) {
   for (int w = 1; w < kHeldThreads / 64; ++w) r = r > sh.part[w] ? r : sh.part[w];
   return r;
 }
-// Takes share i if nobody has: zero, in thread 0, where it was free.
-FOG_DEVICE uint32_t take_share(uint32_t* words, int i) {
-  uint32_t before = 0u;
-  if (threadIdx.x == 0) before = atomicCAS(words + i, 0u, kShareIsTaken);
+// Takes the pieces of share `bid` that nobody has: zero in the threads of those that were free.
+FOG_DEVICE uint32_t take_share(uint32_t* words, int bid) {
+  uint32_t before = 1u;
+  if (threadIdx.x < kPieces) before = atomicCAS(words + kPieces * bid + threadIdx.x, 0u, kIsTaken);
   return before;
 }
-// Leaves `own`, the maximum of this workgroup's share, in its word, takes shares that nobody has, and returns the maximum of all `nb` (at most a word for
-// each thread).  share_max(i) is the maximum of share i; the *extra shares taken stand in sh.extra.
+// Whether any was (behind held_block_max's barriers, between the two calls, for all threads).
+FOG_DEVICE void note_taken(HeldShared& sh, uint32_t before) {
+  const uint64_t got = __ballot(before == 0u);
+  if (threadIdx.x == 0) sh.word = got != 0;
+}
+// Leaves `own`, the maximum of this workgroup's share, in the words of the pieces that it has, takes pieces that nobody has, and returns the maximum of
+// all `nb` shares.  pieces_max(i, j) is the maximum of pieces i ..< j of one share; the *extra takes stand in sh.extra and sh.extra_to.
 template <typename F>
-FOG_DEVICE uint32_t gather_maxima(HeldShared& sh, uint32_t* __restrict__ words, int bid, int nb, uint32_t own, int* extra, F share_max) {
+FOG_DEVICE uint32_t gather_maxima(HeldShared& sh, uint32_t* __restrict__ words, int bid, int nb, uint32_t before, uint32_t own, int* extra, F pieces_max) {
+  constexpr int kWords = kJitSlots / kHeldThreads, kWaves = kHeldThreads / 64;   // words of a thread
+  static_assert(kWords == 2, "the tests below name two");
   const int tid = threadIdx.x;
   *extra = 0;
-  if (tid == 0) __hip_atomic_store(words + bid, kMaxIsIn | own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (before == 0u) __hip_atomic_store(words + kPieces * bid + tid, kMaxIsIn | own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (;;) {
-    const uint32_t w = tid < nb ? __hip_atomic_load(words + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kMaxIsIn;
-    if (__syncthreads_and(w & kMaxIsIn)) return held_block_max(sh, w & 0x7FFFu);
-    if (!__syncthreads_or(w == 0u)) {   // all shares have a workgroup
+    uint32_t w[kWords];
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) {
+      const int at = tid + k * kHeldThreads;
+      w[k] = at < kPieces * nb ? __hip_atomic_load(words + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kMaxIsIn;
+    }
+    if (__syncthreads_and(w[0] & w[1] & kMaxIsIn)) return held_block_max(sh, pkmax_abs_bf16(w[0] & 0x7FFFu, w[1] & 0x7FFFu));
+    if (!__syncthreads_or(w[0] == 0u || w[1] == 0u)) {   // every piece has a workgroup
       __builtin_amdgcn_s_sleep(1);
       continue;
     }
-    // One of the shares that have none, if it still has none: number bid of them, so that the workgroups ask for different ones (all asking for
+    // One of the pieces that have none, if it still has none: number bid of them, so that the workgroups ask for different ones (all asking for
     // the same one queue up at its word: 100 us for 64 shares).
-    const uint64_t free = __ballot(w == 0u);
-    if ((tid & 63) == 0) sh.part[tid >> 6] = (uint32_t)__popcll(free);
-    __syncthreads();
-    uint32_t before = 0, total = 0;
+    uint64_t free[kWords];
 #pragma unroll
-    for (int k = 0; k < kHeldThreads / 64; ++k) {
-      before += k < tid >> 6 ? sh.part[k] : 0u;
-      total += sh.part[k];
+    for (int k = 0; k < kWords; ++k) {
+      free[k] = __ballot(w[k] == 0u);
+      if ((tid & 63) == 0) sh.free[k * kWaves + (tid >> 6)] = (uint32_t)__popcll(free[k]);
     }
-    before += (uint32_t)__popcll(free & ((1ull << (tid & 63)) - 1u));
-    if (w == 0u && before == (uint32_t)bid % total) sh.word = (uint32_t)tid;
     __syncthreads();
-    const int i = (int)sh.word;
-    if (!__syncthreads_or(take_share(words, i) != 0u)) {
-      const uint32_t r = share_max(i);
-      if (tid == 0) {
-        __hip_atomic_store(words + i, kMaxIsIn | r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sh.extra[*extra] = (uint16_t)i;
-      }
-      ++*extra;
+    uint32_t total = 0, ahead[kWords] = {};
+#pragma unroll
+    for (int n = 0; n < kWords * kWaves; ++n) {
+#pragma unroll
+      for (int k = 0; k < kWords; ++k) ahead[k] += n < k * kWaves + (tid >> 6) ? sh.free[n] : 0u;
+      total += sh.free[n];
     }
+#pragma unroll
+    for (int k = 0; k < kWords; ++k)
+      if (w[k] == 0u && ahead[k] + (uint32_t)__popcll(free[k] & ((1ull << (tid & 63)) - 1u)) == (uint32_t)bid % total) sh.word = (uint32_t)(tid + k * kHeldThreads);
+    __syncthreads();
+    // It, or the two or four beside it in its share where there are that many for each workgroup that runs: a take costs 3 us whatever its size.
+    const uint32_t running = (uint32_t)nb - total / kPieces;
+    const int n = total <= running ? 1 : total <= 2 * running ? 2 : 4, first = (int)sh.word & -n;
+    bool mine = false;
+    if (tid < n) mine = atomicCAS(words + first + tid, 0u, kIsTaken) == 0u;
+    const uint64_t got = __ballot(mine);
+    __syncthreads();
+    if (tid == 0) sh.word = (uint32_t)got;
+    __syncthreads();
+    if (sh.word == 0u) continue;
+    const int from = first + __builtin_ctz(sh.word), to = first + 32 - __builtin_clz(sh.word);   // (a piece in between that another workgroup has is done twice)
+    const uint32_t r = pieces_max(from, to);
+    if (mine) __hip_atomic_store(words + first + tid, kMaxIsIn | r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) {
+      sh.extra[*extra] = (uint16_t)from;
+      sh.extra_to[*extra] = (uint16_t)to;
+    }
+    ++*extra;
   }
 }
-// Whether this workgroup is the one that has the first share.
-FOG_DEVICE bool publishes(const HeldShared& sh, int bid, int extra) {
+// Whether thread 0's workgroup is the one that has the first piece.
+FOG_DEVICE bool publishes(const HeldShared& sh, int bid, uint32_t before, int extra) {
   for (int k = 0; k < extra; ++k)
     if (sh.extra[k] == 0) return true;
-  return bid == 0;
+  return bid == 0 && before == 0u;
 }
+template <int N> struct Count { static constexpr int value = N; };
 struct Plain { static constexpr int value = 0; };
 struct Stream { static constexpr int value = 2; };   // non-temporal
 template <int FMT>
@@ -513,8 +543,10 @@ FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, uint32_t* __restri
   const int64_t c0 = begin(bid);
   const int mine = (int)(begin(bid + 1) - c0);                           // chunks of this workgroup's share
   const uint32_t before = take_share(words, bid);   // (the answer is waited for behind the loads)
-  auto source = [&](int i) { return span(b.x[j] + begin(i) * 16, (begin(i + 1) - begin(i)) * 32); };
-  const auto src = source(bid);
+  auto part = [&](int p) { return begin(p / kPieces) + (per + kPieces - 1) / kPieces * (p % kPieces); };   // chunk that piece p begins at, if it has any
+  auto part_end = [&](int p) { const int64_t end = begin(p / kPieces + 1), to = p % kPieces == kPieces - 1 ? end : part(p + 1); return to < end ? to : end; };
+  auto source = [&](int64_t from, int64_t to) { return span(b.x[j] + from * 16, to > from ? (to - from) * 32 : 0); };
+  const auto src = source(c0, c0 + mine);
   uint32_t m[4] = {0, 0, 0, 0};
   auto take = [&](const v4u* a) __attribute__((always_inline)) {
 #pragma unroll
@@ -527,19 +559,20 @@ FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, uint32_t* __restri
     to[0] = __builtin_amdgcn_raw_buffer_load_b128(from, (c + tid) * 32, 0, decltype(policy)::value);
     to[1] = __builtin_amdgcn_raw_buffer_load_b128(from, (c + tid) * 32 + 16, 0, decltype(policy)::value);
   };
-  auto walk = [&](decltype(src) from, int c, int n) __attribute__((always_inline)) {
-    for (; c < n; c += NL * STEP) {
-      v4u t[NL][2];
+  auto walk = [&](decltype(src) from, int c, int n, auto ahead) __attribute__((always_inline)) {
+    constexpr int N = decltype(ahead)::value;
+    for (; c < n; c += N * STEP) {
+      v4u t[N][2];
 #pragma unroll
-      for (int k = 0; k < NL; ++k) fetch(from, c + k * STEP, t[k], Plain{});
+      for (int k = 0; k < N; ++k) fetch(from, c + k * STEP, t[k], Plain{});
 #pragma unroll
-      for (int k = 0; k < NL; ++k) take(t[k]);
+      for (int k = 0; k < N; ++k) take(t[k]);
     }
   };
   auto block_max = [&]() __attribute__((always_inline)) {
     return held_block_max(sh, pkmax_abs_bf16(pkmax_abs_bf16(m[0], m[1]), pkmax_abs_bf16(m[2], m[3])));
   };
-  walk(src, REGS, mine);
+  walk(src, REGS, mine, Count<NL>{});
   v4u v[kHeldRegs][2];
 #pragma unroll
   for (int g = 0; g < kHeldRegs; g += GRP)
@@ -559,18 +592,18 @@ FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, uint32_t* __restri
       for (int i = g; i < g + GRP && i < kHeldRegs; ++i) take(v[i]);
     }
   int extra;
-  if (tid == 0) sh.word = before;
+  note_taken(sh, before);
   const uint32_t own = block_max();
-  if (sh.word != 0u) return;   // taken while this workgroup could not start
-  const uint32_t r = gather_maxima(sh, words, bid, nb, own, &extra, [&](int i) {
+  if (sh.word == 0u) return;   // taken while this workgroup could not start
+  const uint32_t r = gather_maxima(sh, words, bid, nb, before, own, &extra, [&](int p, int q) {
     m[0] = m[1] = m[2] = m[3] = 0u;
-    walk(source(i), 0, (int)(begin(i + 1) - begin(i)));
+    walk(source(part(p), part_end(q - 1)), 0, (int)(part_end(q - 1) - part(p)), Count<NL - 2>{});   // (what is held leaves registers for six)
     return block_max();
   });
   const float a = __uint_as_float(r << 16);
   float rho, inv;
   scale_from_amax(a, FMT, b.margin[j], &rho, &inv);
-  if (tid == 0 && publishes(sh, bid, extra)) {
+  if (tid == 0 && publishes(sh, bid, before, extra)) {
     *b.amax[j] = a;
     *b.scale[j] = rho;
     if (b.scale_inv[j]) *b.scale_inv[j] = inv;
@@ -585,11 +618,10 @@ FOG_DEVICE void held_body(HeldShared& sh, const BatchJobs& b, uint32_t* __restri
 #pragma unroll
         for (int i = g; i < g + GRP && i < kHeldRegs; ++i) put(c0, i * STEP, mine, cast(v[i][0]), cast(v[i][1]));
       }
-    for (int e = -1; e < extra; ++e) {   // what is not held: of this share, and the others that were taken
-      const int i = e < 0 ? bid : sh.extra[e];
-      const auto from = source(i);
-      const int64_t at = begin(i);
-      const int n = (int)(begin(i + 1) - at);
+    for (int e = -1; e < extra; ++e) {   // what is not held: of this share, and the pieces that were taken
+      const int64_t at = e < 0 ? c0 : part(sh.extra[e]), to = e < 0 ? c0 + mine : part_end(sh.extra_to[e] - 1);
+      const auto from = source(at, to);
+      const int n = (int)(to - at);
       for (int c = e < 0 ? REGS : 0; c < n; c += NL * STEP) {
         v4u t[NL][2];
 #pragma unroll
@@ -765,10 +797,10 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint
 // The same in one launch with the abs-max, bound by the bytes over the fabric as quantize_held_kernel is: a workgroup takes a run of tiles, keeps the
 // first kHeldTiles = 10 of them in registers (one unit of 4 rows x 8 columns a thread and tile, 160 registers; 42 M elements on the chip), reads those
 // beyond twice, and transposes one after the other through two LDS tiles in turn, one barrier each.  Loads go through raw buffers over the tile, so that
-// those of all ten are in flight at once (their descriptors do not all fit the scalar registers: 44 wait in lanes of a vector register).  Back to back, us, with the row-major copy / without, two passes -> this: 21 M elements 27.0 / 24.1 -> 21.4 /
-// 19.8, 34 M 34.3 / 29.3 -> 28.0 / 24.4, 42 M 52.8 / 39.7 -> 32.5 / 27.5, 67 M 84.7 / 64.1 -> 76.4 / 60.7, 117 M 145.5 / 112.7 -> 116.7 / 93.1,
-// 151 M 182.5 / 140.8 -> 156.4 / 125.1.  Beside attention forwards of 0 / 16 / 64 / 192 workgroups on another stream, two passes: 34 M 35 / 39 / 41 / 43, 117 M
-// 150 / 154 / 157 / 158; this: 28 / 46 / 53 / 67, 118 / 126 / 187 / 212.
+// those of all ten are in flight at once (their descriptors do not all fit the scalar registers: 44 wait in lanes of a vector register).  Back to back, us, with the row-major copy / without, two passes -> this: 21 M elements 27.4 / 24.1 -> 19.5 /
+// 18.5, 34 M 34.3 / 29.5 -> 27.3 / 24.1, 42 M 54.8 / 39.7 -> 31.9 / 26.8, 67 M 86.8 / 64.4 -> 76.2 / 60.3, 117 M 147.7 / 115.5 -> 116.7 / 93.5,
+// 151 M 183.4 / 142.6 -> 156.9 / 124.1.  Beside attention forwards of 0 / 16 / 64 / 192 workgroups on another stream, two passes: 34 M 35 / 39 / 42 / 43, 117 M
+// 150 / 154 / 157 / 159; this: 27 / 44 / 52 / 71, 117 / 125 / 151-155 / 201.
 constexpr int kHeldTiles = 10;
 struct HeldTranspose {
   const uint16_t* x; uint8_t* q; uint8_t* qT;
@@ -784,6 +816,8 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_transpose_kerne
   const int per = (a.tiles + nb - 1) / nb;
   auto begin = [&](int i) { return per * i < a.tiles ? per * i : a.tiles; };
   const int t0 = begin(bid), mine = begin(bid + 1) - t0;
+  auto part = [&](int p) { return begin(p / kPieces) + (per + kPieces - 1) / kPieces * (p % kPieces); };   // tile that piece p begins at, if it has any
+  auto part_end = [&](int p) { const int end = begin(p / kPieces + 1), to = p % kPieces == kPieces - 1 ? end : part(p + 1); return to < end ? to : end; };
   if (a.absent && bid % (a.absent + 1) != 0) return;
   const uint32_t before = take_share(words, bid);   // (the answer is waited for behind the loads)
   uint32_t m = 0;
@@ -803,16 +837,17 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_transpose_kerne
       u[k] = make_uint4(w.x, w.y, w.z, w.w);
     }
   };
-  auto walk = [&](int from, int to) __attribute__((always_inline)) {   // the maximum of tiles from ..< to
-    for (int t = from; t < to; t += 4) {
-      uint4 u[4][4];
+  auto walk = [&](int from, int to, auto ahead) __attribute__((always_inline)) {   // the maximum of tiles from ..< to
+    constexpr int N = decltype(ahead)::value;
+    for (int t = from; t < to; t += N) {
+      uint4 u[N][4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) fetch(t + k, t + k < to, u[k]);
+      for (int k = 0; k < N; ++k) fetch(t + k, t + k < to, u[k]);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) take(u[k]);
+      for (int k = 0; k < N; ++k) take(u[k]);
     }
   };
-  walk(t0 + kHeldTiles, t0 + mine);
+  walk(t0 + kHeldTiles, t0 + mine, Count<4>{});
   uint4 v[kHeldTiles][4];
 #pragma unroll
   for (int i = 0; i < kHeldTiles; ++i)
@@ -821,18 +856,18 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_transpose_kerne
   for (int i = 0; i < kHeldTiles; ++i)
     take(v[i]);
   int extra;
-  if (tid == 0) sh.word = before;
+  note_taken(sh, before);
   const uint32_t own = held_block_max(sh, m);
-  if (sh.word != 0u) return;   // taken while this workgroup could not start
-  const uint32_t r = gather_maxima(sh, words, bid, nb, own, &extra, [&](int i) {
+  if (sh.word == 0u) return;   // taken while this workgroup could not start
+  const uint32_t r = gather_maxima(sh, words, bid, nb, before, own, &extra, [&](int p, int q) {
     m = 0u;
-    walk(begin(i), begin(i + 1));
+    walk(part(p), part_end(q - 1), Count<3>{});   // (what is held leaves registers for three)
     return held_block_max(sh, m);
   });
   const float am = __uint_as_float(r << 16);
   float rho, inv;
   scale_from_amax(am, FMT, a.margin, &rho, &inv);
-  if (tid == 0 && publishes(sh, bid, extra)) {
+  if (tid == 0 && publishes(sh, bid, before, extra)) {
     *a.amax = am;
     *a.scale = rho;
     if (a.scale_inv) *a.scale_inv = inv;
@@ -889,7 +924,7 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_transpose_kerne
       }
     from = t0 + kHeldTiles;
   }
-  for (int k = -1; k < extra; ++k) again(k < 0 ? from : begin(sh.extra[k]), k < 0 ? t0 + mine : begin(sh.extra[k] + 1));
+  for (int k = -1; k < extra; ++k) again(k < 0 ? from : part(sh.extra[k]), k < 0 ? t0 + mine : part_end(sh.extra_to[k] - 1));
 }
 
 // ---------------------------------------------------------------- general shapes (slow, same results)
@@ -951,15 +986,16 @@ inline int one_word_workgroups(int64_t chunks) { return workgroups(chunks, 512);
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Just-in-time casts in one launch (quantize_held_kernel) instead of an abs-max and a cast pass: from 18 M elements (70 K a compute unit) on, where what the
-// second pass reads again is more than the wait for the maxima costs, to 160 M (625 K), beyond which so much is read again after all that the two
-// passes' many workgroups are ahead.  Batches back to back, us, two passes -> one launch: 17 M elements 17.2 -> 18.3, 20 M 21.8 -> 19.4, 25 M 24.9
-// -> 21.7 (in two tensors 22.6 -> 22.3), 42 M in three 39.1 -> 28.7, 67 M in four 62.8 -> 51.4, 82 M 79.2 -> 69.5, 134 M 124 -> 117, 150 M 148.4 -> 133.7, 184 M
-// 172 -> 186.  (Four steps of the shares in LDS besides: a share of 32 steps 51.3 -> 50, all others up to 4 us slower, the registers spill.)
+// Just-in-time casts in one launch (quantize_held_kernel) instead of an abs-max and a cast pass: from 18 M elements (70 K a compute unit) to 160 M (625 K).
+// Batches back to back, us, two passes -> one launch: 8 M elements 11.7 -> 11.7, 12 M 14.3 -> 13.3, 17 M 18.9 -> 16.1, 20 M 21.8 -> 18.2, 25 M 24.8 -> 20.3
+// (in two tensors 22.8 -> 19.9), 42 M in three 39.5 -> 28.6, 67 M in four 63.5 -> 49.7, 82 M 78.8 -> 66.9, 134 M 123 -> 116, 150 M 147 -> 133, 165 M 160 -> 157, 184 M 178 ->
+// 168: alone it is level or ahead on either side of both lines.  Below the first it has little to give (with transposed copies nothing: 12.6 M elements 15.2 -> 16.1) and
+// more to lose beside another stream's kernel (above); beyond the second three quarters are read again after all.  (Four steps of the shares in LDS besides: a share of 32
+// steps 51.3 -> 50, all others up to 4 us slower, the registers spill.)
 constexpr int64_t kHeldFrom = 70 << 10, kHeldTo = 625 << 10, kHeldMost = (int64_t)1 << 30;   // elements a compute unit, and in all
 constexpr int64_t kHeldStride = 1 << 20;   // of rows where it transposes: a tile's byte offsets stay below 2^31
 inline bool held_pays(int64_t n, int64_t cus) {
-  return cus <= kHeldThreads && n >= kHeldFrom * cus && n <= kHeldTo * cus;
+  return cus <= kHeldShares && n >= kHeldFrom * cus && n <= kHeldTo * cus;
 }
 // One workgroup per compute unit, dealt to the tensors by their sizes, at least one each.
 inline fog_status launch_held(const BatchJobs& b, int64_t total, uint32_t* ws, hipStream_t s, int absent = 0) {
@@ -967,7 +1003,7 @@ inline fog_status launch_held(const BatchJobs& b, int64_t total, uint32_t* ws, h
   h.absent = absent;
   h.total = total;
   h.first[0] = 0;
-  int room = fog_compute_units() < kHeldThreads ? fog_compute_units() : kHeldThreads;
+  int room = fog_compute_units() < kHeldShares ? fog_compute_units() : kHeldShares;
   for (int j = 0; j < kBatchMax; ++j) {
     int nb = 0;
     if (j < b.count) {
@@ -1001,7 +1037,7 @@ inline bool held_transpose_pays(int64_t rows, int64_t cols, int64_t cus) {
   return held_pays(n, cus) && (tiles <= kHeldTiles * cus || (rows > cols && cols > kTile) || 16 * n >= 11 * tiles * kTile * kTile);
 }
 inline fog_status launch_held_transpose(HeldTranspose a, int fmt, uint32_t* ws, hipStream_t s) {
-  const int cus = fog_compute_units() < kHeldThreads ? fog_compute_units() : kHeldThreads;
+  const int cus = fog_compute_units() < kHeldShares ? fog_compute_units() : kHeldShares;
   a.tiles_c = (int)((a.cols + kTile - 1) / kTile);
   a.tiles = (int)tiles_of(a.rows, a.cols);
   const int per = (a.tiles + cus - 1) / cus, nb = (a.tiles + per - 1) / per;
