@@ -797,7 +797,7 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint
 // The same in one launch with the abs-max, bound by the bytes over the fabric as quantize_held_kernel is: a workgroup takes a run of tiles, keeps the
 // first kHeldTiles = 10 of them in registers (one unit of 4 rows x 8 columns a thread and tile, 160 registers; 42 M elements on the chip), reads those
 // beyond twice, and transposes one after the other through two LDS tiles in turn, one barrier each.  Loads go through raw buffers over the tile, so that
-// those of all ten are in flight at once (their descriptors do not all fit the scalar registers: 44 wait in lanes of a vector register).  Back to back, us, with the row-major copy / without, two passes -> this: 21 M elements 27.4 / 24.1 -> 19.5 /
+// those of all ten are in flight at once (their descriptors do not all fit the scalar registers: 72 wait in lanes of vector registers).  Back to back, us, with the row-major copy / without, two passes -> this: 21 M elements 27.4 / 24.1 -> 19.5 /
 // 18.5, 34 M 34.3 / 29.5 -> 27.3 / 24.1, 42 M 54.8 / 39.7 -> 31.9 / 26.8, 67 M 86.8 / 64.4 -> 76.2 / 60.3, 117 M 147.7 / 115.5 -> 116.7 / 93.5,
 // 151 M 183.4 / 142.6 -> 156.9 / 124.1.  Beside attention forwards of 0 / 16 / 64 / 192 workgroups on another stream, two passes: 34 M 35 / 39 / 42 / 43, 117 M
 // 150 / 154 / 157 / 159; this: 27 / 44 / 52 / 71, 117 / 125 / 151-155 / 201.
