@@ -710,3 +710,36 @@ def test_one_launch_casts_on_two_streams_at_once():
                     wrong[i] += (a != b).sum()
     torch.cuda.synchronize()
     assert all(w.item() == 0 for w in wrong)
+
+
+@pytest.mark.parametrize("wgs", [32, 192])
+def test_one_launch_casts_beside_another_kernel(wgs):
+    """While attention forwards on another stream keep some compute units, so that part of a cast's workgroups start late or not before the others are
+    done: every launch has the results of the separate calls, with a transposed copy and without."""
+    rows, cols = 4096, 8192
+    assert fog.probe_cast_plan(rows, cols) and fog.probe_cast_plan(rows, cols, True)
+    x = torch.randn((rows, cols), device="cuda").to(torch.bfloat16)
+    am, sc, si = (torch.zeros(1, device="cuda") for _ in range(3))
+    q, qT = torch.empty((rows, cols), dtype=torch.uint8, device="cuda"), torch.empty((cols, rows), dtype=torch.uint8, device="cuda")
+    fog.amax(x.view(-1), am)
+    fog.scale(am, fp8.E4M3, sc, si)
+    fog.quantize(x, fp8.E4M3, sc, q=q, qT=qT)
+    S, H = 4096, wgs // 32
+    qkv = [torch.zeros((H, S, 128), dtype=torch.uint8, device="cuda") for _ in range(3)]
+    one, rho, O, lse = torch.ones(1, device="cuda"), torch.full((1,), 448.0, device="cuda"), torch.empty((H, S, 128), dtype=torch.bfloat16, device="cuda"), torch.empty((H, S), device="cuda")
+    out = [torch.empty_like(t) for t in (q, qT, am, sc, si)]
+    ws = torch.empty(fog.quantize_jit_workspace(), dtype=torch.uint8, device="cuda")
+    here, other, wrong = torch.cuda.Stream(), torch.cuda.Stream(), torch.zeros((), dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    for n in range(20):
+        for _ in range(3):
+            fog.fp8_attn_fwd(1, H, S, 128, 0.1, False, *qkv, one, one, one, rho, O, lse, stream=other)
+        with torch.cuda.stream(here):
+            for t in out:
+                t.fill_(0xAA if t.dtype == torch.uint8 else -1.0)
+            fog.quantize_jit(x, fp8.E4M3, *out[2:], ws, q=out[0], qT=out[1] if n % 2 else None)
+            for a, b in zip(out, (q, qT, am, sc, si)):
+                if n % 2 or a is not out[1]:
+                    wrong += (a != b).sum()
+    torch.cuda.synchronize()
+    assert wrong.item() == 0
