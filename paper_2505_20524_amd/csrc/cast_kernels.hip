@@ -797,8 +797,9 @@ __global__ __launch_bounds__(kThreads) void quantize_transpose_kernel(const uint
 // The same in one launch with the abs-max, bound by the bytes over the fabric as quantize_held_kernel is: a workgroup takes a run of tiles, keeps the
 // first kHeldTiles = 10 of them in registers (one unit of 4 rows x 8 columns a thread and tile, 160 registers; 42 M elements on the chip), reads those
 // beyond twice, and transposes one after the other through two LDS tiles in turn, one barrier each.  Loads go through raw buffers over the tile, so that
-// those of all ten are in flight at once (their descriptors do not all fit the scalar registers: 72 wait in lanes of vector registers).  Back to back, us, with the row-major copy / without, two passes -> this: 21 M elements 27.4 / 24.1 -> 19.5 /
-// 18.5, 34 M 34.3 / 29.5 -> 27.3 / 24.1, 42 M 54.8 / 39.7 -> 31.9 / 26.8, 67 M 86.8 / 64.4 -> 76.2 / 60.3, 117 M 147.7 / 115.5 -> 116.7 / 93.5,
+// those of all ten are in flight at once (their descriptors do not all fit the scalar registers: 55 wait in lanes of
+// vector registers).  Back to back, us, with the row-major copy / without, two passes -> this: 21 M elements 27.4 / 24.1 -> 19.5 / 18.5 (with an infinity, or a
+// margin that saturates, 20.6 / 19.9; cast again from memory 32 / 30), 34 M 34.3 / 29.5 -> 27.3 / 24.1, 42 M 54.8 / 39.7 -> 31.9 / 26.8, 67 M 86.8 / 64.4 -> 76.2 / 60.3, 117 M 147.7 / 115.5 -> 116.7 / 93.5,
 // 151 M 183.4 / 142.6 -> 156.9 / 124.1.  Beside attention forwards of 0 / 16 / 64 / 192 workgroups on another stream, two passes: 34 M 35 / 39 / 42 / 43, 117 M
 // 150 / 154 / 157 / 159; this: 27 / 44 / 52 / 71, 117 / 125 / 151-155 / 201.
 constexpr int kHeldTiles = 10;
@@ -908,23 +909,24 @@ __global__ __launch_bounds__(kHeldThreads, 2) void quantize_held_transpose_kerne
       for (int k = 0; k < 4; ++k) u[k] = next[k];
     }
   };
-  int from = t0;
-  if (r < 0x7F80u && am * rho <= (FMT == FOG_E4M3 ? 449.0f : 57400.0f)) {   // finite and within the format, as in held_body
+  auto cast_held = [&](auto cast) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < kHeldTiles; ++i)
       if (i < mine) {
         uint2 code[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint4 u = v[i][k];
-          code[k] = make_uint2(cvt4_fp8_finite<FMT>(bf16lo(u.x) * rho, bf16hi(u.x) * rho, bf16lo(u.y) * rho, bf16hi(u.y) * rho),
-                               cvt4_fp8_finite<FMT>(bf16lo(u.z) * rho, bf16hi(u.z) * rho, bf16lo(u.w) * rho, bf16hi(u.w) * rho));
-        }
+        for (int k = 0; k < 4; ++k) code[k] = cast(v[i][k]);
         emit(t0 + i, code);
       }
-    from = t0 + kHeldTiles;
-  }
-  for (int k = -1; k < extra; ++k) again(k < 0 ? from : part(sh.extra[k]), k < 0 ? t0 + mine : part_end(sh.extra_to[k] - 1));
+  };
+  if (r < 0x7F80u && am * rho <= (FMT == FOG_E4M3 ? 449.0f : 57400.0f))   // finite and within the format, as in held_body
+    cast_held([&](uint4 u) __attribute__((always_inline)) {
+      return make_uint2(cvt4_fp8_finite<FMT>(bf16lo(u.x) * rho, bf16hi(u.x) * rho, bf16lo(u.y) * rho, bf16hi(u.y) * rho),
+                        cvt4_fp8_finite<FMT>(bf16lo(u.z) * rho, bf16hi(u.z) * rho, bf16lo(u.w) * rho, bf16hi(u.w) * rho));
+    });
+  else
+    cast_held([&](uint4 u) __attribute__((always_inline)) { return cast8<FMT>(u, rho); });
+  for (int k = -1; k < extra; ++k) again(k < 0 ? t0 + kHeldTiles : part(sh.extra[k]), k < 0 ? t0 + mine : part_end(sh.extra_to[k] - 1));
 }
 
 // ---------------------------------------------------------------- general shapes (slow, same results)

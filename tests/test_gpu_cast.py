@@ -623,7 +623,7 @@ def test_one_launch_cast_of_special_values(special, margin, absent):
 @pytest.mark.parametrize("rows,cols,pad", [(16, 16, 0), (128, 128, 16), (144, 272, 0), (2064, 2032, 48), (4096, 2064, 0), (5104, 8176, 16), (8208, 9232, 0)])
 def test_one_launch_transposing_cast_equals_the_separate_calls(rows, cols, pad, absent):
     """One tile, partly filled tiles at both edges, a few tiles a workgroup, the last workgroup with fewer, ten a workgroup, some more than stay in
-    registers; rows apart in all three tensors; without a row-major copy; infinities and a margin that saturates, through the clamp; and with every second
+    registers; rows apart in all three tensors; without a row-major copy; infinities, NaNs and a margin that saturates, through the clamp; and with every second
     workgroup absent, or all but the first."""
     g = torch.Generator(device="cuda").manual_seed(rows + cols)
     whole = torch.randn((rows, cols + pad), device="cuda", generator=g).to(torch.bfloat16)
@@ -631,7 +631,7 @@ def test_one_launch_transposing_cast_equals_the_separate_calls(rows, cols, pad, 
         whole[:, cols:] = 3.0e38                                    # not part of the tensor
     x = whole[:, :cols]
     ws = torch.randint(0, 256, (fog.quantize_jit_workspace(),), dtype=torch.uint8, device="cuda", generator=g)
-    for fmt, margin, peak, with_q in ((fp8.E4M3, 0, -77.0, True), (fp8.E5M2, 0, 33.0, False), (fp8.E5M2, -2, 9.0, True), (fp8.E4M3, 0, float("inf"), True)):
+    for fmt, margin, peak, with_q in ((fp8.E4M3, 0, -77.0, True), (fp8.E5M2, 0, 33.0, False), (fp8.E5M2, -2, 9.0, True), (fp8.E4M3, 0, float("inf"), True), (fp8.E5M2, 0, float("nan"), True)):
         x[rows // 2, cols - 1] = peak
         x[rows - 1, cols // 3] = 8.0
         am, sc, si, am2, sc2, si2 = (torch.full((1,), -1.0, device="cuda") for _ in range(6))
