@@ -615,8 +615,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(BwdArgs a) {
   };
   // The wave overlaps the two units by itself as well: dP of block kb is produced under its exponentials, the scores of block kb + 1 while its dS are
   // formed, and every operand is read from LDS one matrix instruction ahead.  (All eight products in front of the vector part before, and
-  // uniform load offsets in vector registers: 4 x 16 x 2048 73.5 -> 69.2 us, backward of 1 x 4 x 8192 219 -> 210; 2 x 32 x 4096 level at 225, where the clock
-  // is what gives.)
+  // uniform load offsets in vector registers: 4 x 16 x 2048 73.5 -> 69.2 us.  The whole backward, us, before / offsets alone / order alone / both:
+  // 4 x 16 x 2048 155.0 / 153.6 / 146.9 / 148.5, 1 x 4 x 8192 208 / 209 / 197 / 198, 2 x 32 x 4096 501 / 498 / 501 / 504.  Where four rounds of workgroups keep every
+  // wave slot busy the clock is what gives, and it is half a percent to one behind: 1 x 32/8 x 8192 955 -> 962, 8 x 32/8 x 1024 173.0 -> 175.0; two
+  // rounds are ahead: 8 x 16 x 1024 97.5 -> 95.2, 2 x 32/8 x 2048 not causal 290 -> 284.)
   auto block = [&](int kb, v16f* st, v16f* next, auto stg) __attribute__((always_inline)) {
     constexpr int STG = decltype(stg)::value;
     __builtin_amdgcn_s_waitcnt(0x0074);  // vmcnt = 4: block kb + 1 landed (block kb + 2 may be in flight); lgkmcnt = 0
